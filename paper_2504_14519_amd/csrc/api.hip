@@ -153,6 +153,12 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p) {
     if (cost[r] <= best * 1.03) return r;
   return 1;
 }
+// Whether the query blocks that share keys go to one XCD (next_item): where at least 8 groups of them read keys of their
+// own, so that every XCD has one; with fewer, an XCD would be without, and the keys of so few groups are streamed by
+// all L2s at a rate the memory-side cache does not notice (0.2 TB/s at one K/V head against 2.4 at 40).
+bool items_by_group(const slimpipe_attn_params* p, int ranges) {
+  return (int64_t)p->n_kv_heads * p->batch * ranges >= 8;
+}
 size_t fwd_part_out_bytes(const slimpipe_attn_params* p) {
   size_t n = (size_t)p->batch * (size_t)p->s_q * (size_t)p->n_q_heads * (size_t)p->head_dim * sizeof(float);
   return (n + 255) & ~(size_t)255;
@@ -356,9 +362,10 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   // a counter only where there are more items than compute units (otherwise every workgroup starts at once)
   if ((int64_t)a.items[0] * a.items[1] * a.items[2] <= compute_units()) ticket = nullptr;
   a.ticket = ticket;
+  a.items_by_group = items_by_group(p, n_ranges);
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (ticket && launch_zero_counter(ticket, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
+  if (ticket && launch_zero_counters(ticket, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
   hipError_t e = timed(SLIMPIPE_KERNEL_FWD, st, [&] { return launch_fwd(a, p->batch, p->head_dim, st); });
   if (e != hipSuccess) return SLIMPIPE_ELAUNCH;
   if (parts && out) {
@@ -508,7 +515,8 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   const int64_t cus = compute_units();
   a.dkdv_wgs = (int32_t)cus;
   a.ticket_dkdv = (counters && (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > cus) ? counters : nullptr;
-  a.ticket_dq = (counters && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, one per XCD
+  a.ticket_dq = (counters && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, [8..15]: dq, one per XCD
+  a.items_by_group = items_by_group(p, dq_ranges);
   if ((int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.s_q = p->s_q; a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.group = p->n_q_heads / p->n_kv_heads; a.causal = p->causal;

@@ -27,8 +27,8 @@ __global__ __launch_bounds__(256) void attn_delta_kernel(const BwdArgs a, int ba
   constexpr int NC = D / 8;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gid < 8) {      // the dq and dk/dv kernels of this call, later on the stream, count from zero
-    if (gid == 0 && a.ticket_dq) *a.ticket_dq = 0u;
-    if (a.ticket_dkdv) a.ticket_dkdv[gid] = 0u;      // one counter per XCD
+    if (a.ticket_dq) a.ticket_dq[gid] = 0u;          // one counter per XCD each
+    if (a.ticket_dkdv) a.ticket_dkdv[gid] = 0u;
   }
   const int64_t rh = gid / NC;                 // (b, r, h) flattened
   const int c = (int)(gid % NC);
@@ -213,15 +213,15 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   const bool group_b = wave_u >= NW / 2;
   const int gtid = tid & (GT - 1);
   // Work item: index -> (query block, q head, batch index x key range), the first fastest: the workgroup's own
-  // index, or the next value of the ticket counter (surplus workgroups leave at once).
+  // index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
   int item = blockIdx.x;
   if (a.ticket_dq) {
-    unsigned* slot = reinterpret_cast<unsigned*>(smem);      // (the tile rings are not in use yet)
-    if (threadIdx.x == 0) *slot = atomicAdd(a.ticket_dq, 1u);
+    int* slot = reinterpret_cast<int*>(smem);      // (the tile rings are not in use yet)
+    if (threadIdx.x == 0) *slot = next_item(a.ticket_dq, a.dq_items[0] * a.dq_items[1] * a.dq_items[2], a.dq_items[0], a.items_by_group);
     __syncthreads();
-    item = (int)*slot;
+    item = *slot;
     __syncthreads();
-    if (item >= a.dq_items[0] * a.dq_items[1] * a.dq_items[2]) return;
+    if (item < 0) return;
   }
   item = __builtin_amdgcn_readfirstlane(item);
   const int per_z = a.dq_items[0] * a.dq_items[1];

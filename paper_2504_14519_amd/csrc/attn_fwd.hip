@@ -214,15 +214,15 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
   // Work item: index -> (query block, q head, batch index x key range), the first fastest: the workgroup's own
-  // index, or the next value of the ticket counter (surplus workgroups leave at once).
+  // index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
   int item = blockIdx.x;
   if (a.ticket) {
-    unsigned* slot = reinterpret_cast<unsigned*>(smem);      // (the tile rings are not in use yet)
-    if (threadIdx.x == 0) *slot = atomicAdd(a.ticket, 1u);
+    int* slot = reinterpret_cast<int*>(smem);      // (the tile rings are not in use yet)
+    if (threadIdx.x == 0) *slot = next_item(a.ticket, a.items[0] * a.items[1] * a.items[2], a.items[0], a.items_by_group);
     __syncthreads();
-    item = (int)*slot;
+    item = *slot;
     __syncthreads();
-    if (item >= a.items[0] * a.items[1] * a.items[2]) return;
+    if (item < 0) return;
   }
   item = __builtin_amdgcn_readfirstlane(item);
   const int per_z = a.items[0] * a.items[1];
@@ -378,9 +378,9 @@ static hipError_t launch_fwd_t(const FwdArgs& a, int batch, hipStream_t st) {
   return hipGetLastError();
 }
 
-__global__ void zero_counter_kernel(unsigned* counter) { *counter = 0u; }
-hipError_t launch_zero_counter(unsigned* counter, hipStream_t st) {
-  hipLaunchKernelGGL(zero_counter_kernel, dim3(1), dim3(1), 0, st, counter);
+__global__ void zero_counters_kernel(unsigned* counters) { counters[threadIdx.x] = 0u; }
+hipError_t launch_zero_counters(unsigned* counters, hipStream_t st) {
+  hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(8), 0, st, counters);
   return hipGetLastError();
 }
 

@@ -37,11 +37,12 @@ struct FwdArgs {
   int32_t n_ranges;                                   // >= 1; third item coordinate = batch index * n_ranges + range
   int64_t range_begin[kMaxRanges], range_end[kMaxRanges];
   int64_t out_range_stride, lse_range_stride;         // in elements of the output type / floats
-  // work items = (query block, q head, batch index x range), items[0] * [1] * [2] of them; with `ticket` (a counter
-  // set to zero before the launch) the grid holds more workgroups than items and each takes the next item from the
-  // counter (see BwdArgs::ticket); nullptr: workgroup index = item
+  // work items = (query block, q head, batch index x range), items[0] * [1] * [2] of them; with `ticket` (eight counters
+  // set to zero before the launch, one per XCD) the grid holds more workgroups than items and each takes the next item
+  // from the counters (see next_item and BwdArgs::ticket_dkdv); nullptr: workgroup index = item
   unsigned* ticket;
   int32_t items[3];
+  int32_t items_by_group;      // an XCD takes all query blocks of a (head, batch index x range) (see next_item)
   int64_t q_offset, kv_capacity;
   float scale_log2e;
   int64_t q_stride_b, q_stride_s, q_stride_h;
@@ -77,13 +78,14 @@ struct BwdArgs {
   // instead of deriving it from their index: the hardware hands workgroups to the eight XCDs round-robin whatever
   // their speed, and this lets a faster XCD take more items.  The dk/dv launch then has dkdv_wgs workgroups (one per
   // compute unit) that loop over items, with ticket_dkdv[0..7] one counter per XCD; the dq launch has a quarter more
-  // workgroups than items, one item each, and one counter.
+  // workgroups than items, one item each, and eight counters too.
   // nullptr: workgroup index = item (no room for the counter in the workspace, or no more items than compute units:
   // then every workgroup starts at once and there is nothing to even out).
   unsigned* ticket_dkdv;
   unsigned* ticket_dq;
   int32_t dkdv_wgs;
   int32_t dkdv_items[3];
+  int32_t items_by_group;   // of the dq launch, as in FwdArgs
   int32_t dq_items[3];      // dq work items = (query block, q head, batch index x key range), handed out the same way
   int32_t s_q, n_q_heads, n_kv_heads, group, causal;
   int32_t dq_f32, dq_accumulate, dkv_accumulate;
@@ -112,7 +114,7 @@ hipError_t opt_in_fwd_kernels();
 hipError_t opt_in_bwd_kernels();
 
 hipError_t launch_fwd(const FwdArgs& a, int batch, int head_dim, hipStream_t st);
-hipError_t launch_zero_counter(unsigned* counter, hipStream_t st);
+hipError_t launch_zero_counters(unsigned* counters, hipStream_t st);
 hipError_t launch_delta(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int batch, int head_dim, hipStream_t st);

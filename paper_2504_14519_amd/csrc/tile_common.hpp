@@ -281,6 +281,28 @@ struct KvWalk {
 // vmcnt(0), other counters untouched (gfx9 encoding: vmcnt[3:0]|[15:14], expcnt[6:4], lgkmcnt[11:8]).
 SP_DEV void wait_async() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// The next work item of a forward / dq launch through its ticket counters (eight, zero before the launch), or -1 when
+// all are taken; called by one thread.  Items come in groups of `blocks`, the query blocks that walk the same keys and
+// values.  With `by_group` (at least eight groups with keys of their own) group j belongs to class j mod 8, and a
+// workgroup takes from the class of its own XCD first, so that the blocks which share keys share an L2, and from the
+// other classes in turn when that is used up (a faster XCD ends up doing more).  Otherwise one counter deals the items
+// out in order.  4096 rows on 20480 keys, 40 heads with keys of their own (420 MB of K and V, which every one of the eight
+// L2s otherwise streams in full): forward 1316 -> 1307 us, backward call 1 %.
+SP_DEV int next_item(unsigned* tickets, int n_items, int blocks, bool by_group) {
+  if (!by_group) {
+    const unsigned t = atomicAdd(tickets, 1u);
+    return t < (unsigned)n_items ? (int)t : -1;
+  }
+  int cls = (int)(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11)) & 7u);      // XCC_ID
+  for (int tried = 0; tried < 8; ++tried) {
+    const unsigned t = atomicAdd(tickets + cls, 1u);       // (at most n_items + workgroups tickets: no wrap)
+    const int64_t i = (int64_t)((t / (unsigned)blocks) * 8 + cls) * blocks + t % (unsigned)blocks;
+    if (i < n_items) return (int)i;
+    cls = (cls + 1) & 7;
+  }
+  return -1;
+}
+
 // ---- scheduling helpers ------------------------------------------------------------------------
 #define SP_FENCE() __builtin_amdgcn_sched_barrier(0)
 // Issue priority of a wave while it is in a matrix phase.  Waves are served oldest first, so without

@@ -1,0 +1,41 @@
+"""Work items dealt out by XCD (at least eight groups of query blocks with keys of their own and more items than compute
+units): every row is computed, whatever the number of groups, against slices of the same call small enough to run without
+counters."""
+import math
+
+import pytest
+
+from gpu_util import say
+
+pytestmark = pytest.mark.gpu
+
+
+# (batch, rows, prefix, q heads, kv heads): 8 groups exactly, a count that is no multiple of 8, one block per group
+@pytest.mark.parametrize("B,s,N,Hq,Hkv", [(1, 2304, 2304, 32, 8), (3, 1280, 1536, 21, 21), (1, 200, 456, 300, 300)])
+def test_every_item_is_computed_once(B, s, N, Hq, Hkv):
+    import torch
+    import paper_2504_14519_amd as sp
+    D, scale, G = 64, 0.125, Hq // Hkv
+    say("items by XCD: batch %d, %d rows on %d keys, %d/%d heads" % (B, s, N, Hq, Hkv))
+    g = torch.Generator(device="cuda:0").manual_seed(5)
+    mk = lambda n, h: torch.randn((B, n, h, D), device="cuda:0", generator=g).to(torch.bfloat16)
+    q, do, k, v = mk(s, Hq), mk(s, Hq), mk(N, Hkv), mk(N, Hkv)
+    ws = torch.empty(256, device="cuda:0", dtype=torch.uint8)              # counters, no key ranges
+    o, l = sp.slimpipe_attn_fwd(q, k, v, N - s, 0, N, True, scale, workspace=ws)
+    wsb = torch.full((2 * ((B * Hq * s * 4 + 255) // 256 * 256) + 256,), 0xff, device="cuda:0", dtype=torch.uint8)
+    dk, dv = torch.zeros((B, N, Hkv, D), device="cuda:0"), torch.zeros((B, N, Hkv, D), device="cuda:0")
+    dq = sp.slimpipe_attn_bwd(q, k, v, o, do, l, N - s, 0, N, dk, dv, True, scale, dkv_accumulate=False, workspace=wsb)
+    torch.cuda.synchronize()
+    for h in range(0, Hkv, max(1, Hkv // 7)):       # one K/V head at a time: few items, no counters
+        qs, ks = slice(h * G, (h + 1) * G), slice(h, h + 1)
+        o1, l1 = sp.slimpipe_attn_fwd(q[:, :, qs], k[:, :, ks], v[:, :, ks], N - s, 0, N, True, scale)
+        assert torch.equal(o[:, :, qs], o1) and torch.equal(l[:, qs], l1), h
+        w1 = torch.empty(2 * ((B * G * s * 4 + 255) // 256 * 256), device="cuda:0", dtype=torch.uint8)
+        # (the key/value strides of the one-head views are those of the whole cache, and so are the accumulators')
+        dkf, dvf = torch.zeros_like(dk), torch.zeros_like(dv)
+        dq1 = sp.slimpipe_attn_bwd(q[:, :, qs], k[:, :, ks], v[:, :, ks], o[:, :, qs], do[:, :, qs], l[:, qs].contiguous(), N - s, 0, N,
+                                   dkf[:, :, ks], dvf[:, :, ks], True, scale, dq=torch.zeros_like(q)[:, :, qs], dkv_accumulate=False, workspace=w1)
+        torch.cuda.synchronize()
+        assert torch.equal(dq[:, :, qs], dq1), h
+        assert torch.equal(dk[:, :, ks], dkf[:, :, ks]) and torch.equal(dv[:, :, ks], dvf[:, :, ks]), h
+    assert torch.isfinite(o.float()).all() and torch.isfinite(dq.float()).all() and torch.isfinite(dk).all() and torch.isfinite(dv).all()
