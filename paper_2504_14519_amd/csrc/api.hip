@@ -134,15 +134,31 @@ double visible_pairs_upto(const slimpipe_attn_params* p, int64_t e) {
   return full + (cnt > 0 ? 0.5 * cnt * (first + last) : 0.0);
 }
 
-// One forward workgroup owns 256 query rows of one head and walks the whole key range; a short slice over a
+// One forward workgroup owns 256 query rows and walks the whole key range; a short slice over a
 // long cache leaves compute units idle.  Cutting the key range into R ranges of equal work (one launch,
 // partial (out, lse) per range, then the online-softmax merge) makes R times the workgroups: R is the
 // smallest count that comes within 3% of the best rounds/R, as long as a range keeps at least 1024 keys.
 int fwd_preferred_ranges(const slimpipe_attn_params* p) {
-  const int64_t w = (((int64_t)p->s_q + 255) / 256) * p->n_q_heads * p->batch;
+  const int64_t w = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
   const int64_t keys = p->kv_end - p->kv_begin;
   if (w <= 0 || keys <= 0) return 1;
   const int cus = compute_units();
+  // Less than one block per compute unit: every compute unit runs a chain of ceil(w r / CUs) items, each of about 10 us plus
+  // 2.5 us (head_dim 128; 1.8 us at 64) per 128-key tile, and the merge is a launch of 4.5 us plus its bytes at 4 TB/s
+  // (measured).  The smallest count within 3% of the shortest sum.  (By rounds alone 192 blocks of head_dim 64 on 4238
+  // keys were cut into 4 ranges, three full rounds, which took 262 us of a backward call instead of 220.)  Ranges of
+  // head_dim 64 may be as short as 256 keys: 512 rows on 2048 keys and 4 heads are 8 blocks.
+  if (w < cus) {
+    const bool d64 = p->head_dim == 64;
+    int pick = 1;
+    double best_us = 1e30;
+    for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= (d64 ? 256 : 1024)) && (int64_t)p->batch * r <= 65535; ++r) {
+      const double us = (double)((w * r + cus - 1) / cus) * (10.0 + (d64 ? 1.8 : 2.5) * (double)keys / (128.0 * r)) +
+                        (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
+      if (us < best_us * 0.97) { best_us = us; pick = r; }
+    }
+    return pick;
+  }
   double best = 1e30, cost[kMaxRanges + 1];
   for (int r = 1; r <= kMaxRanges; ++r) {
     // (a range keeps at least 1024 keys; batch * ranges is the grid's z dimension)
@@ -355,10 +371,11 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     a.out_range_stride = 0; a.lse_range_stride = 0;
     a.o_stride_b = p->o_stride_b; a.o_stride_s = p->o_stride_s; a.o_stride_h = p->o_stride_h;
   }
-  a.items[0] = (p->s_q + 255) / 256;
-  a.items[1] = p->n_q_heads;
+  const int64_t blocks = query_blocks(p->s_q, a.group);
+  if (blocks * p->n_kv_heads * p->batch * n_ranges > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
+  a.items[0] = (int32_t)blocks;
+  a.items[1] = p->n_kv_heads;
   a.items[2] = p->batch * n_ranges;
-  if ((int64_t)a.items[0] * a.items[1] * a.items[2] > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   // a counter only where there are more items than compute units (otherwise every workgroup starts at once)
   if ((int64_t)a.items[0] * a.items[1] * a.items[2] <= compute_units()) ticket = nullptr;
   a.ticket = ticket;
@@ -507,10 +524,11 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   a.dkdv_items[0] = (int32_t)(dkdv_key_tiles(p, n_chunks) * split);
   a.dkdv_items[1] = p->n_kv_heads;
   a.dkdv_items[2] = p->batch;
-  a.dq_items[0] = (p->s_q + 255) / 256;
-  a.dq_items[1] = p->n_q_heads;
+  const int64_t blocks = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads);
+  if (blocks * p->n_kv_heads * p->batch * dq_ranges > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
+  a.dq_items[0] = (int32_t)blocks;
+  a.dq_items[1] = p->n_kv_heads;
   a.dq_items[2] = p->batch * dq_ranges;
-  if ((int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   // a counter only where there are more items than compute units (otherwise every workgroup starts at once)
   const int64_t cus = compute_units();
   a.dkdv_wgs = (int32_t)cus;

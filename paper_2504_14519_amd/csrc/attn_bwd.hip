@@ -212,7 +212,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
   const int gtid = tid & (GT - 1);
-  // Work item: index -> (query block, q head, batch index x key range), the first fastest: the workgroup's own
+  // Work item: index -> (query block, kv head, batch index x key range), the first fastest: the workgroup's own
   // index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
   int item = blockIdx.x;
   if (a.ticket_dq) {
@@ -226,11 +226,12 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   item = __builtin_amdgcn_readfirstlane(item);
   const int per_z = a.dq_items[0] * a.dq_items[1];
   const int bz = __builtin_amdgcn_readfirstlane(item / per_z), item_xy = item - bz * per_z;
-  const int h = __builtin_amdgcn_readfirstlane(item_xy / a.dq_items[0]), bx = item_xy - h * a.dq_items[0];
+  const int hk = __builtin_amdgcn_readfirstlane(item_xy / a.dq_items[0]), bx = item_xy - hk * a.dq_items[0];
   const int qblk = a.dq_items[0] - 1 - bx;
-  const int b = bz / a.n_dq_ranges, r = bz - b * a.n_dq_ranges, hk = h / a.group;
+  const int b = bz / a.n_dq_ranges, r = bz - b * a.n_dq_ranges;
   const int64_t kv_begin = a.dq_range_begin[r], kv_end = a.dq_range_end[r];      // this workgroup's key range
-  const int m0 = qblk * BM, wrow0 = m0 + wave_u * 32;
+  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group);
+  const int h = wr.h, wrow0 = wr.row0;
   const int myrow = wrow0 + ql;
   const int myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
 
@@ -253,11 +254,16 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   const int64_t lo = kv_grid_origin(kv_begin, a.kv.n, BN);     // first key of the tile grid
   int64_t hi = kv_end;
   if (a.causal) {
-    const int last_row = (m0 + BM < a.s_q ? m0 + BM : a.s_q);
-    const int64_t lim = a.q_offset + last_row;
+    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q);
     hi = hi < lim ? hi : lim;
   }
   const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  // tiles [0, t_full) lie below what the wave's first row sees and below the end of the range: no mask there (but for a
+  // first tile that starts before the range); one comparison per tile instead of 64-bit positions kept over the loop
+  int64_t see = kv_end;
+  if (a.causal && a.q_offset + wrow0 + 1 < see) see = a.q_offset + wrow0 + 1;
+  const int t_full = __builtin_amdgcn_readfirstlane(see > lo ? (int)((see - lo) / BN) : 0);
+  const bool cut_first = lo < kv_begin;
   const float c = a.scale_log2e;
 
   if (nt > 0) {
@@ -292,14 +298,14 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
       for (int n = 0; n < PASSES; ++n) copy_pass(j, n);
     };
     auto vector_phase = [&](int u, const CopyJob& j) {
-      const int64_t key0 = key0_of(u);
-      const bool need_mask = (key0 < kv_begin) || (key0 + BN > kv_end) || (a.causal && key0 + BN - 1 > a.q_offset + wrow0);
+      const bool need_mask = u >= t_full || (cut_first && u == 0);
       // first key of the range and last visible key of this lane's query relative to the tile: worked out in
       // the masked tiles only, from the thread index (nothing lane-dependent is kept in registers across the
       // loop for it)
       const int t2 = fresh(tid);
       int kmin_rel = 0, kmax_rel = BN;
       if (need_mask) {
+        const int64_t key0 = key0_of(u);
         const int64_t kmin = kv_begin - key0;
         kmin_rel = kmin < 0 ? 0 : (int)kmin;
         const int64_t qpos = a.q_offset + wrow0 + (t2 & 31);
@@ -315,9 +321,15 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
     {
       TileDma<D, BM, T> dma_do;
       dma_do.init(tid);
-      const bf16_t* dobase = a.d_out + (int64_t)b * a.do_stride_b + (int64_t)m0 * a.do_stride_s + (int64_t)h * a.do_stride_h;
-      for (int n = 0; n < TileDma<D, BM, T>::PASSES; ++n)
-        dma_do.issue(smem_lds + DO_BASE, dobase, (uint32_t)a.do_stride_s * 2, a.s_q - m0, wave_u, n);
+      const bf16_t* const dobase = a.d_out + (int64_t)b * a.do_stride_b;
+      for (int n = 0; n < TileDma<D, BM, T>::PASSES; ++n) {
+        // rows 32 w .. 32 w + 31 of the LDS block are those of wave w; the rows this wave copies in pass n belong to
+        // one of them.  The base is moved so that LDS row j is its row j (clamped to the slice, as everywhere).
+        const int w = (n * TileDma<D, BM, T>::RPP + wave_u * (TileDma<D, BM, T>::RPP / NW)) / 32;
+        const WaveRows dr = wave_rows(qblk, w, hk, a.s_q, a.group);
+        const bf16_t* base = dobase + (int64_t)dr.h * a.do_stride_h + (int64_t)(dr.row0 - 32 * w) * a.do_stride_s;
+        dma_do.issue(smem_lds + DO_BASE, base, (uint32_t)a.do_stride_s * 2, a.s_q - dr.row0 + 32 * w, wave_u, n);
+      }
     }
     copy_all(make_copy(0));
     copy_all(make_copy(1));
@@ -328,7 +340,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
     lo_k.init(lane, (int)smem_lds + K_BASE);
     lo_v.init(lane, (int)smem_lds + V_BASE);
     RpBase<D> lo_do;         // this wave's 32 rows of dO
-    lo_do.init(lane, (int)smem_lds + DO_BASE + wave * 32 * D * 2);
+    lo_do.init(lane, (int)smem_lds + DO_BASE + wave_u * 32 * D * 2);
     __syncthreads();
 
     // ring bookkeeping after matrix phase u: every pointer moves one tile on

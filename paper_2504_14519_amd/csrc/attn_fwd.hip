@@ -204,7 +204,7 @@ struct FwdMatrixPhase {
 template <int D, int NW, int BN>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   static_assert(NW == 8, "two groups of four waves");
-  constexpr int BM = NW * 32, KS = D / 16, DB = D / 32, T = NW * 64;
+  constexpr int KS = D / 16, DB = D / 32, T = NW * 64;
   constexpr int TILE_BYTES = BN * D * 2;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int KSLOTS = 3, VSLOTS = 2;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
-  // Work item: index -> (query block, q head, batch index x key range), the first fastest: the workgroup's own
+  // Work item: index -> (query block, kv head, batch index x key range), the first fastest: the workgroup's own
   // index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
   int item = blockIdx.x;
   if (a.ticket) {
@@ -227,11 +227,12 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   item = __builtin_amdgcn_readfirstlane(item);
   const int per_z = a.items[0] * a.items[1];
   const int bz = __builtin_amdgcn_readfirstlane(item / per_z), item_xy = item - bz * per_z;
-  const int h = __builtin_amdgcn_readfirstlane(item_xy / a.items[0]), bx = item_xy - h * a.items[0];
+  const int hk = __builtin_amdgcn_readfirstlane(item_xy / a.items[0]), bx = item_xy - hk * a.items[0];
   const int qblk = a.items[0] - 1 - bx;
-  const int b = bz / a.n_ranges, r = bz - b * a.n_ranges, hk = h / a.group;
+  const int b = bz / a.n_ranges, r = bz - b * a.n_ranges;
   const int64_t kv_begin = a.range_begin[r], kv_end = a.range_end[r];      // this workgroup's key range
-  const int m0 = qblk * BM, wrow0 = m0 + wave_u * 32;
+  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group);
+  const int h = wr.h, wrow0 = wr.row0;
   const int myrow = wrow0 + ql;
   const int myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
 
@@ -251,11 +252,16 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int64_t lo = kv_grid_origin(kv_begin, a.kv.n, BN);     // first key of the tile grid
   int64_t hi = kv_end;
   if (a.causal) {
-    const int last_row = (m0 + BM < a.s_q ? m0 + BM : a.s_q);
-    const int64_t lim = a.q_offset + last_row;
+    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q);
     hi = hi < lim ? hi : lim;
   }
   const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  // tiles [0, t_full) lie below what the wave's first row sees and below the end of the range: no mask there (but for a
+  // first tile that starts before the range); one comparison per tile instead of 64-bit positions kept over the loop
+  int64_t see = kv_end;
+  if (a.causal && a.q_offset + wrow0 + 1 < see) see = a.q_offset + wrow0 + 1;
+  const int t_full = __builtin_amdgcn_readfirstlane(see > lo ? (int)((see - lo) / BN) : 0);
+  const bool cut_first = lo < kv_begin;
   const float c = a.scale_log2e;
 
   if (nt > 0) {
@@ -305,10 +311,10 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     };
     // tail of a matrix phase: mask S(t) where the tile needs it
     auto mask_tile = [&](int t) {
-      const int64_t key0 = key0_of(t);
-      const bool need_mask = (key0 < kv_begin) || (key0 + BN > kv_end) || (a.causal && key0 + BN - 1 > a.q_offset + wrow0);
+      const bool need_mask = t >= t_full || (cut_first && t == 0);
       if (need_mask) {       // first key of the range and last visible key of this lane's query, relative to the tile
         const int t2 = fresh(tid);
+        const int64_t key0 = key0_of(t);
         const int64_t kmin = kv_begin - key0;
         const int kmin_rel = kmin < 0 ? 0 : (int)kmin;
         const int64_t qpos = a.q_offset + wrow0 + (t2 & 31);

@@ -28,6 +28,14 @@ inline __host__ __device__ int64_t kv_grid_origin(int64_t kv_begin, int32_t n_ch
 // of a launch writes its (out, lse) at out + r * out_range_stride, lse + r * lse_range_stride.
 constexpr int kMaxRanges = 16;
 
+// Query blocks.  A forward / dq workgroup is 8 waves of 32 query rows.  The waves of all query heads that share a
+// K/V head are numbered through (ceil(s_q / 32) per head) and cut into blocks of 8, so that only the last block of a
+// K/V head can hold waves without rows: with whole 256-row blocks per head a slice of 777 rows and 8 heads on one K/V
+// head was 32 blocks of which 24 % were padding, and is 25 blocks now.  Slices of a multiple of 256 rows, and heads with
+// K/V of their own, get the blocks they always had.
+inline __host__ __device__ int waves_per_head(int s_q) { return (int)(((unsigned)s_q + 31u) / 32u); }
+inline __host__ __device__ int64_t query_blocks(int s_q, int group) { return ((int64_t)group * waves_per_head(s_q) + 7) / 8; }
+
 struct FwdArgs {
   const __bf16* q;
   KvChunks kv;
@@ -37,7 +45,7 @@ struct FwdArgs {
   int32_t n_ranges;                                   // >= 1; third item coordinate = batch index * n_ranges + range
   int64_t range_begin[kMaxRanges], range_end[kMaxRanges];
   int64_t out_range_stride, lse_range_stride;         // in elements of the output type / floats
-  // work items = (query block, q head, batch index x range), items[0] * [1] * [2] of them; with `ticket` (eight counters
+  // work items = (query block, kv head, batch index x range), items[0] * [1] * [2] of them; with `ticket` (eight counters
   // set to zero before the launch, one per XCD) the grid holds more workgroups than items and each takes the next item
   // from the counters (see next_item and BwdArgs::ticket_dkdv); nullptr: workgroup index = item
   unsigned* ticket;
@@ -86,7 +94,7 @@ struct BwdArgs {
   int32_t dkdv_wgs;
   int32_t dkdv_items[3];
   int32_t items_by_group;   // of the dq launch, as in FwdArgs
-  int32_t dq_items[3];      // dq work items = (query block, q head, batch index x key range), handed out the same way
+  int32_t dq_items[3];      // dq work items = (query block, kv head, batch index x key range), handed out the same way
   int32_t s_q, n_q_heads, n_kv_heads, group, causal;
   int32_t dq_f32, dq_accumulate, dkv_accumulate;
   int64_t q_offset, kv_begin, kv_end, kv_capacity;

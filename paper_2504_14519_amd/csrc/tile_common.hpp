@@ -281,6 +281,23 @@ struct KvWalk {
 // vmcnt(0), other counters untouched (gfx9 encoding: vmcnt[3:0]|[15:14], expcnt[6:4], lgkmcnt[11:8]).
 SP_DEV void wait_async() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// Query head and first row (within the slice) of a wave of a query block (see query_blocks); a wave past the last head
+// gets rows past the end of the slice.  Heads ascend and rows descend with decreasing block number, so that
+// the blocks with the longest key ranges of a head come first when the blocks are started from the last one.
+struct WaveRows { int h, row0; };
+SP_DEV WaveRows wave_rows(int qblk, int wave_u, int hk, int s_q, int group) {
+  const unsigned per = (unsigned)waves_per_head(s_q), slot = (unsigned)qblk * 8u + (unsigned)wave_u;
+  const int hg = __builtin_amdgcn_readfirstlane((int)(slot / per));
+  if (hg >= group) return {hk * group, s_q};
+  return {hk * group + group - 1 - hg, (int)(slot - (unsigned)hg * per) * 32};
+}
+// One past the last row that any wave of a query block holds (a block that reaches the end of a head: s_q).
+SP_DEV int block_row_end(int qblk, int s_q) {
+  const unsigned per = (unsigned)waves_per_head(s_q), slot = (unsigned)qblk * 8u;
+  const unsigned end = (slot - (unsigned)__builtin_amdgcn_readfirstlane((int)(slot / per)) * per + 8u) * 32u;
+  return end < (unsigned)s_q ? (int)end : s_q;
+}
+
 // The next work item of a forward / dq launch through its ticket counters (eight, zero before the launch), or -1 when
 // all are taken; called by one thread.  Items come in groups of `blocks`, the query blocks that walk the same keys and
 // values.  With `by_group` (at least eight groups with keys of their own) group j belongs to class j mod 8, and a
