@@ -101,13 +101,14 @@ int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd);
  * chip's eight XCDs in turn whatever their speed; with counters a faster XCD takes more items; the results do
  * not depend on who computes what), and room for partial dk/dv sums: when the key tiles of a call do not fill the
  * GPU's compute units evenly, or when the counters are there and more items make for a more even finish, the query
- * rows of each key tile are cut into 2, 4 or 8 chunks that run as work items of their own, each writing float32
+ * rows of each key tile are cut into 2 to 8 chunks that run as work items of their own, each writing float32
  * partial sums [chunk][dk, dv][batch][kv head][keys rounded up to 256][head_dim] that a second kernel adds up
  * in chunk order.  The figure returned here includes that room for the split this call would pick;
  * given less, slimpipe_attn_bwd uses the largest split that fits (down to none).  In the same way the dq
  * kernel of a short slice over a long cache is cut into 2 to 16 key ranges of equal work, as the forward is,
  * with float32 partial dq [range][batch, s_q, n_q_heads, head_dim] behind the partial dk/dv that a reduce kernel
- * adds up in range order; that room is included too and used as far as it is there. */
+ * adds up in range order; that room is included too and used as far as it is there.  A backward call with fewer than
+ * two work items per compute unit computes dq and dk/dv in one launch (and adds up their partial sums in one). */
 int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, size_t* bytes);
 
 /* Forward of one query slice against keys [kv_begin, kv_end) of the cached prefix

@@ -187,6 +187,65 @@ size_t fwd_parts_bytes(const slimpipe_attn_params* p, int ranges) {
 size_t dq_parts_bytes(const slimpipe_attn_params* p, int ranges) {
   return ranges <= 1 ? 0 : (size_t)ranges * fwd_part_out_bytes(p);
 }
+
+// ---- the backward's launches -------------------------------------------------------------------------
+struct BwdPlan {
+  int split;         // chunks of a key tile's query stream
+  int dq_ranges;     // key ranges of the dq items
+  bool both;         // dq and dk/dv items in one launch
+  bool dq_first;     // ... the dq items first
+};
+
+// Time at which `na` items of length ta, then `nb` items of length tb, each started on the unit that is free first, are
+// all done on `units` units.
+double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb) {
+  const int64_t full = na / units, extra = na % units;                 // `extra` units hold one item more
+  const double load0 = (double)full * ta, load1 = load0 + (extra ? ta : 0.0);
+  const int64_t n0 = units - extra;
+  if (nb <= 0) return load1;
+  // the smallest finishing time m at which the units hold nb items of length tb between them
+  double best = 1e30;
+  for (int g = 0; g < (extra ? 2 : 1); ++g) {
+    const double load = g ? load1 : load0;
+    for (int k = 1; k <= 64; ++k) {
+      const double m = load + k * tb;
+      if (m >= best) break;
+      const int64_t room = (int64_t)((m - load0) / tb + 1e-9) * n0 + (m > load1 ? (int64_t)((m - load1) / tb + 1e-9) * extra : 0);
+      if (room >= nb) { best = m; break; }
+    }
+  }
+  return best > load1 ? best : load1;
+}
+
+// A call with fewer than two items per compute unit (query blocks + key tiles) runs dq and dk/dv in one launch, with the
+// cuts that finish first by the times below; a larger one runs them one after the other through the ticket counters.
+// Microseconds measured on MI355X: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64), a dk/dv item
+// about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its bytes at 5 TB/s.
+BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket) {
+  const int64_t cus = compute_units();
+  const int64_t wq = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
+  const int64_t wk = dkdv_key_tiles(p, n_chunks) * p->n_kv_heads * p->batch;
+  if (wk <= 0 || wq + wk >= 2 * cus) return {preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p), false, false};
+  const int64_t keys = p->kv_end - p->kv_begin;
+  const double dq_tiles = (double)keys / 64, dq_tile = p->head_dim == 128 ? 2.4 : 1.4;
+  const double stream = (double)(((int64_t)p->s_q + 31) / 32 * (p->n_q_heads / p->n_kv_heads)), dkdv_tile = p->head_dim == 128 ? 1.6 : 1.1;
+  static const int kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+  BwdPlan best{1, 1, true, false};
+  double best_us = 1e30;
+  for (int s : kCuts) {
+    if (s > 8 || (s > 1 && stream / s < 4)) break;             // a chunk keeps at least 4 query tiles
+    for (int r : kCuts) {
+      if (r > 1 && (keys / r < 256 || (int64_t)p->batch * r > 65535)) break;      // a range keeps at least 256 keys
+      const double tq = 8 + dq_tile * dq_tiles / r, tk = 10 + dkdv_tile * stream / s;
+      double us = tq > tk ? list_makespan(cus, wq * r, tq, wk * s, tk) : list_makespan(cus, wk * s, tk, wq * r, tq);
+      double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
+      if (r > 1) bytes += (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4;
+      if (bytes > 0) us += 4 + bytes / 5e6;
+      if (us < best_us * 0.99) { best_us = us; best = {s, r, true, tq > tk}; }
+    }
+  }
+  return best;
+}
 // Cut points of equal work on multiples of 256 keys (no range boundary inside a chunk-grid tile).
 void equal_work_ranges(const slimpipe_attn_params* p, int ranges, int64_t* begin, int64_t* end) {
   const double total = visible_pairs_upto(p, p->kv_end);
@@ -311,8 +370,10 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
   if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_preferred_ranges(p)); return SLIMPIPE_OK; }
   // the tile grid of a chunked call can start up to 255 keys before kv_begin: room for whichever of the
   // two variants asks for more
-  const size_t one = split_bytes(p, 1, preferred_split(p, 1, true)), many = split_bytes(p, 2, preferred_split(p, 2, true));
-  *bytes = delta_bytes(p) + kTicketBytes + (one > many ? one : many) + dq_parts_bytes(p, fwd_preferred_ranges(p));
+  const BwdPlan plan1 = bwd_plan(p, 1, true), plan2 = bwd_plan(p, 2, true);
+  const size_t one = split_bytes(p, 1, plan1.split) + dq_parts_bytes(p, plan1.dq_ranges);
+  const size_t many = split_bytes(p, 2, plan2.split) + dq_parts_bytes(p, plan2.dq_ranges);
+  *bytes = delta_bytes(p) + kTicketBytes + (one > many ? one : many);
   return SLIMPIPE_OK;
 }
 
@@ -497,13 +558,14 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   const bool ticket = workspace_bytes >= delta_bytes(p) + kTicketBytes;
   const size_t fixed = delta_bytes(p) + (ticket ? kTicketBytes : 0);
   unsigned* const counters = ticket ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + delta_bytes(p)) : nullptr;
-  int split = preferred_split(p, n_chunks, ticket);
-  while (split > 1 && fixed + split_bytes(p, n_chunks, split) > workspace_bytes) split /= 2;
+  const BwdPlan plan = bwd_plan(p, n_chunks, ticket);
+  int split = plan.split;
+  while (split > 1 && fixed + split_bytes(p, n_chunks, split) > workspace_bytes) split = plan.both ? split - 1 : split / 2;
   a.n_split = split;
   a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + fixed);
   // what is left of the workspace takes the partial dq of as many key ranges as fit
   const size_t used = fixed + split_bytes(p, n_chunks, split);
-  int dq_ranges = fwd_preferred_ranges(p);
+  int dq_ranges = plan.dq_ranges;
   while (dq_ranges > 1 && (used + dq_parts_bytes(p, dq_ranges) > workspace_bytes || (int64_t)p->batch * dq_ranges > 65535)) --dq_ranges;
   a.n_dq_ranges = dq_ranges;
   for (int r = 0; r < kMaxRanges; ++r) a.dq_range_begin[r] = a.dq_range_end[r] = 0;
@@ -532,8 +594,10 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   // a counter only where there are more items than compute units (otherwise every workgroup starts at once)
   const int64_t cus = compute_units();
   a.dkdv_wgs = (int32_t)cus;
-  a.ticket_dkdv = (counters && (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > cus) ? counters : nullptr;
-  a.ticket_dq = (counters && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, [8..15]: dq, one per XCD
+  a.dq_first = plan.dq_first;
+  const bool counted = counters && !plan.both;
+  a.ticket_dkdv = (counted && (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > cus) ? counters : nullptr;
+  a.ticket_dq = (counted && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, [8..15]: dq, one per XCD
   a.items_by_group = items_by_group(p, dq_ranges);
   if ((int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.s_q = p->s_q; a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
@@ -549,6 +613,10 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (timed(SLIMPIPE_KERNEL_DELTA, st, [&] { return launch_delta(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
+  if (plan.both && !(events && g_prof_on.load(std::memory_order_relaxed))) {      // (per-kernel times: one kernel at a time)
+    if (launch_bwd_both(a, p->head_dim, st) != hipSuccess || launch_both_reduce(a, p->batch, p->head_dim, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
+    return SLIMPIPE_OK;
+  }
   if (timed(SLIMPIPE_KERNEL_DQ, st, [&] { return launch_bwd_dq(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
   if (dq_ranges > 1 &&
       timed(SLIMPIPE_KERNEL_DQ_REDUCE, st, [&] { return launch_dq_reduce(a, p->batch, p->head_dim, st); }, events) != hipSuccess)

@@ -199,30 +199,21 @@ SP_DEV void dq_vector_phase(DqState<D, BN>& st, float c, bool need_mask, int kmi
     }
 }
 
+constexpr int kDqKeysPerTile = 64;
+
+// One work item: index -> (query block, kv head, batch index x key range), the first fastest.
 template <int D, int NW, int BN>
-__global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
+SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
   static_assert(NW == 8, "two groups of four waves");
   constexpr int BM = NW * 32, KS = D / 16, DB = D / 32, T = NW * 64, GT = T / 2;
   constexpr int TILE_BYTES = BN * D * 2;
   constexpr int KSLOTS = 4, VSLOTS = 2;
   constexpr int K_BASE = 0, V_BASE = KSLOTS * TILE_BYTES, DO_BASE = (KSLOTS + VSLOTS) * TILE_BYTES;
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
   const int gtid = tid & (GT - 1);
-  // Work item: index -> (query block, kv head, batch index x key range), the first fastest: the workgroup's own
-  // index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
-  int item = blockIdx.x;
-  if (a.ticket_dq) {
-    int* slot = reinterpret_cast<int*>(smem);      // (the tile rings are not in use yet)
-    if (threadIdx.x == 0) *slot = next_item(a.ticket_dq, a.dq_items[0] * a.dq_items[1] * a.dq_items[2], a.dq_items[0], a.items_by_group);
-    __syncthreads();
-    item = *slot;
-    __syncthreads();
-    if (item < 0) return;
-  }
   item = __builtin_amdgcn_readfirstlane(item);
   const int per_z = a.dq_items[0] * a.dq_items[1];
   const int bz = __builtin_amdgcn_readfirstlane(item / per_z), item_xy = item - bz * per_z;
@@ -322,6 +313,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
       TileDma<D, BM, T> dma_do;
       dma_do.init(tid);
       const bf16_t* const dobase = a.d_out + (int64_t)b * a.do_stride_b;
+#pragma unroll 1
       for (int n = 0; n < TileDma<D, BM, T>::PASSES; ++n) {
         // rows 32 w .. 32 w + 31 of the LDS block are those of wave w; the rows this wave copies in pass n belong to
         // one of them.  The base is moved so that LDS row j is its row j (clamped to the slice, as everywhere).
@@ -363,6 +355,8 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
     for (int u = 0; u + 1 < nt; ++u) {
       vector_phase(u, make_copy(u + 2));                 // tile u+2 rides along
       phase_end();
+      // (the dO rows never move: without this the offsets of their head_dim blocks are kept in registers across the loop)
+      asm volatile("" : "+v"(lo_do.off0));
       dq_matrix_phase<D, BN, true, true>(lo_kt, lo_k, lo_v, lo_do, st);      // dQ of tile u, scores of tile u+1
       advance();
       wait_async();                                      // the copies of the vector phase before have landed
@@ -398,7 +392,22 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   }
 }
 
-constexpr int kDqKeysPerTile = 64;
+// The item is the workgroup's index, or the next one of its XCD's ticket counter (surplus workgroups leave at once).
+template <int D, int NW, int BN>
+__global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  int item = blockIdx.x;
+  if (a.ticket_dq) {
+    int* slot = reinterpret_cast<int*>(smem);      // (the tile rings are not in use yet)
+    if (threadIdx.x == 0) *slot = next_item(a.ticket_dq, a.dq_items[0] * a.dq_items[1] * a.dq_items[2], a.dq_items[0], a.items_by_group);
+    __syncthreads();
+    item = *slot;
+    __syncthreads();
+    if (item < 0) return;
+  }
+  dq_item<D, NW, BN>(a, item, smem);
+}
+
 template <int D>
 constexpr size_t dq_lds_bytes() { return (size_t)6 * kDqKeysPerTile * D * 2 + (size_t)256 * D * 2; }   // 4 K slots + 2 V slots + dO rows
 
@@ -918,12 +927,25 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a)
   }
 }
 
+// The dq and the dk/dv items of one call in ONE launch, workgroup index = item, the kind whose items take longer first.
+// The two kinds are independent of each other; launched one after the other, a small call leaves compute units idle in
+// both launches (777 rows on 33777 keys: 132 dk/dv items on 256 compute units for 313 us after 178 us of dq).  For
+// calls of fewer than two items per compute unit only (bwd_plan in api.hip): in larger ones the tails overlap by 1 % of
+// the call and the ticket counters are worth more.
+template <int D>
+__global__ __launch_bounds__(512) void attn_bwd_both_kernel(const BwdArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int n_dq = a.dq_items[0] * a.dq_items[1] * a.dq_items[2], n_dkdv = a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
+  const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
+  if ((i < first) == (a.dq_first != 0)) dq_item<D, 8, kDqKeysPerTile>(a, a.dq_first ? i : i - n_dkdv, smem);
+  else dkdv_item<D, 8>(a, a.dq_first ? i - n_dq : i, smem);
+}
+
 // dk_acc, dv_acc (+)= the partial sums of the chunks, chunk 0 first.
-__global__ __launch_bounds__(256) void dkdv_reduce_kernel(const BwdArgs a, int batch, int head_dim) {
+SP_DEV void dkdv_reduce(const BwdArgs& a, int64_t gid, int batch, int head_dim) {
   const int64_t nkeys = a.kv_end - a.kv_begin;
   const int dvec = head_dim / 4;
   const int64_t total = (int64_t)batch * a.n_kv_heads * nkeys * dvec;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gid >= total) return;
   const int d = (int)(gid % dvec) * 4;
   const int64_t key = (gid / dvec) % nkeys;
@@ -949,10 +971,9 @@ __global__ __launch_bounds__(256) void dkdv_reduce_kernel(const BwdArgs a, int b
 }
 
 // dq (+)= the partial dq of the key ranges, range 0 first; four head_dim elements per thread.
-__global__ __launch_bounds__(256) void dq_reduce_kernel(const BwdArgs a, int batch, int head_dim) {
+SP_DEV void dq_reduce(const BwdArgs& a, int64_t gid, int batch, int head_dim) {
   const int dvec = head_dim / 4;
   const int64_t total = (int64_t)batch * a.s_q * a.n_q_heads * dvec;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gid >= total) return;
   const int d = (int)(gid % dvec) * 4;
   const int64_t rh = gid / dvec;                     // (b * s_q + row) * heads + h
@@ -972,6 +993,18 @@ __global__ __launch_bounds__(256) void dq_reduce_kernel(const BwdArgs a, int bat
   }
 }
 
+__global__ __launch_bounds__(256) void dkdv_reduce_kernel(const BwdArgs a, int batch, int head_dim) {
+  dkdv_reduce(a, (int64_t)blockIdx.x * 256 + threadIdx.x, batch, head_dim);
+}
+__global__ __launch_bounds__(256) void dq_reduce_kernel(const BwdArgs a, int batch, int head_dim) {
+  dq_reduce(a, (int64_t)blockIdx.x * 256 + threadIdx.x, batch, head_dim);
+}
+// both in one launch, the first dq_blocks workgroups for dq
+__global__ __launch_bounds__(256) void both_reduce_kernel(const BwdArgs a, int batch, int head_dim, unsigned dq_blocks) {
+  if (blockIdx.x < dq_blocks) dq_reduce(a, (int64_t)blockIdx.x * 256 + threadIdx.x, batch, head_dim);
+  else dkdv_reduce(a, (int64_t)(blockIdx.x - dq_blocks) * 256 + threadIdx.x, batch, head_dim);
+}
+
 template <int D, int NW>
 static hipError_t launch_dkdv_t(const BwdArgs& a, int batch, hipStream_t st) {
   if (a.kv_end <= a.kv_begin) return hipSuccess;
@@ -984,12 +1017,27 @@ static hipError_t launch_dkdv_t(const BwdArgs& a, int batch, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <int D>
+constexpr size_t both_lds_bytes() { return dq_lds_bytes<D>() > (size_t)DkdvLds<D, 8>::TOTAL ? dq_lds_bytes<D>() : (size_t)DkdvLds<D, 8>::TOTAL; }
+
+template <int D>
+static hipError_t launch_both_t(const BwdArgs& a, hipStream_t st) {
+  const int64_t items = (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] + (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
+  hipLaunchKernelGGL((attn_bwd_both_kernel<D>), dim3((unsigned)items), dim3(512), both_lds_bytes<D>(), st, a);
+  return hipGetLastError();
+}
+hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st) {
+  return head_dim == 128 ? launch_both_t<128>(a, st) : launch_both_t<64>(a, st);
+}
+
 hipError_t opt_in_bwd_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<128, 8, kDqKeysPerTile>), attr, (int)dq_lds_bytes<128>());
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<64, 8, kDqKeysPerTile>), attr, (int)dq_lds_bytes<64>());
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128, 8>), attr, DkdvLds<128, 8>::TOTAL);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8>), attr, DkdvLds<64, 8>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128>), attr, (int)both_lds_bytes<128>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64>), attr, (int)both_lds_bytes<64>());
   return e;
 }
 
@@ -1013,6 +1061,13 @@ hipError_t launch_dkdv_reduce(const BwdArgs& a, int batch, int head_dim, hipStre
   return hipGetLastError();
 }
 
-
+hipError_t launch_both_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {
+  const int64_t nkeys = a.kv_end - a.kv_begin, dvec = head_dim / 4;
+  const int64_t dq = a.n_dq_ranges > 1 ? ((int64_t)batch * a.s_q * a.n_q_heads * dvec + 255) / 256 : 0;
+  const int64_t dkdv = a.n_split > 1 && nkeys > 0 ? ((int64_t)batch * a.n_kv_heads * nkeys * dvec + 255) / 256 : 0;
+  if (dq + dkdv == 0) return hipSuccess;
+  hipLaunchKernelGGL(both_reduce_kernel, dim3((unsigned)(dq + dkdv)), dim3(256), 0, st, a, batch, head_dim, (unsigned)dq);
+  return hipGetLastError();
+}
 
 }  // namespace slimpipe

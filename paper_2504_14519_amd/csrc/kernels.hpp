@@ -94,6 +94,7 @@ struct BwdArgs {
   int32_t dkdv_wgs;
   int32_t dkdv_items[3];
   int32_t items_by_group;   // of the dq launch, as in FwdArgs
+  int32_t dq_first;         // dq and dk/dv in one launch: the dq items come first
   int32_t dq_items[3];      // dq work items = (query block, kv head, batch index x key range), handed out the same way
   int32_t s_q, n_q_heads, n_kv_heads, group, causal;
   int32_t dq_f32, dq_accumulate, dkv_accumulate;
@@ -128,6 +129,8 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dkdv_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dq_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
+hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st);
+hipError_t launch_both_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);
 hipError_t launch_finalize(const float* acc, __bf16* dst, int64_t n, hipStream_t st);
 hipError_t launch_dq_atomic_probe(float* dq, int s_q, int heads, int key_tiles, int rows_per_step, int placement, int rotate,
