@@ -8,48 +8,78 @@ namespace slimpipe {
 
 // One thread per 8 consecutive head_dim elements of one (row, head).
 //   lse = m + ln sum_r exp(lse_r - m),  out = sum_r exp(lse_r - lse) out_r ; parts with lse_r = -inf weigh 0.
+// HBM bound: every part is read once.  A thread asks for the lse of all (NP >= n_parts) parts and for the 8 elements of the
+// first four parts before it uses any of them, and for four more parts at a time after that (a loop over the parts that
+// skips empty ones pays the memory latency once per part and once more for each lse); indices are 32-bit (I) where they fit,
+// because three 64-bit divisions are more instructions than the rest of the kernel.
+template <int NP, bool F32, class I>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeArgs a) {
-  const int nc = a.head_dim / 8;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t total = a.rows * a.n_q_heads * nc;
+  const I nc = (I)(a.head_dim / 8);
+  const I gid = (I)blockIdx.x * 256 + threadIdx.x;
+  const I total = (I)a.rows * (I)a.n_q_heads * nc;
   if (gid >= total) return;
-  const int c = (int)(gid % nc);
-  const int64_t rh = gid / nc;                       // row * Hq + h
-  const int h = (int)(rh % a.n_q_heads);
-  const int64_t row = rh / a.n_q_heads;              // b * s_q + r
-  const int64_t bq = row / a.s_q, r = row % a.s_q;
+  const I rh = gid / nc;                             // row * Hq + h
+  const int c = (int)(gid - rh * nc);
+  const I row = rh / (I)a.n_q_heads;                 // b * s_q + r
+  const int64_t h = (int64_t)(rh - row * (I)a.n_q_heads);
+  const int64_t bq = (int64_t)(row / (I)a.s_q), r = (int64_t)row - bq * a.s_q;
   const int64_t sidx = (bq * a.n_q_heads + h) * a.s_q + r;
+  const int64_t eoff = (int64_t)rh * a.head_dim + c * 8;
 
-  float m = -INFINITY;
-  for (int p = 0; p < a.n_parts; ++p) m = fmaxf(m, a.lses[p][sidx]);
-  const bool has = m != -INFINITY;
-  float tot = 0.f;
-  if (has)
-    for (int p = 0; p < a.n_parts; ++p) tot += exp2_fast((a.lses[p][sidx] - m) * kLog2e);
-  const float lse = has ? m + __builtin_log2f(tot) * kLn2 : -INFINITY;
-  float acc[8];
+  float lp[NP];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-  const int64_t eoff = rh * a.head_dim + c * 8;
-  if (has) {
-    const float inv = 1.0f / tot;
-    for (int p = 0; p < a.n_parts; ++p) {
-      const float lp = a.lses[p][sidx];
-      if (lp == -INFINITY) continue;          // weight 0: the part's out row is not read (it may be uninitialised)
-      const float w = exp2_fast((lp - m) * kLog2e) * inv;
-      if (a.part_f32) {
+  for (int p = 0; p < NP; ++p) lp[p] = a.lses[p < a.n_parts ? p : 0][sidx];
+  constexpr int BATCH = NP < 4 ? NP : 4;
+  f32x4 x0[BATCH], x1[BATCH];
+  auto load = [&](int p0) {          // 8 elements of parts p0 .. p0 + BATCH - 1 (a part past the last: the last once more)
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      const int p = p0 + j < a.n_parts ? p0 + j : a.n_parts - 1;
+      if constexpr (F32) {
         const f32x4* src = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(a.outs[p]) + eoff);
-        const f32x4 x0 = src[0], x1 = src[1];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) { acc[j] += w * x0[j]; acc[4 + j] += w * x1[j]; }
+        x0[j] = src[0];
+        x1[j] = src[1];
       } else {
         const bf16x8 x = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const bf16_t*>(a.outs[p]) + eoff);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += w * (float)x[j];
+        for (int i = 0; i < 4; ++i) { x0[j][i] = (float)x[i]; x1[j][i] = (float)x[4 + i]; }
       }
     }
+  };
+  load(0);
+
+  float m = -INFINITY;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    if (p >= a.n_parts) lp[p] = -INFINITY;
+    m = fmaxf(m, lp[p]);
   }
-  const int64_t ooff = bq * a.o_stride_b + r * a.o_stride_s + (int64_t)h * a.o_stride_h + c * 8;
+  const bool has = m != -INFINITY;
+  float w[NP], tot = 0.f;
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    w[p] = exp2_fast((lp[p] - m) * kLog2e);
+    if (p < a.n_parts) tot += w[p];
+  }
+  const float lse = has ? m + __builtin_log2f(tot) * kLn2 : -INFINITY, inv = 1.0f / tot;
+  float acc[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+#pragma unroll
+  for (int p0 = 0; p0 < NP; p0 += BATCH) {
+    if (p0 > 0) {
+      if (p0 >= a.n_parts) break;
+      load(p0);
+    }
+#pragma unroll
+    for (int j = 0; j < BATCH; ++j) {
+      if (p0 + j >= NP || lp[p0 + j] == -INFINITY) continue;   // weight 0, whatever the part's out row holds (it may be uninitialised)
+      const float wp = w[p0 + j] * inv;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { acc[i] += wp * x0[j][i]; acc[4 + i] += wp * x1[j][i]; }
+    }
+  }
+  const int64_t ooff = bq * a.o_stride_b + r * a.o_stride_s + h * a.o_stride_h + c * 8;
   if (a.out_f32) {
     f32x4* dst = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + ooff);
     dst[0] = f32x4{acc[0], acc[1], acc[2], acc[3]};
@@ -67,11 +97,27 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const MergeArgs a) {
   if (c == 0) a.lse[sidx] = lse;
 }
 
+template <int NP>
+static void launch_merge_t(const MergeArgs& a, int64_t total, hipStream_t st) {
+  dim3 grid((unsigned)((total + 255) / 256)), block(256);
+  const bool small = total < (int64_t)1 << 31;
+  if (a.part_f32) {
+    if (small) hipLaunchKernelGGL((attn_merge_kernel<NP, true, uint32_t>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((attn_merge_kernel<NP, true, int64_t>), grid, block, 0, st, a);
+  } else {
+    if (small) hipLaunchKernelGGL((attn_merge_kernel<NP, false, uint32_t>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((attn_merge_kernel<NP, false, int64_t>), grid, block, 0, st, a);
+  }
+}
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st) {
   const int64_t total = a.rows * a.n_q_heads * (a.head_dim / 8);
   if (total <= 0) return hipSuccess;
-  dim3 grid((unsigned)((total + 255) / 256)), block(256);
-  hipLaunchKernelGGL(attn_merge_kernel, grid, block, 0, st, a);
+  if (a.n_parts <= 1) launch_merge_t<1>(a, total, st);
+  else if (a.n_parts <= 2) launch_merge_t<2>(a, total, st);
+  else if (a.n_parts <= 3) launch_merge_t<3>(a, total, st);
+  else if (a.n_parts <= 4) launch_merge_t<4>(a, total, st);
+  else if (a.n_parts <= 8) launch_merge_t<8>(a, total, st);
+  else launch_merge_t<16>(a, total, st);
   return hipGetLastError();
 }
 
