@@ -280,7 +280,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
       CopyJob j;
       j.src = walk.ptr;
       j.dst = smem_lds + (copies_k ? K_BASE + (t % KSLOTS) * TILE_BYTES : V_BASE + (t % VSLOTS) * TILE_BYTES);
-      j.rows = walk.rows(a.kv, BN);
+      j.rows = walk.rows(BN);
       if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s);
       return j;
     };

@@ -295,7 +295,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
       CopyJob j;
       j.src = walk.ptr;
       j.dst = smem_lds + (copies_k ? K_BASE + (t % KSLOTS) * TILE_BYTES : V_BASE + (t % VSLOTS) * TILE_BYTES);
-      j.rows = walk.rows(a.kv, BN);
+      j.rows = walk.rows(BN);
       if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s);
       return j;
     };

@@ -251,31 +251,31 @@ struct TileDma {
 };
 
 // Walks the key tiles of a chunked K/V prefix in increasing order: where the tile "now" starts.  All
-// members are uniform.  A step is two additions; the chunk's base pointer (a scalar load from the
-// kernel arguments) and the product row * stride are needed only when the walk enters a new chunk.
+// members are uniform.  A step is a few 32-bit scalar instructions (a wave issues in order: scalar work of a tile delays the
+// vector work behind it); the chunk's base pointer (a scalar load from the kernel arguments) and the product row * stride
+// are needed only when the walk enters a new chunk.
 struct KvWalk {
   const bf16_t* ptr;       // first row of the tile (batch and head offset included)
-  int chunk, row;          // current chunk, first row of the tile inside it
+  int chunk, left;         // current chunk, its rows from the tile's first row on (a chunk has fewer than 2^31 rows)
   SP_DEV void seek(const bf16_t* const* table, const KvChunks& kv, int64_t key0, int64_t head_off, int64_t stride_s) {
     chunk = kv.n > 1 ? __builtin_amdgcn_readfirstlane((int)(key0 / kv.len)) : 0;
-    row = (int)(key0 - (int64_t)chunk * kv.len);
+    const int row = (int)(key0 - (int64_t)chunk * kv.len);
+    left = (int)(kv.len - row < 0x7fffffff ? kv.len - row : 0x7fffffff);
     ptr = table[chunk] + head_off + (int64_t)row * stride_s;
   }
   // to the next tile; tile_step = tile * stride_s
   SP_DEV void step(const bf16_t* const* table, const KvChunks& kv, int tile, int64_t tile_step, int64_t head_off, int64_t stride_s) {
-    row += tile;
+    left -= tile;
     ptr += tile_step;
-    if (row >= kv.len && chunk + 1 < kv.n) {
-      row -= (int)kv.len;
+    if (left <= 0 && chunk + 1 < kv.n) {
       ++chunk;
+      const int row = -left;
+      left += (int)kv.len;
       ptr = table[chunk] + head_off + (int64_t)row * stride_s;
     }
   }
   // rows of the chunk from the tile's first row on, at most `tile`
-  SP_DEV int rows(const KvChunks& kv, int tile) const {
-    const int64_t left = kv.len - row;
-    return left > tile ? tile : (int)left;
-  }
+  SP_DEV int rows(int tile) const { return left > tile ? tile : left; }
 };
 
 // vmcnt(0), other counters untouched (gfx9 encoding: vmcnt[3:0]|[15:14], expcnt[6:4], lgkmcnt[11:8]).
