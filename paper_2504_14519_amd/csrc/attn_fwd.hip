@@ -4,7 +4,7 @@
 // One workgroup = 8 wavefronts, each owning 32 query rows of one head.  The key range is walked
 // in tiles of BN keys staged in LDS.  Per tile and wave:
 //   S^T = K Q^T        A = K rows from LDS (row-packed), B = Q held in registers
-//   online softmax     the C layout gives every lane ONE query column, so row sums (and the rare row maximum)
+//   online softmax     the C layout gives every lane ONE query column, so the row max / row sum
 //                      are in-lane reductions plus one exchange between the two half-waves
 //   O^T += V^T P^T     A = V through the transposed LDS read, B = P straight from the C registers
 // Scores and probabilities never leave registers.
@@ -24,9 +24,8 @@ namespace slimpipe {
 constexpr int kFwdKeysPerTile = 128;
 // operand look-ahead of the matrix phase (LDS reads issued this many MFMAs early)
 constexpr int kFwdLook = 2;
-// How far the probabilities of a tile may grow before the reference of the online softmax moves: the sum over a lane's
-// share of a tile (see fwd_softmax).
-constexpr float kFwdRefSlack = 1024.f;
+// 32-key blocks of a tile whose row maxima are taken at the tail of the matrix phase (the rest: vector phase)
+constexpr int fwd_rowmax_first_blocks(int kb) { return (kb + 1) / 2; }
 
 template <int D, int BN>
 struct FwdState {
@@ -35,7 +34,8 @@ struct FwdState {
   f32x16 o[DB];
   f32x16 s[KB];
   bf16x8 p[KB][2];
-  float m_run, l_run;          // reference of the exponents (scaled scores), sum of exp2(score - m_run) so far
+  float m_run, l_run;          // running maximum of the scaled scores, sum of exp2(score - m_run) so far
+  float mx;          // maximum of this lane's raw scores over the first half of the tile's keys in `s`
 };
 
 // Masks the raw scores of a tile: kmin_rel <= key <= kmax_rel stay, the others become -inf.
@@ -54,60 +54,70 @@ SP_DEV void fwd_mask(FwdState<D, BN>& st, int kmin_rel, int kmax_rel, int g) {
     }
 }
 
-// P(t) = exp2(c S(t) - m) with the reference m the tiles before have left, and its row sums.  The online softmax needs
-// no exact maximum: any m works that keeps the exponentials in range, because P and O are scaled alike and bf16 and
-// float32 have the same relative precision at any size.  So the row maximum of a tile (32 max3 instructions, an exchange
-// and a dependent chain in the phase that bounds this kernel) is taken only when the tile's own row sum says that m has
-// become too small: more than kFwdRefSlack in one lane's share of a row, or not a number (the first tile starts from
-// m = -inf, and infinite scores end there too).  m never exceeds the running maximum, so nothing underflows that did not
-// before, and a row's decision depends on that row alone.  S stays in its registers until the next matrix phase
-// overwrites it, so the rare tile is simply computed again.  (Error of out against 64 bits: 1.45-1.61e-3 with the exact
-// maximum, 1.49-1.66e-3 so: the same bf16 rounding of the weights, whose largest no longer sit just below a power of two.)  Measured, before and after: 16384 rows on 131072 keys (8 heads of
-// 128) 6.75 -> 6.42 ms, 4096 rows on 20480 keys (40 heads) 1.44 -> 1.36 ms.
+// Row maxima of the raw scores of a tile, in two parts (the vector unit is the bottleneck of this
+// kernel, so the work is split evenly between the two kinds of phase): the first half of the keys
+// at the tail of the matrix phase, the rest in the vector phase.
+template <int D, int BN>
+SP_DEV float fwd_rowmax_first(const FwdState<D, BN>& st) {
+  constexpr int KB = BN / 32;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < fwd_rowmax_first_blocks(KB); ++kb)
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(st.s[kb][i], st.s[kb][i + 1]), mx);
+  return mx;
+}
+template <int D, int BN>
+SP_DEV float fwd_rowmax_rest(const FwdState<D, BN>& st, float mx) {
+  constexpr int KB = BN / 32;
+#pragma unroll
+  for (int kb = fwd_rowmax_first_blocks(KB); kb < KB; ++kb)
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(st.s[kb][i], st.s[kb][i + 1]), mx);
+  return xhalf_max(mx);
+}
+
+// P(t) = online softmax of S(t); rescales O and the running sum when a row maximum moves.
+// The exponents are relative to the EXACT running maximum.  A reference that is allowed to lag behind it keeps every
+// exponential in range too and saves the maximum (5 % of the forward), but then the dominating weight of a row, exactly 1
+// here, lies anywhere in a binade and loses up to 2^-9 to the rounding to bf16 in P V while the row sum keeps it whole:
+// float32 out against 64 bits, 8192 keys, scores of standard deviation 4 nats: 5.1e-4 with the exact maximum, 1.31e-3
+// with one that lags by up to 2^10 (8 nats: 3.2e-4 and 1.22e-3).
 template <int D, int BN, class H>
 SP_DEV void fwd_softmax(FwdState<D, BN>& st, float c, H&& hook) {
   constexpr int KB = BN / 32, DB = D / 32;
-  auto exponentials = [&](float m, auto&& at) {
-    float sum = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) {
-      at(kb);
-      f32x16 e;
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        e[i] = exp2_fast(__builtin_fmaf(st.s[kb][i], c, -m));
-        sum += e[i];
-      }
-      st.p[kb][0] = pack8(e, 0);
-      st.p[kb][1] = pack8(e, 8);
-      // pin: without a use here the optimiser sinks this arithmetic past the phase barrier that follows
-      asm volatile("" : "+v"(st.p[kb][0]), "+v"(st.p[kb][1]));
-    }
-    return sum;
-  };
-  float l_add = exponentials(st.m_run, hook);
-  if (__builtin_amdgcn_ballot_w64(!(l_add <= kFwdRefSlack)) != 0) {
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-      for (int i = 0; i < 16; i += 2) mx = fmaxf(fmaxf(st.s[kb][i], st.s[kb][i + 1]), mx);
-    mx = xhalf_max(mx);
-    // (the two half-waves hold different keys of the same query: if one has to move, both do)
-    const bool move = !(xhalf_max(l_add <= kFwdRefSlack ? 0.f : 1.f) == 0.f);
-    const float m_new = move ? fmaxf(st.m_run, mx * c) : st.m_run;
-    const float m_eff = (m_new == -INFINITY) ? 0.f : m_new;
-    const float alpha = exp2_fast(st.m_run - m_eff);     // m_run = -inf -> 0; 1 where the reference stays
+  hook(0);
+  const float mx = fwd_rowmax_rest<D, BN>(st, st.mx);
+  hook(1);
+  const float m_new = fmaxf(st.m_run, mx * c);
+  const float m_eff = (m_new == -INFINITY) ? 0.f : m_new;
+  // rescale only when some row of the wave moved its maximum (rare once a few tiles are in)
+  if (__builtin_amdgcn_ballot_w64(m_new != st.m_run) != 0) {
+    const float alpha = exp2_fast(st.m_run - m_eff);     // m_run = -inf -> 0
     st.l_run *= alpha;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
       for (int i = 0; i < 16; ++i) st.o[db][i] *= alpha;
-    st.m_run = m_new;
-    l_add = exponentials(m_eff, [](int) {});
+  }
+  st.m_run = m_new;
+  float l_add = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    hook(2 + kb);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const float p = exp2_fast(__builtin_fmaf(st.s[kb][i], c, -m_eff));
+      st.s[kb][i] = p;
+      l_add += p;
+    }
+    st.p[kb][0] = pack8(st.s[kb], 0);
+    st.p[kb][1] = pack8(st.s[kb], 8);
+    // pin: without a use here the optimiser sinks this arithmetic past the phase barrier that follows
+    asm volatile("" : "+v"(st.p[kb][0]), "+v"(st.p[kb][1]));
   }
   st.l_run += l_add;
-  asm volatile("" : "+v"(st.l_run), "+v"(st.m_run));
+  asm volatile("" : "+v"(st.l_run));
 }
 
 // out = O / l, lse = (m + log2 l) ln 2; rows that saw no key: out = 0, lse = -inf.
@@ -268,7 +278,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   if (nt > 0) {
     const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
     auto key0_of = [&](int t) { return lo + (int64_t)t * BN; };
-    // Per tile t a wave runs the matrix phase MM(t): O^T += V(t-1)^T P(t-1)^T, S(t)^T = K(t) Q^T, mask
+    // Per tile t a wave runs the matrix phase MM(t): O^T += V(t-1)^T P(t-1)^T, S(t)^T = K(t) Q^T, row maxima
     // of S(t); and the vector phase VV(t): P(t) = online softmax of S(t).  K(t) is read in MM(t) only, V(t) in
     // MM(t+1) only.  Tile copies are issued from vector phases only, by the four waves of the group that
     // is in one (next to the LDS reads and MFMAs of a matrix phase they stall the wave): group A copies
@@ -280,7 +290,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     const int gtid = tid & (GT - 1);
     TileDma<D, BN, GT> dma;
     constexpr int PASSES = TileDma<D, BN, GT>::PASSES;   // copy instructions per tile and wave
-    constexpr int HOOKS = BN / 32, PPH = (PASSES + HOOKS - 1) / HOOKS;   // copy instructions per softmax hook
+    constexpr int HOOKS = 2 + BN / 32, PPH = (PASSES + HOOKS - 1) / HOOKS;   // copy instructions per softmax hook
     dma.init(gtid);
     const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
     const unsigned smem_lds = lds_addr(smem);
@@ -310,8 +320,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
         for (int n = part * PPH; n < (part + 1) * PPH && n < PASSES; ++n) copy_pass(j, n);
       });
     };
-    // tail of a matrix phase: mask S(t) where the tile needs it
-    auto mask_tile = [&](int t) {
+    // tail of a matrix phase: mask S(t) where the tile needs it and take its row maxima (balances the two kinds of phase)
+    auto rowmax_tile = [&](int t) {
       const bool need_mask = t >= t_full || (cut_first && t == 0);
       if (need_mask) {       // first key of the range and last visible key of this lane's query, relative to the tile
         const int t2 = fresh(tid);
@@ -325,6 +335,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
         const int kmax_rel = kmax < -1 ? -1 : (kmax > BN ? BN : (int)kmax);
         fwd_mask<D, BN>(st, kmin_rel, kmax_rel, (t2 >> 5) & 1);
       }
+      st.mx = fwd_rowmax_first<D, BN>(st);
+      asm volatile("" : "+v"(st.mx));      // keep it on this side of the phase barrier
     };
 
     // prologue: K(0), K(1) (group A), V(0) (group B)
@@ -348,7 +360,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     // one phase at the end.
     if (group_b) phase_end();
     { FwdMatrixPhase<D, BN, false, true, kFwdLook> ph{lo_v, lo_k, st}; ph.run(); }
-    mask_tile(0);
+    rowmax_tile(0);
     advance();
     wait_async();
     phase_end();
@@ -356,7 +368,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
       vector_phase(make_copy(copies_k ? t + 2 : t + 1));
       phase_end();
       { FwdMatrixPhase<D, BN, true, true, kFwdLook> ph{lo_v, lo_k, st}; ph.run(); }
-      mask_tile(t + 1);
+      rowmax_tile(t + 1);
       advance();
       wait_async();                                      // the copies of the vector phase before have landed
       phase_end();

@@ -1,5 +1,5 @@
-"""The forward's online softmax moves its reference only when a tile's row sum has grown large: scores that keep growing,
-jump, fall, or sit far below the reference, against the fp64 oracle through the C ABI."""
+"""The forward's online softmax with a reference that has to move: scores that keep growing, jump, fall, or grow by little
+from tile to tile, against the fp64 oracle through the C ABI."""
 import math
 
 import numpy as np
@@ -14,10 +14,10 @@ pytestmark = pytest.mark.gpu
 S, N, HQ, HKV = 290, 1290, 4, 2
 # factor on the keys (a power of two each, so that the scaled keys are bf16 again), by 128-key tile
 RAMPS = {
-    "growing": lambda t: 2.0 ** (t - 4),                       # the reference moves in most tiles
+    "growing": lambda t: 2.0 ** (t - 4),                       # the maximum moves in most tiles
     "jump and fall": lambda t: 64.0 if t == 5 else 1.0,        # one tile far above, the rest far below it
     "falling": lambda t: 2.0 ** (5 - t),
-    "just below the slack": lambda t: 2.0 if t % 2 else 0.5,
+    "up and down by a little": lambda t: 2.0 if t % 2 else 0.5,
 }
 
 
