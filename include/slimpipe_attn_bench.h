@@ -25,6 +25,18 @@ enum {
 int slimpipe_attn_profile_enable(int enable);
 int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t launches[SLIMPIPE_KERNEL_KINDS]);
 
+/* How slimpipe_attn_bwd (n_chunks = 1) or slimpipe_attn_bwd_chunked would cut a call into work items with a workspace of
+ * workspace_bytes (slimpipe_attn_bwd_noalloc: the two row statistics + 256 bytes).  Host code only, nothing is launched. */
+typedef struct slimpipe_bwd_plan {
+  int32_t one_launch;      /* dq and dk/dv items in one launch (fewer than two items per compute unit before any cut) */
+  int32_t dq_first;        /* in that launch the dq items come first */
+  int32_t dkdv_split;      /* chunks of a key tile's query stream */
+  int32_t dq_ranges;       /* key ranges of a query block */
+  int64_t dkdv_items, dq_items;
+  int32_t compute_units;   /* of the current device (256 where no device can be asked) */
+} slimpipe_bwd_plan;
+int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_bwd_plan* plan);
+
 /* The rate, in TFLOP/s, at which this GPU sustains a pure stream of the bf16 MFMA instruction the attention
  * kernels use, with constant operands (random_operands == 0) or with random ones (!= 0), under which the chip
  * is power limited and clocks lower.  Runs two short kernels (about 20 ms each) on the stream and waits for them.

@@ -31,6 +31,13 @@ class AttnParams(ctypes.Structure):
     ]
 
 
+class BwdPlan(ctypes.Structure):
+    _fields_ = [
+        ("one_launch", ctypes.c_int32), ("dq_first", ctypes.c_int32), ("dkdv_split", ctypes.c_int32), ("dq_ranges", ctypes.c_int32),
+        ("dkdv_items", ctypes.c_int64), ("dq_items", ctypes.c_int64), ("compute_units", ctypes.c_int32),
+    ]
+
+
 def library_path():
     return _LIB_PATH
 
@@ -87,6 +94,8 @@ def _load():
     L.slimpipe_attn_profile_enable.restype = ctypes.c_int
     L.slimpipe_attn_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_int64)]
     L.slimpipe_attn_profile_read.restype = ctypes.c_int
+    L.slimpipe_attn_bwd_plan.argtypes = [P, i32, ctypes.c_size_t, ctypes.POINTER(BwdPlan)]
+    L.slimpipe_attn_bwd_plan.restype = ctypes.c_int
     L.slimpipe_attn_strerror.argtypes = [ctypes.c_int]
     L.slimpipe_attn_strerror.restype = ctypes.c_char_p
     return L
@@ -368,6 +377,13 @@ def slimpipe_attn_xcd_rate(iters=20000, rounds=4):
         sel = xcc == x
         out[int(x)] = (int(sel.sum()), float((t1[sel] - t0[sel]).double().mean()) / 1e5, float(int(t1[sel].max()) - base) / 1e5)
     return out
+
+
+def slimpipe_attn_bwd_plan(params, n_chunks, workspace_bytes):
+    """How a backward call would be cut into work items with a workspace of that size (host code only)."""
+    plan = BwdPlan()
+    _check(lib.slimpipe_attn_bwd_plan(ctypes.byref(params), n_chunks, workspace_bytes, ctypes.byref(plan)), "bwd_plan")
+    return plan
 
 
 def slimpipe_attn_profile_enable(enable):

@@ -221,11 +221,19 @@ double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb
 // cuts that finish first by the times below; a larger one runs them one after the other through the ticket counters.
 // Microseconds measured on MI355X: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64), a dk/dv item
 // about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its bytes at 5 TB/s.
-BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket) {
+// The partial sums of the cuts take at most `room` bytes: a small call chooses among the pairs that fit, a large one takes
+// first as many chunks and then as many key ranges as fit.
+BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_t room) {
   const int64_t cus = compute_units();
   const int64_t wq = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
   const int64_t wk = dkdv_key_tiles(p, n_chunks) * p->n_kv_heads * p->batch;
-  if (wk <= 0 || wq + wk >= 2 * cus) return {preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p), false, false};
+  if (wk <= 0 || wq + wk >= 2 * cus) {
+    BwdPlan plan{preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p), false, false};
+    while (plan.split > 1 && split_bytes(p, n_chunks, plan.split) > room) plan.split /= 2;
+    const size_t used = split_bytes(p, n_chunks, plan.split);
+    while (plan.dq_ranges > 1 && (dq_parts_bytes(p, plan.dq_ranges) > room - used || (int64_t)p->batch * plan.dq_ranges > 65535)) --plan.dq_ranges;
+    return plan;
+  }
   const int64_t keys = p->kv_end - p->kv_begin;
   const double dq_tiles = (double)keys / 64, dq_tile = p->head_dim == 128 ? 2.4 : 1.4;
   const double stream = (double)(((int64_t)p->s_q + 31) / 32 * (p->n_q_heads / p->n_kv_heads)), dkdv_tile = p->head_dim == 128 ? 1.6 : 1.1;
@@ -236,6 +244,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket) {
     if (s > 8 || (s > 1 && stream / s < 4)) break;             // a chunk keeps at least 4 query tiles
     for (int r : kCuts) {
       if (r > 1 && (keys / r < 256 || (int64_t)p->batch * r > 65535)) break;      // a range keeps at least 256 keys
+      if (split_bytes(p, n_chunks, s) + dq_parts_bytes(p, r) > room) break;       // (1, 1) needs none
       const double tq = 8 + dq_tile * dq_tiles / r, tk = 10 + dkdv_tile * stream / s;
       double us = tq > tk ? list_makespan(cus, wq * r, tq, wk * s, tk) : list_makespan(cus, wk * s, tk, wq * r, tq);
       double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
@@ -245,6 +254,15 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket) {
     }
   }
   return best;
+}
+// The plan of a call with a workspace of this many bytes: the best one when its partial sums fit, otherwise the best of
+// those that do.  (Cutting the best plan down to the room there is leaves its order of the two kinds: 2387 rows on 52005 keys
+// planned 10 ranges of short dq items behind the dk/dv items; undivided, the dq items are the longer kind and came last.)
+BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t workspace_bytes) {
+  const bool ticket = workspace_bytes >= delta_bytes(p) + kTicketBytes;
+  const size_t room = workspace_bytes - delta_bytes(p) - (ticket ? kTicketBytes : 0);
+  const BwdPlan plan = bwd_plan(p, n_chunks, ticket, SIZE_MAX);
+  return split_bytes(p, n_chunks, plan.split) + dq_parts_bytes(p, plan.dq_ranges) <= room ? plan : bwd_plan(p, n_chunks, ticket, room);
 }
 // Cut points of equal work on multiples of 256 keys (no range boundary inside a chunk-grid tile).
 void equal_work_ranges(const slimpipe_attn_params* p, int ranges, int64_t* begin, int64_t* end) {
@@ -335,6 +353,23 @@ int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t l
   return rc;
 }
 
+int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_bwd_plan* out) {
+  if (!p || !out) return SLIMPIPE_EINVAL_NULL;
+  int rc = slimpipe_attn_validate(p, 1);
+  if (rc != SLIMPIPE_OK) return rc;
+  if (n_chunks < 1 || n_chunks > kMaxChunks) return SLIMPIPE_EINVAL_SHAPE;
+  if (workspace_bytes < delta_bytes(p)) return SLIMPIPE_EWORKSPACE;
+  const BwdPlan plan = bwd_plan_within(p, n_chunks, workspace_bytes);
+  out->one_launch = plan.both;
+  out->dq_first = plan.both && plan.dq_first;
+  out->dkdv_split = plan.split;
+  out->dq_ranges = plan.dq_ranges;
+  out->dkdv_items = dkdv_key_tiles(p, n_chunks) * plan.split * p->n_kv_heads * p->batch;
+  out->dq_items = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch * plan.dq_ranges;
+  out->compute_units = compute_units();
+  return SLIMPIPE_OK;
+}
+
 int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd) {
   if (!p) return SLIMPIPE_EINVAL_NULL;
   if (p->batch <= 0 || p->s_q <= 0 || p->n_q_heads <= 0 || p->n_kv_heads <= 0) return SLIMPIPE_EINVAL_SHAPE;
@@ -370,7 +405,7 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
   if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_preferred_ranges(p)); return SLIMPIPE_OK; }
   // the tile grid of a chunked call can start up to 255 keys before kv_begin: room for whichever of the
   // two variants asks for more
-  const BwdPlan plan1 = bwd_plan(p, 1, true), plan2 = bwd_plan(p, 2, true);
+  const BwdPlan plan1 = bwd_plan(p, 1, true, SIZE_MAX), plan2 = bwd_plan(p, 2, true, SIZE_MAX);
   const size_t one = split_bytes(p, 1, plan1.split) + dq_parts_bytes(p, plan1.dq_ranges);
   const size_t many = split_bytes(p, 2, plan2.split) + dq_parts_bytes(p, plan2.dq_ranges);
   *bytes = delta_bytes(p) + kTicketBytes + (one > many ? one : many);
@@ -558,15 +593,12 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   const bool ticket = workspace_bytes >= delta_bytes(p) + kTicketBytes;
   const size_t fixed = delta_bytes(p) + (ticket ? kTicketBytes : 0);
   unsigned* const counters = ticket ? reinterpret_cast<unsigned*>(static_cast<char*>(workspace) + delta_bytes(p)) : nullptr;
-  const BwdPlan plan = bwd_plan(p, n_chunks, ticket);
-  int split = plan.split;
-  while (split > 1 && fixed + split_bytes(p, n_chunks, split) > workspace_bytes) split = plan.both ? split - 1 : split / 2;
+  const BwdPlan plan = bwd_plan_within(p, n_chunks, workspace_bytes);
+  const int split = plan.split, dq_ranges = plan.dq_ranges;
   a.n_split = split;
   a.part = reinterpret_cast<float*>(static_cast<char*>(workspace) + fixed);
-  // what is left of the workspace takes the partial dq of as many key ranges as fit
+  // the partial dq behind the partial dk/dv
   const size_t used = fixed + split_bytes(p, n_chunks, split);
-  int dq_ranges = plan.dq_ranges;
-  while (dq_ranges > 1 && (used + dq_parts_bytes(p, dq_ranges) > workspace_bytes || (int64_t)p->batch * dq_ranges > 65535)) --dq_ranges;
   a.n_dq_ranges = dq_ranges;
   for (int r = 0; r < kMaxRanges; ++r) a.dq_range_begin[r] = a.dq_range_end[r] = 0;
   if (dq_ranges > 1) {

@@ -159,3 +159,32 @@ def test_backward_workspace_follows_the_split_policy(sp):
     # (none below 512 tiles); dq in two key ranges
     assert sp.slimpipe_attn_workspace_bytes(params(4096, 8, 1, 31 * 4096, 32 * 4096), True) == \
         stats(4096, 8) + counters + parts(2, 1, 32 * 4096) + 2 * dq_part(4096, 8)
+
+
+@pytest.mark.parametrize("s,Hq,Hkv,D,keys,batch", [(2387, 8, 1, 128, 52005, 1), (777, 8, 1, 128, 33777, 1), (512, 4, 4, 64, 2048, 1),
+                                                  (300, 8, 2, 128, 2560, 1), (1337, 12, 4, 64, 4238, 3), (64, 8, 1, 128, 60000, 1)])
+def test_backward_plan_is_made_for_the_workspace_it_gets(sp, s, Hq, Hkv, D, keys, batch):
+    """A call of few items is cut for the room there is: whatever the workspace, the kind of item that takes longer AS CUT
+    comes first in the launch (times of the items as the library states them), and the cuts fit."""
+    import types
+    q = types.SimpleNamespace(shape=(batch, s, Hq, D), stride=lambda i, st=(s * Hq * D, Hq * D, D, 1): st[i])
+    k = types.SimpleNamespace(shape=(batch, keys, Hkv, D), stride=lambda i, st=(keys * Hkv * D, Hkv * D, D, 1): st[i])
+    p = sp.make_params(q, k, q, keys - s, 0, keys, True, None)
+    stats = 2 * ((batch * Hq * s * 4 + 255) // 256 * 256)
+    full = sp.slimpipe_attn_workspace_bytes(p, True)
+    stream = (s + 31) // 32 * (Hq // Hkv)
+    for room in sorted({stats, stats + 256, full} | {stats + 256 + (full - stats - 256) * i // 8 for i in range(1, 8)}):
+        plan = sp.slimpipe_attn_bwd_plan(p, 1, room)
+        assert plan.one_launch == 1
+        assert plan.dq_items + plan.dkdv_items > 0
+        dq = 8 + (2.4 if D == 128 else 1.4) * keys / 64 / plan.dq_ranges
+        dkdv = 10 + (1.6 if D == 128 else 1.1) * stream / plan.dkdv_split
+        assert plan.dq_first == (1 if dq > dkdv else 0), (room, plan.dkdv_split, plan.dq_ranges)
+        parts = (plan.dkdv_split * 2 * batch * Hkv * ((keys + 255) // 256 * 256) * D * 4 if plan.dkdv_split > 1 else 0) + \
+                (plan.dq_ranges * batch * s * Hq * D * 4 if plan.dq_ranges > 1 else 0)
+        assert stats + (256 if room >= stats + 256 else 0) + parts <= room
+        if room <= stats + 256:
+            assert plan.dkdv_split == 1 and plan.dq_ranges == 1
+    more = sp.slimpipe_attn_bwd_plan(p, 1, 4 * full)
+    assert (more.dkdv_split, more.dq_ranges) == (plan.dkdv_split, plan.dq_ranges), "the query asks for all the room that is used"
+    assert sp.lib.slimpipe_attn_bwd_plan(ctypes.byref(p), 1, stats - 16, ctypes.byref(more)) == -6
