@@ -111,8 +111,8 @@ def main():
     dk_out = torch.empty((1, N, Hkv, D), device=dev, dtype=torch.bfloat16)
     dv_out = torch.empty((1, N, Hkv, D), device=dev, dtype=torch.bfloat16)
     # one workspace for every backward call of the step: the largest any slice asks for
-    ws_bytes = max(sp.slimpipe_attn_workspace_bytes(sp.make_params(q[:, :s], k, outs[0], i * s, 0, (i + 1) * s, True, scale), True)
-                   for i in slices)
+    bwd_params = [sp.make_params(q[:, :s], k, outs[0], i * s, 0, (i + 1) * s, True, scale) for i in slices]
+    ws_bytes = max(sp.slimpipe_attn_workspace_bytes(p, True) for p in bwd_params)
     ws = torch.empty(ws_bytes, device=dev, dtype=torch.uint8)
     # forward: room for partial results when a slice's query blocks would not fill the GPU (0 for the 256K workload)
     fws_bytes = 0 if args.no_fwd_ranges else max(
@@ -201,32 +201,36 @@ def main():
     prof = sp.slimpipe_attn_profile_read()
     sp.slimpipe_attn_profile_enable(False)
 
+    # backward calls of few work items run dq and dk/dv in one launch ("bwd_both"); the others in a launch each
+    one = [sp.slimpipe_attn_bwd_plan(p, n if args.chunked else 1, ws_bytes).one_launch for p in bwd_params]
+    pairs_one = sum(x for x, o in zip(pairs, one) if o)
+    kind_pairs = {"fwd": pairs_total, "dq": pairs_total - pairs_one, "dkdv": pairs_total - pairs_one, "bwd_both": pairs_one}
     # Flop per visible pair and q head, in units of D.  "issued": what each kernel computes (S = QK^T and dP = dO V^T are
     # computed by BOTH backward kernels).  "credited": the 10*D of the backward counted once, the duplicated 4*D split
     # evenly between dq and dk/dv, so that the credited figures add up to the 14*D of `value`.
-    issued = {"fwd": 4.0, "dq": 6.0, "dkdv": 8.0}
-    credited = {"fwd": 4.0, "dq": 4.0, "dkdv": 6.0}
+    issued = {"fwd": 4.0, "dq": 6.0, "dkdv": 8.0, "bwd_both": 14.0}
+    credited = {"fwd": 4.0, "dq": 4.0, "dkdv": 6.0, "bwd_both": 10.0}
     kshare = {kk: prof[kk][0] for kk in issued}
     dom = max(kshare, key=kshare.get)
     dom_ms, dom_n = prof[dom]
-    per_d = D * Hq * pairs_total * args.steps
+    per_pair = D * Hq * args.steps
 
-    def rate(flop_units, ms):
-        return flop_units * per_d / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
+    def rate(flop_units, ms, kind="fwd"):
+        return flop_units * per_pair * kind_pairs[kind] / (ms * 1e-3) / 1e12 if ms > 0 else 0.0
 
-    achieved = rate(credited[dom], dom_ms)
-    bwd_ms = sum(prof[kk][0] for kk in ("delta", "dq", "dq_reduce", "dkdv", "dkdv_reduce"))
+    achieved = rate(credited[dom], dom_ms, dom)
+    bwd_ms = sum(prof[kk][0] for kk in ("delta", "dq", "dq_reduce", "dkdv", "dkdv_reduce", "bwd_both", "both_reduce"))
     roofline = {
         "bound": "mfma", "kernel": dom, "achieved": round(achieved, 1), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
         "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": stored_traffic(c["name"], dom),
         "flop_accounting": "credited: %g*D per visible pair and q head for %s (S and dP, which both backward kernels "
                            "compute, counted once and split between them); the kernel issues %g*D" % (credited[dom], dom, issued[dom]),
-        "achieved_issued": round(rate(issued[dom], dom_ms), 1), "frac_issued": round(rate(issued[dom], dom_ms) / PEAK_BF16_TFLOPS, 4),
+        "achieved_issued": round(rate(issued[dom], dom_ms, dom), 1), "frac_issued": round(rate(issued[dom], dom_ms, dom) / PEAK_BF16_TFLOPS, 4),
         "launches": int(dom_n), "avg_launch_ms": round(dom_ms / max(1, dom_n), 4),
-        "flops_per_launch_avg_credited": credited[dom] * per_d / max(1, dom_n),
+        "flops_per_launch_avg_credited": credited[dom] * per_pair * kind_pairs[dom] / max(1, dom_n),
         "kernel_ms_per_step": {kk: round(prof[kk][0] / args.steps, 3) for kk in prof},
-        "kernel_tflops_issued": {kk: round(rate(issued[kk], prof[kk][0]), 1) for kk in issued if prof[kk][0] > 0},
-        "kernel_tflops_credited": {kk: round(rate(credited[kk], prof[kk][0]), 1) for kk in issued if prof[kk][0] > 0},
+        "kernel_tflops_issued": {kk: round(rate(issued[kk], prof[kk][0], kk), 1) for kk in issued if prof[kk][0] > 0},
+        "kernel_tflops_credited": {kk: round(rate(credited[kk], prof[kk][0], kk), 1) for kk in issued if prof[kk][0] > 0},
         "backward_tflops_10D": round(rate(10.0, bwd_ms), 1),
         "ms_per_step_with_event_bracketing": round(ms_per_step_pass2, 3),
     }

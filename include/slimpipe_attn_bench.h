@@ -13,14 +13,19 @@
 extern "C" {
 #endif
 
-/* Per-kernel timing.  While enabled, every kernel the library enqueues is bracketed by HIP events recorded on
- * the caller's stream.  slimpipe_attn_profile_read waits for the recorded events, adds up the elapsed time per
+/* Per-kernel timing.  While enabled, the kernels of every entry point but slimpipe_attn_bwd_noalloc (and but the
+ * one-workgroup kernel that clears the forward's counters) are bracketed by HIP events recorded on the caller's stream; the
+ * launches are the same as without it.  slimpipe_attn_profile_read waits for the recorded events, adds up the elapsed time per
  * kernel kind since the last read and clears the records.  The records are process-wide and guarded by a mutex:
- * enabling the switch serialises the launches of concurrent host threads. */
+ * enabling the switch serialises the launches of concurrent host threads.  Both arrays of slimpipe_attn_profile_read have
+ * SLIMPIPE_KERNEL_KINDS entries. */
 enum {
   SLIMPIPE_KERNEL_FWD = 0, SLIMPIPE_KERNEL_DELTA = 1, SLIMPIPE_KERNEL_DQ = 2, SLIMPIPE_KERNEL_DKDV = 3,
   SLIMPIPE_KERNEL_MERGE = 4, SLIMPIPE_KERNEL_FINALIZE = 5, SLIMPIPE_KERNEL_DKDV_REDUCE = 6,
-  SLIMPIPE_KERNEL_DQ_REDUCE = 7, SLIMPIPE_KERNEL_KINDS = 8
+  SLIMPIPE_KERNEL_DQ_REDUCE = 7,
+  SLIMPIPE_KERNEL_BWD_BOTH = 8,       /* dq and dk/dv items of a small backward call in one launch */
+  SLIMPIPE_KERNEL_BOTH_REDUCE = 9,    /* the reduce of both, for such a call */
+  SLIMPIPE_KERNEL_KINDS = 10
 };
 int slimpipe_attn_profile_enable(int enable);
 int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t launches[SLIMPIPE_KERNEL_KINDS]);

@@ -334,7 +334,8 @@ def slimpipe_attn_finalize_bf16(acc, dst=None):
     return dst
 
 
-KERNEL_KINDS = ("fwd", "delta", "dq", "dkdv", "merge", "finalize", "dkdv_reduce", "dq_reduce")
+KERNEL_KINDS = ("fwd", "delta", "dq", "dkdv", "merge", "finalize", "dkdv_reduce", "dq_reduce",
+                "bwd_both", "both_reduce")
 
 
 def slimpipe_attn_mfma_rate(random_operands):

@@ -645,8 +645,11 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (timed(SLIMPIPE_KERNEL_DELTA, st, [&] { return launch_delta(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
-  if (plan.both && !(events && g_prof_on.load(std::memory_order_relaxed))) {      // (per-kernel times: one kernel at a time)
-    if (launch_bwd_both(a, p->head_dim, st) != hipSuccess || launch_both_reduce(a, p->batch, p->head_dim, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
+  if (plan.both) {
+    if (timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_both(a, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
+    if ((split > 1 || dq_ranges > 1) &&
+        timed(SLIMPIPE_KERNEL_BOTH_REDUCE, st, [&] { return launch_both_reduce(a, p->batch, p->head_dim, st); }, events) != hipSuccess)
+      return SLIMPIPE_ELAUNCH;
     return SLIMPIPE_OK;
   }
   if (timed(SLIMPIPE_KERNEL_DQ, st, [&] { return launch_bwd_dq(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
