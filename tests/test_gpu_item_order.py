@@ -10,9 +10,12 @@ from gpu_util import say
 pytestmark = pytest.mark.gpu
 
 
-# (batch, rows, prefix, q heads, kv heads): 8 groups exactly, a count that is no multiple of 8, one block per group
-@pytest.mark.parametrize("B,s,N,Hq,Hkv", [(1, 2304, 2304, 32, 8), (3, 1280, 1536, 21, 21), (1, 200, 456, 300, 300)])
-def test_every_item_is_computed_once(B, s, N, Hq, Hkv):
+# (batch, rows, prefix, q heads, kv heads, backward through the counters): 8 groups exactly, with heads that share keys (the
+# backward of the first is small enough for the one launch without counters, that of the second is not), a count that is no
+# multiple of 8, one block per group
+@pytest.mark.parametrize("B,s,N,Hq,Hkv,counted", [(1, 2304, 2304, 32, 8, False), (1, 4096, 4096, 32, 8, True), (3, 1280, 1536, 21, 21, True),
+                                                  (1, 200, 456, 300, 300, True)])
+def test_every_item_is_computed_once(B, s, N, Hq, Hkv, counted):
     import torch
     import paper_2504_14519_amd as sp
     D, scale, G = 64, 0.125, Hq // Hkv
@@ -26,10 +29,15 @@ def test_every_item_is_computed_once(B, s, N, Hq, Hkv):
     dk, dv = torch.zeros((B, N, Hkv, D), device="cuda:0"), torch.zeros((B, N, Hkv, D), device="cuda:0")
     dq = sp.slimpipe_attn_bwd(q, k, v, o, do, l, N - s, 0, N, dk, dv, True, scale, dkv_accumulate=False, workspace=wsb)
     torch.cuda.synchronize()
+    plan = sp.slimpipe_attn_bwd_plan(sp.make_params(q, k, o, N - s, 0, N, True, scale), 1, wsb.numel())
+    assert plan.dkdv_split == 1 and plan.dq_ranges == 1 and plan.dq_items > plan.compute_units      # (the forward's items are as many)
+    assert plan.one_launch == (0 if counted else 1) and B * Hkv >= 8
     for h in range(0, Hkv, max(1, Hkv // 7)):       # one K/V head at a time: few items, no counters
         qs, ks = slice(h * G, (h + 1) * G), slice(h, h + 1)
         o1, l1 = sp.slimpipe_attn_fwd(q[:, :, qs], k[:, :, ks], v[:, :, ks], N - s, 0, N, True, scale)
         assert torch.equal(o[:, :, qs], o1) and torch.equal(l[:, qs], l1), h
+        p1 = sp.make_params(q[:, :, qs], k[:, :, ks], o1, N - s, 0, N, True, scale)
+        assert sp.slimpipe_attn_bwd_plan(p1, 1, 1 << 40).one_launch == 1
         w1 = torch.empty(2 * ((B * G * s * 4 + 255) // 256 * 256), device="cuda:0", dtype=torch.uint8)
         # (the key/value strides of the one-head views are those of the whole cache, and so are the accumulators')
         dkf, dvf = torch.zeros_like(dk), torch.zeros_like(dv)
