@@ -271,7 +271,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
     const bool copies_k = !group_b;
     const bf16_t* const* table = copies_k ? a.kv.k : a.kv.v;
     KvWalk walk;             // the next tile this group copies
-    walk.seek(table, a.kv, lo, head_off, a.kv_stride_s);
+    walk.seek(table, a.kv, kv_chunk_of(a.kv, lo), lo, head_off, a.kv_stride_s);
     const int64_t kv_tile_step = (int64_t)BN * a.kv_stride_s;
     struct CopyJob { const bf16_t* src; unsigned dst; int rows; };
     // tile t (the one the walk stands on) of K (slot t % KSLOTS) or V (slot t % VSLOTS); the walk moves on
@@ -281,7 +281,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
       j.src = walk.ptr;
       j.dst = smem_lds + (copies_k ? K_BASE + (t % KSLOTS) * TILE_BYTES : V_BASE + (t % VSLOTS) * TILE_BYTES);
       j.rows = walk.rows(BN);
-      if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s);
+      if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s, [&] { return key0_of(t + 1); });
       return j;
     };
     auto copy_pass = [&](const CopyJob& j, int n) { dma.issue(j.dst, j.src, row_bytes, j.rows, gwave_u, n); };

@@ -252,31 +252,40 @@ struct TileDma {
 
 // Walks the key tiles of a chunked K/V prefix in increasing order: where the tile "now" starts.  All
 // members are uniform.  A step is a few 32-bit scalar instructions (a wave issues in order: scalar work of a tile delays the
-// vector work behind it); the chunk's base pointer (a scalar load from the kernel arguments) and the product row * stride
-// are needed only when the walk enters a new chunk.
+// vector work behind it); the chunk's base pointer (a scalar load from the kernel arguments) and 64-bit products are needed
+// only when the walk comes to the end of a chunk, or of the rows that `left` can count (a chunk may have more).
 struct KvWalk {
   const bf16_t* ptr;       // first row of the tile (batch and head offset included)
-  int chunk, left;         // current chunk, its rows from the tile's first row on (a chunk has fewer than 2^31 rows)
-  SP_DEV void seek(const bf16_t* const* table, const KvChunks& kv, int64_t key0, int64_t head_off, int64_t stride_s) {
-    chunk = kv.n > 1 ? __builtin_amdgcn_readfirstlane((int)(key0 / kv.len)) : 0;
-    const int row = (int)(key0 - (int64_t)chunk * kv.len);
-    left = (int)(kv.len - row < 0x7fffffff ? kv.len - row : 0x7fffffff);
-    ptr = table[chunk] + head_off + (int64_t)row * stride_s;
+  int chunk, left;         // current chunk, its rows from the tile's first row on as far as 31 bits count them
+  __host__ __device__ __forceinline__ void seek(const bf16_t* const* table, const KvChunks& kv, int at_chunk, int64_t key0, int64_t head_off,
+                                                int64_t stride_s) {
+    chunk = at_chunk;      // key0 / kv.len (0 when there is one chunk)
+    const int64_t row = key0 - (int64_t)chunk * kv.len;
+    left = count(kv.len - row);
+    ptr = table[chunk] + head_off + row * stride_s;
   }
-  // to the next tile; tile_step = tile * stride_s
-  SP_DEV void step(const bf16_t* const* table, const KvChunks& kv, int tile, int64_t tile_step, int64_t head_off, int64_t stride_s) {
+  // to the next tile, whose first key is key_of_next(); tile_step = tile * stride_s
+  template <class F>
+  __host__ __device__ __forceinline__ void step(const bf16_t* const* table, const KvChunks& kv, int tile, int64_t tile_step, int64_t head_off,
+                                                int64_t stride_s, F&& key_of_next) {
     left -= tile;
     ptr += tile_step;
-    if (left <= 0 && chunk + 1 < kv.n) {
-      ++chunk;
-      const int row = -left;
-      left += (int)kv.len;
-      ptr = table[chunk] + head_off + (int64_t)row * stride_s;
+    if (left < tile) {
+      int64_t row = key_of_next() - (int64_t)chunk * kv.len;
+      if (row >= kv.len && chunk + 1 < kv.n) {
+        ++chunk;
+        row -= kv.len;
+        ptr = table[chunk] + head_off + row * stride_s;
+      }
+      left = count(kv.len - row);
     }
   }
   // rows of the chunk from the tile's first row on, at most `tile`
-  SP_DEV int rows(int tile) const { return left > tile ? tile : left; }
+  __host__ __device__ __forceinline__ int rows(int tile) const { return left > tile ? tile : left; }
+  static __host__ __device__ __forceinline__ int count(int64_t rows) { return (int)(rows < 0x7fffffff ? rows : 0x7fffffff); }
 };
+// Chunk of a key, uniform.
+SP_DEV int kv_chunk_of(const KvChunks& kv, int64_t key) { return kv.n > 1 ? __builtin_amdgcn_readfirstlane((int)(key / kv.len)) : 0; }
 
 // vmcnt(0), other counters untouched (gfx9 encoding: vmcnt[3:0]|[15:14], expcnt[6:4], lgkmcnt[11:8]).
 SP_DEV void wait_async() { __builtin_amdgcn_s_waitcnt(0x0F70); }
