@@ -42,3 +42,19 @@ def test_merge_of_n_parts(n, f32):
     # weights of exponents up to ~30 good to 30 * 2^-23 each, at most 16 terms of at most ~5
     assert np.isfinite(o).all() and np.abs(o - ref).max() <= 1e-4
     assert np.abs(o[:, 5]).max() == 0.0
+
+
+@pytest.mark.parametrize("n", [1, 3, 6])
+def test_rows_without_a_weight(n):
+    """No part has a weight above zero: -inf in all, or not a number in some and -inf in the rest.  The row is 0, lse -inf."""
+    import torch
+    import paper_2504_14519_amd as sp
+    B, s, H, D = 1, 70, 2, 64
+    say("merge of %d parts without a weight" % n)
+    outs = [torch.ones((B, s, H, D), device="cuda:0") for _ in range(n)]
+    lses = [torch.full((B, H, s), -math.inf, device="cuda:0") for _ in range(n)]
+    lses[0][:, :, 3:40] = math.nan
+    lses[-1][:, :, 30:50] = math.nan
+    out, lse = sp.slimpipe_attn_merge(outs, lses, out_dtype=sp.F32)
+    torch.cuda.synchronize()
+    assert (out == 0).all() and (lse == -math.inf).all()
