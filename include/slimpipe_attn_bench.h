@@ -33,7 +33,7 @@ int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t l
 /* How slimpipe_attn_bwd (n_chunks = 1) or slimpipe_attn_bwd_chunked would cut a call into work items with a workspace of
  * workspace_bytes (slimpipe_attn_bwd_noalloc: the two row statistics + 256 bytes).  Host code only, nothing is launched. */
 typedef struct slimpipe_bwd_plan {
-  int32_t one_launch;      /* dq and dk/dv items in one launch (fewer than two items per compute unit before any cut) */
+  int32_t one_launch;      /* dq and dk/dv items in one launch */
   int32_t dq_first;        /* in that launch the dq items come first */
   int32_t dkdv_split;      /* chunks of a key tile's query stream */
   int32_t dq_ranges;       /* key ranges of a query block */

@@ -221,8 +221,8 @@ double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb
 // cuts that finish first by the times below; a larger one runs them one after the other through the ticket counters.
 // Microseconds measured on MI355X: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64), a dk/dv item
 // about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its bytes at 5 TB/s.
-// The partial sums of the cuts take at most `room` bytes: a small call chooses among the pairs that fit, a large one takes
-// first as many chunks and then as many key ranges as fit.
+// The partial sums of the cuts take at most `room` bytes (SIZE_MAX: all that are wanted): a small call chooses among the
+// pairs that fit, a large one takes first as many chunks and then as many key ranges as fit.
 BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_t room) {
   const int64_t cus = compute_units();
   const int64_t wq = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
@@ -247,10 +247,18 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
       if (split_bytes(p, n_chunks, s) + dq_parts_bytes(p, r) > room) break;       // (1, 1) needs none
       const double tq = 8 + dq_tile * dq_tiles / r, tk = 10 + dkdv_tile * stream / s;
       double us = tq > tk ? list_makespan(cus, wq * r, tq, wk * s, tk) : list_makespan(cus, wk * s, tk, wq * r, tq);
+      // Where no cut fits and the items are long, one launch can have as long a tail as two, and then two are faster: a
+      // kind that has part of a power-limited chip to itself runs at a higher clock (dq items alone on 128 of 256 units take 0.55
+      // of the time above).  Measured without cuts, two launches / one: 2856 / 3094, 759 / 788, 4332 / 4669, 4029 / 4178 us
+      // where the model gives one launch 0.87, 0.96, 1.00, 1.00 of two; at 0.63 to 0.80 of it one is faster by 9 to 48 %, and by
+      // up to 11 % where items are short.  With a cut of either kind two launches were never faster.
+      bool both = true;
+      if (room != SIZE_MAX && s == 1 && r == 1 && tq >= 300 && tk >= 300)
+        both = us <= 0.85 * (list_makespan(cus, wq, tq, 0, 0) + list_makespan(cus, wk, tk, 0, 0));
       double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
       if (r > 1) bytes += (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4;
       if (bytes > 0) us += 4 + bytes / 5e6;
-      if (us < best_us * 0.99) { best_us = us; best = {s, r, true, tq > tk}; }
+      if (us < best_us * 0.99) { best_us = us; best = {s, r, both, tq > tk}; }
     }
   }
   return best;

@@ -188,3 +188,17 @@ def test_backward_plan_is_made_for_the_workspace_it_gets(sp, s, Hq, Hkv, D, keys
     more = sp.slimpipe_attn_bwd_plan(p, 1, 4 * full)
     assert (more.dkdv_split, more.dq_ranges) == (plan.dkdv_split, plan.dq_ranges), "the query asks for all the room that is used"
     assert sp.lib.slimpipe_attn_bwd_plan(ctypes.byref(p), 1, stats - 16, ctypes.byref(more)) == -6
+
+
+@pytest.mark.parametrize("s,Hq,Hkv,D,keys,batch,one", [(4096, 8, 1, 128, 57344, 1, 0), (8192, 8, 1, 128, 49152, 1, 0), (6000, 8, 1, 128, 60000, 1, 0),
+                                                      (1608, 8, 1, 64, 22396, 2, 0), (3343, 8, 2, 128, 31065, 1, 1), (1989, 16, 16, 128, 2563, 1, 1)])
+def test_backward_without_room_for_cuts_takes_the_faster_launches(sp, s, Hq, Hkv, D, keys, batch, one):
+    """Long undivided items that one launch cannot even out run as two launches (measured: 3 to 8 % faster there); with the
+    workspace the library asks for the same calls are cut and take one."""
+    import types
+    q = types.SimpleNamespace(shape=(batch, s, Hq, D), stride=lambda i, st=(s * Hq * D, Hq * D, D, 1): st[i])
+    k = types.SimpleNamespace(shape=(batch, keys, Hkv, D), stride=lambda i, st=(keys * Hkv * D, Hkv * D, D, 1): st[i])
+    p = sp.make_params(q, k, q, keys - s, 0, keys, True, None)
+    least = sp.slimpipe_attn_bwd_plan(p, 1, 2 * ((batch * Hq * s * 4 + 255) // 256 * 256) + 256)
+    assert (least.one_launch, least.dkdv_split, least.dq_ranges) == (one, 1, 1)
+    assert sp.slimpipe_attn_bwd_plan(p, 1, sp.slimpipe_attn_workspace_bytes(p, True)).one_launch == 1
