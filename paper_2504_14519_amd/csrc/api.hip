@@ -134,12 +134,36 @@ double visible_pairs_upto(const slimpipe_attn_params* p, int64_t e) {
   return full + (cnt > 0 ? 0.5 * cnt * (first + last) : 0.0);
 }
 
+// How the query rows are cut into blocks (see kernels.hpp) for a call on `keys` keys that may be cut into up to `ranges` key
+// ranges.  Heads are packed where that takes a tenth of the blocks or more, the blocks (times the ranges) fill the chip, so that
+// fewer blocks are fewer rounds or more ranges, and little of the work is at the causal diagonal: a block that holds the end
+// of one head and the start of the next walks the keys of the one with masked tiles for the other (about 1.1 us per 128-key
+// tile of the forward), and on an idle chip 8 full waves load and store 2 to 3 us longer than 2.  Packed against padded over
+// 160 shapes: where the rule packs, forward 0.68 to 1.00 and backward call 0.69 to 1.00 of the time (777 rows on 33777 keys 0.88
+// and 0.86); packing everything costs up to 1.45 (4679 rows on 8817 keys, 4/1 heads of 64: 87 against 127 us).
+int head_waves_of(const slimpipe_attn_params* p, int64_t keys, int ranges) {
+  const int packed = packed_head_waves(p->s_q), padded = padded_head_waves(p->s_q), group = p->n_q_heads / p->n_kv_heads;
+  const int64_t rows_packed = query_blocks(packed, group), rows_padded = query_blocks(padded, group);
+  const bool pack = 10 * rows_packed <= 9 * rows_padded && (!p->causal || keys >= 12 * (int64_t)p->s_q) &&
+                    rows_padded * p->n_kv_heads * p->batch * ranges >= compute_units();
+  return pack ? packed : padded;
+}
+// Key ranges of at least min_keys a call can be cut into.
+int most_ranges(const slimpipe_attn_params* p, int64_t min_keys) {
+  const int64_t r = (p->kv_end - p->kv_begin) / min_keys;
+  return r < 1 ? 1 : (r > kMaxRanges ? kMaxRanges : (int)r);
+}
+constexpr int64_t min_range_keys(int head_dim) { return head_dim == 64 ? 256 : 1024; }
+int64_t all_query_blocks(const slimpipe_attn_params* p, int head_waves) {
+  return query_blocks(head_waves, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
+}
+
 // One forward workgroup owns 256 query rows and walks the whole key range; a short slice over a
 // long cache leaves compute units idle.  Cutting the key range into R ranges of equal work (one launch,
 // partial (out, lse) per range, then the online-softmax merge) makes R times the workgroups: R is the
 // smallest count that comes within 3% of the best rounds/R, as long as a range keeps at least 1024 keys.
-int fwd_preferred_ranges(const slimpipe_attn_params* p) {
-  const int64_t w = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
+int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
+  const int64_t w = all_query_blocks(p, head_waves);
   const int64_t keys = p->kv_end - p->kv_begin;
   if (w <= 0 || keys <= 0) return 1;
   const int cus = compute_units();
@@ -152,7 +176,7 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p) {
     const bool d64 = p->head_dim == 64;
     int pick = 1;
     double best_us = 1e30;
-    for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= (d64 ? 256 : 1024)) && (int64_t)p->batch * r <= 65535; ++r) {
+    for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
       const double us = (double)((w * r + cus - 1) / cus) * (10.0 + (d64 ? 1.8 : 2.5) * (double)keys / (128.0 * r)) +
                         (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
       if (us < best_us * 0.97) { best_us = us; pick = r; }
@@ -182,6 +206,17 @@ size_t fwd_part_out_bytes(const slimpipe_attn_params* p) {
 size_t fwd_parts_bytes(const slimpipe_attn_params* p, int ranges) {
   return ranges <= 1 ? 0 : (size_t)ranges * (fwd_part_out_bytes(p) + stat_bytes(p));
 }
+struct FwdPlan {
+  int head_waves;    // of the query blocks
+  int ranges;        // key ranges
+};
+// The forward's plan when the partial results of the ranges take at most `room` bytes.
+FwdPlan fwd_plan(const slimpipe_attn_params* p, size_t room) {
+  const int hw = head_waves_of(p, p->kv_end - p->kv_begin, fwd_parts_bytes(p, 2) > room ? 1 : most_ranges(p, min_range_keys(p->head_dim)));
+  int ranges = fwd_preferred_ranges(p, hw);
+  while (ranges > 1 && (fwd_parts_bytes(p, ranges) > room || (int64_t)p->batch * ranges > 65535)) --ranges;
+  return {hw, ranges};
+}
 // The dq kernel has the forward's launch shape and is cut into key ranges the same way; its partial results are
 // float32 [range][batch, s_q, heads, head_dim].
 size_t dq_parts_bytes(const slimpipe_attn_params* p, int ranges) {
@@ -190,6 +225,7 @@ size_t dq_parts_bytes(const slimpipe_attn_params* p, int ranges) {
 
 // ---- the backward's launches -------------------------------------------------------------------------
 struct BwdPlan {
+  int head_waves;    // of the dq query blocks
   int split;         // chunks of a key tile's query stream
   int dq_ranges;     // key ranges of the dq items
   bool both;         // dq and dk/dv items in one launch
@@ -225,10 +261,11 @@ double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb
 // pairs that fit, a large one takes first as many chunks and then as many key ranges as fit.
 BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_t room) {
   const int64_t cus = compute_units();
-  const int64_t wq = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
+  const int hw = head_waves_of(p, p->kv_end - p->kv_begin, dq_parts_bytes(p, 2) > room ? 1 : most_ranges(p, 256));
+  const int64_t wq = all_query_blocks(p, hw);
   const int64_t wk = dkdv_key_tiles(p, n_chunks) * p->n_kv_heads * p->batch;
   if (wk <= 0 || wq + wk >= 2 * cus) {
-    BwdPlan plan{preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p), false, false};
+    BwdPlan plan{hw, preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p, hw), false, false};
     while (plan.split > 1 && split_bytes(p, n_chunks, plan.split) > room) plan.split /= 2;
     const size_t used = split_bytes(p, n_chunks, plan.split);
     while (plan.dq_ranges > 1 && (dq_parts_bytes(p, plan.dq_ranges) > room - used || (int64_t)p->batch * plan.dq_ranges > 65535)) --plan.dq_ranges;
@@ -238,7 +275,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
   const double dq_tiles = (double)keys / 64, dq_tile = p->head_dim == 128 ? 2.4 : 1.4;
   const double stream = (double)(((int64_t)p->s_q + 31) / 32 * (p->n_q_heads / p->n_kv_heads)), dkdv_tile = p->head_dim == 128 ? 1.6 : 1.1;
   static const int kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  BwdPlan best{1, 1, true, false};
+  BwdPlan best{hw, 1, 1, true, false};
   double best_us = 1e30;
   for (int s : kCuts) {
     if (s > 8 || (s > 1 && stream / s < 4)) break;             // a chunk keeps at least 4 query tiles
@@ -258,7 +295,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
       double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
       if (r > 1) bytes += (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4;
       if (bytes > 0) us += 4 + bytes / 5e6;
-      if (us < best_us * 0.99) { best_us = us; best = {s, r, both, tq > tk}; }
+      if (us < best_us * 0.99) { best_us = us; best = {hw, s, r, both, tq > tk}; }
     }
   }
   return best;
@@ -373,7 +410,7 @@ int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size
   out->dkdv_split = plan.split;
   out->dq_ranges = plan.dq_ranges;
   out->dkdv_items = dkdv_key_tiles(p, n_chunks) * plan.split * p->n_kv_heads * p->batch;
-  out->dq_items = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch * plan.dq_ranges;
+  out->dq_items = all_query_blocks(p, plan.head_waves) * plan.dq_ranges;
   out->compute_units = compute_units();
   return SLIMPIPE_OK;
 }
@@ -410,7 +447,7 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
   if (!bytes) return SLIMPIPE_EINVAL_NULL;
   int rc = slimpipe_attn_validate(p, is_bwd);
   if (rc != SLIMPIPE_OK) return rc;
-  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_preferred_ranges(p)); return SLIMPIPE_OK; }
+  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_plan(p, SIZE_MAX).ranges); return SLIMPIPE_OK; }
   // the tile grid of a chunked call can start up to 255 keys before kv_begin: room for whichever of the
   // two variants asks for more
   const BwdPlan plan1 = bwd_plan(p, 1, true, SIZE_MAX), plan2 = bwd_plan(p, 2, true, SIZE_MAX);
@@ -427,7 +464,8 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
 static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const void* const* k_chunks,
                     const void* const* v_chunks, int32_t n_chunks, int64_t chunk_len, int32_t n_ranges,
                     const int64_t* range_begin, const int64_t* range_end, float* part_out, int64_t part_out_elems,
-                    float* part_lse, int64_t part_lse_elems, void* out, float* lse, void* hip_stream, unsigned* ticket = nullptr) {
+                    float* part_lse, int64_t part_lse_elems, void* out, float* lse, void* hip_stream, unsigned* ticket = nullptr,
+                    int head_waves = 0) {      // (0: chosen here)
   int rc = slimpipe_attn_validate(p, 0);
   if (rc != SLIMPIPE_OK) return rc;
   const bool parts = part_out != nullptr;
@@ -441,7 +479,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (parts && (!aligned16(part_out) || (reinterpret_cast<uintptr_t>(part_lse) & 3u) || part_out_elems % 4 != 0)) return SLIMPIPE_EINVAL_ALIGN;
   FwdArgs a;
   memset(&a.kv, 0, sizeof(a.kv));
-  int64_t last_key = 0;
+  int64_t last_key = 0, keys = 0;
   for (int r = 0; r < kMaxRanges; ++r) {
     a.range_begin[r] = a.range_end[r] = 0;
     if (r >= n_ranges) continue;
@@ -449,6 +487,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     a.range_begin[r] = range_begin[r];
     a.range_end[r] = range_end[r];
     if (range_end[r] > last_key) last_key = range_end[r];
+    keys += range_end[r] - range_begin[r];
   }
   for (int i = 0; i < n_chunks; ++i) {
     if (last_key > 0 && (!k_chunks[i] || !v_chunks[i])) return SLIMPIPE_EINVAL_NULL;
@@ -475,7 +514,8 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     a.out_range_stride = 0; a.lse_range_stride = 0;
     a.o_stride_b = p->o_stride_b; a.o_stride_s = p->o_stride_s; a.o_stride_h = p->o_stride_h;
   }
-  const int64_t blocks = query_blocks(p->s_q, a.group);
+  a.head_waves = head_waves ? head_waves : head_waves_of(p, keys, n_ranges);
+  const int64_t blocks = query_blocks(a.head_waves, a.group);
   if (blocks * p->n_kv_heads * p->batch * n_ranges > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.items[0] = (int32_t)blocks;
   a.items[1] = p->n_kv_heads;
@@ -518,18 +558,18 @@ static int fwd_auto(const slimpipe_attn_params* p, const void* q_slice, const vo
   unsigned* ticket = (workspace && workspace_bytes >= kTicketBytes) ? static_cast<unsigned*>(workspace) : nullptr;
   char* parts_base = ticket ? static_cast<char*>(workspace) + kTicketBytes : static_cast<char*>(workspace);
   const size_t parts_room = ticket ? workspace_bytes - kTicketBytes : workspace_bytes;
-  int ranges = workspace ? fwd_preferred_ranges(p) : 1;
-  while (ranges > 1 && (fwd_parts_bytes(p, ranges) > parts_room || (int64_t)p->batch * ranges > 65535)) --ranges;
+  const FwdPlan plan = fwd_plan(p, workspace ? parts_room : 0);
+  const int ranges = plan.ranges;
   if (ranges <= 1)
     return fwd_impl(p, q_slice, k_chunks, v_chunks, n_chunks, chunk_len, 1, &p->kv_begin, &p->kv_end, nullptr, 0, nullptr, 0, out,
-                    lse, hip_stream, ticket);
+                    lse, hip_stream, ticket, plan.head_waves);
   int64_t begin[kMaxRanges], end[kMaxRanges];
   equal_work_ranges(p, ranges, begin, end);
   float* part_out = reinterpret_cast<float*>(parts_base);
   float* part_lse = reinterpret_cast<float*>(parts_base + (size_t)ranges * fwd_part_out_bytes(p));
   return fwd_impl(p, q_slice, k_chunks, v_chunks, n_chunks, chunk_len, ranges, begin, end, part_out,
                   (int64_t)(fwd_part_out_bytes(p) / sizeof(float)), part_lse, (int64_t)(stat_bytes(p) / sizeof(float)), out, lse,
-                  hip_stream, ticket);
+                  hip_stream, ticket, plan.head_waves);
 }
 
 int slimpipe_attn_fwd(const slimpipe_attn_params* p, const void* q_slice, const void* k_prefix,
@@ -626,7 +666,8 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   a.dkdv_items[0] = (int32_t)(dkdv_key_tiles(p, n_chunks) * split);
   a.dkdv_items[1] = p->n_kv_heads;
   a.dkdv_items[2] = p->batch;
-  const int64_t blocks = query_blocks(p->s_q, p->n_q_heads / p->n_kv_heads);
+  a.head_waves = plan.head_waves;
+  const int64_t blocks = query_blocks(plan.head_waves, p->n_q_heads / p->n_kv_heads);
   if (blocks * p->n_kv_heads * p->batch * dq_ranges > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.dq_items[0] = (int32_t)blocks;
   a.dq_items[1] = p->n_kv_heads;

@@ -221,7 +221,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
   const int qblk = a.dq_items[0] - 1 - bx;
   const int b = bz / a.n_dq_ranges, r = bz - b * a.n_dq_ranges;
   const int64_t kv_begin = a.dq_range_begin[r], kv_end = a.dq_range_end[r];      // this workgroup's key range
-  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group);
+  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group, a.head_waves);
   const int h = wr.h, wrow0 = wr.row0;
   const int myrow = wrow0 + ql;
   const int myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
@@ -245,7 +245,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
   const int64_t lo = kv_grid_origin(kv_begin, a.kv.n, BN);     // first key of the tile grid
   int64_t hi = kv_end;
   if (a.causal) {
-    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q);
+    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q, a.head_waves);
     hi = hi < lim ? hi : lim;
   }
   const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
@@ -318,7 +318,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
         // rows 32 w .. 32 w + 31 of the LDS block are those of wave w; the rows this wave copies in pass n belong to
         // one of them.  The base is moved so that LDS row j is its row j (clamped to the slice, as everywhere).
         const int w = (n * TileDma<D, BM, T>::RPP + wave_u * (TileDma<D, BM, T>::RPP / NW)) / 32;
-        const WaveRows dr = wave_rows(qblk, w, hk, a.s_q, a.group);
+        const WaveRows dr = wave_rows(qblk, w, hk, a.s_q, a.group, a.head_waves);
         const bf16_t* base = dobase + (int64_t)dr.h * a.do_stride_h + (int64_t)(dr.row0 - 32 * w) * a.do_stride_s;
         dma_do.issue(smem_lds + DO_BASE, base, (uint32_t)a.do_stride_s * 2, a.s_q - dr.row0 + 32 * w, wave_u, n);
       }

@@ -242,7 +242,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int qblk = a.items[0] - 1 - bx;
   const int b = bz / a.n_ranges, r = bz - b * a.n_ranges;
   const int64_t kv_begin = a.range_begin[r], kv_end = a.range_end[r];      // this workgroup's key range
-  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group);
+  const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group, a.head_waves);
   const int h = wr.h, wrow0 = wr.row0;
   const int myrow = wrow0 + ql;
   const int myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int64_t lo = kv_grid_origin(kv_begin, a.kv.n, BN);     // first key of the tile grid
   int64_t hi = kv_end;
   if (a.causal) {
-    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q);
+    const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q, a.head_waves);
     hi = hi < lim ? hi : lim;
   }
   const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;

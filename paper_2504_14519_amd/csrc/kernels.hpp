@@ -29,12 +29,12 @@ inline __host__ __device__ int64_t kv_grid_origin(int64_t kv_begin, int32_t n_ch
 constexpr int kMaxRanges = 16;
 
 // Query blocks.  A forward / dq workgroup is 8 waves of 32 query rows.  The waves of all query heads that share a
-// K/V head are numbered through (ceil(s_q / 32) per head) and cut into blocks of 8, so that only the last block of a
-// K/V head can hold waves without rows: with whole 256-row blocks per head a slice of 777 rows and 8 heads on one K/V
-// head was 32 blocks of which 24 % were padding, and is 25 blocks now.  Slices of a multiple of 256 rows, and heads with
-// K/V of their own, get the blocks they always had.
-inline __host__ __device__ int waves_per_head(int s_q) { return (int)(((unsigned)s_q + 31u) / 32u); }
-inline __host__ __device__ int64_t query_blocks(int s_q, int group) { return ((int64_t)group * waves_per_head(s_q) + 7) / 8; }
+// K/V head are numbered through, head_waves per head, and cut into blocks of 8.  head_waves is the host's choice: a multiple of
+// 8 gives every head blocks of its own, the last one with waves past the slice; ceil(s_q / 32) packs the heads, so that only
+// the last block of a K/V head can hold waves without rows (777 rows, 8 heads on one K/V head: 25 blocks instead of 32).
+inline __host__ __device__ int packed_head_waves(int s_q) { return (int)(((unsigned)s_q + 31u) / 32u); }
+inline __host__ __device__ int padded_head_waves(int s_q) { return (int)(((unsigned)s_q + 255u) / 256u * 8u); }
+inline __host__ __device__ int64_t query_blocks(int head_waves, int group) { return ((int64_t)group * head_waves + 7) / 8; }
 
 struct FwdArgs {
   const __bf16* q;
@@ -51,6 +51,7 @@ struct FwdArgs {
   unsigned* ticket;
   int32_t items[3];
   int32_t items_by_group;      // an XCD takes all query blocks of a (head, batch index x range) (see next_item)
+  int32_t head_waves;          // of the query blocks
   int64_t q_offset, kv_capacity;
   float scale_log2e;
   int64_t q_stride_b, q_stride_s, q_stride_h;
@@ -94,6 +95,7 @@ struct BwdArgs {
   int32_t dkdv_wgs;
   int32_t dkdv_items[3];
   int32_t items_by_group;   // of the dq launch, as in FwdArgs
+  int32_t head_waves;       // of the dq query blocks, as in FwdArgs
   int32_t dq_first;         // dq and dk/dv in one launch: the dq items come first
   int32_t dq_items[3];      // dq work items = (query block, kv head, batch index x key range), handed out the same way
   int32_t s_q, n_q_heads, n_kv_heads, group, causal;

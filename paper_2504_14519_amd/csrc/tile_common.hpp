@@ -294,15 +294,15 @@ SP_DEV void wait_async() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 // gets rows past the end of the slice.  Heads ascend and rows descend with decreasing block number, so that
 // the blocks with the longest key ranges of a head come first when the blocks are started from the last one.
 struct WaveRows { int h, row0; };
-SP_DEV WaveRows wave_rows(int qblk, int wave_u, int hk, int s_q, int group) {
-  const unsigned per = (unsigned)waves_per_head(s_q), slot = (unsigned)qblk * 8u + (unsigned)wave_u;
+SP_DEV WaveRows wave_rows(int qblk, int wave_u, int hk, int s_q, int group, int head_waves) {
+  const unsigned per = (unsigned)head_waves, slot = (unsigned)qblk * 8u + (unsigned)wave_u;
   const int hg = __builtin_amdgcn_readfirstlane((int)(slot / per));
   if (hg >= group) return {hk * group, s_q};
   return {hk * group + group - 1 - hg, (int)(slot - (unsigned)hg * per) * 32};
 }
 // One past the last row that any wave of a query block holds (a block that reaches the end of a head: s_q).
-SP_DEV int block_row_end(int qblk, int s_q) {
-  const unsigned per = (unsigned)waves_per_head(s_q), slot = (unsigned)qblk * 8u;
+SP_DEV int block_row_end(int qblk, int s_q, int head_waves) {
+  const unsigned per = (unsigned)head_waves, slot = (unsigned)qblk * 8u;
   const unsigned end = (slot - (unsigned)__builtin_amdgcn_readfirstlane((int)(slot / per)) * per + 8u) * 32u;
   return end < (unsigned)s_q ? (int)end : s_q;
 }
