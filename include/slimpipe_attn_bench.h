@@ -39,6 +39,7 @@ typedef struct slimpipe_bwd_plan {
   int32_t dq_ranges;       /* key ranges of a query block */
   int64_t dkdv_items, dq_items;
   int32_t compute_units;   /* of the current device (256 where no device can be asked) */
+  int32_t dq_by_xcd;       /* the dq items that share keys are dealt to one XCD */
 } slimpipe_bwd_plan;
 int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_bwd_plan* plan);
 

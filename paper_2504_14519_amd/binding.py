@@ -34,7 +34,7 @@ class AttnParams(ctypes.Structure):
 class BwdPlan(ctypes.Structure):
     _fields_ = [
         ("one_launch", ctypes.c_int32), ("dq_first", ctypes.c_int32), ("dkdv_split", ctypes.c_int32), ("dq_ranges", ctypes.c_int32),
-        ("dkdv_items", ctypes.c_int64), ("dq_items", ctypes.c_int64), ("compute_units", ctypes.c_int32),
+        ("dkdv_items", ctypes.c_int64), ("dq_items", ctypes.c_int64), ("compute_units", ctypes.c_int32), ("dq_by_xcd", ctypes.c_int32),
     ]
 
 

@@ -193,11 +193,15 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
     if (cost[r] <= best * 1.03) return r;
   return 1;
 }
-// Whether the query blocks that share keys go to one XCD (next_item): where at least 8 groups of them read keys of their
-// own, so that every XCD has one; with fewer, an XCD would be without, and the keys of so few groups are streamed by
-// all L2s at a rate the memory-side cache does not notice (0.2 TB/s at one K/V head against 2.4 at 40).
-bool items_by_group(const slimpipe_attn_params* p, int ranges) {
-  return (int64_t)p->n_kv_heads * p->batch * ranges >= 8;
+// Whether the query blocks that share keys go to one XCD (next_item).  At least 8 groups of them read keys of their own, so
+// that every XCD has one; with fewer, an XCD would be without, and the keys of so few groups are streamed by
+// all L2s at a rate the memory-side cache does not notice (0.2 TB/s at one K/V head against 2.4 at 40).  And only for
+// undivided items on 3072 keys or more: a surplus workgroup finds all eight classes used up one after the other, about 10 us,
+// which short items do not win back.  By group against one counter over 60 shapes: forward 0.91 to 1.01 of the time where the rule
+// says yes (16/16 heads of 128, 2 x 6089 rows on 10389 keys 711 -> 671 us), but up to 1.15 below 3072 keys (64/8 heads of 64, 4 x
+// 307 rows on 858) and up to 1.10 with key ranges (40/40 heads of 64, 3 x 1367 rows on 7804, 6 ranges).
+bool items_by_group(const slimpipe_attn_params* p, int64_t keys, int ranges) {
+  return (int64_t)p->n_kv_heads * p->batch >= 8 && ranges == 1 && keys >= 3072;
 }
 size_t fwd_part_out_bytes(const slimpipe_attn_params* p) {
   size_t n = (size_t)p->batch * (size_t)p->s_q * (size_t)p->n_q_heads * (size_t)p->head_dim * sizeof(float);
@@ -412,6 +416,8 @@ int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size
   out->dkdv_items = dkdv_key_tiles(p, n_chunks) * plan.split * p->n_kv_heads * p->batch;
   out->dq_items = all_query_blocks(p, plan.head_waves) * plan.dq_ranges;
   out->compute_units = compute_units();
+  out->dq_by_xcd = !plan.both && out->dq_items > out->compute_units && workspace_bytes >= delta_bytes(p) + kTicketBytes &&
+                   items_by_group(p, p->kv_end - p->kv_begin, plan.dq_ranges);
   return SLIMPIPE_OK;
 }
 
@@ -523,7 +529,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   // a counter only where there are more items than compute units (otherwise every workgroup starts at once)
   if ((int64_t)a.items[0] * a.items[1] * a.items[2] <= compute_units()) ticket = nullptr;
   a.ticket = ticket;
-  a.items_by_group = items_by_group(p, n_ranges);
+  a.items_by_group = items_by_group(p, keys, n_ranges);
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (ticket && launch_zero_counters(ticket, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
@@ -679,7 +685,7 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   const bool counted = counters && !plan.both;
   a.ticket_dkdv = (counted && (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > cus) ? counters : nullptr;
   a.ticket_dq = (counted && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, [8..15]: dq, one per XCD
-  a.items_by_group = items_by_group(p, dq_ranges);
+  a.items_by_group = items_by_group(p, p->kv_end - p->kv_begin, dq_ranges);
   if ((int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.s_q = p->s_q; a.n_q_heads = p->n_q_heads; a.n_kv_heads = p->n_kv_heads;
   a.group = p->n_q_heads / p->n_kv_heads; a.causal = p->causal;

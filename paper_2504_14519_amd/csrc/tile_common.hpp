@@ -309,7 +309,7 @@ SP_DEV int block_row_end(int qblk, int s_q, int head_waves) {
 
 // The next work item of a forward / dq launch through its ticket counters (eight, zero before the launch), or -1 when
 // all are taken; called by one thread.  Items come in groups of `blocks`, the query blocks that walk the same keys and
-// values.  With `by_group` (at least eight groups with keys of their own) group j belongs to class j mod 8, and a
+// values.  With `by_group` (the host's choice: items_by_group in api.hip) group j belongs to class j mod 8, and a
 // workgroup takes from the class of its own XCD first, so that the blocks which share keys share an L2, and from the
 // other classes in turn when that is used up (a faster XCD ends up doing more).  Otherwise one counter deals the items
 // out in order.  4096 rows on 20480 keys, 40 heads with keys of their own (420 MB of K and V, which every one of the eight

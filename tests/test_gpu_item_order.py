@@ -1,6 +1,6 @@
-"""Work items dealt out by XCD (at least eight groups of query blocks with keys of their own and more items than compute
-units): every row is computed, whatever the number of groups, against slices of the same call small enough to run without
-counters."""
+"""Work items handed out through the ticket counters, one for all or one per XCD (undivided items on 3072 keys and more, at least
+eight groups of query blocks with keys of their own): every row is computed, whatever the number of groups, against slices of
+the same call small enough to run without counters."""
 import math
 
 import pytest
@@ -10,12 +10,11 @@ from gpu_util import say
 pytestmark = pytest.mark.gpu
 
 
-# (batch, rows, prefix, q heads, kv heads, backward through the counters): 8 groups exactly, with heads that share keys (the
-# backward of the first is small enough for the one launch without counters, that of the second is not), a count that is no
-# multiple of 8, one block per group
-@pytest.mark.parametrize("B,s,N,Hq,Hkv,counted", [(1, 2304, 2304, 32, 8, False), (1, 4096, 4096, 32, 8, True), (3, 1280, 1536, 21, 21, True),
-                                                  (1, 200, 456, 300, 300, True)])
-def test_every_item_is_computed_once(B, s, N, Hq, Hkv, counted):
+# (batch, rows, prefix, q heads, kv heads, counters of the dq items: none (the one launch), one for all, one per XCD): 8 groups
+# exactly, with heads that share keys, a count that is no multiple of 8, one block per group
+@pytest.mark.parametrize("B,s,N,Hq,Hkv,counters", [(1, 2304, 2304, 32, 8, 0), (1, 4096, 4096, 32, 8, 8), (3, 1280, 1536, 21, 21, 1),
+                                                   (3, 1280, 3328, 21, 21, 8), (1, 200, 456, 300, 300, 1), (1, 200, 3100, 300, 300, 8)])
+def test_every_item_is_computed_once(B, s, N, Hq, Hkv, counters):
     import torch
     import paper_2504_14519_amd as sp
     D, scale, G = 64, 0.125, Hq // Hkv
@@ -31,7 +30,7 @@ def test_every_item_is_computed_once(B, s, N, Hq, Hkv, counted):
     torch.cuda.synchronize()
     plan = sp.slimpipe_attn_bwd_plan(sp.make_params(q, k, o, N - s, 0, N, True, scale), 1, wsb.numel())
     assert plan.dkdv_split == 1 and plan.dq_ranges == 1 and plan.dq_items > plan.compute_units      # (the forward's items are as many)
-    assert plan.one_launch == (0 if counted else 1) and B * Hkv >= 8
+    assert (plan.one_launch, plan.dq_by_xcd) == {0: (1, 0), 1: (0, 0), 8: (0, 1)}[counters] and B * Hkv >= 8
     for h in range(0, Hkv, max(1, Hkv // 7)):       # one K/V head at a time: few items, no counters
         qs, ks = slice(h * G, (h + 1) * G), slice(h, h + 1)
         o1, l1 = sp.slimpipe_attn_fwd(q[:, :, qs], k[:, :, ks], v[:, :, ks], N - s, 0, N, True, scale)
