@@ -196,12 +196,12 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
 // Whether the query blocks that share keys go to one XCD (next_item).  At least 8 groups of them read keys of their own, so
 // that every XCD has one; with fewer, an XCD would be without, and the keys of so few groups are streamed by
 // all L2s at a rate the memory-side cache does not notice (0.2 TB/s at one K/V head against 2.4 at 40).  And only for
-// undivided items on 3072 keys or more: a surplus workgroup finds all eight classes used up one after the other, about 10 us,
-// which short items do not win back.  By group against one counter over 60 shapes: forward 0.91 to 1.01 of the time where the rule
-// says yes (16/16 heads of 128, 2 x 6089 rows on 10389 keys 711 -> 671 us), but up to 1.15 below 3072 keys (64/8 heads of 64, 4 x
-// 307 rows on 858) and up to 1.10 with key ranges (40/40 heads of 64, 3 x 1367 rows on 7804, 6 ranges).
+// items that walk 3072 keys or more: a surplus workgroup finds all eight classes used up one after the other, about 10 us,
+// which short items do not win back.  By group against one counter over 110 shapes: forward 0.80 to 1.02 of the time where the rule
+// says yes (16/16 heads of 128, 2 x 6089 rows on 10389 keys 718 -> 674 us; 40/40 heads, 4096 rows on 20480 keys in 2 ranges 1395 ->
+// 1368), but up to 1.15 on shorter items (64/8 heads of 64, 4 x 307 rows on 858 keys; 40/40, 3 x 1367 rows on 7804 in 6 ranges 1.10).
 bool items_by_group(const slimpipe_attn_params* p, int64_t keys, int ranges) {
-  return (int64_t)p->n_kv_heads * p->batch >= 8 && ranges == 1 && keys >= 3072;
+  return (int64_t)p->n_kv_heads * p->batch >= 8 && keys >= 3072 * (int64_t)ranges;
 }
 size_t fwd_part_out_bytes(const slimpipe_attn_params* p) {
   size_t n = (size_t)p->batch * (size_t)p->s_q * (size_t)p->n_q_heads * (size_t)p->head_dim * sizeof(float);

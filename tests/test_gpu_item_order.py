@@ -1,5 +1,5 @@
-"""Work items handed out through the ticket counters, one for all or one per XCD (undivided items on 3072 keys and more, at least
-eight groups of query blocks with keys of their own): every row is computed, whatever the number of groups, against slices of
+"""Work items handed out through the ticket counters, one for all or one per XCD (items that walk 3072 keys and more, at
+least eight groups of query blocks with keys of their own): every row is computed, whatever the number of groups, against slices of
 the same call small enough to run without counters."""
 import math
 
