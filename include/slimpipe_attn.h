@@ -91,7 +91,7 @@ int slimpipe_attn_init(void);
  * backward needs).  No device access. */
 int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd);
 
-/* Bytes of device workspace the call would like.  Forward: 256 bytes for a counter through which the workgroups take
+/* Bytes of device workspace the call would like.  Forward: 256 bytes for the counters through which the workgroups take
  * their work items (see the backward below), plus, when the call is a short slice over a long cache whose query
  * blocks leave compute units idle, room for the float32 partial (out, lse) of the 2 to 16
  * key ranges of equal work the call is cut into (see slimpipe_attn_fwd).  Backward needs two floats per
@@ -115,12 +115,12 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
 /* Forward of one query slice against keys [kv_begin, kv_end) of the cached prefix
  * (Sec. 4.1.2; partial ranges: Sec. 4.2.2).  Writes out (dtype p->out_dtype, strides o_*) and
  * lse [batch, n_q_heads, s_q].  Scores are never stored.
- *   workspace : may be NULL (16-byte aligned otherwise).  Its first 256 bytes, when it has them, hold the counter
- *               through which the workgroups take their work items (set to zero by a one-thread kernel ahead of
- *               the forward kernel; the results do not depend on it).  Given slimpipe_attn_workspace_bytes(p, 0)
+ *   workspace : may be NULL (16-byte aligned otherwise).  Its first 256 bytes, when it has them, hold the counters
+ *               through which the workgroups take their work items (set to zero by a one-workgroup kernel ahead of
+ *               the forward kernel; the results do not depend on them).  Given slimpipe_attn_workspace_bytes(p, 0)
  *               bytes, a call whose query blocks would not fill the GPU cuts [kv_begin, kv_end) into ranges of
  *               equal work (cut points on multiples of 256 keys), computes them in one launch into float32
- *               partials behind the counter and merges them (the rule of slimpipe_attn_merge) into (out, lse)
+ *               partials behind the counters and merges them (the rule of slimpipe_attn_merge) into (out, lse)
  *               in the same call; given less room it uses as many ranges as fit, down to the undivided
  *               computation. */
 int slimpipe_attn_fwd(const slimpipe_attn_params* p,
@@ -138,7 +138,8 @@ int slimpipe_attn_fwd(const slimpipe_attn_params* p,
  *              owned by one workgroup (or a fixed number of them whose partial sums are added in a
  *              fixed order) that sums queries and the heads of a GQA group in a fixed order, so
  *              results are bit-reproducible from run to run for the same workspace size.
- * Enqueues: delta pre-pass, dq kernel, dk/dv kernel, and the reduce kernel when the stream is split. */
+ * Enqueues the delta pre-pass, then the dq kernel and the dk/dv kernel, each with a reduce kernel when it was cut, or
+ * for small calls one kernel for both and one reduce kernel when either was cut (slimpipe_attn_workspace_bytes). */
 int slimpipe_attn_bwd(const slimpipe_attn_params* p,
                       const void* q_slice, const void* k_prefix, const void* v_prefix,
                       const void* out, const void* d_out, const float* lse,
@@ -150,13 +151,13 @@ int slimpipe_attn_bwd(const slimpipe_attn_params* p,
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and kernels as slimpipe_attn_bwd,
  * and bit for bit the results it gives with a workspace of the minimum size (the dk/dv query stream is not split,
  * dq is not cut into key ranges), but what the kernels exchange - the two row-statistic arrays (delta and lse in
- * log2 units, one float each per (batch, q head, row)) and the 256-byte counter through which workgroups take their
+ * log2 units, one float each per (batch, q head, row)) and the 256 bytes of counters through which workgroups take their
  * work items - lives in a fixed array of 4 MiB + 256 bytes in device memory that belongs to the library, one copy per
  * GPU, held until the process ends.  The call allocates nothing (no hipMalloc / hipFree, no events) and does not
  * synchronise.
  *   limit : batch * n_q_heads * s_q <= slimpipe_attn_noalloc_max_rows() = 524288, each array rounded up to 256
  *           bytes; beyond that SLIMPIPE_ETOOLARGE is returned and nothing is launched.
- *   The array keeps the last call's contents; every call overwrites the entries it reads and sets the counter to
+ *   The array keeps the last call's contents; every call overwrites the entries it reads and sets the counters to
  *   zero itself (nothing has to start at zero).  All calls on one GPU share it: two calls whose kernels may overlap
  *   on one GPU (different streams, or host threads) race - serialise them, or use slimpipe_attn_bwd with a
  *   workspace each.  Graph capture: call slimpipe_attn_init() before the capture begins. */

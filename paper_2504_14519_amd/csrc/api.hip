@@ -17,7 +17,7 @@ using namespace slimpipe;
 // until the process ends.  Host code never uses this name as an address: it asks the runtime for the device
 // address once per device (ensure_device_ready) and passes that pointer to the kernels.
 constexpr size_t kScratchBytes = (size_t)4 << 20;          // the two statistics arrays
-constexpr size_t kScratchTicketBytes = 256;                // + the counter the workgroups take their work items from
+constexpr size_t kScratchTicketBytes = 256;                // + the counters the workgroups take their work items from
 static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchTicketBytes];
 
 namespace {
@@ -160,18 +160,24 @@ int64_t all_query_blocks(const slimpipe_attn_params* p, int head_waves) {
 
 // One forward workgroup owns 256 query rows and walks the whole key range; a short slice over a
 // long cache leaves compute units idle.  Cutting the key range into R ranges of equal work (one launch,
-// partial (out, lse) per range, then the online-softmax merge) makes R times the workgroups: R is the
-// smallest count that comes within 3% of the best rounds/R, as long as a range keeps at least 1024 keys.
+// partial (out, lse) per range, then the online-softmax merge) makes R times the workgroups.  With a block per compute
+// unit or more, R is the smallest count that comes within 3% of the best rounds/R, ranges keeping at least 1024 keys;
+// with less, the smallest within 3% of the shortest time of the sum below, ranges keeping min_range_keys.
 int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
   const int64_t w = all_query_blocks(p, head_waves);
   const int64_t keys = p->kv_end - p->kv_begin;
   if (w <= 0 || keys <= 0) return 1;
   const int cus = compute_units();
   // Less than one block per compute unit: every compute unit runs a chain of ceil(w r / CUs) items, each of about 10 us plus
-  // 2.5 us (head_dim 128; 1.8 us at 64) per 128-key tile, and the merge is a launch of 4.5 us plus its bytes at 4 TB/s
-  // (measured).  The smallest count within 3% of the shortest sum.  (By rounds alone 192 blocks of head_dim 64 on 4238
-  // keys were cut into 4 ranges, three full rounds, which took 262 us of a backward call instead of 220.)  Ranges of
-  // head_dim 64 may be as short as 256 keys: 512 rows on 2048 keys and 4 heads are 8 blocks.
+  // 2.5 us (head_dim 128; 1.8 us at 64) per 128-key tile, and the merge is a launch of 4.5 us plus its bytes at 4 TB/s.
+  // The tile times are those of a half-filled chip; measured are 2.2 us (32 items) to 3.4 us (247 items; 3.7 in short chains)
+  // at head_dim 128 and 1.7 to 2.2 at 64, so the sum is a fifth to a quarter short where it fills the chip.  What counts is the pick:
+  // over 35 shapes of 1 to 247 blocks, every count up to 16 timed, it is within 3% of the best allowed count in 30, and in
+  // five small calls 15 ranges are taken where 16 cut the keys evenly (2 to 4 us).  With tile times that grow with the busy share (2.2 +
+  // share) the sum comes within 15%, but the picks are the same on the 20 shapes it was fitted to and 0.6% slower at
+  // head_dim 128 where they differ.  (By rounds alone 192 blocks of head_dim 64 on 4238 keys were cut into 4 ranges, three
+  // full rounds, which took 262 us of a backward call instead of 220.)  Ranges of head_dim 64 may be as short as 256 keys:
+  // 512 rows on 2048 keys and 4 heads are 8 blocks.
   if (w < cus) {
     const bool d64 = p->head_dim == 64;
     int pick = 1;
@@ -259,8 +265,9 @@ double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb
 
 // A call with fewer than two items per compute unit (query blocks + key tiles) runs dq and dk/dv in one launch, with the
 // cuts that finish first by the times below; a larger one runs them one after the other through the ticket counters.
-// Microseconds measured on MI355X: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64), a dk/dv item
-// about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its bytes at 5 TB/s.
+// Microseconds measured on MI355X with the chip full: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64; 1.3 to
+// 1.5 at 128 with 25 to 130 units busy), a dk/dv item about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its
+// bytes at 5 TB/s.
 // The partial sums of the cuts take at most `room` bytes (SIZE_MAX: all that are wanted): a small call chooses among the
 // pairs that fit, a large one takes first as many chunks and then as many key ranges as fit.
 BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_t room) {

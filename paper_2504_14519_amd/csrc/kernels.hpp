@@ -88,8 +88,8 @@ struct BwdArgs {
   // their speed, and this lets a faster XCD take more items.  The dk/dv launch then has dkdv_wgs workgroups (one per
   // compute unit) that loop over items, with ticket_dkdv[0..7] one counter per XCD; the dq launch has a quarter more
   // workgroups than items, one item each, and eight counters too.
-  // nullptr: workgroup index = item (no room for the counter in the workspace, or no more items than compute units:
-  // then every workgroup starts at once and there is nothing to even out).
+  // nullptr: workgroup index = item (no room for the counters in the workspace, or no more items than compute units, when
+  // every workgroup starts at once and there is nothing to even out, or dq and dk/dv in one launch).
   unsigned* ticket_dkdv;
   unsigned* ticket_dq;
   int32_t dkdv_wgs;
