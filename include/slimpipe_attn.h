@@ -104,7 +104,7 @@ int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd);
  * rows of each key tile are cut into 2 to 8 chunks that run as work items of their own, each writing float32
  * partial sums [chunk][dk, dv][batch][kv head][keys rounded up to 256][head_dim] that a second kernel adds up
  * in chunk order.  The figure returned here includes that room for the split this call would pick;
- * given less, slimpipe_attn_bwd uses the largest split that fits (down to none).  In the same way the dq
+ * given less, slimpipe_attn_bwd uses cuts whose sums fit (down to none).  In the same way the dq
  * kernel of a short slice over a long cache is cut into 2 to 16 key ranges of equal work, as the forward is,
  * with float32 partial dq [range][batch, s_q, n_q_heads, head_dim] behind the partial dk/dv that a reduce kernel
  * adds up in range order; that room is included too and used as far as it is there.  A backward call with fewer than
