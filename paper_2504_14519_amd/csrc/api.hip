@@ -52,6 +52,7 @@ int ensure_device_ready(void** scratch_ptr = nullptr) {
   std::call_once(d.once, [&d] {
     d.status = opt_in_fwd_kernels();
     if (d.status == hipSuccess) d.status = opt_in_bwd_kernels();
+    if (d.status == hipSuccess) d.status = opt_in_small_kernels();
     if (d.status == hipSuccess) d.status = hipGetSymbolAddress(&d.scratch, HIP_SYMBOL(scratch));
     if (d.status == hipSuccess && d.scratch == nullptr) d.status = hipErrorInvalidSymbol;
   });
@@ -158,6 +159,12 @@ int64_t all_query_blocks(const slimpipe_attn_params* p, int head_waves) {
   return query_blocks(head_waves, p->n_q_heads / p->n_kv_heads) * p->n_kv_heads * p->batch;
 }
 
+// Microseconds of a call with w < compute units query blocks of 256 rows in r key ranges (see fwd_preferred_ranges).
+double fwd_blocks_us(const slimpipe_attn_params* p, int64_t w, int r) {
+  const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
+  return (double)((w * r + cus - 1) / cus) * (10.0 + (p->head_dim == 64 ? 1.8 : 2.5) * (double)keys / (128.0 * r)) +
+         (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
+}
 // One forward workgroup owns 256 query rows and walks the whole key range; a short slice over a
 // long cache leaves compute units idle.  Cutting the key range into R ranges of equal work (one launch,
 // partial (out, lse) per range, then the online-softmax merge) makes R times the workgroups.  With a block per compute
@@ -169,7 +176,7 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
   if (w <= 0 || keys <= 0) return 1;
   const int cus = compute_units();
   // Less than one block per compute unit: every compute unit runs a chain of ceil(w r / CUs) items, each of about 10 us plus
-  // 2.5 us (head_dim 128; 1.8 us at 64) per 128-key tile, and the merge is a launch of 4.5 us plus its bytes at 4 TB/s.
+  // 2.5 us (head_dim 128; 1.8 us at 64) per 128-key tile, and the merge is a launch of 4.5 us plus its bytes at 4 TB/s (fwd_blocks_us).
   // The tile times are those of a half-filled chip; measured are 2.2 us (32 items) to 3.4 us (247 items; 3.7 in short chains)
   // at head_dim 128 and 1.7 to 2.2 at 64, so the sum is a fifth to a quarter short where it fills the chip.  What counts is the pick:
   // over 35 shapes of 1 to 247 blocks, every count up to 16 timed, it is within 3% of the best allowed count in 30, and in
@@ -179,12 +186,10 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
   // full rounds, which took 262 us of a backward call instead of 220.)  Ranges of head_dim 64 may be as short as 256 keys:
   // 512 rows on 2048 keys and 4 heads are 8 blocks.
   if (w < cus) {
-    const bool d64 = p->head_dim == 64;
     int pick = 1;
     double best_us = 1e30;
     for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
-      const double us = (double)((w * r + cus - 1) / cus) * (10.0 + (d64 ? 1.8 : 2.5) * (double)keys / (128.0 * r)) +
-                        (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
+      const double us = fwd_blocks_us(p, w, r);
       if (us < best_us * 0.97) { best_us = us; pick = r; }
     }
     return pick;
@@ -216,16 +221,44 @@ size_t fwd_part_out_bytes(const slimpipe_attn_params* p) {
 size_t fwd_parts_bytes(const slimpipe_attn_params* p, int ranges) {
   return ranges <= 1 ? 0 : (size_t)ranges * (fwd_part_out_bytes(p) + stat_bytes(p));
 }
+// Microseconds of a call through the small kernel (32 query rows a workgroup, the 8 waves sharing out the keys of its range) in
+// r key ranges: 8.7 (head_dim 64: 7) + 1.3 (1.4) per step of a wave, which is 32 (64) keys, times the rounds of workgroups, + the merge.
+double fwd_small_us(const slimpipe_attn_params* p, int r) {
+  const bool d64 = p->head_dim == 64;
+  const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
+  const int64_t wgs = ((int64_t)p->s_q + 31) / 32 * p->n_q_heads * p->batch * r, per_step = 8 * (d64 ? 64 : 32);
+  const double steps = (double)((keys + r * per_step - 1) / (r * per_step)), rounds = (double)((wgs + cus - 1) / cus);
+  return (d64 ? 7.0 : 8.7) + 2 * (rounds - 1) + rounds * steps * (d64 ? 1.4 : 1.3) +
+         (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
+}
 struct FwdPlan {
   int head_waves;    // of the query blocks
   int ranges;        // key ranges
+  bool small;        // 32-row workgroups (attn_fwd_small_kernel)
 };
-// The forward's plan when the partial results of the ranges take at most `room` bytes.
-FwdPlan fwd_plan(const slimpipe_attn_params* p, size_t room) {
+// The forward's plan when the partial results of the ranges take at most `room` bytes.  A call that lends no workspace (`lent` false),
+// or a smaller one than it is asked for, goes through the kernel of slimpipe_attn_fwd_ranges: undivided, it returns what a range of
+// that call returns, bit for bit.
+FwdPlan fwd_plan(const slimpipe_attn_params* p, bool lent, size_t room) {
   const int hw = head_waves_of(p, p->kv_end - p->kv_begin, fwd_parts_bytes(p, 2) > room ? 1 : most_ranges(p, min_range_keys(p->head_dim)));
   int ranges = fwd_preferred_ranges(p, hw);
   while (ranges > 1 && (fwd_parts_bytes(p, ranges) > room || (int64_t)p->batch * ranges > 65535)) --ranges;
-  return {hw, ranges};
+  // With less than one 256-row block per compute unit the small kernel is taken, in the number of ranges (none shorter than the
+  // 256-row blocks may have) that makes it fastest, where its time is shorter.  Over 57 calls of up to 1.2 x 65536 (row, head) pairs, both kernels timed in 1 to 8
+  // ranges: the pick is within 2 % of the best in the mean, at most 1.7 % slower than the 256-row blocks, 1.53 times as fast in the mean
+  // and up to 2.6 times (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).  It loses where keys are long: every workgroup
+  // reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
+  const int64_t w = all_query_blocks(p, hw), keys = p->kv_end - p->kv_begin;
+  if (lent && w < compute_units() && keys > 0) {
+    double best_us = fwd_blocks_us(p, w, ranges) * 0.97;
+    int pick = 0;
+    for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
+      const double us = fwd_small_us(p, r);
+      if (us < best_us) { best_us = us * 0.99; pick = r; }
+    }
+    if (pick && fwd_parts_bytes(p, pick) <= room) return {hw, pick, true};
+  }
+  return {hw, ranges, false};
 }
 // The dq kernel has the forward's launch shape and is cut into key ranges the same way; its partial results are
 // float32 [range][batch, s_q, heads, head_dim].
@@ -265,8 +298,8 @@ double list_makespan(int64_t units, int64_t na, double ta, int64_t nb, double tb
 
 // A call with fewer than two items per compute unit (query blocks + key tiles) runs dq and dk/dv in one launch, with the
 // cuts that finish first by the times below; a larger one runs them one after the other through the ticket counters.
-// Microseconds measured on MI355X with the chip full: a dq item is about 8 + 2.4 per 64-key tile (head_dim 128; 1.4 at 64; 1.3 to
-// 1.5 at 128 with 25 to 130 units busy), a dk/dv item about 10 + 1.6 (1.1) per 32-row query tile; a reduce launch 4 + its
+// Microseconds measured on MI355X with the chip full: a dq item is about 8 + 2.4 per 64 keys (head_dim 128; 1.4 at 64; 1.3 to
+// 1.5 at 128 with 25 to 130 units busy), a dk/dv item about 10 + 1.6 (1.1) per 32 query rows; a reduce launch 4 + its
 // bytes at 5 TB/s.
 // The partial sums of the cuts take at most `room` bytes (SIZE_MAX: all that are wanted): a small call chooses among the
 // pairs that fit, a large one takes first as many chunks and then as many key ranges as fit.
@@ -460,7 +493,7 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
   if (!bytes) return SLIMPIPE_EINVAL_NULL;
   int rc = slimpipe_attn_validate(p, is_bwd);
   if (rc != SLIMPIPE_OK) return rc;
-  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_plan(p, SIZE_MAX).ranges); return SLIMPIPE_OK; }
+  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_plan(p, true, SIZE_MAX).ranges); return SLIMPIPE_OK; }
   // the tile grid of a chunked call can start up to 255 keys before kv_begin: room for whichever of the
   // two variants asks for more
   const BwdPlan plan1 = bwd_plan(p, 1, true, SIZE_MAX), plan2 = bwd_plan(p, 2, true, SIZE_MAX);
@@ -478,7 +511,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
                     const void* const* v_chunks, int32_t n_chunks, int64_t chunk_len, int32_t n_ranges,
                     const int64_t* range_begin, const int64_t* range_end, float* part_out, int64_t part_out_elems,
                     float* part_lse, int64_t part_lse_elems, void* out, float* lse, void* hip_stream, unsigned* ticket = nullptr,
-                    int head_waves = 0) {      // (0: chosen here)
+                    int head_waves = 0, bool small = false) {      // (head_waves 0: chosen here)
   int rc = slimpipe_attn_validate(p, 0);
   if (rc != SLIMPIPE_OK) return rc;
   const bool parts = part_out != nullptr;
@@ -529,6 +562,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   }
   a.head_waves = head_waves ? head_waves : head_waves_of(p, keys, n_ranges);
   const int64_t blocks = query_blocks(a.head_waves, a.group);
+  // (32-row workgroups are at most 8 times as many)
   if (blocks * p->n_kv_heads * p->batch * n_ranges > (int64_t)1 << 30) return SLIMPIPE_EINVAL_SHAPE;
   a.items[0] = (int32_t)blocks;
   a.items[1] = p->n_kv_heads;
@@ -539,8 +573,9 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   a.items_by_group = items_by_group(p, keys, n_ranges);
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  if (ticket && launch_zero_counters(ticket, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
-  hipError_t e = timed(SLIMPIPE_KERNEL_FWD, st, [&] { return launch_fwd(a, p->batch, p->head_dim, st); });
+  if (small) a.items[0] = (int32_t)(((int64_t)p->s_q + 31) / 32);
+  else if (ticket && launch_zero_counters(ticket, st) != hipSuccess) return SLIMPIPE_ELAUNCH;
+  hipError_t e = timed(SLIMPIPE_KERNEL_FWD, st, [&] { return small ? launch_fwd_small(a, p->batch, p->head_dim, st) : launch_fwd(a, p->batch, p->head_dim, st); });
   if (e != hipSuccess) return SLIMPIPE_ELAUNCH;
   if (parts && out) {
     MergeArgs m;
@@ -571,18 +606,18 @@ static int fwd_auto(const slimpipe_attn_params* p, const void* q_slice, const vo
   unsigned* ticket = (workspace && workspace_bytes >= kTicketBytes) ? static_cast<unsigned*>(workspace) : nullptr;
   char* parts_base = ticket ? static_cast<char*>(workspace) + kTicketBytes : static_cast<char*>(workspace);
   const size_t parts_room = ticket ? workspace_bytes - kTicketBytes : workspace_bytes;
-  const FwdPlan plan = fwd_plan(p, workspace ? parts_room : 0);
+  const FwdPlan plan = fwd_plan(p, ticket != nullptr, workspace ? parts_room : 0);
   const int ranges = plan.ranges;
   if (ranges <= 1)
     return fwd_impl(p, q_slice, k_chunks, v_chunks, n_chunks, chunk_len, 1, &p->kv_begin, &p->kv_end, nullptr, 0, nullptr, 0, out,
-                    lse, hip_stream, ticket, plan.head_waves);
+                    lse, hip_stream, ticket, plan.head_waves, plan.small);
   int64_t begin[kMaxRanges], end[kMaxRanges];
   equal_work_ranges(p, ranges, begin, end);
   float* part_out = reinterpret_cast<float*>(parts_base);
   float* part_lse = reinterpret_cast<float*>(parts_base + (size_t)ranges * fwd_part_out_bytes(p));
   return fwd_impl(p, q_slice, k_chunks, v_chunks, n_chunks, chunk_len, ranges, begin, end, part_out,
                   (int64_t)(fwd_part_out_bytes(p) / sizeof(float)), part_lse, (int64_t)(stat_bytes(p) / sizeof(float)), out, lse,
-                  hip_stream, ticket, plan.head_waves);
+                  hip_stream, ticket, plan.head_waves, plan.small);
 }
 
 int slimpipe_attn_fwd(const slimpipe_attn_params* p, const void* q_slice, const void* k_prefix,

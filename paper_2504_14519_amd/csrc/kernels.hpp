@@ -123,8 +123,10 @@ struct MergeArgs {
 // every instantiation of the forward / backward kernels; api.hip calls them once per device.
 hipError_t opt_in_fwd_kernels();
 hipError_t opt_in_bwd_kernels();
+hipError_t opt_in_small_kernels();
 
 hipError_t launch_fwd(const FwdArgs& a, int batch, int head_dim, hipStream_t st);
+hipError_t launch_fwd_small(const FwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_zero_counters(unsigned* counters, hipStream_t st);
 hipError_t launch_delta(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t st);

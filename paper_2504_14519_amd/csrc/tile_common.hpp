@@ -217,6 +217,11 @@ SP_DEV void dma4(const void* base, uint32_t lane_off, unsigned lds_base) {      
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                :: "v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
+// 16 bytes per lane: lane i lands at lds_base + 16*i
+SP_DEV void dma16(const void* base, uint32_t lane_off, unsigned lds_base) {     // base uniform, lane_off in bytes
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(lane_off), "s"(base), "s"(lds_base) : "memory", "m0");
+}
 // A tile copy with nothing but two per-lane constants (packed into one register): THREADS/NC rows per pass with THREADS a
 // multiple of 16*NC (THREADS = 256, NC = 16: 16 rows per pass), so pass n handles row
 // r0 + (THREADS/NC)*n of the tile and, the row step being a multiple of 16, the SAME swizzled chunk.
