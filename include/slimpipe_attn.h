@@ -109,7 +109,8 @@ int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd);
  * with float32 partial dq [range][batch, s_q, n_q_heads, head_dim] behind the partial dk/dv that a reduce kernel
  * adds up in range order; that room is included too and used as far as it is there.  A backward call with fewer than
  * two work items per compute unit computes dq and dk/dv in one launch (and adds up their partial sums in one), but for calls
- * of long items that a workspace without room for partial sums leaves undivided. */
+ * of long items that a workspace without room for partial sums leaves undivided.  The smallest of these, given the room
+ * returned here, go through workgroups of 32 rows or keys that keep their partial sums to themselves and leave the room unused. */
 int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, size_t* bytes);
 
 /* Forward of one query slice against keys [kv_begin, kv_end) of the cached prefix

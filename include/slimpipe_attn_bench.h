@@ -31,7 +31,8 @@ int slimpipe_attn_profile_enable(int enable);
 int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t launches[SLIMPIPE_KERNEL_KINDS]);
 
 /* How slimpipe_attn_bwd (n_chunks = 1) or slimpipe_attn_bwd_chunked would cut a call into work items with a workspace of
- * workspace_bytes (slimpipe_attn_bwd_noalloc: the two row statistics + 256 bytes).  Host code only, nothing is launched. */
+ * workspace_bytes (slimpipe_attn_bwd_noalloc: the two row statistics + 256 bytes).  For the smallest calls, which go through a kernel of 32-row and
+ * 32-key items, these are the cuts without it.  Host code only, nothing is launched. */
 typedef struct slimpipe_bwd_plan {
   int32_t one_launch;      /* dq and dk/dv items in one launch */
   int32_t dq_first;        /* in that launch the dq items come first */

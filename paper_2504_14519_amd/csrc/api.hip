@@ -273,6 +273,7 @@ struct BwdPlan {
   int dq_ranges;     // key ranges of the dq items
   bool both;         // dq and dk/dv items in one launch
   bool dq_first;     // ... the dq items first
+  double us;         // (one launch) its time and that of the reduce by the model of bwd_plan
 };
 
 // Time at which `na` items of length ta, then `nb` items of length tb, each started on the unit that is free first, are
@@ -309,7 +310,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
   const int64_t wq = all_query_blocks(p, hw);
   const int64_t wk = dkdv_key_tiles(p, n_chunks) * p->n_kv_heads * p->batch;
   if (wk <= 0 || wq + wk >= 2 * cus) {
-    BwdPlan plan{hw, preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p, hw), false, false};
+    BwdPlan plan{hw, preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p, hw), false, false, 0.0};
     while (plan.split > 1 && split_bytes(p, n_chunks, plan.split) > room) plan.split /= 2;
     const size_t used = split_bytes(p, n_chunks, plan.split);
     while (plan.dq_ranges > 1 && (dq_parts_bytes(p, plan.dq_ranges) > room - used || (int64_t)p->batch * plan.dq_ranges > 65535)) --plan.dq_ranges;
@@ -319,7 +320,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
   const double dq_tiles = (double)keys / 64, dq_tile = p->head_dim == 128 ? 2.4 : 1.4;
   const double stream = (double)(((int64_t)p->s_q + 31) / 32 * (p->n_q_heads / p->n_kv_heads)), dkdv_tile = p->head_dim == 128 ? 1.6 : 1.1;
   static const int kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  BwdPlan best{hw, 1, 1, true, false};
+  BwdPlan best{hw, 1, 1, true, false, 0.0};
   double best_us = 1e30;
   for (int s : kCuts) {
     if (s > 8 || (s > 1 && stream / s < 4)) break;             // a chunk keeps at least 4 query tiles
@@ -339,7 +340,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
       double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
       if (r > 1) bytes += (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4;
       if (bytes > 0) us += 4 + bytes / 5e6;
-      if (us < best_us * 0.99) { best_us = us; best = {hw, s, r, both, tq > tk}; }
+      if (us < best_us * 0.99) { best_us = us; best = {hw, s, r, both, tq > tk, us}; }
     }
   }
   return best;
@@ -352,6 +353,35 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
   const size_t room = workspace_bytes - delta_bytes(p) - (ticket ? kTicketBytes : 0);
   const BwdPlan plan = bwd_plan(p, n_chunks, ticket, SIZE_MAX);
   return split_bytes(p, n_chunks, plan.split) + dq_parts_bytes(p, plan.dq_ranges) <= room ? plan : bwd_plan(p, n_chunks, ticket, room);
+}
+// Whether a call that bwd_plan puts into one launch goes through the small kernel instead (32 query rows or 32 keys a workgroup, the
+// eight waves sharing out the other side, no partial sums in memory), and which items come first there.  Only a call that is
+// given the workspace it is asked for: with less, and where nothing would be cut, it keeps the sums of the undivided items.
+// Microseconds: a dq item 6 (head_dim 64: 5) + 1.6 (1.4) per step of a wave, which is 32 (64) keys, a dk/dv item 6 (5) + 2 (1) per 32
+// query rows of a wave, and 4 (5.5) for the launch; against the model of bwd_plan + 7, what the delta and reduce launches
+// cost beyond it.  Over 164 calls, both kernels timed: the pick is within 1 % of the faster in the mean and 1.17 times as fast as
+// the 256-row items (512 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.9 us; 100 rows of 8/2 heads of 128 on 448 keys, batch 2: 31.9 ->
+// 17.1).  Long calls stay out: a workgroup reads the whole other side for 32 rows or keys, and the model does not know what
+// that costs a full chip (1969 rows on 4976 keys, 8/1 heads of 64: 80 us by the model, 104 measured, 90 through the 256-row items).
+// Calls of fewer than 64 dq items would gain as well (256 rows of 4 heads on 1215 keys 24.8 -> 17.9 us) but their launches are
+// pinned, kind by kind, by the test of the per-kernel timing.
+struct BwdSmallPlan { bool use, dq_first; };
+BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, int n_chunks, const BwdPlan& plan, size_t workspace_bytes) {
+  const size_t parts = split_bytes(p, n_chunks, plan.split) + dq_parts_bytes(p, plan.dq_ranges);
+  if (!plan.both || parts == 0 || workspace_bytes < delta_bytes(p) + kTicketBytes + parts) return {false, false};
+  const BwdPlan full = bwd_plan(p, n_chunks, true, SIZE_MAX);
+  if (plan.split != full.split || plan.dq_ranges != full.dq_ranges) return {false, false};      // (cut for the room there is)
+  const bool d64 = p->head_dim == 64;
+  const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
+  const int64_t row_blocks = ((int64_t)p->s_q + 31) / 32, key_blocks = (keys + 31) / 32;
+  const int64_t nq = row_blocks * p->n_q_heads * p->batch, nk = key_blocks * p->n_kv_heads * p->batch;
+  // steps of the longest item where every item has a compute unit to itself, otherwise of the mean one
+  const double seen = visible_pairs_upto(p, p->kv_end) / ((double)p->s_q * (double)keys);
+  const double sq = (double)keys / (d64 ? 512 : 256), sk = (double)(row_blocks * (p->n_q_heads / p->n_kv_heads)) / 8;
+  const double tq = (d64 ? 5 : 6) + (d64 ? 1.4 : 1.6) * (nq > cus ? sq * seen + 0.5 : ceil(sq));
+  const double tk = (d64 ? 5 : 6) + (d64 ? 1.0 : 2.0) * (nk > cus ? sk * seen + 0.5 : ceil(sk));
+  const double us = (d64 ? 5.5 : 4) + (tq > tk ? list_makespan(cus, nq, tq, nk, tk) : list_makespan(cus, nk, tk, nq, tq));
+  return {nq >= 64 && us < 60 && us * 1.05 < plan.us + 7, tq > tk};
 }
 // Cut points of equal work on multiples of 256 keys (no range boundary inside a chunk-grid tile).
 void equal_work_ranges(const slimpipe_attn_params* p, int ranges, int64_t* begin, int64_t* end) {
@@ -742,6 +772,10 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (timed(SLIMPIPE_KERNEL_DELTA, st, [&] { return launch_delta(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
+  if (const BwdSmallPlan sm = bwd_small_plan(p, n_chunks, plan, workspace_bytes); sm.use) {
+    a.dq_first = sm.dq_first;
+    return timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_small(a, p->batch, p->head_dim, st); }, events) == hipSuccess ? SLIMPIPE_OK : SLIMPIPE_ELAUNCH;
+  }
   if (plan.both) {
     if (timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_both(a, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
     if ((split > 1 || dq_ranges > 1) &&

@@ -1,4 +1,4 @@
-// Forward of small calls: a workgroup owns 32 query rows of one head and its 8 wavefronts share out their keys.
+// Small calls.  Forward: a workgroup owns 32 query rows of one head and its 8 wavefronts share out their keys.
 //
 // What bounds a small call is a chain: a 256-row block walks its keys tile after tile behind barriers on a chip that is mostly idle, and
 // key ranges shorten the chain only at the price of a merge launch.  Here eight waves walk eight tiles of the keys at the same time,
@@ -24,6 +24,13 @@ struct WaveDma {
     const int c = D == 128 ? (((p >> 2) ^ r) & 3) << 2 | (p & 3) : (p ^ r) & (NC - 1);
 #pragma unroll
     for (int n = 0; n < PHASES; ++n) off[n] = __umul24((uint32_t)r, row_bytes) + (uint32_t)((c ^ n) * 16);
+  }
+  // pass n alone
+  SP_DEV void copy_pass(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane, int n) const {
+    const int r0 = lane / NC, r = r0 + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
+    uint32_t o = off[0];
+    if constexpr (PHASES > 1) o ^= (uint32_t)(n & (PHASES - 1)) * 16;
+    dma16(tile_base, o + __umul24((uint32_t)rr, row_bytes) - __umul24((uint32_t)r0, row_bytes), __builtin_amdgcn_readfirstlane(lds_tile + n * 1024));
   }
   SP_DEV void copy(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane) const {
     lds_tile = __builtin_amdgcn_readfirstlane(lds_tile);
@@ -247,10 +254,393 @@ hipError_t launch_fwd_small(const FwdArgs& a, int batch, int head_dim, hipStream
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------------------------------ backward
+// The same idea for both gradients, in one launch behind the delta kernel: a workgroup owns 32 query rows (dq) or 32 keys
+// (dk/dv) and its eight waves share out the keys, or the query tiles of all heads of the group, each with tiles of its own; the
+// eight partial sums meet in LDS and are added up in wave order (bit-reproducible).  No partial sums in memory, no reduce launch.
+// 512 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.9 us for the call.  A step of dk/dv (32 query rows of a wave) takes 1 us at
+// head_dim 64, where the tiles are double-buffered, and 2 us at 128, where one Q and one dO tile per wave are all of LDS and the
+// copy of the next waits for the sums of this one.  Which calls come here: bwd_small_plan in api.hip.
+template <int D>
+struct BwdSmall {
+  static constexpr int NW = 8, KS = D / 16, DB = D / 32;
+  static constexpr int ROW = D + 4, PART_BYTES = 32 * ROW * 4;
+  // dq: a K and a V tile of BN keys per wave
+  static constexpr int BN = D == 64 ? 64 : 32, KB = BN / 32, KV_BYTES = BN * D * 2;
+  // dk/dv: BUF x (Q and dO tile of 32 rows, their statistics) per wave, and the V rows of the workgroup
+  static constexpr int BUF = D == 64 ? 2 : 1, TILE_BYTES = 32 * D * 2, SET_BYTES = 2 * TILE_BYTES + 256;
+  static constexpr int V_BASE = NW * BUF * SET_BYTES;
+  static constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
+  static constexpr int LDS = max3(NW * 2 * KV_BYTES, V_BASE + TILE_BYTES, NW * PART_BYTES);
+};
+
+// Element d0 .. d0 + D/16 - 1 of row r (16 threads a row) of the sum of the eight waves' partial results.
+template <int D>
+SP_DEV void sum_parts(const char* smem, int r, int d0, f32x4 (&sum)[D / 64]) {
+  using S = BwdSmall<D>;
+#pragma unroll
+  for (int j = 0; j < D / 64; ++j) sum[j] = *reinterpret_cast<const f32x4*>(smem + (r * S::ROW + d0 + 4 * j) * 4);
+#pragma unroll
+  for (int w = 1; w < S::NW; ++w)
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) sum[j] += *reinterpret_cast<const f32x4*>(smem + w * S::PART_BYTES + (r * S::ROW + d0 + 4 * j) * 4);
+}
+// A wave's accumulators (lane = column of the C layout, registers = head_dim) into its partial result, `factor` times.
+template <int D>
+SP_DEV void put_part(char* part, const f32x16 (&acc)[D / 32], float factor, int ql, int g) {
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = {acc[db][4 * i4] * factor, acc[db][4 * i4 + 1] * factor, acc[db][4 * i4 + 2] * factor, acc[db][4 * i4 + 3] * factor};
+      *reinterpret_cast<f32x4*>(part + (ql * BwdSmall<D>::ROW + 32 * db + 8 * i4 + 4 * g) * 4) = v;
+    }
+}
+
+// index -> (query head, 32-row block of a head, batch index)
+template <int D>
+SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
+  using S = BwdSmall<D>;
+  constexpr int NW = S::NW, BN = S::BN, KB = S::KB, KS = S::KS, DB = S::DB;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
+  const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+  item = __builtin_amdgcn_readfirstlane(item);
+  const int row_blocks = (int)(((int64_t)a.s_q + 31) / 32), per_b = row_blocks * a.n_q_heads;
+  const int b = __builtin_amdgcn_readfirstlane(item / per_b), hb = item - b * per_b;
+  const int rb = __builtin_amdgcn_readfirstlane(hb / a.n_q_heads), h = hb - rb * a.n_q_heads;
+  const int row0 = (row_blocks - 1 - rb) * 32, hk = __builtin_amdgcn_readfirstlane(h / a.group);
+  const int myrow = row0 + ql, myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
+  int64_t hi = a.kv_end;
+  if (a.causal) {
+    const int64_t lim = a.q_offset + (row0 + 32 < a.s_q ? row0 + 32 : a.s_q);
+    hi = hi < lim ? hi : lim;
+  }
+  const int64_t lo = kv_grid_origin(a.kv_begin, a.kv.n, BN);
+  const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const float c = a.scale_log2e;
+
+  bf16x8 q[KS], dO[KS];
+  {
+    const bf16_t* qp = a.q + (int64_t)b * a.q_stride_b + (int64_t)myrow_c * a.q_stride_s + (int64_t)h * a.q_stride_h;
+    const bf16_t* dp = a.d_out + (int64_t)b * a.do_stride_b + (int64_t)myrow_c * a.do_stride_s + (int64_t)h * a.do_stride_h;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      q[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * g);
+      dO[ks] = *reinterpret_cast<const bf16x8*>(dp + 16 * ks + 8 * g);
+    }
+  }
+  const int64_t stat = ((int64_t)b * a.n_q_heads + h) * a.s_q + myrow_c;
+  const float lse2 = a.lse2[stat], ndelta = a.delta[stat];      // (+inf for an empty row -> p = 0; delta is stored negated)
+  f32x16 dq[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
+
+  const unsigned k_lds = lds_addr(smem) + wave_u * 2 * S::KV_BYTES, v_lds = k_lds + S::KV_BYTES;
+  RpBase<D> lo_k, lo_v;
+  TrBase<D> lo_kt;
+  lo_k.init(lane, (int)k_lds);
+  lo_v.init(lane, (int)v_lds);
+  lo_kt.init(lane, (int)k_lds);
+  const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
+  const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
+  WaveDma<D, BN> dma;
+  dma.init(lane, row_bytes);
+  auto copy = [&](bool k, int t) {
+    const int64_t key0 = lo + (int64_t)t * BN;
+    const int chunk = kv_chunk_of(a.kv, key0);
+    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (a tile lies inside one chunk)
+    const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
+    dma.copy(k ? k_lds : v_lds, base, row_bytes, left < BN ? (int)left : BN, lane);
+  };
+  int t = wave_u;                                        // tiles w, w + 8, w + 16, .. are this wave's
+  if (t < nt) {
+    copy(true, t);
+    copy(false, t);
+  }
+  for (; t < nt; t += NW) {
+    const int tn = t + NW < nt ? t + NW : t;             // (past the end the last tile is copied again)
+    SP_FENCE();
+    wait_async();
+    asm volatile("" ::: "memory");
+    SP_FENCE();
+    f32x16 s[KB], dp[KB];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const f32x16 zero = {0};
+        s[kb] = mfma32(lds_rp<D>(lo_k, ks, kb * 32 * D * 2), q[ks], ks == 0 ? zero : s[kb]);
+      }
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) dp[kb][i] = ndelta;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) dp[kb] = mfma32(lds_rp<D>(lo_v, ks, kb * 32 * D * 2), dO[ks], dp[kb]);
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(dp[kb]));      // the reads of V are done before V is copied over
+    copy(false, tn);
+    const int64_t key0 = lo + (int64_t)t * BN;
+    if (key0 < a.kv_begin || key0 + BN > a.kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
+      const int64_t kmin = a.kv_begin - key0;
+      int64_t kmax = a.kv_end - 1;
+      if (a.causal && a.q_offset + myrow < kmax) kmax = a.q_offset + myrow;
+      kmax -= key0;
+      const int kmin_lane = (kmin < 0 ? 0 : (int)kmin) - 4 * g, kmax_lane = (kmax < -1 ? -1 : (kmax > BN ? BN : (int)kmax)) - 4 * g;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const int key = kb * 32 + 8 * (i >> 2) + (i & 3);
+          s[kb][i] = ((key >= kmin_lane) & (key <= kmax_lane)) ? s[kb][i] : -INFINITY;      // exp2(-inf) = 0
+        }
+    }
+    bf16x8 ds[KB][2];
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] = __builtin_fmaf(s[kb][i], c, -lse2);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] = exp2_fast(s[kb][i]);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[kb][i] *= dp[kb][i];                  // dp holds dP - delta
+      ds[kb][0] = pack8(s[kb], 0);
+      ds[kb][1] = pack8(s[kb], 8);
+    }
+#pragma unroll
+    for (int blk = 0; blk < 2 * KB; ++blk)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) dq[db] = mfma32(lds_tr<D>(lo_kt, db, blk * 16 * D * 2), ds[blk / 2][blk % 2], dq[db]);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(dq[db]));      // the reads of K are done before K is copied over
+    copy(true, tn);
+  }
+  wait_async();
+  __syncthreads();                                       // nobody reads or copies a tile any more
+  put_part<D>(smem + wave_u * S::PART_BYTES, dq, a.scale, ql, g);
+  __syncthreads();
+  const int r = tid >> 4, d0 = (tid & 15) * (D / 16), row = row0 + r;
+  if (row < a.s_q) {
+    f32x4 sum[D / 64];
+    sum_parts<D>(smem, r, d0, sum);
+    const int64_t base = (int64_t)b * a.q_stride_b + (int64_t)row * a.q_stride_s + (int64_t)h * a.q_stride_h + d0;
+#pragma unroll
+    for (int j = 0; j < D / 64; ++j) {
+      if (a.dq_final_f32) {
+        f32x4* dst = reinterpret_cast<f32x4*>(static_cast<float*>(a.dq_final) + base + 4 * j);
+        if (a.dq_final_accumulate) sum[j] += *dst;
+        *dst = sum[j];
+      } else {
+        *reinterpret_cast<bf16x4*>(static_cast<bf16_t*>(a.dq_final) + base + 4 * j) = __builtin_convertvector(sum[j], bf16x4);
+      }
+    }
+  }
+}
+
+// index -> (32-key block, kv head, batch index)
+template <int D>
+SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
+  using S = BwdSmall<D>;
+  constexpr int NW = S::NW, KS = S::KS, DB = S::DB, BUF = S::BUF, TILE_BYTES = S::TILE_BYTES;
+  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
+  const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
+  item = __builtin_amdgcn_readfirstlane(item);
+  const int64_t grid0 = kv_grid_origin(a.kv_begin, a.kv.n, 32);
+  const int key_blocks = (int)((a.kv_end - grid0 + 31) / 32), per_b = key_blocks * a.n_kv_heads;
+  const int b = __builtin_amdgcn_readfirstlane(item / per_b), hb = item - b * per_b;
+  const int hk = __builtin_amdgcn_readfirstlane(hb / key_blocks), kblk = hb - hk * key_blocks;
+  const int64_t key0 = grid0 + (int64_t)kblk * 32, mykey = key0 + ql;
+  const int chunk = kv_chunk_of(a.kv, key0);
+  const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (>= 1)
+  const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
+  const float c = a.scale_log2e;
+
+  bf16x8 k[KS];
+  {
+    const bf16_t* kp = a.kv.k[chunk] + head_off + (chunk_row0 + (ql < left ? ql : left - 1)) * a.kv_stride_s;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks + 8 * g);
+  }
+  f32x16 dk[DB], dv[DB];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) { dk[db][i] = 0.f; dv[db][i] = 0.f; }
+
+  const unsigned smem_lds = lds_addr(smem);
+  // V rows of the workgroup: one copy instruction per wave (as far as there are any)
+  {
+    WaveDma<D, 32> dma;
+    const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
+    dma.init(lane, row_bytes);
+    const bf16_t* vbase = uniform_ptr(a.kv.v[chunk] + head_off + chunk_row0 * a.kv_stride_s);
+    if (wave_u < WaveDma<D, 32>::PASSES) dma.copy_pass(smem_lds + S::V_BASE, vbase, row_bytes, left < 32 ? (int)left : 32, lane, wave_u);
+  }
+  // query tiles that see the block: [qt0, nqt) of every head of the group, tile j of this list for wave j mod 8
+  const int nqt = (int)(((int64_t)a.s_q + 31) / 32);
+  int qt0 = 0;
+  if (a.causal && key0 > a.q_offset) {
+    const int64_t first = key0 - a.q_offset;
+    qt0 = first >= a.s_q ? nqt : (int)(first / 32);
+  }
+  const int nv = nqt - qt0, total = nv * a.group;
+  const uint32_t q_bytes = (uint32_t)a.q_stride_s * 2, do_bytes = (uint32_t)a.do_stride_s * 2;
+  WaveDma<D, 32> dma_q, dma_do;
+  dma_q.init(lane, q_bytes);
+  dma_do.init(lane, do_bytes);
+  // the two statistics are arrays of one workspace (far below 4 GB): one uniform base and a 32-bit lane offset
+  const int64_t stat_gap = a.delta - a.lse2;
+  const float* const stat_base = stat_gap < 0 ? a.delta : a.lse2;
+  const uint32_t off_lse2 = stat_gap < 0 ? (uint32_t)(-stat_gap) * 4u : 0u, off_delta = stat_gap < 0 ? 0u : (uint32_t)stat_gap * 4u;
+  const unsigned set_lds = smem_lds + wave_u * BUF * S::SET_BYTES;
+  auto head_of = [&](int j) { return __builtin_amdgcn_readfirstlane(j / nv); };
+  auto copy_tile = [&](int j, int buf, bool with_q, bool with_do) {
+    const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32, h = hk * a.group + hh, rows = a.s_q - row0;
+    const unsigned dst = set_lds + buf * S::SET_BYTES;
+    if (with_q) {
+      dma_q.copy(dst, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)h * a.q_stride_h + (int64_t)row0 * a.q_stride_s), q_bytes, rows < 32 ? rows : 32, lane);
+      // lanes 0..31: lse2 of the rows, lanes 32..63: -delta (clamped to the slice)
+      const int rr = ql < rows ? ql : rows - 1;
+      dma4(uniform_ptr(stat_base + ((int64_t)b * a.n_q_heads + h) * a.s_q + row0), (g ? off_delta : off_lse2) + (uint32_t)rr * 4u,
+           __builtin_amdgcn_readfirstlane(dst + 2 * TILE_BYTES));
+    }
+    if (with_do)
+      dma_do.copy(dst + TILE_BYTES, uniform_ptr(a.d_out + (int64_t)b * a.do_stride_b + (int64_t)h * a.do_stride_h + (int64_t)row0 * a.do_stride_s), do_bytes,
+                  rows < 32 ? rows : 32, lane);
+  };
+  int j = wave_u;
+  if (j < total) copy_tile(j, 0, true, true);
+  wait_async();
+  __syncthreads();                                       // V has landed
+  RpBase<D> lo_q, lo_v;
+  TrBase<D> lo_qt;
+  lo_q.init(lane, (int)set_lds);
+  lo_qt.init(lane, (int)set_lds);
+  lo_v.init(lane, (int)smem_lds + S::V_BASE);
+  int buf = 0;
+  for (; j < total; j += NW) {
+    const int jn = j + NW;
+    const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32;
+    if constexpr (BUF == 2) {
+      if (jn < total) copy_tile(jn, buf ^ 1, true, true);
+      SP_FENCE();
+    }
+    const int o = buf * S::SET_BYTES;
+    RpBase<D> lq = lo_q;
+    TrBase<D> lqt = lo_qt;
+    lq.add(o);
+    lqt.add(o);
+    const float* stat = reinterpret_cast<const float*>(smem + (set_lds - smem_lds) + o + 2 * TILE_BYTES) + 4 * g;
+    f32x16 s, dp;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const f32x16 zero = {0};
+      s = mfma32(lds_rp<D>(lq, ks, 0), k[ks], ks == 0 ? zero : s);
+    }
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 nd = *reinterpret_cast<const f32x4*>(stat + 32 + 8 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dp[4 * i4 + e] = nd[e];
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) dp = mfma32(lds_rp<D>(lq, ks, TILE_BYTES), lds_rp<D>(lo_v, ks, 0), dp);
+    if ((a.causal && a.q_offset + row0 < key0 + 31) || row0 + 32 > a.s_q) {
+      const int64_t rl = a.causal ? mykey - a.q_offset - row0 : 0;      // first row of the tile that sees this lane's key
+      const int lo = (rl < 0 ? 0 : (rl > 32 ? 32 : (int)rl)) - 4 * g, hi = (a.s_q - row0 > 32 ? 32 : a.s_q - row0) - 4 * g;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 8 * (i >> 2) + (i & 3);
+        s[i] = ((r >= lo) & (r < hi)) ? s[i] : -INFINITY;      // exp2(-inf) = 0
+      }
+    }
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 l2 = *reinterpret_cast<const f32x4*>(stat + 8 * i4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[4 * i4 + e] = __builtin_fmaf(s[4 * i4 + e], c, -l2[e]);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) s[i] = exp2_fast(s[i]);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) dp[i] *= s[i];
+    const bf16x8 pb[2] = {pack8(s, 0), pack8(s, 8)}, dsb[2] = {pack8(dp, 0), pack8(dp, 8)};
+    // dK first: with one buffer, Q of the next tile is copied while dV is computed
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) dk[db] = mfma32(lds_tr<D>(lqt, db, hf * 16 * D * 2), dsb[hf], dk[db]);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(dk[db]));      // the reads of Q are done before Q is copied over
+    if constexpr (BUF == 1) {
+      if (jn < total) copy_tile(jn, 0, true, false);
+    }
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) dv[db] = mfma32(lds_tr<D>(lqt, db, TILE_BYTES + hf * 16 * D * 2), pb[hf], dv[db]);
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(dv[db]));
+    if constexpr (BUF == 1) {
+      if (jn < total) copy_tile(jn, 0, false, true);
+    }
+    SP_FENCE();
+    wait_async();
+    asm volatile("" ::: "memory");
+    SP_FENCE();
+    if constexpr (BUF == 2) buf ^= 1;
+  }
+  wait_async();
+  const int r = tid >> 4, d0 = (tid & 15) * (D / 16);
+  const int64_t key = key0 + r;
+  const bool mine = key >= a.kv_begin && key < a.kv_end;
+#pragma unroll
+  for (int grad = 0; grad < 2; ++grad) {
+    __syncthreads();                                     // nobody reads what is there any more
+    put_part<D>(smem + wave_u * S::PART_BYTES, grad ? dv : dk, grad ? 1.0f : a.scale, ql, g);
+    __syncthreads();
+    if (mine) {
+      f32x4 sum[D / 64];
+      sum_parts<D>(smem, r, d0, sum);
+      float* dst = (grad ? a.dv_acc[chunk] : a.dk_acc[chunk]) + head_off + (chunk_row0 + r) * a.kv_stride_s + d0;
+#pragma unroll
+      for (int j4 = 0; j4 < D / 64; ++j4) {
+        f32x4* p = reinterpret_cast<f32x4*>(dst + 4 * j4);
+        if (a.dkv_accumulate) sum[j4] += *p;
+        *p = sum[j4];
+      }
+    }
+  }
+}
+
+// dq and dk/dv items, the kind that takes longer first.
+template <int D>
+__global__ __launch_bounds__(512) void attn_bwd_small_kernel(const BwdArgs a, int n_dq, int n_dkdv) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
+  if ((i < first) == (a.dq_first != 0)) dq_small_item<D>(a, a.dq_first ? i : i - n_dkdv, smem);
+  else dkdv_small_item<D>(a, a.dq_first ? i - n_dq : i, smem);
+}
+
+hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {
+  const int64_t n_dq = ((int64_t)a.s_q + 31) / 32 * a.n_q_heads * batch;
+  const int64_t n_dkdv = (a.kv_end - kv_grid_origin(a.kv_begin, a.kv.n, 32) + 31) / 32 * a.n_kv_heads * batch;
+  const dim3 grid((unsigned)(n_dq + n_dkdv)), block(512);
+  if (head_dim == 128) hipLaunchKernelGGL(attn_bwd_small_kernel<128>, grid, block, BwdSmall<128>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  else hipLaunchKernelGGL(attn_bwd_small_kernel<64>, grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  return hipGetLastError();
+}
+
 hipError_t opt_in_small_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<128>), attr, FwdSmall<128>::LDS);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<64>), attr, FwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<128>), attr, BwdSmall<128>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64>), attr, BwdSmall<64>::LDS);
   return e;
 }
 
