@@ -441,21 +441,26 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // nothing else until the matrix pipe has taken it, so vector work only hides behind the MFMAs of
 // ANOTHER wave of the same SIMD.)  Q and dO tiles sit in rings of four LDS slots, the row statistics
 // in a ring of four; group A copies Q(u+2) and the statistics, group B copies dO(u+2).
+// Query rows of a tile.  At head_dim 64 the scores of 64 rows fit the registers that head_dim 128 needs for its operands and
+// accumulators; twice the work per tile halves the barriers, cursor steps and copy instructions per pair: 8192 rows on 40960 keys,
+// 16/2 heads, 2635 -> 2437 us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 220 -> 209 us.
+constexpr int dkdv_rows_per_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
+
 template <int D>
 struct DkdvState {
-  static constexpr int KS = D / 16, DB = D / 32;
+  static constexpr int KS = D / 16, DB = D / 32, QB = dkdv_rows_per_tile(D) / 32;
   bf16x8 kreg[KS];
   f32x16 dk[DB], dv[DB];
-  f32x16 s, dp;
-  bf16x8 pb[2], dsb[2];      // 16 query rows each
-  f32x4 lse2v[4];            // lse2 of this lane's 16 rows of the tile in `s`: fetched by the matrix phase (the LDS
-                             // latency passes while the score MFMAs run), used first thing by the vector phase
+  f32x16 s[QB], dp[QB];
+  bf16x8 pb[QB][2], dsb[QB][2];      // 16 query rows each
+  f32x4 lse2v[QB][4];                // lse2 of this lane's rows of the tile in `s`: fetched by the matrix phase (the LDS
+                                     // latency passes while the score MFMAs run), used first thing by the vector phase
 };
 
 // LDS layout (bytes): Q ring, dO ring, V rows of the workgroup, statistics ring
 template <int D, int NW>
 struct DkdvLds {
-  static constexpr int BMQ = 32, SLOTS = 4;
+  static constexpr int BMQ = dkdv_rows_per_tile(D), SLOTS = 4;
   static constexpr int TILE_BYTES = BMQ * D * 2;
   static constexpr int Q_BASE = 0, DO_BASE = SLOTS * TILE_BYTES, V_BASE = 2 * SLOTS * TILE_BYTES;
   static constexpr int V_BYTES = NW * 32 * D * 2;
@@ -467,44 +472,52 @@ struct DkdvLds {
 template <int D, int NW, bool WITH_ACC, bool WITH_SCORES, int LOOK>
 struct DkdvMatrixPhase {
   using L = DkdvLds<D, NW>;
-  static constexpr int KS = D / 16, DB = D / 32;
-  static constexpr int N_AC = WITH_ACC ? 4 * DB : 0, N_SC = WITH_SCORES ? 2 * KS : 0, N = N_AC + N_SC;
+  static constexpr int KS = D / 16, DB = D / 32, QB = DkdvState<D>::QB;
+  static constexpr int N_AC = WITH_ACC ? 4 * DB * QB : 0, N_SC = WITH_SCORES ? 2 * KS * QB : 0, N = N_AC + N_SC;
   static constexpr int NBUF = LOOK + 1, HALF = 16 * D * 2;
   const TrBase<D>& lo_qt;      // Q(u-1), transposed; dO(u-1) sits DO_BASE further
   const RpBase<D>& lo_q;       // Q(u), row-packed; dO(u) sits DO_BASE further
   const RpBase<D>& lo_v;       // this wave's 32 rows of V
   DkdvState<D>& st;
   const float* stat;           // LDS: lse2 of the rows of tile u, this lane's half (rows 8 i4 + 4 g .. + 3 at [8 i4 .. + 3]);
-                               // -delta of the same rows 32 floats further
+                               // -delta of the same rows BMQ floats further
   bf16x8 abuf[NBUF];
   bf16x8 vb[2];
+
+  // matrix instruction j of the scores: head_dim block ks, query block qb, S or dP
+  static constexpr int ks_of(int j) { return j / (2 * QB); }
+  static constexpr int qb_of(int j) { return j % (2 * QB) / 2; }
 
   template <int M>
   SP_DEV void reads() {
     if constexpr (WITH_SCORES && M == N_AC + LOOK + 2) {
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) st.lse2v[i4] = *reinterpret_cast<const f32x4*>(stat + 8 * i4);
+      for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) st.lse2v[qb][i4] = *reinterpret_cast<const f32x4*>(stat + 32 * qb + 8 * i4);
     }
     // the accumulator of dP(u) starts from -delta of its rows (dP of the tile before was packed into dsb by the
     // vector phase and is dead): the matrix pipe delivers dP - delta
     if constexpr (WITH_SCORES && M == (N_AC > 0 ? 2 : 0)) {
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const f32x4 nd = *reinterpret_cast<const f32x4*>(stat + 32 + 8 * i4);
+      for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) st.dp[4 * i4 + e] = nd[e];
-      }
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const f32x4 nd = *reinterpret_cast<const f32x4*>(stat + L::BMQ + 32 * qb + 8 * i4);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) st.dp[qb][4 * i4 + e] = nd[e];
+        }
     }
     if constexpr (M < N_AC) {
-      constexpr int h = M / (2 * DB), db = (M % (2 * DB)) / 2;
+      constexpr int h = M / (2 * DB), db = (M % (2 * DB)) / 2;      // h: 16 query rows
       abuf[M % NBUF] = lds_tr<D>(lo_qt, db, ((M & 1) ? 0 : L::DO_BASE) + h * HALF);
     } else if constexpr (M < N) {
-      constexpr int j = M - N_AC, ks = j / 2;
+      constexpr int j = M - N_AC, ks = ks_of(j), qb = qb_of(j);
       if constexpr ((j & 1) == 0) {
-        abuf[M % NBUF] = lds_rp<D>(lo_q, ks, 0);
+        abuf[M % NBUF] = lds_rp<D>(lo_q, ks, qb * 32 * D * 2);
       } else {
-        abuf[M % NBUF] = lds_rp<D>(lo_q, ks, L::DO_BASE);
-        vb[ks & 1] = lds_rp<D>(lo_v, ks, 0);
+        abuf[M % NBUF] = lds_rp<D>(lo_q, ks, L::DO_BASE + qb * 32 * D * 2);
+        if constexpr (qb == 0) vb[ks & 1] = lds_rp<D>(lo_v, ks, 0);
       }
     }
   }
@@ -512,13 +525,13 @@ struct DkdvMatrixPhase {
   SP_DEV void mfma() {
     if constexpr (M < N_AC) {
       constexpr int h = M / (2 * DB), db = (M % (2 * DB)) / 2;
-      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(abuf[M % NBUF], st.pb[h], st.dv[db]);
-      else st.dk[db] = mfma32(abuf[M % NBUF], st.dsb[h], st.dk[db]);
+      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(abuf[M % NBUF], st.pb[h / 2][h % 2], st.dv[db]);
+      else st.dk[db] = mfma32(abuf[M % NBUF], st.dsb[h / 2][h % 2], st.dk[db]);
     } else {
-      constexpr int j = M - N_AC, ks = j / 2;
+      constexpr int j = M - N_AC, ks = ks_of(j), qb = qb_of(j);
       const f32x16 zero = {0};
-      if constexpr ((j & 1) == 0) st.s = mfma32(abuf[M % NBUF], st.kreg[ks], ks == 0 ? zero : st.s);
-      else st.dp = mfma32(abuf[M % NBUF], vb[ks & 1], st.dp);
+      if constexpr ((j & 1) == 0) st.s[qb] = mfma32(abuf[M % NBUF], st.kreg[ks], ks == 0 ? zero : st.s[qb]);
+      else st.dp[qb] = mfma32(abuf[M % NBUF], vb[ks & 1], st.dp[qb]);
     }
   }
   template <int M>
@@ -546,42 +559,47 @@ struct DkdvMatrixPhase {
   }
 };
 
-// P = exp2(c S - lse2) on visible pairs, dS = P (dP - delta), where `dp` arrives as dP - delta; element i of a lane is query row
-// 8*(i/4) + 4g + i%4 of the tile, the lane's column is its key.  `hook(i)`, i = 0..3, is called at four
+// P = exp2(c S - lse2) on visible pairs, dS = P (dP - delta), where `dp` arrives as dP - delta; element i of block qb of a lane is
+// query row 32 qb + 8*(i/4) + 4g + i%4 of the tile, the lane's column is its key.  `hook(i)`, i = 0..3, is called at four
 // points spread over the phase (asynchronous tile copies ride there).
 template <int D, class H>
-SP_DEV void dkdv_vector_phase(DkdvState<D>& st, const float* stat, float c, bool need_mask, int rmin_rel, int rmax_rel,
-                              int g, H&& hook) {
+SP_DEV void dkdv_vector_phase(DkdvState<D>& st, float c, bool need_mask, int rmin_rel, int rmax_rel, int g, H&& hook) {
+  constexpr int QB = DkdvState<D>::QB;
   if (need_mask) {
-    // row (8*(i/4) + 4g + i%4) in [rmin_rel, rmax_rel), with the lane's part moved to the bounds: the row
+    // row (32 qb + 8*(i/4) + 4g + i%4) in [rmin_rel, rmax_rel), with the lane's part moved to the bounds: the row
     // numbers are immediates then (a register per element otherwise, hoisted out of the tile loop)
     const int lo = rmin_rel - 4 * g, hi = rmax_rel - 4 * g;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int r = 8 * (i >> 2) + (i & 3);
-      st.s[i] = ((r >= lo) & (r < hi)) ? st.s[i] : -INFINITY;      // exp2(-inf) = 0
-    }
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int r = 32 * qb + 8 * (i >> 2) + (i & 3);
+        st.s[qb][i] = ((r >= lo) & (r < hi)) ? st.s[qb][i] : -INFINITY;      // exp2(-inf) = 0
+      }
   }
-  // Stage by stage over all 16 elements, so that neighbouring instructions do not depend on each other.
+  // Stage by stage over the 16 elements of a block, so that neighbouring instructions do not depend on each other.
   // No LDS read here: lse2 is in registers (the matrix phase fetched it) and delta is in dP already.  This
   // phase is the longer of the two, and an LDS read in it waits for about 280 cycles behind the reads of the
   // group that is in its matrix phase.
-  hook(0);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) st.s[i] = __builtin_fmaf(st.s[i], c, -st.lse2v[i >> 2][i & 3]);
-  hook(1);
+  for (int qb = 0; qb < QB; ++qb) {
+    if (qb == 0) hook(0);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) st.s[i] = exp2_fast(st.s[i]);
-  hook(2);
+    for (int i = 0; i < 16; ++i) st.s[qb][i] = __builtin_fmaf(st.s[qb][i], c, -st.lse2v[qb][i >> 2][i & 3]);
+    if (qb == 0) hook(1);
 #pragma unroll
-  for (int i = 0; i < 16; ++i) st.dp[i] *= st.s[i];       // dp holds dP - delta
-  hook(3);
+    for (int i = 0; i < 16; ++i) st.s[qb][i] = exp2_fast(st.s[qb][i]);
+    if (qb == QB - 1) hook(2);
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    st.pb[h] = pack8(st.s, 8 * h);
-    st.dsb[h] = pack8(st.dp, 8 * h);
-    // pin: without a use here the optimiser sinks this arithmetic past the phase barrier
-    asm volatile("" : "+v"(st.pb[h]), "+v"(st.dsb[h]));
+    for (int i = 0; i < 16; ++i) st.dp[qb][i] *= st.s[qb][i];       // dp holds dP - delta
+    if (qb == QB - 1) hook(3);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      st.pb[qb][h] = pack8(st.s[qb], 8 * h);
+      st.dsb[qb][h] = pack8(st.dp[qb], 8 * h);
+      // pin: without a use here the optimiser sinks this arithmetic past the phase barrier
+      asm volatile("" : "+v"(st.pb[qb][h]), "+v"(st.dsb[qb][h]));
+    }
   }
 }
 
@@ -740,8 +758,9 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       j.row_bytes = src_row_bytes;
       j.dst = smem_lds + (copies_q ? L::Q_BASE : L::DO_BASE) + slot * TILE_BYTES;
       j.rows = a.s_q - cc.row0;
-      // lanes 0..31: lse2 of rows row0 .. row0+31, lanes 32..63: delta of the same rows (clamped to the slice)
-      const int t2 = fresh(tid), ql2 = t2 & 31, g2 = (t2 >> 5) & 1;
+      // 32 rows a tile: lanes 0..31 lse2 of rows row0 .. row0+31, lanes 32..63 delta of the same rows (clamped to the slice).
+      // 64 rows: lse2 of row0 .. row0+63, and a second copy with delta
+      const int t2 = fresh(tid), ql2 = t2 & (BMQ - 1), g2 = BMQ == 32 ? (t2 >> 5) & 1 : 0;
       const int rr = ql2 < j.rows ? ql2 : j.rows - 1;
       j.stat_src = cc.stat;
       j.stat_off = (g2 ? stat_off_delta : stat_off_lse2) + (uint32_t)rr * 4u;
@@ -749,10 +768,13 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       return j;
     };
     auto copy_pass = [&](const CopyJob& j, int n) { dma.issue(j.dst, j.src, j.row_bytes, j.rows, gwave_u, n); };
-    // every wave of group A writes the same 64 statistics (no branch in the phase: identical data)
+    // every wave of group A writes the same statistics (no branch in the phase: identical data)
     auto copy_part = [&](const CopyJob& j, bool with_stats, int part) {
       if (part < PASSES) copy_pass(j, part);
-      if (part == 3 && with_stats) dma4(j.stat_src, j.stat_off, j.stat_dst);
+      if (part == 3 && with_stats) {
+        dma4(j.stat_src, j.stat_off, j.stat_dst);
+        if constexpr (BMQ == 64) dma4(j.stat_src, j.stat_off - stat_off_lse2 + stat_off_delta, j.stat_dst + 4 * BMQ);
+      }
     };
     auto copy_all = [&](const CopyJob& j, bool with_stats) {
       for (int part = 0; part < 4; ++part) copy_part(j, with_stats, part);
@@ -794,19 +816,18 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       return reinterpret_cast<const float*>(smem + L::STAT_BASE + sl * L::STAT_BYTES) + 4 * ((fresh(tid) >> 5) & 1);
     };
     // vector phase of tile u (ring slot vslot, first row row0), with the copies of job j riding along
-    auto vector_phase = [&](int u, int vslot, int row0, const CopyJob& j) {
+    auto vector_phase = [&](int u, int row0, const CopyJob& j) {
       const bool need_mask = seq_lo + u < total_m;
-      int rmin_rel = 0, rmax_rel = 32;
+      int rmin_rel = 0, rmax_rel = BMQ;
       if (need_mask) {
         // first row of the tile that sees this lane's key (worked out here, in the rare masked tiles,
         // rather than kept in a register across the loop)
         const int64_t rl = a.causal ? tile_key0 + wave_u * 32 + (fresh(tid) & 31) - a.q_offset - row0 : 0;
-        rmin_rel = rl < 0 ? 0 : (rl > 32 ? 32 : (int)rl);
+        rmin_rel = rl < 0 ? 0 : (rl > BMQ ? BMQ : (int)rl);
         const int left = a.s_q - row0;
-        rmax_rel = left > 32 ? 32 : left;
+        rmax_rel = left > BMQ ? BMQ : left;
       }
-      const float* stat = reinterpret_cast<const float*>(smem + L::STAT_BASE + vslot * L::STAT_BYTES);
-      dkdv_vector_phase<D>(st, stat, c, need_mask, rmin_rel, rmax_rel, (fresh(tid) >> 5) & 1, [&](int part) { copy_part(j, copies_q, part); });
+      dkdv_vector_phase<D>(st, c, need_mask, rmin_rel, rmax_rel, (fresh(tid) >> 5) & 1, [&](int part) { copy_part(j, copies_q, part); });
     };
     // Both groups run the same code; group B starts one phase (one barrier) later and group A idles
     // one phase at the end.
@@ -822,7 +843,7 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
     int vslot = 0, cslot = 2;            // ring slots of the tile of the vector phase and of the tile being copied
     for (int u = 0; u + 1 < cnt; ++u) {
       const int row0_new = cc.row0;
-      vector_phase(u, vslot, row0_cur, make_copy(cc, cslot));      // tile u+2 rides along
+      vector_phase(u, row0_cur, make_copy(cc, cslot));      // tile u+2 rides along
       cursor_next(cc);
       row0_cur = row0_nxt;
       row0_nxt = row0_new;
@@ -836,7 +857,7 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       wait_async();                                      // the copies of the vector phase before have landed
       phase_end();
     }
-    vector_phase(cnt - 1, vslot, row0_cur, make_copy(cc, cslot));   // (copies the last tile once more)
+    vector_phase(cnt - 1, row0_cur, make_copy(cc, cslot));   // (copies the last tile once more)
     phase_end();
     { DkdvMatrixPhase<D, NW, true, false, 2> ph{lo_qt, lo_q, lo_v, st, nullptr}; ph.run(); }     // sums of the last tile
     wait_async();
