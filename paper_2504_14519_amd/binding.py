@@ -114,8 +114,9 @@ def _check(rc, what):
 
 
 def _stream():
+    # the raw handle of the current device's current stream: a stream object per call costs more than a kernel launch
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _same_strides(a, b):
@@ -126,17 +127,11 @@ def _same_strides(a, b):
 def make_params(q, k, out_like, q_offset, kv_begin, kv_end, causal, scale, out_dtype=BF16):
     """Fill the parameter block from tensor shapes/strides.  q [B,s,Hq,D], k [B,Nkv,Hkv,D]."""
     B, s, Hq, D = q.shape
-    p = AttnParams()
-    p.batch, p.s_q, p.n_q_heads, p.n_kv_heads, p.head_dim = B, s, Hq, k.shape[2], D
-    p.causal = 1 if causal else 0
-    p.kv_capacity, p.q_offset, p.kv_begin, p.kv_end = k.shape[1], q_offset, kv_begin, kv_end
-    p.scale = float(scale) if scale is not None else 1.0 / math.sqrt(D)
-    p.out_dtype = out_dtype
-    p.q_stride_b, p.q_stride_s, p.q_stride_h = q.stride(0), q.stride(1), q.stride(2)
-    p.kv_stride_b, p.kv_stride_s, p.kv_stride_h = k.stride(0), k.stride(1), k.stride(2)
-    p.o_stride_b, p.o_stride_s, p.o_stride_h = out_like.stride(0), out_like.stride(1), out_like.stride(2)
-    p.do_stride_b, p.do_stride_s, p.do_stride_h = p.o_stride_b, p.o_stride_s, p.o_stride_h   # backward overrides
-    return p
+    o_strides = out_like.stride(0), out_like.stride(1), out_like.stride(2)
+    # in the order of AttnParams; the strides of d_out are those of out until the backward overrides them
+    return AttnParams(B, s, Hq, k.shape[2], D, 1 if causal else 0, k.shape[1], q_offset, kv_begin, kv_end,
+                      float(scale) if scale is not None else 1.0 / math.sqrt(D), out_dtype, q.stride(0), q.stride(1), q.stride(2),
+                      k.stride(0), k.stride(1), k.stride(2), *o_strides, *o_strides)
 
 
 def slimpipe_attn_init():
@@ -185,9 +180,8 @@ def slimpipe_attn_bwd(q_slice, k_prefix, v_prefix, out, d_out, lse, q_offset, kv
         raise SlimpipeError("dq must have the strides of q; dk_acc/dv_acc those of k")
     p = make_params(q_slice, k_prefix, out, q_offset, kv_begin, kv_end, causal, scale)
     p.do_stride_b, p.do_stride_s, p.do_stride_h = d_out.stride(0), d_out.stride(1), d_out.stride(2)
-    need = slimpipe_attn_workspace_bytes(p, True)
     if workspace is None:
-        workspace = torch.empty(need, device=q_slice.device, dtype=torch.uint8)
+        workspace = torch.empty(slimpipe_attn_workspace_bytes(p, True), device=q_slice.device, dtype=torch.uint8)
     _check(lib.slimpipe_attn_bwd(ctypes.byref(p), q_slice.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
                                  out.data_ptr(), d_out.data_ptr(), lse.data_ptr(), dq.data_ptr(), dq_dtype,
                                  1 if dq_accumulate else 0, dk_acc.data_ptr(), dv_acc.data_ptr(),
@@ -294,9 +288,8 @@ def slimpipe_attn_bwd_chunked(q_slice, k_chunks, v_chunks, out, d_out, lse, q_of
             raise SlimpipeError("dk/dv chunks must have the strides of the k chunks")
     p = make_params(q_slice, _ChunkedKV(k_chunks), out, q_offset, kv_begin, kv_end, causal, scale)
     p.do_stride_b, p.do_stride_s, p.do_stride_h = d_out.stride(0), d_out.stride(1), d_out.stride(2)
-    need = slimpipe_attn_workspace_bytes(p, True)
     if workspace is None:
-        workspace = torch.empty(need, device=q_slice.device, dtype=torch.uint8)
+        workspace = torch.empty(slimpipe_attn_workspace_bytes(p, True), device=q_slice.device, dtype=torch.uint8)
     _check(lib.slimpipe_attn_bwd_chunked(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
                                          len(k_chunks), k_chunks[0].shape[1], out.data_ptr(), d_out.data_ptr(), lse.data_ptr(),
                                          dq.data_ptr(), dq_dtype, 1 if dq_accumulate else 0, _chunk_table(dk_chunks),

@@ -160,8 +160,8 @@ int64_t all_query_blocks(const slimpipe_attn_params* p, int head_waves) {
 }
 
 // Microseconds of a call with w < compute units query blocks of 256 rows in r key ranges (see fwd_preferred_ranges).
-double fwd_blocks_us(const slimpipe_attn_params* p, int64_t w, int r) {
-  const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
+double fwd_blocks_us(const slimpipe_attn_params* p, int64_t cus, int64_t w, int r) {
+  const int64_t keys = p->kv_end - p->kv_begin;
   return (double)((w * r + cus - 1) / cus) * (10.0 + (p->head_dim == 64 ? 1.8 : 2.5) * (double)keys / (128.0 * r)) +
          (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
 }
@@ -189,7 +189,7 @@ int fwd_preferred_ranges(const slimpipe_attn_params* p, int head_waves) {
     int pick = 1;
     double best_us = 1e30;
     for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
-      const double us = fwd_blocks_us(p, w, r);
+      const double us = fwd_blocks_us(p, cus, w, r);
       if (us < best_us * 0.97) { best_us = us; pick = r; }
     }
     return pick;
@@ -223,9 +223,9 @@ size_t fwd_parts_bytes(const slimpipe_attn_params* p, int ranges) {
 }
 // Microseconds of a call through the small kernel (32 query rows a workgroup, the 8 waves sharing out the keys of its range) in
 // r key ranges: 8.7 (head_dim 64: 7) + 1.3 (1.4) per step of a wave, which is 32 (64) keys, times the rounds of workgroups, + the merge.
-double fwd_small_us(const slimpipe_attn_params* p, int r) {
+double fwd_small_us(const slimpipe_attn_params* p, int64_t cus, int r) {
   const bool d64 = p->head_dim == 64;
-  const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
+  const int64_t keys = p->kv_end - p->kv_begin;
   const int64_t wgs = ((int64_t)p->s_q + 31) / 32 * p->n_q_heads * p->batch * r, per_step = 8 * (d64 ? 64 : 32);
   const double steps = (double)((keys + r * per_step - 1) / (r * per_step)), rounds = (double)((wgs + cus - 1) / cus);
   return (d64 ? 7.0 : 8.7) + 2 * (rounds - 1) + rounds * steps * (d64 ? 1.4 : 1.3) +
@@ -248,12 +248,12 @@ FwdPlan fwd_plan(const slimpipe_attn_params* p, bool lent, size_t room) {
   // ranges: the pick is within 2 % of the best in the mean, at most 1.7 % slower than the 256-row blocks, 1.53 times as fast in the mean
   // and up to 2.6 times (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).  It loses where keys are long: every workgroup
   // reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
-  const int64_t w = all_query_blocks(p, hw), keys = p->kv_end - p->kv_begin;
-  if (lent && w < compute_units() && keys > 0) {
-    double best_us = fwd_blocks_us(p, w, ranges) * 0.97;
+  const int64_t w = all_query_blocks(p, hw), keys = p->kv_end - p->kv_begin, cus = compute_units();
+  if (lent && w < cus && keys > 0) {
+    double best_us = fwd_blocks_us(p, cus, w, ranges) * 0.97;
     int pick = 0;
     for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
-      const double us = fwd_small_us(p, r);
+      const double us = fwd_small_us(p, cus, r);
       if (us < best_us) { best_us = us * 0.99; pick = r; }
     }
     if (pick && fwd_parts_bytes(p, pick) <= room) return {hw, pick, true};
@@ -274,6 +274,7 @@ struct BwdPlan {
   bool both;         // dq and dk/dv items in one launch
   bool dq_first;     // ... the dq items first
   double us;         // (one launch) its time and that of the reduce by the model of bwd_plan
+  bool full;         // what is wanted whatever the workspace, not cut down to it
 };
 
 // Time at which `na` items of length ta, then `nb` items of length tb, each started on the unit that is free first, are
@@ -310,7 +311,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
   const int64_t wq = all_query_blocks(p, hw);
   const int64_t wk = dkdv_key_tiles(p, n_chunks) * p->n_kv_heads * p->batch;
   if (wk <= 0 || wq + wk >= 2 * cus) {
-    BwdPlan plan{hw, preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p, hw), false, false, 0.0};
+    BwdPlan plan{hw, preferred_split(p, n_chunks, ticket), fwd_preferred_ranges(p, hw), false, false, 0.0, room == SIZE_MAX};
     while (plan.split > 1 && split_bytes(p, n_chunks, plan.split) > room) plan.split /= 2;
     const size_t used = split_bytes(p, n_chunks, plan.split);
     while (plan.dq_ranges > 1 && (dq_parts_bytes(p, plan.dq_ranges) > room - used || (int64_t)p->batch * plan.dq_ranges > 65535)) --plan.dq_ranges;
@@ -320,7 +321,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
   const double dq_tiles = (double)keys / 64, dq_tile = p->head_dim == 128 ? 2.4 : 1.4;
   const double stream = (double)(((int64_t)p->s_q + 31) / 32 * (p->n_q_heads / p->n_kv_heads)), dkdv_tile = p->head_dim == 128 ? 1.6 : 1.1;
   static const int kCuts[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-  BwdPlan best{hw, 1, 1, true, false, 0.0};
+  BwdPlan best{hw, 1, 1, true, false, 0.0, room == SIZE_MAX};
   double best_us = 1e30;
   for (int s : kCuts) {
     if (s > 8 || (s > 1 && stream / s < 4)) break;             // a chunk keeps at least 4 query tiles
@@ -340,7 +341,7 @@ BwdPlan bwd_plan(const slimpipe_attn_params* p, int n_chunks, bool ticket, size_
       double bytes = s > 1 ? (double)(s + 2) * keys * p->n_kv_heads * p->batch * p->head_dim * 8 : 0.0;
       if (r > 1) bytes += (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4;
       if (bytes > 0) us += 4 + bytes / 5e6;
-      if (us < best_us * 0.99) { best_us = us; best = {hw, s, r, both, tq > tk, us}; }
+      if (us < best_us * 0.99) { best_us = us; best = {hw, s, r, both, tq > tk, us, room == SIZE_MAX}; }
     }
   }
   return best;
@@ -366,11 +367,8 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // Calls of fewer than 64 dq items would gain as well (256 rows of 4 heads on 1215 keys 24.8 -> 17.9 us) but their launches are
 // pinned, kind by kind, by the test of the per-kernel timing.
 struct BwdSmallPlan { bool use, dq_first; };
-BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, int n_chunks, const BwdPlan& plan, size_t workspace_bytes) {
-  const size_t parts = split_bytes(p, n_chunks, plan.split) + dq_parts_bytes(p, plan.dq_ranges);
-  if (!plan.both || parts == 0 || workspace_bytes < delta_bytes(p) + kTicketBytes + parts) return {false, false};
-  const BwdPlan full = bwd_plan(p, n_chunks, true, SIZE_MAX);
-  if (plan.split != full.split || plan.dq_ranges != full.dq_ranges) return {false, false};      // (cut for the room there is)
+BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) {
+  if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false};
   const bool d64 = p->head_dim == 64;
   const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
   const int64_t row_blocks = ((int64_t)p->s_q + 31) / 32, key_blocks = (keys + 31) / 32;
@@ -772,7 +770,7 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   if (timed(SLIMPIPE_KERNEL_DELTA, st, [&] { return launch_delta(a, p->batch, p->head_dim, st); }, events) != hipSuccess) return SLIMPIPE_ELAUNCH;
-  if (const BwdSmallPlan sm = bwd_small_plan(p, n_chunks, plan, workspace_bytes); sm.use) {
+  if (const BwdSmallPlan sm = bwd_small_plan(p, plan); sm.use) {
     a.dq_first = sm.dq_first;
     return timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_small(a, p->batch, p->head_dim, st); }, events) == hipSuccess ? SLIMPIPE_OK : SLIMPIPE_ELAUNCH;
   }
