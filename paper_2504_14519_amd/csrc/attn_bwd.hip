@@ -201,6 +201,9 @@ SP_DEV void dq_vector_phase(DqState<D, BN>& st, float c, bool need_mask, int kmi
 
 // Keys of a tile.  At head_dim 64 the scores of 128 keys fit the registers that head_dim 128 needs for its operands and accumulators,
 // and a tile has the matrix work of a head_dim 128 tile for the same barriers: 8192 rows on 40960 keys, 16/2 heads, 1675 -> 1598 us.
+// The calls that run dq and dk/dv in one launch keep 64 (kBothDqKeys): their items walk few keys, and the longer first and last
+// tile of an item costs more than the barriers (917 rows on 1230 keys, 16 heads: 45.2 us with 64, 46.8 with 128).
+constexpr int kBothDqKeys = 64;
 constexpr int dq_keys_per_tile(int head_dim) { return head_dim == 64 ? 128 : 64; }
 
 // One work item: index -> (query block, kv head, batch index x key range), the first fastest.
@@ -960,7 +963,7 @@ __global__ __launch_bounds__(512) void attn_bwd_both_kernel(const BwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_dq = a.dq_items[0] * a.dq_items[1] * a.dq_items[2], n_dkdv = a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
-  if ((i < first) == (a.dq_first != 0)) dq_item<D, 8, dq_keys_per_tile(D)>(a, a.dq_first ? i : i - n_dkdv, smem);
+  if ((i < first) == (a.dq_first != 0)) dq_item<D, 8, kBothDqKeys>(a, a.dq_first ? i : i - n_dkdv, smem);
   else dkdv_item<D, 8>(a, a.dq_first ? i - n_dq : i, smem);
 }
 
