@@ -451,9 +451,9 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // 16/2 heads, 2635 -> 2437 us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 220 -> 209 us.
 constexpr int dkdv_rows_per_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
 
-template <int D>
+template <int D, int BMQ>
 struct DkdvState {
-  static constexpr int KS = D / 16, DB = D / 32, QB = dkdv_rows_per_tile(D) / 32;
+  static constexpr int KS = D / 16, DB = D / 32, QB = BMQ / 32;
   bf16x8 kreg[KS];
   f32x16 dk[DB], dv[DB];
   f32x16 s[QB], dp[QB];
@@ -463,9 +463,9 @@ struct DkdvState {
 };
 
 // LDS layout (bytes): Q ring, dO ring, V rows of the workgroup, statistics ring
-template <int D, int NW>
+template <int D, int NW, int ROWS>
 struct DkdvLds {
-  static constexpr int BMQ = dkdv_rows_per_tile(D), SLOTS = 4;
+  static constexpr int BMQ = ROWS, SLOTS = 4;
   static constexpr int TILE_BYTES = BMQ * D * 2;
   static constexpr int Q_BASE = 0, DO_BASE = SLOTS * TILE_BYTES, V_BASE = 2 * SLOTS * TILE_BYTES;
   static constexpr int V_BYTES = NW * 32 * D * 2;
@@ -474,16 +474,16 @@ struct DkdvLds {
   static constexpr int TOTAL = STAT_BASE + SLOTS * STAT_BYTES;
 };
 
-template <int D, int NW, bool WITH_ACC, bool WITH_SCORES, int LOOK>
+template <int D, int NW, int BMQ, bool WITH_ACC, bool WITH_SCORES, int LOOK>
 struct DkdvMatrixPhase {
-  using L = DkdvLds<D, NW>;
-  static constexpr int KS = D / 16, DB = D / 32, QB = DkdvState<D>::QB;
+  using L = DkdvLds<D, NW, BMQ>;
+  static constexpr int KS = D / 16, DB = D / 32, QB = BMQ / 32;
   static constexpr int N_AC = WITH_ACC ? 4 * DB * QB : 0, N_SC = WITH_SCORES ? 2 * KS * QB : 0, N = N_AC + N_SC;
   static constexpr int NBUF = LOOK + 1, HALF = 16 * D * 2;
   const TrBase<D>& lo_qt;      // Q(u-1), transposed; dO(u-1) sits DO_BASE further
   const RpBase<D>& lo_q;       // Q(u), row-packed; dO(u) sits DO_BASE further
   const RpBase<D>& lo_v;       // this wave's 32 rows of V
-  DkdvState<D>& st;
+  DkdvState<D, BMQ>& st;
   const float* stat;           // LDS: lse2 of the rows of tile u, this lane's half (rows 8 i4 + 4 g .. + 3 at [8 i4 .. + 3]);
                                // -delta of the same rows BMQ floats further
   bf16x8 abuf[NBUF];
@@ -567,9 +567,9 @@ struct DkdvMatrixPhase {
 // P = exp2(c S - lse2) on visible pairs, dS = P (dP - delta), where `dp` arrives as dP - delta; element i of block qb of a lane is
 // query row 32 qb + 8*(i/4) + 4g + i%4 of the tile, the lane's column is its key.  `hook(i)`, i = 0..3, is called at four
 // points spread over the phase (asynchronous tile copies ride there).
-template <int D, class H>
-SP_DEV void dkdv_vector_phase(DkdvState<D>& st, float c, bool need_mask, int rmin_rel, int rmax_rel, int g, H&& hook) {
-  constexpr int QB = DkdvState<D>::QB;
+template <int D, int BMQ, class H>
+SP_DEV void dkdv_vector_phase(DkdvState<D, BMQ>& st, float c, bool need_mask, int rmin_rel, int rmax_rel, int g, H&& hook) {
+  constexpr int QB = BMQ / 32;
   if (need_mask) {
     // row (32 qb + 8*(i/4) + 4g + i%4) in [rmin_rel, rmax_rel), with the lane's part moved to the bounds: the row
     // numbers are immediates then (a register per element otherwise, hoisted out of the tile loop)
@@ -608,15 +608,15 @@ SP_DEV void dkdv_vector_phase(DkdvState<D>& st, float c, bool need_mask, int rmi
   }
 }
 
-static_assert((DkdvLds<128, 8>::SLOTS & (DkdvLds<128, 8>::SLOTS - 1)) == 0, "ring slots are stepped with a mask");
+static_assert((DkdvLds<128, 8, 32>::SLOTS & (DkdvLds<128, 8, 32>::SLOTS - 1)) == 0, "ring slots are stepped with a mask");
 
 // One work item: index -> (key tile * n_split + chunk of that tile's query stream, kv head, batch index), the first
 // fastest.
-template <int D, int NW>
+template <int D, int NW, int BMQ>
 SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
   static_assert(NW == 8, "two groups of four waves");
-  using L = DkdvLds<D, NW>;
-  constexpr int BNK = NW * 32, BMQ = L::BMQ, KS = D / 16, DB = D / 32, T = NW * 64, GT = T / 2;
+  using L = DkdvLds<D, NW, BMQ>;
+  constexpr int BNK = NW * 32, KS = D / 16, DB = D / 32, T = NW * 64, GT = T / 2;
   constexpr int TILE_BYTES = L::TILE_BYTES, SLOTS = L::SLOTS;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
@@ -640,7 +640,7 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
   const int64_t mykey = tile_key0 + wave_u * 32 + ql;
   const int64_t mykey_c = mykey < a.kv_end ? mykey : a.kv_end - 1;
 
-  DkdvState<D> st;
+  DkdvState<D, BMQ> st;
   {
     // K as B operand: column = my key, k-slots = head_dim 16*ks + 8g ..
     const bf16_t* kp = a.kv.k[kchunk] + head_off + (chunk_row0 + (mykey_c - tile_key0)) * a.kv_stride_s;
@@ -832,12 +832,12 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
         const int left = a.s_q - row0;
         rmax_rel = left > BMQ ? BMQ : left;
       }
-      dkdv_vector_phase<D>(st, c, need_mask, rmin_rel, rmax_rel, (fresh(tid) >> 5) & 1, [&](int part) { copy_part(j, copies_q, part); });
+      dkdv_vector_phase<D, BMQ>(st, c, need_mask, rmin_rel, rmax_rel, (fresh(tid) >> 5) & 1, [&](int part) { copy_part(j, copies_q, part); });
     };
     // Both groups run the same code; group B starts one phase (one barrier) later and group A idles
     // one phase at the end.
     if (group_b) phase_end();
-    { DkdvMatrixPhase<D, NW, false, true, 2> ph{lo_qt, lo_q, lo_v, st, stat_of(0)}; ph.run(); }     // scores of tile 0
+    { DkdvMatrixPhase<D, NW, BMQ, false, true, 2> ph{lo_qt, lo_q, lo_v, st, stat_of(0)}; ph.run(); }     // scores of tile 0
     advance();
     wait_async();
     phase_end();
@@ -857,14 +857,14 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       phase_end();
       // (V never moves: without this the eight offsets of its head_dim blocks are kept in registers across the loop)
       asm volatile("" : "+v"(lo_v.off0));
-      { DkdvMatrixPhase<D, NW, true, true, 2> ph{lo_qt, lo_q, lo_v, st, stat_of(vslot)}; ph.run(); }    // sums of tile u, scores of tile u+1
+      { DkdvMatrixPhase<D, NW, BMQ, true, true, 2> ph{lo_qt, lo_q, lo_v, st, stat_of(vslot)}; ph.run(); }    // sums of tile u, scores of tile u+1
       advance();
       wait_async();                                      // the copies of the vector phase before have landed
       phase_end();
     }
     vector_phase(cnt - 1, row0_cur, make_copy(cc, cslot));   // (copies the last tile once more)
     phase_end();
-    { DkdvMatrixPhase<D, NW, true, false, 2> ph{lo_qt, lo_q, lo_v, st, nullptr}; ph.run(); }     // sums of the last tile
+    { DkdvMatrixPhase<D, NW, BMQ, true, false, 2> ph{lo_qt, lo_q, lo_v, st, nullptr}; ph.run(); }     // sums of the last tile
     wait_async();
     phase_end();
     if (!group_b) phase_end();
@@ -948,7 +948,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a)
       __syncthreads();                                      // read by all before the first tile copy lands there
       if (item < 0) return;
     }
-    dkdv_item<D, NW>(a, item, smem);
+    dkdv_item<D, NW, dkdv_rows_per_tile(D)>(a, item, smem);
     if (!a.ticket_dkdv) return;
   }
 }
@@ -958,13 +958,13 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a)
 // both launches (777 rows on 33777 keys: 132 dk/dv items on 256 compute units for 313 us after 178 us of dq).  For
 // calls of fewer than two items per compute unit only (bwd_plan in api.hip): in larger ones the tails overlap by 1 % of
 // the call and the ticket counters are worth more.
-template <int D>
+template <int D, int BMQ>
 __global__ __launch_bounds__(512) void attn_bwd_both_kernel(const BwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_dq = a.dq_items[0] * a.dq_items[1] * a.dq_items[2], n_dkdv = a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
   if ((i < first) == (a.dq_first != 0)) dq_item<D, 8, kBothDqKeys>(a, a.dq_first ? i : i - n_dkdv, smem);
-  else dkdv_item<D, 8>(a, a.dq_first ? i - n_dq : i, smem);
+  else dkdv_item<D, 8, BMQ>(a, a.dq_first ? i - n_dq : i, smem);
 }
 
 // dk_acc, dv_acc (+)= the partial sums of the chunks, chunk 0 first.
@@ -1038,32 +1038,43 @@ static hipError_t launch_dkdv_t(const BwdArgs& a, int batch, hipStream_t st) {
   // with a ticket counter: one workgroup per compute unit (the kernel's LDS allows one at a time), each looping over items
   const int64_t wgs = a.ticket_dkdv ? (items < a.dkdv_wgs ? items : a.dkdv_wgs) : items;
   dim3 grid((unsigned)wgs), block(NW * 64);
-  constexpr size_t smem = DkdvLds<D, NW>::TOTAL;
+  constexpr size_t smem = DkdvLds<D, NW, dkdv_rows_per_tile(D)>::TOTAL;
   hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, NW>), grid, block, smem, st, a);
   return hipGetLastError();
 }
 
 template <int D>
-constexpr size_t both_lds_bytes() { return dq_lds_bytes<D>() > (size_t)DkdvLds<D, 8>::TOTAL ? dq_lds_bytes<D>() : (size_t)DkdvLds<D, 8>::TOTAL; }
+constexpr size_t both_lds_bytes() {
+  constexpr size_t dkdv = DkdvLds<D, 8, dkdv_rows_per_tile(D)>::TOTAL;
+  return dq_lds_bytes<D>() > dkdv ? dq_lds_bytes<D>() : dkdv;
+}
 
-template <int D>
+template <int D, int BMQ>
 static hipError_t launch_both_t(const BwdArgs& a, hipStream_t st) {
   const int64_t items = (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] + (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
-  hipLaunchKernelGGL((attn_bwd_both_kernel<D>), dim3((unsigned)items), dim3(512), both_lds_bytes<D>(), st, a);
+  hipLaunchKernelGGL((attn_bwd_both_kernel<D, BMQ>), dim3((unsigned)items), dim3(512), both_lds_bytes<D>(), st, a);
   return hipGetLastError();
 }
+// At head_dim 64 a chunk of fewer than 512 query rows is walked in tiles of 32: its first tile is a chain of copy, scores and
+// softmax that nothing hides, and with 64 rows it is twice as long (256 rows of 4 heads on 5073 keys, 128 rows a chunk: 27.3 us with
+// 32-row tiles, 29.7 with 64).  So is every call whose heads would be padded by more than 4 % (400 rows are 416 or 448: 73.3 us
+// against 77.3 on 12400 keys, 8/2 heads).
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st) {
-  return head_dim == 128 ? launch_both_t<128>(a, st) : launch_both_t<64>(a, st);
+  if (head_dim == 128) return launch_both_t<128, 32>(a, st);
+  const int64_t t32 = ((int64_t)a.s_q + 31) / 32, t64 = (t32 + 1) / 2;
+  const bool wide = (int64_t)a.s_q * a.group >= 512 * (int64_t)a.n_split && 25 * (2 * t64 - t32) <= t32;
+  return wide ? launch_both_t<64, 64>(a, st) : launch_both_t<64, 32>(a, st);
 }
 
 hipError_t opt_in_bwd_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<128, 8, dq_keys_per_tile(128)>), attr, (int)dq_lds_bytes<128>());
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<64, 8, dq_keys_per_tile(64)>), attr, (int)dq_lds_bytes<64>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128, 8>), attr, DkdvLds<128, 8>::TOTAL);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8>), attr, DkdvLds<64, 8>::TOTAL);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128>), attr, (int)both_lds_bytes<128>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64>), attr, (int)both_lds_bytes<64>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128, 8>), attr, DkdvLds<128, 8, dkdv_rows_per_tile(128)>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8>), attr, DkdvLds<64, 8, dkdv_rows_per_tile(64)>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128, 32>), attr, (int)both_lds_bytes<128>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 64>), attr, (int)both_lds_bytes<64>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 32>), attr, (int)both_lds_bytes<64>());
   return e;
 }
 
