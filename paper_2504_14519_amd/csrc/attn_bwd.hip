@@ -436,19 +436,20 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // Key-stationary twin of the dq kernel: 8 waves x 32 keys of one KV head; K lives in registers and V
 // in LDS as B operands, dK^T and dV^T accumulate in registers, and the query rows that can see the
 // keys (every query tile, for every head of the GQA group, in a fixed order: the sums are
-// reproducible) stream through LDS as tiles of 32 rows of Q and dO.  Per tile u a wave runs
+// reproducible) stream through LDS as tiles of 32 (head_dim 64: 64) rows of Q and dO.  Per tile u a wave runs
 //   matrix phase MM(u): dV^T += dO(u-1)^T P(u-1),  dK^T += Q(u-1)^T dS(u-1)    (transposed reads)
 //                       S(u) = Q(u) K^T,  dP(u) = dO(u) V^T - delta              (row-packed reads; the
 //                       accumulator of dP starts from -delta, and lse2 of the tile is fetched on the way)
 //   vector phase VV(u): P = exp2(c S - lse2),  dS = P (dP - delta), packed to bf16
-// and the two wave groups run one phase apart exactly as in the dq kernel.  (One wave per SIMD with
-// twice the registers cannot overlap the two kinds of work: a wave that has issued an MFMA issues
-// nothing else until the matrix pipe has taken it, so vector work only hides behind the MFMAs of
-// ANOTHER wave of the same SIMD.)  Q and dO tiles sit in rings of four LDS slots, the row statistics
+// and the two wave groups run one phase apart exactly as in the dq kernel.  (P behind the MFMAs of dP
+// and dS behind those of dV in the SAME wave, with one barrier a tile, was built and is slower, 4146 -> 4349 us for 8192
+// rows on 40960 keys and 16/2 heads: a wave issues in order, and what its vector instructions wait for its next MFMA
+// waits for too.)  Q and dO tiles sit in rings of four LDS slots, the row statistics
 // in a ring of four; group A copies Q(u+2) and the statistics, group B copies dO(u+2).
+
 // Query rows of a tile.  At head_dim 64 the scores of 64 rows fit the registers that head_dim 128 needs for its operands and
 // accumulators; twice the work per tile halves the barriers, cursor steps and copy instructions per pair: 8192 rows on 40960 keys,
-// 16/2 heads, 2635 -> 2437 us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 220 -> 209 us.
+// 16/2 heads, 2635 -> 2437 us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 210 -> 201 us the call.
 constexpr int dkdv_rows_per_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
 
 template <int D, int BMQ>

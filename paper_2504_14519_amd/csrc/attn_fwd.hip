@@ -9,8 +9,8 @@
 //   O^T += V^T P^T     A = V through the transposed LDS read, B = P straight from the C registers
 // Scores and probabilities never leave registers.
 //
-// Schedule.  A wave that has issued an MFMA issues nothing else until the matrix pipe has taken it,
-// so vector work only hides behind the MFMAs of ANOTHER wave of the same SIMD.  A wave therefore
+// Schedule.  A wave issues in order, so what its vector instructions wait for its next MFMA waits for
+// too; the vector work of a tile hides best behind the MFMAs of ANOTHER wave of the same SIMD.  A wave therefore
 // alternates a matrix phase MM(t): O += P(t-1) V(t-1), S(t) = K(t) Q^T with a vector phase
 // VV(t): P(t) = softmax(S(t)); waves 0-3 (group A) and 4-7 (group B) run the same sequence shifted by
 // one phase, one workgroup barrier per phase, so every SIMD hosts one wave in each kind of phase.

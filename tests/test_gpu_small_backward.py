@@ -31,6 +31,12 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
     qb, kb, vb, dob = (normal_bf16(shape, 33, t) for t, shape in (("q", (B, s, Hq, D)), ("k", (B, N, Hkv, D)), ("v", (B, N, Hkv, D)), ("do", (B, s, Hq, D))))
     q64, k64, v64, do64 = (bf16_bits_to_f64(x) for x in (qb, kb, vb, dob))
     q, k, v, do = (dev_bf16(x) for x in (qb, kb, vb, dob))
+
+    def inside_of_longer(x, fill):                         # a slice of a longer sequence
+        wide = torch.full((B, s + 3, Hq, D), fill, device="cuda:0", dtype=x.dtype)
+        wide[:, 2:2 + s] = x
+        return wide[:, 2:2 + s]
+    q, do = inside_of_longer(q, float("nan")), inside_of_longer(do, float("nan"))
     o_ref, l_ref = attn_fwd(q64, k64, v64, off, b, e, causal, scale)
     out = torch.from_numpy(o_ref).to("cuda:0").to(torch.bfloat16)
     lse = torch.from_numpy(l_ref).to("cuda:0").float()
@@ -41,7 +47,7 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
         say("small backward: B=%d s=%d N=%d %d/%d D=%d off=%d [%d,%d) causal %d chunk %d" % (B, s, N, Hq, Hkv, D, off, b, e, causal, chunk))
         ws = torch.full((sp.slimpipe_attn_workspace_bytes(p, True),), 255, device="cuda:0", dtype=torch.uint8)
         dk, dv = torch.full((B, N, Hkv, D), 0.5, device="cuda:0"), torch.full((B, N, Hkv, D), -0.25, device="cuda:0")
-        dq = torch.full((B, s, Hq, D), 2.0, device="cuda:0", dtype=torch.float32 if dtype == sp.F32 else torch.bfloat16)
+        dq = inside_of_longer(torch.full((B, s, Hq, D), 2.0, device="cuda:0", dtype=torch.float32 if dtype == sp.F32 else torch.bfloat16), 9.0)
         kw = dict(dq=dq, dq_dtype=dtype, dq_accumulate=accumulate, dkv_accumulate=accumulate, workspace=ws)
         if chunk:
             cut = lambda x: [x[:, i:i + chunk].contiguous() for i in range(0, N, chunk)]
@@ -51,6 +57,7 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
         else:
             sp.slimpipe_attn_bwd(q, k, v, out, do, lse, off, b, e, dk, dv, causal, scale, **kw)
         torch.cuda.synchronize()
+        assert (dq._base[:, :2] == 9.0).all() and (dq._base[:, 2 + s:] == 9.0).all(), "rows beside the slice keep what they held"
         inside = [i for i in range(N) if b <= i < e]
         outside = [i for i in range(N) if not b <= i < e]
         old = (2.0, 0.5, -0.25) if accumulate else (0.0, 0.0, 0.0)
