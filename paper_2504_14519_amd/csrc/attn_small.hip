@@ -107,7 +107,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   auto copy = [&](bool k, int t) {
     const int64_t key0 = lo + (int64_t)t * BN;
     const int chunk = kv_chunk_of(a.kv, key0);
-    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = a.kv.len - row;
+    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;      // (a tile lies inside one chunk; keys past the range are not read)
     const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
     dma.copy(k ? k_lds : v_lds, base, row_bytes, left < BN ? (int)left : BN, lane);
   };

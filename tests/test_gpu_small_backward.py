@@ -31,6 +31,7 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
     qb, kb, vb, dob = (normal_bf16(shape, 33, t) for t, shape in (("q", (B, s, Hq, D)), ("k", (B, N, Hkv, D)), ("v", (B, N, Hkv, D)), ("do", (B, s, Hq, D))))
     q64, k64, v64, do64 = (bf16_bits_to_f64(x) for x in (qb, kb, vb, dob))
     q, k, v, do = (dev_bf16(x) for x in (qb, kb, vb, dob))
+    k[:, e:], v[:, e:] = float("nan"), float("nan")          # what the cache holds behind the range is not read
 
     def inside_of_longer(x, fill):                         # a slice of a longer sequence
         wide = torch.full((B, s + 3, Hq, D), fill, device="cuda:0", dtype=x.dtype)

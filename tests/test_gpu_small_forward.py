@@ -33,6 +33,7 @@ def test_small_forward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk, ws):
     scale = 1.0 / math.sqrt(D)
     qb, kb, vb = (normal_bf16(shape, 32, t) for t, shape in (("q", (B, s, Hq, D)), ("k", (B, N, Hkv, D)), ("v", (B, N, Hkv, D))))
     q, k, v = (dev_bf16(x) for x in (qb, kb, vb))
+    k[:, e:], v[:, e:] = float("nan"), float("nan")          # what the cache holds behind the range is not read
     wide = torch.full((B, s + 3, Hq, D), float("nan"), device="cuda:0", dtype=torch.bfloat16)       # a slice of a longer sequence
     wide[:, 2:2 + s] = q
     q = wide[:, 2:2 + s]
