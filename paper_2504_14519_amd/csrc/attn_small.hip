@@ -107,7 +107,9 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   auto copy = [&](bool k, int t) {
     const int64_t key0 = lo + (int64_t)t * BN;
     const int chunk = kv_chunk_of(a.kv, key0);
-    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;      // (a tile lies inside one chunk; keys past the range are not read)
+    // a tile lies inside one chunk; rows past the range are clamped to its last key (the large kernel clamps at the end of the
+    // chunk, so a NaN its last tile finds behind the range reaches its output)
+    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;
     const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
     dma.copy(k ? k_lds : v_lds, base, row_bytes, left < BN ? (int)left : BN, lane);
   };
