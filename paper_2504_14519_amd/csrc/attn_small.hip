@@ -12,43 +12,6 @@
 
 namespace slimpipe {
 
-// A wave's own tile copy (64 lanes, 1 KB an instruction): 64 / (D / 8) rows per pass.  The lane's offset inside the rows of a pass
-// is the same in every pass but for the swizzle (head_dim 128: bits 0..1 of the chunk alternate with the pass), so a full tile
-// costs scalar additions only; in a tile with fewer rows they are clamped to those that exist.
-template <int D, int ROWS>
-struct WaveDma {
-  static constexpr int NC = D / 8, RPP = 64 / NC, PASSES = ROWS / RPP, PHASES = D == 128 ? 4 : 1;
-  uint32_t off[PHASES];
-  SP_DEV void init(int lane, uint32_t row_bytes) {
-    const int r = lane / NC, p = lane % NC;
-    const int c = D == 128 ? (((p >> 2) ^ r) & 3) << 2 | (p & 3) : (p ^ r) & (NC - 1);
-#pragma unroll
-    for (int n = 0; n < PHASES; ++n) off[n] = __umul24((uint32_t)r, row_bytes) + (uint32_t)((c ^ n) * 16);
-  }
-  // pass n alone
-  SP_DEV void copy_pass(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane, int n) const {
-    const int r0 = lane / NC, r = r0 + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
-    uint32_t o = off[0];
-    if constexpr (PHASES > 1) o ^= (uint32_t)(n & (PHASES - 1)) * 16;
-    dma16(tile_base, o + __umul24((uint32_t)rr, row_bytes) - __umul24((uint32_t)r0, row_bytes), __builtin_amdgcn_readfirstlane(lds_tile + n * 1024));
-  }
-  SP_DEV void copy(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane) const {
-    lds_tile = __builtin_amdgcn_readfirstlane(lds_tile);
-    if (rows_avail >= ROWS) {
-      const char* base = reinterpret_cast<const char*>(tile_base);
-#pragma unroll
-      for (int n = 0; n < PASSES; ++n, base += (uint64_t)RPP * row_bytes) dma16(base, off[n % PHASES], lds_tile + n * 1024);
-    } else {
-      const int r0 = lane / NC;
-#pragma unroll
-      for (int n = 0; n < PASSES; ++n) {
-        const int r = r0 + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
-        dma16(tile_base, off[n % PHASES] + __umul24((uint32_t)rr, row_bytes) - __umul24((uint32_t)r0, row_bytes), lds_tile + n * 1024);
-      }
-    }
-  }
-};
-
 template <int D>
 struct FwdSmall {
   static constexpr int NW = 8, BN = D == 64 ? 64 : 32, KB = BN / 32, KS = D / 16, DB = D / 32;
@@ -476,11 +439,9 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   const unsigned smem_lds = lds_addr(smem);
   // V rows of the workgroup: one copy instruction per wave (as far as there are any)
   {
-    WaveDma<D, 32> dma;
-    const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
-    dma.init(lane, row_bytes);
     const bf16_t* vbase = uniform_ptr(a.kv.v[chunk] + head_off + chunk_row0 * a.kv_stride_s);
-    if (wave_u < WaveDma<D, 32>::PASSES) dma.copy_pass(smem_lds + S::V_BASE, vbase, row_bytes, left < 32 ? (int)left : 32, lane, wave_u);
+    if (wave_u < WaveDma<D, 32>::PASSES)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::V_BASE, vbase, (uint32_t)a.kv_stride_s * 2, left < 32 ? (int)left : 32, lane, wave_u);
   }
   // query tiles that see the block: [qt0, nqt) of every head of the group, tile j of this list for wave j mod 8
   const int nqt = (int)(((int64_t)a.s_q + 31) / 32);

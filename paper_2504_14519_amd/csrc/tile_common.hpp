@@ -19,6 +19,7 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 #define SP_DEV __device__ __forceinline__
+#define SP_HOST_DEV __host__ __device__ __forceinline__      // (index arithmetic that tests run on the host)
 
 // v_mfma_f32_32x32x16_bf16.  With lane = 32*g + r (r = lane & 31, g = lane >> 5):
 //   A (32 x 16): lane holds row r, k = 8g .. 8g+7
@@ -64,7 +65,7 @@ SP_DEV bf16x8 pack8(const f32x16& c, int base) {
 // (16 consecutive rows, same chunk) and the transposed read (4 consecutive rows x 4 consecutive
 // chunks) then touch 16 distinct 16-byte bank groups.  D = 64 uses c ^ (row & 7).
 template <int D>
-SP_DEV int tile_off(int row, int chunk) {
+SP_HOST_DEV int tile_off(int row, int chunk) {
   if constexpr (D == 128) {
     const int u = chunk >> 2, i = chunk & 3;
     const int p = (((u ^ row) & 3) << 2) | ((i ^ (row >> 2)) & 3);
@@ -252,6 +253,52 @@ struct TileDma {
     const uint32_t off = __umul24((uint32_t)r, row_bytes) + (rcv >> 16);
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(off), "s"(tile_base), "s"(lds) : "memory", "m0");
+  }
+};
+
+// Product of two numbers below 2^24 (full rate), modulo 2^32.
+SP_HOST_DEV uint32_t mul24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b & 0xffffffu); }
+
+// A wave's own tile copy (64 lanes, 1 KB an instruction): 64 / (D / 8) rows per pass.  The lane's offset inside the rows of a pass
+// is the same in every pass but for the swizzle (head_dim 128: bits 0..1 of the chunk alternate with the pass), so a full tile
+// costs scalar additions only; in a tile with fewer rows they are clamped to those that exist.
+template <int D, int ROWS>
+struct WaveDma {
+  static constexpr int NC = D / 8, RPP = 64 / NC, PASSES = ROWS / RPP, PHASES = D == 128 ? 4 : 1;
+  uint32_t off[PHASES];
+  // byte offset inside its row of the chunk that pass n brings to the lane's place
+  static SP_HOST_DEV uint32_t chunk_off(int lane, int n) {
+    const int r = lane / NC, p = lane % NC;
+    const int c = D == 128 ? (((p >> 2) ^ r) & 3) << 2 | (p & 3) : (p ^ r) & (NC - 1);
+    return (uint32_t)(c ^ (n & (PHASES - 1))) * 16;
+  }
+  SP_HOST_DEV void init(int lane, uint32_t row_bytes) {
+#pragma unroll
+    for (int n = 0; n < PHASES; ++n) off[n] = mul24((uint32_t)(lane / NC), row_bytes) + chunk_off(lane, n);
+  }
+  // the lane's source in pass n relative to the tile's first row, rows clamped to `rows_avail`: from the prepared offsets, and on its own
+  SP_HOST_DEV uint32_t clamped(int lane, int n, uint32_t row_bytes, int rows_avail) const {
+    const int r0 = lane / NC, r = r0 + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
+    return off[n % PHASES] + mul24((uint32_t)rr, row_bytes) - mul24((uint32_t)r0, row_bytes);
+  }
+  static SP_HOST_DEV uint32_t pass_off(int lane, int n, uint32_t row_bytes, int rows_avail) {
+    const int r = lane / NC + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
+    return mul24((uint32_t)rr, row_bytes) + chunk_off(lane, n);
+  }
+  // pass n alone
+  static SP_DEV void copy_pass(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane, int n) {
+    dma16(tile_base, pass_off(lane, n, row_bytes, rows_avail), __builtin_amdgcn_readfirstlane(lds_tile + n * 1024));
+  }
+  SP_DEV void copy(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane) const {
+    lds_tile = __builtin_amdgcn_readfirstlane(lds_tile);
+    if (rows_avail >= ROWS) {
+      const char* base = reinterpret_cast<const char*>(tile_base);
+#pragma unroll
+      for (int n = 0; n < PASSES; ++n, base += (uint64_t)RPP * row_bytes) dma16(base, off[n % PHASES], lds_tile + n * 1024);
+    } else {
+#pragma unroll
+      for (int n = 0; n < PASSES; ++n) dma16(tile_base, clamped(lane, n, row_bytes, rows_avail), lds_tile + n * 1024);
+    }
   }
 };
 

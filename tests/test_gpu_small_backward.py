@@ -71,3 +71,42 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
         assert (dk[:, outside] == 0.5).all() and (dv[:, outside] == -0.25).all(), "keys outside the range keep what they held"
         res.append((dq, dk, dv))
     assert all(torch.equal(x, y) for x, y in zip(res[0], res[1]))
+
+
+def _rows_apart(x, pad, fill):
+    """x with `pad` more elements between its rows, which hold `fill`."""
+    import torch
+    B, n, H, D = x.shape
+    wide = torch.full((B, n, H * D + pad), fill, device=x.device, dtype=x.dtype)
+    view = wide[:, :, :H * D].unflatten(2, (H, D))
+    view.copy_(x)
+    return view
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("pad", [8, 16, 24, 40])
+def test_small_backward_with_rows_apart(D, pad):
+    """Row strides that are any multiple of 8 elements: the bytes between the rows are not read, and not written."""
+    import torch
+    import paper_2504_14519_amd as sp
+    B, s, N, Hq, Hkv = 1, 300, 740, 8, 1
+    off, scale = N - s, 1.0 / math.sqrt(D)
+    qb, kb, vb, dob = (normal_bf16(shape, 34, t) for t, shape in (("q", (B, s, Hq, D)), ("k", (B, N, Hkv, D)), ("v", (B, N, Hkv, D)), ("do", (B, s, Hq, D))))
+    q64, k64, v64, do64 = (bf16_bits_to_f64(x) for x in (qb, kb, vb, dob))
+    q, k, v, do = (_rows_apart(dev_bf16(x), pad, 100.0) for x in (qb, kb, vb, dob))
+    o_ref, l_ref = attn_fwd(q64, k64, v64, off, 0, N, True, scale)
+    out = torch.from_numpy(o_ref).to("cuda:0").to(torch.bfloat16)
+    lse = torch.from_numpy(l_ref).to("cuda:0").float()
+    ref = attn_bwd(q64, k64, v64, host_f64(out), do64, l_ref, off, 0, N, True, scale)
+    say("small backward, rows %d elements apart, D=%d" % (pad, D))
+    dk, dv = (_rows_apart(torch.zeros((B, N, Hkv, D), device="cuda:0"), pad, 5.0) for _ in range(2))
+    dq = _rows_apart(torch.zeros((B, s, Hq, D), device="cuda:0"), pad, 5.0)
+    p = sp.make_params(q, k, out, off, 0, N, True, scale)
+    ws = torch.empty(sp.slimpipe_attn_workspace_bytes(p, True), device="cuda:0", dtype=torch.uint8)
+    sp.slimpipe_attn_bwd(q, k, v, out, do, lse, off, 0, N, dk, dv, True, scale, dq=dq, dq_dtype=sp.F32, dkv_accumulate=False, workspace=ws)
+    torch.cuda.synchronize()
+    for name, g, r in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):
+        err = rel_l2(host_f64(g), r)
+        say("%s rel-L2 %.3e" % (name, err))
+        assert err <= TOL_GRAD, name
+        assert (g._base[:, :, -pad:] == 5.0).all(), name

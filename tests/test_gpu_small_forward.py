@@ -54,3 +54,32 @@ def test_small_forward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk, ws):
         el = max_abs(host_f64(lse), l_ref)          # fails on a differing -inf pattern, too
         say("out max-abs %.3e lse %.3e" % (eo, el))
         assert eo <= TOL_OUT and el <= TOL_LSE
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("pad", [8, 16, 24, 40])
+def test_small_forward_with_rows_apart(D, pad):
+    """Row strides that are any multiple of 8 elements."""
+    import torch
+    import paper_2504_14519_amd as sp
+    B, s, N, Hq, Hkv = 1, 70, 740, 8, 1
+    scale = 1.0 / math.sqrt(D)
+
+    def rows_apart(bits):
+        x = dev_bf16(bits)
+        wide = torch.full((x.shape[0], x.shape[1], x.shape[2] * D + pad), 100.0, device="cuda:0", dtype=x.dtype)
+        view = wide[:, :, :x.shape[2] * D].unflatten(2, (x.shape[2], D))
+        view.copy_(x)
+        return view
+    bits = [normal_bf16(shape, 35, t) for t, shape in (("q", (B, s, Hq, D)), ("k", (B, N, Hkv, D)), ("v", (B, N, Hkv, D)))]
+    q, k, v = (rows_apart(x) for x in bits)
+    o_ref, l_ref = attn_fwd(*(bf16_bits_to_f64(x) for x in bits), N - s, 0, N, True, scale)
+    say("small forward, rows %d elements apart, D=%d" % (pad, D))
+    p = sp.make_params(q, k, q, N - s, 0, N, True, scale, sp.F32)
+    work = torch.full((sp.slimpipe_attn_workspace_bytes(p, False),), 255, device="cuda:0", dtype=torch.uint8)
+    out, lse = sp.slimpipe_attn_fwd(q, k, v, N - s, 0, N, True, scale, out_dtype=sp.F32, workspace=work)
+    torch.cuda.synchronize()
+    eo, _ = out_err(host_f64(out), o_ref, False)
+    el = max_abs(host_f64(lse), l_ref)
+    say("out max-abs %.3e lse %.3e" % (eo, el))
+    assert eo <= TOL_OUT and el <= TOL_LSE
