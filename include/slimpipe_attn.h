@@ -25,7 +25,8 @@
  *     visible keys of the call (natural log, scale inside).
  *   - Key j is visible to query row r iff kv_begin <= j < kv_end and (causal == 0 or
  *     j <= q_offset + r).  A row that sees no key gets out = 0, lse = -inf and contributes no
- *     gradient.  An empty range is legal.
+ *     gradient.  A key that no row sees may hold anything, NaN and infinities too; its dk, dv are 0.  An
+ *     empty range is legal.
  *   - Query head h reads KV head h / (n_q_heads / n_kv_heads).
  *   - q, k, v, d_out are bf16.  All strides are in elements, must be multiples of 8 and the base
  *     pointers 16-byte aligned.

@@ -231,6 +231,11 @@ double fwd_small_us(const slimpipe_attn_params* p, int64_t cus, int r) {
   return (d64 ? 7.0 : 8.7) + 2 * (rounds - 1) + rounds * steps * (d64 ? 1.4 : 1.3) +
          (r > 1 ? 4.5 + (double)(r + 1) * p->s_q * p->n_q_heads * p->batch * p->head_dim * 4 / 4e6 : 0.0);
 }
+// One past the last key before `end` that any row sees (`begin` when none does).
+int64_t seen_end(const slimpipe_attn_params* p, int64_t begin, int64_t end) {
+  if (p->causal && p->q_offset + p->s_q < end) end = p->q_offset + p->s_q;
+  return end > begin ? end : begin;
+}
 struct FwdPlan {
   int head_waves;    // of the query blocks
   int ranges;        // key ranges
@@ -559,7 +564,7 @@ static int fwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     if (r >= n_ranges) continue;
     if (range_begin[r] < 0 || range_begin[r] > range_end[r] || range_end[r] > p->kv_capacity) return SLIMPIPE_EINVAL_RANGE;
     a.range_begin[r] = range_begin[r];
-    a.range_end[r] = range_end[r];
+    a.range_end[r] = seen_end(p, range_begin[r], range_end[r]);
     if (range_end[r] > last_key) last_key = range_end[r];
     keys += range_end[r] - range_begin[r];
   }
@@ -736,6 +741,8 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     a.dq_range_stride = 0;
     a.dq_stride_b = p->q_stride_b; a.dq_stride_s = p->q_stride_s; a.dq_stride_h = p->q_stride_h;
   }
+  for (int r = 0; r < dq_ranges; ++r) a.dq_range_end[r] = seen_end(p, a.dq_range_begin[r], a.dq_range_end[r]);
+  a.seen_end = seen_end(p, p->kv_begin, p->kv_end);
   a.dq_final = dq;
   a.dq_final_f32 = (dq_dtype == SLIMPIPE_F32); a.dq_final_accumulate = dq_accumulate ? 1 : 0;
   a.nkeys_pad = dkdv_key_tiles(p, n_chunks) * dkdv_keys_per_workgroup();

@@ -253,7 +253,7 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
     const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q, a.head_waves);
     hi = hi < lim ? hi : lim;
   }
-  const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int nt = hi > kv_begin ? (int)((hi - lo + BN - 1) / BN) : 0;
   // tiles [0, t_full) lie below what the wave's first row sees and below the end of the range: no mask there (but for a
   // first tile that starts before the range); one comparison per tile instead of 64-bit positions kept over the loop
   int64_t see = kv_end;
@@ -278,6 +278,8 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
     KvWalk walk;             // the next tile this group copies
     walk.seek(table, a.kv, kv_chunk_of(a.kv, lo), lo, head_off, a.kv_stride_s);
     const int64_t kv_tile_step = (int64_t)BN * a.kv_stride_s;
+    // rows of the last tile that lie in the key range
+    const int last_rows = __builtin_amdgcn_readfirstlane((int)(kv_end - key0_of(nt - 1) < BN ? kv_end - key0_of(nt - 1) : BN));
     struct CopyJob { const bf16_t* src; unsigned dst; int rows; };
     // tile t (the one the walk stands on) of K (slot t % KSLOTS) or V (slot t % VSLOTS); the walk moves on
     // unless t is the last tile: past the end the last tile is copied again
@@ -285,13 +287,13 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
       CopyJob j;
       j.src = walk.ptr;
       j.dst = smem_lds + (copies_k ? K_BASE + (t % KSLOTS) * TILE_BYTES : V_BASE + (t % VSLOTS) * TILE_BYTES);
-      j.rows = walk.rows(BN);
+      j.rows = walk.rows(t + 1 < nt ? BN : last_rows);
       if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s, [&] { return key0_of(t + 1); });
       return j;
     };
     auto copy_pass = [&](const CopyJob& j, int n) { dma.issue(j.dst, j.src, row_bytes, j.rows, gwave_u, n); };
-    auto copy_all = [&](const CopyJob& j) {
-      for (int n = 0; n < PASSES; ++n) copy_pass(j, n);
+    auto copy_all = [&](const CopyJob& j, int first) {
+      for (int n = 0; n < PASSES; ++n) dma.issue(j.dst, j.src, row_bytes, j.rows, gwave_u, n, first);
     };
     auto vector_phase = [&](int u, const CopyJob& j) {
       const bool need_mask = u >= t_full || (cut_first && u == 0);
@@ -328,8 +330,8 @@ SP_DEV void dq_item(const BwdArgs& a, int item, char* smem) {
         dma_do.issue(smem_lds + DO_BASE, base, (uint32_t)a.do_stride_s * 2, a.s_q - dr.row0 + 32 * w, wave_u, n);
       }
     }
-    copy_all(make_copy(0));
-    copy_all(make_copy(1));
+    copy_all(make_copy(0), (int)(kv_begin - lo));        // (rows of tile 0 before the range are clamped)
+    copy_all(make_copy(1), 0);
     wait_async();
     TrBase<D> lo_kt;         // K(u-1), transposed
     RpBase<D> lo_k, lo_v;    // K(u), V(u), row-packed
@@ -786,12 +788,13 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       for (int part = 0; part < 4; ++part) copy_part(j, with_stats, part);
     };
 
-    // prologue: V rows of the workgroup (all threads), Q(0), Q(1) + statistics (group A), dO(0), dO(1) (group B)
+    // prologue: V rows of the workgroup that any row sees (dS of the others is P = 0 times dP: whatever the cache holds there must
+    // not reach dP; K only enters S, which the mask replaces), all threads; Q(0), Q(1) + statistics (group A), dO(0), dO(1) (group B)
     {
       TileDma<D, BNK, T> dma_v;
       dma_v.init(tid);
       const bf16_t* vbase = a.kv.v[kchunk] + head_off + chunk_row0 * a.kv_stride_s;
-      const int64_t avail = a.kv_end - tile_key0;
+      const int64_t avail = a.seen_end - tile_key0;
       for (int n = 0; n < TileDma<D, BNK, T>::PASSES; ++n)
         dma_v.issue(smem_lds + L::V_BASE, vbase, (uint32_t)a.kv_stride_s * 2, avail > BNK ? BNK : (int)avail, wave_u, n);
     }

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     const int64_t lim = a.q_offset + block_row_end(qblk, a.s_q, a.head_waves);
     hi = hi < lim ? hi : lim;
   }
-  const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int nt = hi > kv_begin ? (int)((hi - lo + BN - 1) / BN) : 0;
   // tiles [0, t_full) lie below what the wave's first row sees and below the end of the range: no mask there (but for a
   // first tile that starts before the range); one comparison per tile instead of 64-bit positions kept over the loop
   int64_t see = kv_end;
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     // K(t+2) during VV(t) into a ring of three slots, group B copies V(t+1) during its VV(t) into a ring
     // of two, and each group waits for its copies at the end of its next matrix phase.  Copies are
     // branch-free: a tile past the end of the range re-copies the last tile (nobody reads it), rows
-    // past the end of the chunk are clamped.  Each group walks its operand's chunk list tile by tile.
+    // outside the range are clamped.  Each group walks its operand's chunk list tile by tile.
     constexpr int GT = T / 2;                            // threads of one group
     const int gtid = tid & (GT - 1);
     TileDma<D, BN, GT> dma;
@@ -300,19 +300,21 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     KvWalk walk;             // the next tile this group copies
     walk.seek(table, a.kv, kv_chunk_of(a.kv, lo), lo, head_off, a.kv_stride_s);
     const int64_t kv_tile_step = (int64_t)BN * a.kv_stride_s;
+    // rows of the last tile that lie in the key range
+    const int last_rows = __builtin_amdgcn_readfirstlane((int)(kv_end - key0_of(nt - 1) < BN ? kv_end - key0_of(nt - 1) : BN));
     struct CopyJob { const bf16_t* src; unsigned dst; int rows; };
     // tile t (the one the walk stands on) into its ring slot; the walk moves on unless t is the last tile
     auto make_copy = [&](int t) {
       CopyJob j;
       j.src = walk.ptr;
       j.dst = smem_lds + (copies_k ? K_BASE + (t % KSLOTS) * TILE_BYTES : V_BASE + (t % VSLOTS) * TILE_BYTES);
-      j.rows = walk.rows(BN);
+      j.rows = walk.rows(t + 1 < nt ? BN : last_rows);
       if (t + 1 < nt) walk.step(table, a.kv, BN, kv_tile_step, head_off, a.kv_stride_s, [&] { return key0_of(t + 1); });
       return j;
     };
     auto copy_pass = [&](const CopyJob& j, int n) { dma.issue(j.dst, j.src, row_bytes, j.rows, gwave_u, n); };
-    auto copy_all = [&](const CopyJob& j) {
-      for (int n = 0; n < PASSES; ++n) copy_pass(j, n);
+    auto copy_all = [&](const CopyJob& j, int first) {
+      for (int n = 0; n < PASSES; ++n) dma.issue(j.dst, j.src, row_bytes, j.rows, gwave_u, n, first);
     };
     // vector phase of tile t that also copies one tile
     auto vector_phase = [&](const CopyJob& j) {
@@ -340,8 +342,9 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     };
 
     // prologue: K(0), K(1) (group A), V(0) (group B)
-    if (copies_k) { copy_all(make_copy(0)); copy_all(make_copy(1)); }
-    else copy_all(make_copy(0));
+    const int first = (int)(kv_begin - lo);              // rows of tile 0 before the range
+    copy_all(make_copy(0), first);
+    if (copies_k) copy_all(make_copy(1), 0);
     wait_async();
     RpOffsets<D> lo_k;       // K(t), row-packed (registers are plentiful here: one offset per head_dim block)
     TrOffsets<D> lo_v;       // V(t-1), transposed

@@ -42,7 +42,8 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
     hi = hi < lim ? hi : lim;
   }
   const int64_t lo = kv_grid_origin(kv_begin, a.kv.n, BN);
-  const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int nt = hi > kv_begin ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int before = (int)(kv_begin - lo);               // rows of tile 0 before the range
   const float c = a.scale_log2e;
 
   bf16x8 q[KS];
@@ -67,20 +68,20 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
   dma.init(lane, row_bytes);
-  auto copy = [&](bool k, int t) {
+  auto copy = [&](bool k, int t, int first) {
     const int64_t key0 = lo + (int64_t)t * BN;
     const int chunk = kv_chunk_of(a.kv, key0);
-    // a tile lies inside one chunk; rows past the range are clamped to its last key (the large kernel clamps at the end of the
-    // chunk, so a NaN its last tile finds behind the range reaches its output)
+    // (a tile lies inside one chunk; rows outside the range are clamped to its first and last key)
     const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;
     const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
-    dma.copy(k ? k_lds : v_lds, base, row_bytes, left < BN ? (int)left : BN, lane);
+    dma.copy(k ? k_lds : v_lds, base, row_bytes, first, left < BN ? (int)left : BN, lane);
   };
   constexpr int PASSES = WaveDma<D, BN>::PASSES;
   int t = wave_u;                                        // tiles w, w + 8, w + 16, .. are this wave's
   if (t < nt) {
-    copy(true, t);
-    copy(false, t);
+    const int first = t == 0 ? before : 0;
+    copy(true, t, first);
+    copy(false, t, first);
   }
   for (; t < nt; t += NW) {
     const int tn = t + NW < nt ? t + NW : t;             // (past the end the last tile is copied again)
@@ -99,7 +100,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
       }
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(s[kb]));      // the reads of K are done before K is copied over
-    copy(true, tn);
+    copy(true, tn, 0);
     const int64_t key0 = lo + (int64_t)t * BN;
     if (key0 < kv_begin || key0 + BN > kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
       const int64_t kmin = kv_begin - key0;
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
       for (int db = 0; db < DB; ++db) o[db] = mfma32(lds_tr<D>(lo_v, db, blk * 16 * D * 2), p[blk / 2][blk % 2], o[db]);
 #pragma unroll
     for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(o[db]));      // the reads of V are done before V is copied over
-    copy(false, tn);
+    copy(false, tn, 0);
   }
   wait_async();
   __syncthreads();                                       // nobody reads or copies a tile any more
@@ -275,13 +276,15 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const int rb = __builtin_amdgcn_readfirstlane(hb / a.n_q_heads), h = hb - rb * a.n_q_heads;
   const int row0 = (row_blocks - 1 - rb) * 32, hk = __builtin_amdgcn_readfirstlane(h / a.group);
   const int myrow = row0 + ql, myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
-  int64_t hi = a.kv_end;
+  const int64_t kv_end = a.seen_end;
+  int64_t hi = kv_end;
   if (a.causal) {
     const int64_t lim = a.q_offset + (row0 + 32 < a.s_q ? row0 + 32 : a.s_q);
     hi = hi < lim ? hi : lim;
   }
   const int64_t lo = kv_grid_origin(a.kv_begin, a.kv.n, BN);
-  const int nt = hi > lo ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int nt = hi > a.kv_begin ? (int)((hi - lo + BN - 1) / BN) : 0;
+  const int before = (int)(a.kv_begin - lo);             // rows of tile 0 before the range
   const float c = a.scale_log2e;
 
   bf16x8 q[KS], dO[KS];
@@ -312,17 +315,18 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
   dma.init(lane, row_bytes);
-  auto copy = [&](bool k, int t) {
+  auto copy = [&](bool k, int t, int first) {
     const int64_t key0 = lo + (int64_t)t * BN;
     const int chunk = kv_chunk_of(a.kv, key0);
-    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (a tile lies inside one chunk)
+    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;      // (a tile lies inside one chunk; clamped as in the forward)
     const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
-    dma.copy(k ? k_lds : v_lds, base, row_bytes, left < BN ? (int)left : BN, lane);
+    dma.copy(k ? k_lds : v_lds, base, row_bytes, first, left < BN ? (int)left : BN, lane);
   };
   int t = wave_u;                                        // tiles w, w + 8, w + 16, .. are this wave's
   if (t < nt) {
-    copy(true, t);
-    copy(false, t);
+    const int first = t == 0 ? before : 0;
+    copy(true, t, first);
+    copy(false, t, first);
   }
   for (; t < nt; t += NW) {
     const int tn = t + NW < nt ? t + NW : t;             // (past the end the last tile is copied again)
@@ -348,11 +352,11 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
       for (int kb = 0; kb < KB; ++kb) dp[kb] = mfma32(lds_rp<D>(lo_v, ks, kb * 32 * D * 2), dO[ks], dp[kb]);
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(dp[kb]));      // the reads of V are done before V is copied over
-    copy(false, tn);
+    copy(false, tn, 0);
     const int64_t key0 = lo + (int64_t)t * BN;
-    if (key0 < a.kv_begin || key0 + BN > a.kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
+    if (key0 < a.kv_begin || key0 + BN > kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
       const int64_t kmin = a.kv_begin - key0;
-      int64_t kmax = a.kv_end - 1;
+      int64_t kmax = kv_end - 1;
       if (a.causal && a.q_offset + myrow < kmax) kmax = a.q_offset + myrow;
       kmax -= key0;
       const int kmin_lane = (kmin < 0 ? 0 : (int)kmin) - 4 * g, kmax_lane = (kmax < -1 ? -1 : (kmax > BN ? BN : (int)kmax)) - 4 * g;
@@ -382,7 +386,7 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
       for (int db = 0; db < DB; ++db) dq[db] = mfma32(lds_tr<D>(lo_kt, db, blk * 16 * D * 2), ds[blk / 2][blk % 2], dq[db]);
 #pragma unroll
     for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(dq[db]));      // the reads of K are done before K is copied over
-    copy(true, tn);
+    copy(true, tn, 0);
   }
   wait_async();
   __syncthreads();                                       // nobody reads or copies a tile any more
@@ -420,7 +424,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   const int hk = __builtin_amdgcn_readfirstlane(hb / key_blocks), kblk = hb - hk * key_blocks;
   const int64_t key0 = grid0 + (int64_t)kblk * 32, mykey = key0 + ql;
   const int chunk = kv_chunk_of(a.kv, key0);
-  const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (>= 1)
+  const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.seen_end > key0 ? a.seen_end - key0 : 1;      // keys to read (a block that no row sees reads one)
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
   const float c = a.scale_log2e;
 
@@ -465,7 +469,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32, h = hk * a.group + hh, rows = a.s_q - row0;
     const unsigned dst = set_lds + buf * S::SET_BYTES;
     if (with_q) {
-      dma_q.copy(dst, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)h * a.q_stride_h + (int64_t)row0 * a.q_stride_s), q_bytes, rows < 32 ? rows : 32, lane);
+      dma_q.copy(dst, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)h * a.q_stride_h + (int64_t)row0 * a.q_stride_s), q_bytes, 0, rows < 32 ? rows : 32, lane);
       // lanes 0..31: lse2 of the rows, lanes 32..63: -delta (clamped to the slice)
       const int rr = ql < rows ? ql : rows - 1;
       dma4(uniform_ptr(stat_base + ((int64_t)b * a.n_q_heads + h) * a.s_q + row0), (g ? off_delta : off_lse2) + (uint32_t)rr * 4u,
@@ -473,7 +477,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     }
     if (with_do)
       dma_do.copy(dst + TILE_BYTES, uniform_ptr(a.d_out + (int64_t)b * a.do_stride_b + (int64_t)h * a.do_stride_h + (int64_t)row0 * a.do_stride_s), do_bytes,
-                  rows < 32 ? rows : 32, lane);
+                  0, rows < 32 ? rows : 32, lane);
   };
   int j = wave_u;
   if (j < total) copy_tile(j, 0, true, true);

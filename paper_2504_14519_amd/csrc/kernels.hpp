@@ -43,6 +43,8 @@ struct FwdArgs {
   float* lse;
   int32_t s_q, n_q_heads, group, causal, out_f32;
   int32_t n_ranges;                                   // >= 1; third item coordinate = batch index * n_ranges + range
+  // [range_begin, range_end): without the keys behind the last one that any row sees.  No key outside is read (rows of a tile that
+  // lie outside are clamped): the cache may hold anything there, and a weight of 0 times a NaN is a NaN
   int64_t range_begin[kMaxRanges], range_end[kMaxRanges];
   int64_t out_range_stride, lse_range_stride;         // in elements of the output type / floats
   // work items = (query block, kv head, batch index x range), items[0] * [1] * [2] of them; with `ticket` (eight counters
@@ -75,7 +77,7 @@ struct BwdArgs {
   // caller's buffer; with several it is the float32 workspace [range][batch, s_q, heads, head_dim] that
   // dq_reduce_kernel adds up into dq_final.
   int32_t n_dq_ranges;
-  int64_t dq_range_begin[kMaxRanges], dq_range_end[kMaxRanges];
+  int64_t dq_range_begin[kMaxRanges], dq_range_end[kMaxRanges];      // (as in FwdArgs)
   int64_t dq_range_stride;                       // elements between the partial dq of two ranges
   int64_t dq_stride_b, dq_stride_s, dq_stride_h; // of `dq` as the dq kernel writes it
   void* dq_final;                                // the caller's dq (q strides) when n_dq_ranges > 1
@@ -101,6 +103,7 @@ struct BwdArgs {
   int32_t s_q, n_q_heads, n_kv_heads, group, causal;
   int32_t dq_f32, dq_accumulate, dkv_accumulate;
   int64_t q_offset, kv_begin, kv_end, kv_capacity;
+  int64_t seen_end;         // keys of [seen_end, kv_end) are seen by no row: their dk, dv are 0, whatever the cache holds there
   float scale, scale_log2e;
   int64_t q_stride_b, q_stride_s, q_stride_h;
   int64_t kv_stride_b, kv_stride_s, kv_stride_h;

@@ -242,12 +242,14 @@ struct TileDma {
   }
   // pass n of the tile whose first row starts at `tile_base` (uniform) into the LDS tile at byte address
   // `lds_tile` (uniform); `wave` is the uniform index of the calling wave among the THREADS/64 that copy
-  SP_DEV void issue(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int wave, int n) const {
+  // (rows before `first` < rows_avail are clamped as well)
+  SP_DEV void issue(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int wave, int n, int first = 0) const {
     const unsigned lds = lds_tile + (n * THREADS + wave * 64) * 16;
     // (from an opaque copy: the row of every pass would otherwise be kept in a register of its own
     // across the caller's loop)
     const uint32_t rcv = (uint32_t)fresh((int)rc);
     int r = (int)(rcv & 0xffffu) + RPP * n;
+    r = r > first ? r : first;
     r = r < rows_avail ? r : rows_avail - 1;
     // (24-bit multiply, full rate: r < 2^16 and a row is shorter than 2^23 bytes, checked by the host)
     const uint32_t off = __umul24((uint32_t)r, row_bytes) + (rcv >> 16);
@@ -261,7 +263,7 @@ SP_HOST_DEV uint32_t mul24(uint32_t a, uint32_t b) { return (a & 0xffffffu) * (b
 
 // A wave's own tile copy (64 lanes, 1 KB an instruction): 64 / (D / 8) rows per pass.  The lane's offset inside the rows of a pass
 // is the same in every pass but for the swizzle (head_dim 128: bits 0..1 of the chunk alternate with the pass), so a full tile
-// costs scalar additions only; in a tile with fewer rows they are clamped to those that exist.
+// costs scalar additions only; in a tile with fewer rows they are clamped to [first, rows_avail).
 template <int D, int ROWS>
 struct WaveDma {
   static constexpr int NC = D / 8, RPP = 64 / NC, PASSES = ROWS / RPP, PHASES = D == 128 ? 4 : 1;
@@ -276,9 +278,9 @@ struct WaveDma {
 #pragma unroll
     for (int n = 0; n < PHASES; ++n) off[n] = mul24((uint32_t)(lane / NC), row_bytes) + chunk_off(lane, n);
   }
-  // the lane's source in pass n relative to the tile's first row, rows clamped to `rows_avail`: from the prepared offsets, and on its own
-  SP_HOST_DEV uint32_t clamped(int lane, int n, uint32_t row_bytes, int rows_avail) const {
-    const int r0 = lane / NC, r = r0 + RPP * n, rr = r < rows_avail ? r : rows_avail - 1;
+  // the lane's source in pass n relative to the tile's first row, rows clamped: from the prepared offsets, and on its own
+  SP_HOST_DEV uint32_t clamped(int lane, int n, uint32_t row_bytes, int first, int rows_avail) const {
+    const int r0 = lane / NC, r = r0 + RPP * n > first ? r0 + RPP * n : first, rr = r < rows_avail ? r : rows_avail - 1;
     return off[n % PHASES] + mul24((uint32_t)rr, row_bytes) - mul24((uint32_t)r0, row_bytes);
   }
   static SP_HOST_DEV uint32_t pass_off(int lane, int n, uint32_t row_bytes, int rows_avail) {
@@ -289,15 +291,15 @@ struct WaveDma {
   static SP_DEV void copy_pass(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane, int n) {
     dma16(tile_base, pass_off(lane, n, row_bytes, rows_avail), __builtin_amdgcn_readfirstlane(lds_tile + n * 1024));
   }
-  SP_DEV void copy(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int rows_avail, int lane) const {
+  SP_DEV void copy(unsigned lds_tile, const bf16_t* tile_base, uint32_t row_bytes, int first, int rows_avail, int lane) const {
     lds_tile = __builtin_amdgcn_readfirstlane(lds_tile);
-    if (rows_avail >= ROWS) {
+    if (first <= 0 && rows_avail >= ROWS) {
       const char* base = reinterpret_cast<const char*>(tile_base);
 #pragma unroll
       for (int n = 0; n < PASSES; ++n, base += (uint64_t)RPP * row_bytes) dma16(base, off[n % PHASES], lds_tile + n * 1024);
     } else {
 #pragma unroll
-      for (int n = 0; n < PASSES; ++n) dma16(tile_base, clamped(lane, n, row_bytes, rows_avail), lds_tile + n * 1024);
+      for (int n = 0; n < PASSES; ++n) dma16(tile_base, clamped(lane, n, row_bytes, first, rows_avail), lds_tile + n * 1024);
     }
   }
 };

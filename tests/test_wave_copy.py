@@ -23,8 +23,11 @@ static void check(int64_t stride) {
       full += (int64_t)w.off[n % W::PHASES] + (int64_t)n * W::RPP * row_bytes != (int64_t)row * row_bytes + chunk * 16;
       for (int rows : {1, 2, ROWS / 2 + 1, ROWS - 1, ROWS}) {
         const int64_t want = (int64_t)(row < rows ? row : rows - 1) * row_bytes + chunk * 16;
-        clamped += (int64_t)w.clamped(lane, n, row_bytes, rows) != want;
         alone += (int64_t)W::pass_off(lane, n, row_bytes, rows) != want;
+        for (int first : {-5, 0, 1, rows - 1}) {
+          const int r = row < first ? first : row;
+          if (first < rows) clamped += (int64_t)w.clamped(lane, n, row_bytes, first, rows) != (int64_t)(r < rows ? r : rows - 1) * row_bytes + chunk * 16;
+        }
       }
     }
   if (full || clamped || alone) printf("D %d rows %d stride %d: full %d clamped %d alone %d\n", D, ROWS, (int)stride, full, clamped, alone);
