@@ -32,7 +32,7 @@ int slimpipe_attn_profile_read(double total_ms[SLIMPIPE_KERNEL_KINDS], int64_t l
 
 /* How slimpipe_attn_bwd (n_chunks = 1) or slimpipe_attn_bwd_chunked would cut a call into work items with a workspace of
  * workspace_bytes (slimpipe_attn_bwd_noalloc: the two row statistics + 256 bytes).  For the smallest calls, which go through a kernel of 32-row and
- * 32-key items, these are the cuts without it.  Host code only, nothing is launched. */
+ * 32-key items (slimpipe_attn_call_path says which), these are the cuts without it.  Host code only, nothing is launched. */
 typedef struct slimpipe_bwd_plan {
   int32_t one_launch;      /* dq and dk/dv items in one launch */
   int32_t dq_first;        /* in that launch the dq items come first */
@@ -43,6 +43,16 @@ typedef struct slimpipe_bwd_plan {
   int32_t dq_by_xcd;       /* the dq items that share keys are dealt to one XCD */
 } slimpipe_bwd_plan;
 int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_bwd_plan* plan);
+
+/* Which kernels slimpipe_attn_fwd / slimpipe_attn_bwd (n_chunks = 1) or their chunked variants take for a call with a workspace
+ * of workspace_bytes (0, forward only: none).  Host code only, nothing is launched. */
+typedef struct slimpipe_call_path {
+  int32_t small;           /* workgroups of 32 rows (backward: and of 32 keys) whose waves share out the other side */
+  int32_t ranges;          /* key ranges the forward, or dq, is cut into */
+  int32_t dq_tile_keys;    /* backward: keys of a tile of the dq items */
+  int32_t dkdv_tile_rows;  /* backward: query rows of a tile of the dk/dv items */
+} slimpipe_call_path;
+int slimpipe_attn_call_path(const slimpipe_attn_params* p, int is_bwd, int32_t n_chunks, size_t workspace_bytes, slimpipe_call_path* path);
 
 /* The rate, in TFLOP/s, at which this GPU sustains a pure stream of the bf16 MFMA instruction the attention
  * kernels use, with constant operands (random_operands == 0) or with random ones (!= 0), under which the chip

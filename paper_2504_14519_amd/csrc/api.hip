@@ -265,6 +265,11 @@ FwdPlan fwd_plan(const slimpipe_attn_params* p, bool lent, size_t room) {
   }
   return {hw, ranges, false};
 }
+// The plan of a call with a workspace of this many bytes (0: none): [ticket counter, 256 bytes][partial results of the ranges].
+FwdPlan fwd_plan_within(const slimpipe_attn_params* p, size_t workspace_bytes) {
+  const bool lent = workspace_bytes >= kTicketBytes;
+  return fwd_plan(p, lent, lent ? workspace_bytes - kTicketBytes : workspace_bytes);
+}
 // The dq kernel has the forward's launch shape and is cut into key ranges the same way; its partial results are
 // float32 [range][batch, s_q, heads, head_dim].
 size_t dq_parts_bytes(const slimpipe_attn_params* p, int ranges) {
@@ -494,6 +499,27 @@ int slimpipe_attn_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size
   return SLIMPIPE_OK;
 }
 
+int slimpipe_attn_call_path(const slimpipe_attn_params* p, int is_bwd, int32_t n_chunks, size_t workspace_bytes, slimpipe_call_path* path) {
+  if (!p || !path) return SLIMPIPE_EINVAL_NULL;
+  int rc = slimpipe_attn_validate(p, is_bwd);
+  if (rc != SLIMPIPE_OK) return rc;
+  if (n_chunks < 1 || n_chunks > kMaxChunks) return SLIMPIPE_EINVAL_SHAPE;
+  memset(path, 0, sizeof(*path));
+  if (!is_bwd) {
+    const FwdPlan plan = fwd_plan_within(p, workspace_bytes);
+    path->small = plan.small;
+    path->ranges = plan.ranges;
+    return SLIMPIPE_OK;
+  }
+  if (workspace_bytes < delta_bytes(p)) return SLIMPIPE_EWORKSPACE;
+  const BwdPlan plan = bwd_plan_within(p, n_chunks, workspace_bytes);
+  path->small = bwd_small_plan(p, plan).use;
+  path->ranges = path->small ? 1 : plan.dq_ranges;
+  path->dq_tile_keys = path->small ? small_dq_tile_keys(p->head_dim) : dq_tile_keys(p->head_dim, plan.both);
+  path->dkdv_tile_rows = path->small ? 32 : dkdv_tile_rows(p->head_dim, p->s_q, p->n_q_heads / p->n_kv_heads, plan.split, plan.both);
+  return SLIMPIPE_OK;
+}
+
 int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd) {
   if (!p) return SLIMPIPE_EINVAL_NULL;
   if (p->batch <= 0 || p->s_q <= 0 || p->n_q_heads <= 0 || p->n_kv_heads <= 0) return SLIMPIPE_EINVAL_SHAPE;
@@ -638,8 +664,7 @@ static int fwd_auto(const slimpipe_attn_params* p, const void* q_slice, const vo
   if (workspace && !aligned16(workspace)) return SLIMPIPE_EINVAL_ALIGN;
   unsigned* ticket = (workspace && workspace_bytes >= kTicketBytes) ? static_cast<unsigned*>(workspace) : nullptr;
   char* parts_base = ticket ? static_cast<char*>(workspace) + kTicketBytes : static_cast<char*>(workspace);
-  const size_t parts_room = ticket ? workspace_bytes - kTicketBytes : workspace_bytes;
-  const FwdPlan plan = fwd_plan(p, ticket != nullptr, workspace ? parts_room : 0);
+  const FwdPlan plan = fwd_plan_within(p, workspace ? workspace_bytes : 0);
   const int ranges = plan.ranges;
   if (ranges <= 1)
     return fwd_impl(p, q_slice, k_chunks, v_chunks, n_chunks, chunk_len, 1, &p->kv_begin, &p->kv_end, nullptr, 0, nullptr, 0, out,

@@ -1063,11 +1063,16 @@ static hipError_t launch_both_t(const BwdArgs& a, hipStream_t st) {
 // softmax that nothing hides, and with 64 rows it is twice as long (256 rows of 4 heads on 5073 keys, 128 rows a chunk: 27.3 us with
 // 32-row tiles, 29.7 with 64).  So is every call whose heads would be padded by more than 4 % (400 rows are 416 or 448: 73.3 us
 // against 77.3 on 12400 keys, 8/2 heads).
+int dkdv_tile_rows(int head_dim, int s_q, int group, int n_split, bool one_launch) {
+  if (head_dim == 128 || !one_launch) return dkdv_rows_per_tile(head_dim);
+  const int64_t t32 = ((int64_t)s_q + 31) / 32, t64 = (t32 + 1) / 2;
+  return (int64_t)s_q * group >= 512 * (int64_t)n_split && 25 * (2 * t64 - t32) <= t32 ? 64 : 32;
+}
+int dq_tile_keys(int head_dim, bool one_launch) { return one_launch ? kBothDqKeys : dq_keys_per_tile(head_dim); }
+
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st) {
   if (head_dim == 128) return launch_both_t<128, 32>(a, st);
-  const int64_t t32 = ((int64_t)a.s_q + 31) / 32, t64 = (t32 + 1) / 2;
-  const bool wide = (int64_t)a.s_q * a.group >= 512 * (int64_t)a.n_split && 25 * (2 * t64 - t32) <= t32;
-  return wide ? launch_both_t<64, 64>(a, st) : launch_both_t<64, 32>(a, st);
+  return dkdv_tile_rows(64, a.s_q, a.group, a.n_split, true) == 64 ? launch_both_t<64, 64>(a, st) : launch_both_t<64, 32>(a, st);
 }
 
 hipError_t opt_in_bwd_kernels() {

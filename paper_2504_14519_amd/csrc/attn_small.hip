@@ -602,6 +602,8 @@ hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, hipStream
   return hipGetLastError();
 }
 
+int small_dq_tile_keys(int head_dim) { return head_dim == 128 ? BwdSmall<128>::BN : BwdSmall<64>::BN; }
+
 hipError_t opt_in_small_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<128>), attr, FwdSmall<128>::LDS);

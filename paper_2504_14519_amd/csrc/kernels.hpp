@@ -136,7 +136,10 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dkdv_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dq_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
+int dq_tile_keys(int head_dim, bool one_launch);
+int dkdv_tile_rows(int head_dim, int s_q, int group, int n_split, bool one_launch);
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st);
+int small_dq_tile_keys(int head_dim);
 hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_both_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);

@@ -43,6 +43,7 @@ def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
     lse = torch.from_numpy(l_ref).to("cuda:0").float()
     dq_r, dk_r, dv_r = attn_bwd(q64, k64, v64, host_f64(out), do64, l_ref, off, b, e, causal, scale)
     p = sp.make_params(q, k, out, off, b, e, causal, scale)
+    assert sp.slimpipe_attn_call_path(p, True, -(-N // chunk) if chunk else 1, sp.slimpipe_attn_workspace_bytes(p, True)).small == 1
     res = []
     for dtype, accumulate in ((sp.F32, True), (sp.F32, True), (sp.BF16, False)):
         say("small backward: B=%d s=%d N=%d %d/%d D=%d off=%d [%d,%d) causal %d chunk %d" % (B, s, N, Hq, Hkv, D, off, b, e, causal, chunk))
@@ -103,6 +104,7 @@ def test_small_backward_with_rows_apart(D, pad):
     dq = _rows_apart(torch.zeros((B, s, Hq, D), device="cuda:0"), pad, 5.0)
     p = sp.make_params(q, k, out, off, 0, N, True, scale)
     ws = torch.empty(sp.slimpipe_attn_workspace_bytes(p, True), device="cuda:0", dtype=torch.uint8)
+    assert sp.slimpipe_attn_call_path(p, True, 1, ws.numel()).small == 1
     sp.slimpipe_attn_bwd(q, k, v, out, do, lse, off, 0, N, dk, dv, True, scale, dq=dq, dq_dtype=sp.F32, dkv_accumulate=False, workspace=ws)
     torch.cuda.synchronize()
     for name, g, r in zip(("dq", "dk", "dv"), (dq, dk, dv), ref):

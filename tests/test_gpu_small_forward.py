@@ -43,6 +43,8 @@ def test_small_forward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk, ws):
         lse = torch.full((B, Hq, s), 7.0, device="cuda:0")
         p = sp.make_params(q, k, out, off, b, e, causal, scale, dtype)
         work = torch.full((sp.slimpipe_attn_workspace_bytes(p, False) if ws else 256,), 255, device="cuda:0", dtype=torch.uint8)
+        path = sp.slimpipe_attn_call_path(p, False, 1, work.numel())
+        assert path.small == (N > 1) and (path.ranges > 1) == (N >= 3000)          # (a single key: the 256-row blocks)
         say("small forward: B=%d s=%d N=%d %d/%d D=%d off=%d [%d,%d) causal %d chunk %d" % (B, s, N, Hq, Hkv, D, off, b, e, causal, chunk))
         if chunk:
             cut = lambda x: [x[:, i:i + chunk].contiguous() for i in range(0, N, chunk)]
@@ -77,6 +79,7 @@ def test_small_forward_with_rows_apart(D, pad):
     say("small forward, rows %d elements apart, D=%d" % (pad, D))
     p = sp.make_params(q, k, q, N - s, 0, N, True, scale, sp.F32)
     work = torch.full((sp.slimpipe_attn_workspace_bytes(p, False),), 255, device="cuda:0", dtype=torch.uint8)
+    assert sp.slimpipe_attn_call_path(p, False, 1, work.numel()).small == 1
     out, lse = sp.slimpipe_attn_fwd(q, k, v, N - s, 0, N, True, scale, out_dtype=sp.F32, workspace=work)
     torch.cuda.synchronize()
     eo, _ = out_err(host_f64(out), o_ref, False)

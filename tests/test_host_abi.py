@@ -202,3 +202,27 @@ def test_backward_without_room_for_cuts_takes_the_faster_launches(sp, s, Hq, Hkv
     least = sp.slimpipe_attn_bwd_plan(p, 1, 2 * ((batch * Hq * s * 4 + 255) // 256 * 256) + 256)
     assert (least.one_launch, least.dkdv_split, least.dq_ranges) == (one, 1, 1)
     assert sp.slimpipe_attn_bwd_plan(p, 1, sp.slimpipe_attn_workspace_bytes(p, True)).one_launch == 1
+
+
+def test_call_path_reports_the_kernels_of_a_call(sp):
+    """The path query answers for the workspace it is asked about, and refuses what the calls refuse."""
+    import types
+    def params(B, s, Hq, Hkv, D, keys):
+        q = types.SimpleNamespace(shape=(B, s, Hq, D), stride=lambda i, st=(s * Hq * D, Hq * D, D, 1): st[i])
+        k = types.SimpleNamespace(shape=(B, keys, Hkv, D), stride=lambda i, st=(keys * Hkv * D, Hkv * D, D, 1): st[i])
+        return sp.make_params(q, k, q, keys - s, 0, keys, True, None)
+    def path(p, bwd, room):
+        c = sp.slimpipe_attn_call_path(p, bwd, 1, room)
+        return (c.small, c.ranges, c.dq_tile_keys, c.dkdv_tile_rows) if bwd else (c.small, c.ranges)
+    tiny, large = params(1, 512, 4, 4, 64, 2048), params(1, 16384, 8, 1, 128, 131072)
+    assert [path(tiny, False, n) for n in (0, 256)] == [(0, 1), (1, 1)]
+    least = 2 * 4 * 512 * 4
+    assert path(tiny, True, sp.slimpipe_attn_workspace_bytes(tiny, True)) == (1, 1, 64, 32)
+    assert path(tiny, True, least) == (0, 1, 64, 64)
+    assert path(large, False, 1 << 40) == (0, 1) and path(large, True, 1 << 40) == (0, 1, 64, 32)
+    out = (ctypes.c_int32 * 4)()
+    call = lambda p, bwd, n, room: sp.lib.slimpipe_attn_call_path(ctypes.byref(p), bwd, n, room, ctypes.cast(out, ctypes.POINTER(sp.binding.CallPath)))
+    assert call(tiny, 1, 1, least - 16) == -6 and call(tiny, 0, 0, 0) == -2 and call(tiny, 0, 65, 0) == -2
+    assert sp.lib.slimpipe_attn_call_path(ctypes.byref(tiny), 0, 1, 0, None) == -1 and sp.lib.slimpipe_attn_call_path(None, 0, 1, 0, None) == -1
+    tiny.head_dim = 96
+    assert call(tiny, 0, 1, 256) == -2
