@@ -241,34 +241,44 @@ struct FwdPlan {
   int ranges;        // key ranges
   bool small;        // 32-row workgroups (attn_fwd_small_kernel)
 };
-// The forward's plan when the partial results of the ranges take at most `room` bytes.  A call that lends no workspace (`lent` false),
-// or a smaller one than it is asked for, goes through the kernel of slimpipe_attn_fwd_ranges: undivided, it returns what a range of
-// that call returns, bit for bit.
-FwdPlan fwd_plan(const slimpipe_attn_params* p, bool lent, size_t room) {
+// The plan with 256-row blocks when the partial results of the ranges take at most `room` bytes.
+FwdPlan fwd_blocks_plan(const slimpipe_attn_params* p, size_t room) {
   const int hw = head_waves_of(p, p->kv_end - p->kv_begin, fwd_parts_bytes(p, 2) > room ? 1 : most_ranges(p, min_range_keys(p->head_dim)));
   int ranges = fwd_preferred_ranges(p, hw);
   while (ranges > 1 && (fwd_parts_bytes(p, ranges) > room || (int64_t)p->batch * ranges > 65535)) --ranges;
-  // With less than one 256-row block per compute unit the small kernel is taken, in the number of ranges (none shorter than the
-  // 256-row blocks may have) that makes it fastest, where its time is shorter.  Over 57 calls of up to 1.2 x 65536 (row, head) pairs, both kernels timed in 1 to 8
-  // ranges: the pick is within 2 % of the best in the mean, at most 1.7 % slower than the 256-row blocks, 1.53 times as fast in the mean
-  // and up to 2.6 times (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).  It loses where keys are long: every workgroup
-  // reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
-  const int64_t w = all_query_blocks(p, hw), keys = p->kv_end - p->kv_begin, cus = compute_units();
-  if (lent && w < cus && keys > 0) {
-    double best_us = fwd_blocks_us(p, cus, w, ranges) * 0.97;
-    int pick = 0;
-    for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
-      const double us = fwd_small_us(p, cus, r);
-      if (us < best_us) { best_us = us * 0.99; pick = r; }
-    }
-    if (pick && fwd_parts_bytes(p, pick) <= room) return {hw, pick, true};
-  }
   return {hw, ranges, false};
 }
+// What the forward would do with all the room it wants.
+// With less than one 256-row block per compute unit the small kernel is taken, in the number of ranges (none shorter than the
+// 256-row blocks may have) that makes it fastest, where its time is shorter.  Over 57 calls of up to 1.2 x 65536 (row, head) pairs, both kernels timed in 1 to 8
+// ranges: the pick is within 2 % of the best in the mean, at most 1.7 % slower than the 256-row blocks, 1.53 times as fast in the mean
+// and up to 2.6 times (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).  It loses where keys are long: every workgroup
+// reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
+FwdPlan fwd_plan_wanted(const slimpipe_attn_params* p) {
+  const FwdPlan blocks = fwd_blocks_plan(p, SIZE_MAX);
+  const int64_t w = all_query_blocks(p, blocks.head_waves), keys = p->kv_end - p->kv_begin, cus = compute_units();
+  if (w >= cus || keys <= 0) return blocks;
+  double best_us = fwd_blocks_us(p, cus, w, blocks.ranges) * 0.97;
+  int pick = 0;
+  for (int r = 1; r <= kMaxRanges && (r == 1 || keys / r >= min_range_keys(p->head_dim)) && (int64_t)p->batch * r <= 65535; ++r) {
+    const double us = fwd_small_us(p, cus, r);
+    if (us < best_us) { best_us = us * 0.99; pick = r; }
+  }
+  return pick ? FwdPlan{blocks.head_waves, pick, true} : blocks;
+}
 // The plan of a call with a workspace of this many bytes (0: none): [ticket counter, 256 bytes][partial results of the ranges].
+// The small kernel is taken only when it is what the call wants with all the room, and has that room.  With less, or without
+// a workspace, the call keeps the kernel of slimpipe_attn_fwd_ranges, in as many ranges as fit: undivided, it
+// returns what a range of that call returns, bit for bit.  (Choosing anew for the room there is would take the small kernel wherever
+// the lack of ranges makes the 256-row blocks slow: other bits with every other size of the workspace.)
 FwdPlan fwd_plan_within(const slimpipe_attn_params* p, size_t workspace_bytes) {
   const bool lent = workspace_bytes >= kTicketBytes;
-  return fwd_plan(p, lent, lent ? workspace_bytes - kTicketBytes : workspace_bytes);
+  const size_t room = lent ? workspace_bytes - kTicketBytes : workspace_bytes;
+  if (lent) {
+    const FwdPlan wanted = fwd_plan_wanted(p);
+    if (wanted.small && fwd_parts_bytes(p, wanted.ranges) <= room) return wanted;
+  }
+  return fwd_blocks_plan(p, room);
 }
 // The dq kernel has the forward's launch shape and is cut into key ranges the same way; its partial results are
 // float32 [range][batch, s_q, heads, head_dim].
@@ -552,7 +562,7 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
   if (!bytes) return SLIMPIPE_EINVAL_NULL;
   int rc = slimpipe_attn_validate(p, is_bwd);
   if (rc != SLIMPIPE_OK) return rc;
-  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_plan(p, true, SIZE_MAX).ranges); return SLIMPIPE_OK; }
+  if (!is_bwd) { *bytes = kTicketBytes + fwd_parts_bytes(p, fwd_plan_wanted(p).ranges); return SLIMPIPE_OK; }
   // the tile grid of a chunked call can start up to 255 keys before kv_begin: room for whichever of the
   // two variants asks for more
   const BwdPlan plan1 = bwd_plan(p, 1, true, SIZE_MAX), plan2 = bwd_plan(p, 2, true, SIZE_MAX);

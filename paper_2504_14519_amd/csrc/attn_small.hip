@@ -6,7 +6,7 @@
 // partial results meet in LDS.  512 rows on 2048 keys, 4 heads of 64 (64 workgroups): 18.1 -> 11.9 us; 512 rows of 8 heads of 128 on one
 // K/V head, 2048 keys: 34.6 -> 19.1; 1024 rows: 35.5 -> 19.8.  A wave's step (32 keys, 64 at head_dim 64) takes 1.3 us, most of it
 // latency of the copies: one K and one V tile per wave are all of LDS, so K of the next step is copied during softmax and P V, V
-// during the scores and the softmax.  Which calls come here: fwd_plan in api.hip.
+// during the scores and the softmax.  Which calls come here: fwd_plan_within in api.hip.
 #include "kernels.hpp"
 #include "tile_common.hpp"
 

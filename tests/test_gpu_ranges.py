@@ -143,3 +143,22 @@ def test_backward_of_a_short_slice_cuts_dq_into_key_ranges(dq_dtype_name, accumu
         res[name] = dq.float().cpu()
     assert torch.equal(res["ranges"], res["ranges again"])
     assert torch.allclose(res["ranges"], res["undivided"], rtol=2e-2 if dq_dtype == sp.BF16 else 1e-4, atol=1e-2 if dq_dtype == sp.BF16 else 1e-4)
+
+
+@pytest.mark.parametrize("s,N,Hq,Hkv,D", [(336, 9624, 8, 1, 64), (1862, 18838, 8, 2, 64), (1900, 31226, 4, 1, 128), (512, 2048, 4, 4, 64), (40, 4096, 2, 1, 128)])
+def test_forward_with_less_than_it_asks_for_is_undivided_bit_for_bit(s, N, Hq, Hkv, D):
+    import torch
+    import paper_2504_14519_amd as sp
+    g = torch.Generator(device="cuda:0").manual_seed(8)
+    q, k, v = (torch.randn((1, n, h, D), device="cuda:0", generator=g).to(torch.bfloat16) for n, h in ((s, Hq), (N, Hkv), (N, Hkv)))
+    po, pl, _, _ = sp.slimpipe_attn_fwd_ranges(q, k, v, N - s, [(0, N)], True, None, merged=False)
+    need = sp.slimpipe_attn_workspace_bytes(sp.make_params(q, k, po[0], N - s, 0, N, True, None, sp.F32), False)
+    two = 256 + 2 * ((s * Hq * D * 4 + 255) // 256 * 256 + (s * Hq * 4 + 255) // 256 * 256)
+    for room in {0, 256, two - 16}:
+        if room >= need:
+            continue
+        say("undivided: %d rows on %d keys, %d/%d heads of %d, %d of %d bytes" % (s, N, Hq, Hkv, D, room, need))
+        ws = torch.full((room,), 255, device="cuda:0", dtype=torch.uint8) if room else None
+        o, l = sp.slimpipe_attn_fwd(q, k, v, N - s, 0, N, True, None, out_dtype=sp.F32, workspace=ws)
+        torch.cuda.synchronize()
+        assert torch.equal(o, po[0]) and torch.equal(l, pl[0]), room

@@ -226,3 +226,33 @@ def test_call_path_reports_the_kernels_of_a_call(sp):
     assert sp.lib.slimpipe_attn_call_path(ctypes.byref(tiny), 0, 1, 0, None) == -1 and sp.lib.slimpipe_attn_call_path(None, 0, 1, 0, None) == -1
     tiny.head_dim = 96
     assert call(tiny, 0, 1, 256) == -2
+
+
+def test_forward_takes_the_small_kernel_only_with_the_workspace_it_asks_for(sp):
+    """With a smaller workspace, or none, a forward call keeps the kernel of slimpipe_attn_fwd_ranges, undivided where no two ranges
+    fit; with the one it asks for, or a larger one, it takes the same path."""
+    import random
+    import types
+    rng = random.Random(4)
+    shapes = [(1, 336, 8, 1, 64, 9624), (1, 1862, 8, 2, 64, 18838), (1, 1900, 4, 1, 128, 31226), (1, 512, 4, 1, 128, 8092), (1, 512, 4, 4, 64, 2048)]
+    for _ in range(4000):
+        Hq, Hkv = rng.choice([(8, 1), (4, 4), (8, 2), (12, 4), (16, 16), (4, 1), (40, 40), (1, 1)])
+        s = int(2 ** rng.uniform(0, 13))
+        shapes.append((rng.choice([1, 1, 2, 3]), s, Hq, Hkv, rng.choice([64, 128]), s + int(2 ** rng.uniform(0, 17))))
+    asked_small = 0
+    for B, s, Hq, Hkv, D, keys in shapes:
+        q = types.SimpleNamespace(shape=(B, s, Hq, D), stride=lambda i, st=(s * Hq * D, Hq * D, D, 1): st[i])
+        k = types.SimpleNamespace(shape=(B, keys, Hkv, D), stride=lambda i, st=(keys * Hkv * D, Hkv * D, D, 1): st[i])
+        p = sp.make_params(q, k, q, keys - s, 0, keys, True, None)
+        need = sp.slimpipe_attn_workspace_bytes(p, False)
+        path = lambda room: (lambda c: (c.small, c.ranges))(sp.slimpipe_attn_call_path(p, False, 1, room))
+        per_range = lambda n: n * sum((x * 4 + 255) // 256 * 256 for x in (B * s * Hq * D, B * s * Hq))
+        want = path(need)
+        assert need == 256 + (per_range(want[1]) if want[1] > 1 else 0), (B, s, Hq, Hkv, D, keys)
+        assert path(1 << 50) == want
+        asked_small += want[0]
+        for room in {0, 255, 256, need // 2, need - 16, 256 + per_range(2) - 16} - {need}:
+            if room < need:
+                small, ranges = path(room)
+                assert small == 0 and (ranges == 1 or 256 + per_range(ranges) <= room), (B, s, Hq, Hkv, D, keys, room)
+    assert 500 < asked_small < len(shapes) - 500
