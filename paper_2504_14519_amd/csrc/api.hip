@@ -401,6 +401,28 @@ BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) 
   const double us = (d64 ? 5.5 : 4) + (tq > tk ? list_makespan(cus, nq, tq, nk, tk) : list_makespan(cus, nk, tk, nq, tq));
   return {nq >= 64 && us < 60 && us * 1.05 < plan.us + 7, tq > tk};
 }
+// Tiles of the large backward at head_dim 64: 128 or 64 keys (dq), 64 or 32 query rows (dk/dv).  The larger ones have half the
+// barriers and copies per pair; a short walk pays for them in its first and last tile, which nothing hides, and in padding.
+// Over 470 drawn calls of two launches, larger against smaller tile: dq 0.93 to 1.01 of the time where the rule says 128, always
+// taking 128 costs up to 1.21 (64 rows of 40 heads on 141 keys, batch 8).
+int dq_tile_keys(const slimpipe_attn_params* p, const BwdPlan& plan) {
+  if (p->head_dim == 128 || plan.both) return 64;
+  const double walk = visible_pairs_upto(p, p->kv_end) / ((double)p->s_q * plan.dq_ranges);      // keys that an item's row sees, in the mean
+  return walk >= 3072 || (walk >= 1024 && p->s_q >= 512) ? 128 : 64;
+}
+// dk/dv in two launches: 0.89 to 1.01 of the time where the rule says 64 rows (1400 rows an item and more, with padding more);
+// always taking 64 costs up to 1.75 (40 rows of 40 heads on 5278 keys, batch 4) and 1.13 to 1.19 at 512 rows.  In one launch, where a long
+// item ends the call, the line is lower: 512 rows a chunk (256 rows of 4 heads on 5073 keys, 128 rows a chunk: 27.3 us with 32-row tiles,
+// 29.7 with 64) and 4 % of padding (400 rows are 416 or 448: 73.3 us against 77.3 on 12400 keys, 8/2 heads); over 360 drawn calls 0.88 to
+// 1.05 of the time where it says 64.
+int dkdv_tile_rows(const slimpipe_attn_params* p, const BwdPlan& plan) {
+  if (p->head_dim == 128 || p->kv_end <= p->kv_begin) return 32;
+  const int64_t group = p->n_q_heads / p->n_kv_heads, t32 = ((int64_t)p->s_q + 31) / 32, t64 = (t32 + 1) / 2;
+  const double padding = (double)(2 * t64 - t32) / (double)t32;
+  if (plan.both) return p->s_q * group >= 512 * (int64_t)plan.split && padding <= 0.04 ? 64 : 32;
+  const double walk = visible_pairs_upto(p, p->kv_end) / (double)(p->kv_end - p->kv_begin) * (double)group / plan.split;      // rows that see an item's key
+  return walk * (0.08 - padding) >= 112 ? 64 : 32;
+}
 // Cut points of equal work on multiples of 256 keys (no range boundary inside a chunk-grid tile).
 void equal_work_ranges(const slimpipe_attn_params* p, int ranges, int64_t* begin, int64_t* end) {
   const double total = visible_pairs_upto(p, p->kv_end);
@@ -525,8 +547,8 @@ int slimpipe_attn_call_path(const slimpipe_attn_params* p, int is_bwd, int32_t n
   const BwdPlan plan = bwd_plan_within(p, n_chunks, workspace_bytes);
   path->small = bwd_small_plan(p, plan).use;
   path->ranges = path->small ? 1 : plan.dq_ranges;
-  path->dq_tile_keys = path->small ? small_dq_tile_keys(p->head_dim) : dq_tile_keys(p->head_dim, plan.both);
-  path->dkdv_tile_rows = path->small ? 32 : dkdv_tile_rows(p->head_dim, p->s_q, p->n_q_heads / p->n_kv_heads, plan.split, plan.both);
+  path->dq_tile_keys = path->small ? small_dq_tile_keys(p->head_dim) : dq_tile_keys(p, plan);
+  path->dkdv_tile_rows = path->small ? 32 : dkdv_tile_rows(p, plan);
   return SLIMPIPE_OK;
 }
 
@@ -794,6 +816,8 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   const int64_t cus = compute_units();
   a.dkdv_wgs = (int32_t)cus;
   a.dq_first = plan.dq_first;
+  a.dq_tile_keys = dq_tile_keys(p, plan);
+  a.dkdv_tile_rows = dkdv_tile_rows(p, plan);
   const bool counted = counters && !plan.both;
   a.ticket_dkdv = (counted && (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2] > cus) ? counters : nullptr;
   a.ticket_dq = (counted && (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] > cus) ? counters + 8 : nullptr;     // [0..7]: dk/dv, [8..15]: dq, one per XCD

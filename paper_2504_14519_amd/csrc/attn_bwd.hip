@@ -201,10 +201,9 @@ SP_DEV void dq_vector_phase(DqState<D, BN>& st, float c, bool need_mask, int kmi
 
 // Keys of a tile.  At head_dim 64 the scores of 128 keys fit the registers that head_dim 128 needs for its operands and accumulators,
 // and a tile has the matrix work of a head_dim 128 tile for the same barriers: 8192 rows on 40960 keys, 16/2 heads, 1675 -> 1598 us.
-// The calls that run dq and dk/dv in one launch keep 64 (kBothDqKeys): their items walk few keys, and the longer first and last
-// tile of an item costs more than the barriers (917 rows on 1230 keys, 16 heads: 45.2 us with 64, 46.8 with 128).
+// Calls whose items walk few keys keep 64 (dq_tile_keys in api.hip), and so do those that run dq and dk/dv in one launch: the
+// longer first and last tile of an item costs more than the barriers (917 rows on 1230 keys, 16 heads: 45.2 us with 64, 46.8 with 128).
 constexpr int kBothDqKeys = 64;
-constexpr int dq_keys_per_tile(int head_dim) { return head_dim == 64 ? 128 : 64; }
 
 // One work item: index -> (query block, kv head, batch index x key range), the first fastest.
 template <int D, int NW, int BN>
@@ -415,23 +414,23 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_kernel(const BwdArgs a) {
   dq_item<D, NW, BN>(a, item, smem);
 }
 
-template <int D>
-constexpr size_t dq_lds_bytes() { return (size_t)6 * dq_keys_per_tile(D) * D * 2 + (size_t)256 * D * 2; }   // 4 K slots + 2 V slots + dO rows
+template <int D, int BN>
+constexpr size_t dq_lds_bytes() { return (size_t)6 * BN * D * 2 + (size_t)256 * D * 2; }   // 4 K slots + 2 V slots + dO rows
 
 template <int D, int NW, int BN>
 static hipError_t launch_dq_t(const BwdArgs& a, int batch, hipStream_t st) {
   constexpr int BM = NW * 32;
-  static_assert(BM == 256 && BN == dq_keys_per_tile(D), "dq_lds_bytes assumes this shape");
+  static_assert(BM == 256, "dq_lds_bytes assumes this shape");
   const int64_t items = (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2];
   const int64_t wgs = a.ticket_dq ? items + items / 4 + 64 : items;      // (see launch_dkdv_t)
   dim3 grid((unsigned)wgs), block(NW * 64);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, BN>), grid, block, dq_lds_bytes<D>(), st, a);
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, NW, BN>), grid, block, (dq_lds_bytes<D, BN>()), st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {
-  if (head_dim == 128) return launch_dq_t<128, 8, dq_keys_per_tile(128)>(a, batch, st);
-  return launch_dq_t<64, 8, dq_keys_per_tile(64)>(a, batch, st);
+  if (head_dim == 128) return launch_dq_t<128, 8, 64>(a, batch, st);
+  return a.dq_tile_keys == 128 ? launch_dq_t<64, 8, 128>(a, batch, st) : launch_dq_t<64, 8, 64>(a, batch, st);
 }
 
 // ------------------------------------------------------------------------------------ dk / dv
@@ -452,7 +451,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // Query rows of a tile.  At head_dim 64 the scores of 64 rows fit the registers that head_dim 128 needs for its operands and
 // accumulators; twice the work per tile halves the barriers, cursor steps and copy instructions per pair: 8192 rows on 40960 keys,
 // 16/2 heads, 2635 -> 2437 us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 210 -> 201 us the call.
-constexpr int dkdv_rows_per_tile(int head_dim) { return head_dim == 64 ? 64 : 32; }
+// Calls that this does not pay for keep 32: dkdv_tile_rows in api.hip.
 
 template <int D, int BMQ>
 struct DkdvState {
@@ -926,7 +925,7 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
 // XCD c take class c in order first and move on to the next class when theirs is used up.  Items of one class are the
 // same chunk of the query stream (8 or 4 chunks) for one key tile after the other, so the workgroups that share an
 // L2 walk the same eighth of Q and dO.  A workgroup leaves after it has found all eight classes empty.
-template <int D, int NW>
+template <int D, int NW, int BMQ>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int n_items = a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
@@ -952,7 +951,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a)
       __syncthreads();                                      // read by all before the first tile copy lands there
       if (item < 0) return;
     }
-    dkdv_item<D, NW, dkdv_rows_per_tile(D)>(a, item, smem);
+    dkdv_item<D, NW, BMQ>(a, item, smem);
     if (!a.ticket_dkdv) return;
   }
 }
@@ -1035,61 +1034,52 @@ __global__ __launch_bounds__(256) void both_reduce_kernel(const BwdArgs a, int b
   else dkdv_reduce(a, (int64_t)(blockIdx.x - dq_blocks) * 256 + threadIdx.x, batch, head_dim);
 }
 
-template <int D, int NW>
+template <int D, int NW, int BMQ>
 static hipError_t launch_dkdv_t(const BwdArgs& a, int batch, hipStream_t st) {
   if (a.kv_end <= a.kv_begin) return hipSuccess;
   const int64_t items = (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
   // with a ticket counter: one workgroup per compute unit (the kernel's LDS allows one at a time), each looping over items
   const int64_t wgs = a.ticket_dkdv ? (items < a.dkdv_wgs ? items : a.dkdv_wgs) : items;
   dim3 grid((unsigned)wgs), block(NW * 64);
-  constexpr size_t smem = DkdvLds<D, NW, dkdv_rows_per_tile(D)>::TOTAL;
-  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, NW>), grid, block, smem, st, a);
+  constexpr size_t smem = DkdvLds<D, NW, BMQ>::TOTAL;
+  hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, NW, BMQ>), grid, block, smem, st, a);
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, int BMQ>
 constexpr size_t both_lds_bytes() {
-  constexpr size_t dkdv = DkdvLds<D, 8, dkdv_rows_per_tile(D)>::TOTAL;
-  return dq_lds_bytes<D>() > dkdv ? dq_lds_bytes<D>() : dkdv;
+  constexpr size_t dq = dq_lds_bytes<D, kBothDqKeys>(), dkdv = DkdvLds<D, 8, BMQ>::TOTAL;
+  return dq > dkdv ? dq : dkdv;
 }
 
 template <int D, int BMQ>
 static hipError_t launch_both_t(const BwdArgs& a, hipStream_t st) {
   const int64_t items = (int64_t)a.dq_items[0] * a.dq_items[1] * a.dq_items[2] + (int64_t)a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
-  hipLaunchKernelGGL((attn_bwd_both_kernel<D, BMQ>), dim3((unsigned)items), dim3(512), both_lds_bytes<D>(), st, a);
+  hipLaunchKernelGGL((attn_bwd_both_kernel<D, BMQ>), dim3((unsigned)items), dim3(512), (both_lds_bytes<D, BMQ>()), st, a);
   return hipGetLastError();
 }
-// At head_dim 64 a chunk of fewer than 512 query rows is walked in tiles of 32: its first tile is a chain of copy, scores and
-// softmax that nothing hides, and with 64 rows it is twice as long (256 rows of 4 heads on 5073 keys, 128 rows a chunk: 27.3 us with
-// 32-row tiles, 29.7 with 64).  So is every call whose heads would be padded by more than 4 % (400 rows are 416 or 448: 73.3 us
-// against 77.3 on 12400 keys, 8/2 heads).
-int dkdv_tile_rows(int head_dim, int s_q, int group, int n_split, bool one_launch) {
-  if (head_dim == 128 || !one_launch) return dkdv_rows_per_tile(head_dim);
-  const int64_t t32 = ((int64_t)s_q + 31) / 32, t64 = (t32 + 1) / 2;
-  return (int64_t)s_q * group >= 512 * (int64_t)n_split && 25 * (2 * t64 - t32) <= t32 ? 64 : 32;
-}
-int dq_tile_keys(int head_dim, bool one_launch) { return one_launch ? kBothDqKeys : dq_keys_per_tile(head_dim); }
-
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st) {
   if (head_dim == 128) return launch_both_t<128, 32>(a, st);
-  return dkdv_tile_rows(64, a.s_q, a.group, a.n_split, true) == 64 ? launch_both_t<64, 64>(a, st) : launch_both_t<64, 32>(a, st);
+  return a.dkdv_tile_rows == 64 ? launch_both_t<64, 64>(a, st) : launch_both_t<64, 32>(a, st);
 }
 
 hipError_t opt_in_bwd_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<128, 8, dq_keys_per_tile(128)>), attr, (int)dq_lds_bytes<128>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<64, 8, dq_keys_per_tile(64)>), attr, (int)dq_lds_bytes<64>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128, 8>), attr, DkdvLds<128, 8, dkdv_rows_per_tile(128)>::TOTAL);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8>), attr, DkdvLds<64, 8, dkdv_rows_per_tile(64)>::TOTAL);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128, 32>), attr, (int)both_lds_bytes<128>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 64>), attr, (int)both_lds_bytes<64>());
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 32>), attr, (int)both_lds_bytes<64>());
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<128, 8, 64>), attr, (int)dq_lds_bytes<128, 64>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<64, 8, 128>), attr, (int)dq_lds_bytes<64, 128>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dq_kernel<64, 8, 64>), attr, (int)dq_lds_bytes<64, 64>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<128, 8, 32>), attr, DkdvLds<128, 8, 32>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8, 64>), attr, DkdvLds<64, 8, 64>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_dkdv_kernel<64, 8, 32>), attr, DkdvLds<64, 8, 32>::TOTAL);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<128, 32>), attr, (int)both_lds_bytes<128, 32>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 64>), attr, (int)both_lds_bytes<64, 64>());
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_both_kernel<64, 32>), attr, (int)both_lds_bytes<64, 32>());
   return e;
 }
 
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {
-  if (head_dim == 128) return launch_dkdv_t<128, 8>(a, batch, st);
-  return launch_dkdv_t<64, 8>(a, batch, st);
+  if (head_dim == 128) return launch_dkdv_t<128, 8, 32>(a, batch, st);
+  return a.dkdv_tile_rows == 64 ? launch_dkdv_t<64, 8, 64>(a, batch, st) : launch_dkdv_t<64, 8, 32>(a, batch, st);
 }
 
 hipError_t launch_dq_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {

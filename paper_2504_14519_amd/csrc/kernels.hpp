@@ -109,6 +109,7 @@ struct BwdArgs {
   int64_t kv_stride_b, kv_stride_s, kv_stride_h;
   int64_t o_stride_b, o_stride_s, o_stride_h;
   int64_t do_stride_b, do_stride_s, do_stride_h;
+  int32_t dq_tile_keys, dkdv_tile_rows;      // keys of a dq tile, query rows of a dk/dv tile (head_dim 64 has two of each)
 };
 
 struct MergeArgs {
@@ -136,8 +137,6 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 hipError_t launch_bwd_dkdv(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dkdv_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_dq_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
-int dq_tile_keys(int head_dim, bool one_launch);
-int dkdv_tile_rows(int head_dim, int s_q, int group, int n_split, bool one_launch);
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st);
 int small_dq_tile_keys(int head_dim);
 hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, hipStream_t st);

@@ -256,3 +256,20 @@ def test_forward_takes_the_small_kernel_only_with_the_workspace_it_asks_for(sp):
                 small, ranges = path(room)
                 assert small == 0 and (ranges == 1 or 256 + per_range(ranges) <= room), (B, s, Hq, Hkv, D, keys, room)
     assert 500 < asked_small < len(shapes) - 500
+
+
+@pytest.mark.parametrize("B,s,Hq,Hkv,keys,dq_keys,dkdv_rows", [
+    (4, 40, 40, 40, 5278, 64, 32), (8, 64, 32, 32, 870, 64, 32), (8, 160, 32, 8, 1184, 64, 32), (8, 512, 40, 40, 528, 64, 32),
+    (8, 288, 16, 16, 800, 64, 32), (2, 1024, 16, 16, 13392, 128, 32), (2, 64, 32, 32, 16000, 128, 32),
+    (4, 731, 12, 4, 8822, 128, 32), (4, 683, 64, 8, 1194, 64, 64), (4, 2432, 32, 32, 3921, 128, 64), (1, 8192, 16, 2, 40960, 128, 64)])
+def test_two_launch_backward_of_head_dim_64_takes_large_tiles_where_walks_are_long(sp, B, s, Hq, Hkv, keys, dq_keys, dkdv_rows):
+    """Measured: 64-row dk/dv tiles take up to 1.75 times as long on short or padded walks, 128-key dq tiles up to 1.2 times."""
+    import types
+    D = 64
+    q = types.SimpleNamespace(shape=(B, s, Hq, D), stride=lambda i, st=(s * Hq * D, Hq * D, D, 1): st[i])
+    k = types.SimpleNamespace(shape=(B, keys, Hkv, D), stride=lambda i, st=(keys * Hkv * D, Hkv * D, D, 1): st[i])
+    p = sp.make_params(q, k, q, keys - s, 0, keys, True, None)
+    need = sp.slimpipe_attn_workspace_bytes(p, True)
+    assert sp.slimpipe_attn_bwd_plan(p, 1, need).one_launch == 0
+    path = sp.slimpipe_attn_call_path(p, True, 1, need)
+    assert (path.small, path.dq_tile_keys, path.dkdv_tile_rows) == (0, dq_keys, dkdv_rows)
