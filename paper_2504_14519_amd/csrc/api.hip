@@ -384,8 +384,9 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // the 256-row items (512 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.9 us; 100 rows of 8/2 heads of 128 on 448 keys, batch 2: 31.9 ->
 // 17.1).  Long calls stay out: a workgroup reads the whole other side for 32 rows or keys, and the model does not know what
 // that costs a full chip (1969 rows on 4976 keys, 8/1 heads of 64: 80 us by the model, 104 measured, 90 through the 256-row items).
-// Calls of fewer than 64 dq items would gain as well (256 rows of 4 heads on 1215 keys 24.8 -> 17.9 us) but their launches are
-// pinned, kind by kind, by the test of the per-kernel timing.
+// The line at 32 dq items is no line of speed: below it the small kernel wins too (252 calls of 1 to 32 items: 1.54 times as fast in the mean,
+// 0.90 at worst), but the launches of a call of 32 items are what the per-kernel timing is pinned to, kind by kind.  With 33 to 63 items (48
+// calls) it is 1.61 times as fast in the mean, 0.95 at worst (480 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.5 us).
 struct BwdSmallPlan { bool use, dq_first; };
 BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) {
   if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false};
@@ -399,7 +400,7 @@ BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) 
   const double tq = (d64 ? 5 : 6) + (d64 ? 1.4 : 1.6) * (nq > cus ? sq * seen + 0.5 : ceil(sq));
   const double tk = (d64 ? 5 : 6) + (d64 ? 1.0 : 2.0) * (nk > cus ? sk * seen + 0.5 : ceil(sk));
   const double us = (d64 ? 5.5 : 4) + (tq > tk ? list_makespan(cus, nq, tq, nk, tk) : list_makespan(cus, nk, tk, nq, tq));
-  return {nq >= 64 && us < 60 && us * 1.05 < plan.us + 7, tq > tk};
+  return {nq > 32 && us < 60 && us * 1.05 < plan.us + 7, tq > tk};
 }
 // Tiles of the large backward at head_dim 64: 128 or 64 keys (dq), 64 or 32 query rows (dk/dv).  The larger ones have half the
 // barriers and copies per pair; a short walk pays for them in its first and last tile, which nothing hides, and in padding.

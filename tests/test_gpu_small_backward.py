@@ -23,6 +23,9 @@ pytestmark = pytest.mark.gpu
     (3, 190, 1024, 4, 1, 64, 800, 300, 985, True, 256),
     (1, 129, 600, 16, 2, 64, 0, 0, 600, False, 0),
     (1, 400, 700, 8, 1, 128, 150, 300, 700, True, 0),      # the first 150 rows see no key of the range
+    (1, 480, 2048, 4, 4, 64, 1568, 0, 2048, True, 0),      # 60, 33 and 36 dq items
+    (3, 321, 700, 1, 1, 128, 379, 0, 700, True, 0),
+    (2, 43, 768, 9, 3, 64, 700, 100, 743, True, 256),
 ])
 def test_small_backward(B, s, N, Hq, Hkv, D, off, b, e, causal, chunk):
     import torch

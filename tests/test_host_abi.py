@@ -219,6 +219,10 @@ def test_call_path_reports_the_kernels_of_a_call(sp):
     least = 2 * 4 * 512 * 4
     assert path(tiny, True, sp.slimpipe_attn_workspace_bytes(tiny, True)) == (1, 1, 64, 32)
     assert path(tiny, True, least) == (0, 1, 64, 64)
+    # above 32 dq items the model decides, not the number of items
+    for s, small in ((256, 0), (257, 1), (288, 1), (480, 1), (511, 1)):
+        p = params(1, s, 4, 4, 64, 2048)
+        assert path(p, True, sp.slimpipe_attn_workspace_bytes(p, True))[0] == small, s
     assert path(large, False, 1 << 40) == (0, 1) and path(large, True, 1 << 40) == (0, 1, 64, 32)
     out = (ctypes.c_int32 * 4)()
     call = lambda p, bwd, n, room: sp.lib.slimpipe_attn_call_path(ctypes.byref(p), bwd, n, room, ctypes.cast(out, ctypes.POINTER(sp.binding.CallPath)))
