@@ -424,7 +424,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   const int hk = __builtin_amdgcn_readfirstlane(hb / key_blocks), kblk = hb - hk * key_blocks;
   const int64_t key0 = grid0 + (int64_t)kblk * 32, mykey = key0 + ql;
   const int chunk = kv_chunk_of(a.kv, key0);
-  const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.seen_end > key0 ? a.seen_end - key0 : 1;      // keys to read (a block that no row sees reads one)
+  const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (>= 1)
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
   const float c = a.scale_log2e;
 
@@ -444,8 +444,10 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   // V rows of the workgroup: one copy instruction per wave (as far as there are any)
   {
     const bf16_t* vbase = uniform_ptr(a.kv.v[chunk] + head_off + chunk_row0 * a.kv_stride_s);
-    if (wave_u < WaveDma<D, 32>::PASSES)
-      WaveDma<D, 32>::copy_pass(smem_lds + S::V_BASE, vbase, (uint32_t)a.kv_stride_s * 2, left < 32 ? (int)left : 32, lane, wave_u);
+    // (rows that some row sees: dS of the others is P = 0 times dP, and what the cache holds there must not reach dP)
+    const int64_t seen = a.seen_end - key0;
+    if (wave_u < WaveDma<D, 32>::PASSES && seen > 0)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::V_BASE, vbase, (uint32_t)a.kv_stride_s * 2, seen < 32 ? (int)seen : 32, lane, wave_u);
   }
   // query tiles that see the block: [qt0, nqt) of every head of the group, tile j of this list for wave j mod 8
   const int nqt = (int)(((int64_t)a.s_q + 31) / 32);
