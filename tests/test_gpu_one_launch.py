@@ -1,5 +1,6 @@
-"""Backward calls of fewer than two work items per compute unit run dq and dk/dv in one launch: the same items, so undivided
-the same bits as in the two launches of a call of many sequences, and at every workspace size the same sums in another order."""
+"""Backward calls of fewer than two work items per compute unit run dq and dk/dv in one launch: the same items, so undivided the same
+bits as in the two launches of a call of many sequences (at head_dim 64 where dk/dv walks tiles of the same rows, or has one
+query head per K/V head: the order of the sums over a group is that of the tiles), and at every workspace size the same sums in another order."""
 import math
 
 import pytest
