@@ -126,7 +126,7 @@ int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, siz
  *               in the same call; given less room it uses as many ranges as fit, down to the undivided
  *               computation.  A call of few query blocks that is given what slimpipe_attn_workspace_bytes(p, 0)
  *               asks for may be computed by workgroups of 32 rows whose waves share out the keys (another order of
- *               the float32 sums); with less it is cut as above, and where not even two ranges fit, or
+ *               the float32 sums, and probabilities rounded to bf16 relative to each wave's own maximum); with less it is cut as above, and where not even two ranges fit, or
  *               with NULL, it returns what slimpipe_attn_fwd_ranges returns for its range, bit for bit. */
 int slimpipe_attn_fwd(const slimpipe_attn_params* p,
                       const void* q_slice, const void* k_prefix, const void* v_prefix,

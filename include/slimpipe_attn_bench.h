@@ -1,7 +1,7 @@
 /*
  * slimpipe_attn_bench.h - measurement aids of libslimpipe_attn (not part of the paper's method, not needed to
- * use the library): per-kernel event timing and the sustained rate of the matrix instruction on this GPU.
- * Used by bench.py only.  Same conventions as slimpipe_attn.h (status codes, device pointers, streams).
+ * use the library): per-kernel event timing, the kernels and cuts a call would take, and the sustained rate of the matrix instruction on this GPU.
+ * Used by bench.py and the tests.  Same conventions as slimpipe_attn.h (status codes, device pointers, streams).
  */
 #ifndef SLIMPIPE_ATTN_BENCH_H
 #define SLIMPIPE_ATTN_BENCH_H

@@ -120,7 +120,8 @@ def _check(rc, what):
 
 
 def _stream():
-    # the raw handle of the current device's current stream: a stream object per call costs more than a kernel launch
+    # the raw handle of the current device's current stream, through two private functions of torch: 0.3 us; the public call
+    # builds a stream object, 2.9 us
     import torch
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 

@@ -404,7 +404,7 @@ BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) 
 }
 // Tiles of the large backward at head_dim 64: 128 or 64 keys (dq), 64 or 32 query rows (dk/dv).  The larger ones have half the
 // barriers and copies per pair; a short walk pays for them in its first and last tile, which nothing hides, and in padding.
-// Over 470 drawn calls of two launches, larger against smaller tile: dq 0.93 to 1.01 of the time where the rule says 128, always
+// Over 470 calls of random sizes in two launches, larger against smaller tile: dq 0.93 to 1.01 of the time where the rule says 128, always
 // taking 128 costs up to 1.21 (64 rows of 40 heads on 141 keys, batch 8).
 int dq_tile_keys(const slimpipe_attn_params* p, const BwdPlan& plan) {
   if (p->head_dim == 128 || plan.both) return 64;
@@ -414,7 +414,7 @@ int dq_tile_keys(const slimpipe_attn_params* p, const BwdPlan& plan) {
 // dk/dv in two launches: 0.89 to 1.01 of the time where the rule says 64 rows (1400 rows an item and more, with padding more);
 // always taking 64 costs up to 1.75 (40 rows of 40 heads on 5278 keys, batch 4) and 1.13 to 1.19 at 512 rows.  In one launch, where a long
 // item ends the call, the line is lower: 512 rows a chunk (256 rows of 4 heads on 5073 keys, 128 rows a chunk: 27.3 us with 32-row tiles,
-// 29.7 with 64) and 4 % of padding (400 rows are 416 or 448: 73.3 us against 77.3 on 12400 keys, 8/2 heads); over 360 drawn calls 0.88 to
+// 29.7 with 64) and 4 % of padding (400 rows are 416 or 448: 73.3 us against 77.3 on 12400 keys, 8/2 heads); over 360 calls 0.88 to
 // 1.05 of the time where it says 64.
 int dkdv_tile_rows(const slimpipe_attn_params* p, const BwdPlan& plan) {
   if (p->head_dim == 128 || p->kv_end <= p->kv_begin) return 32;
