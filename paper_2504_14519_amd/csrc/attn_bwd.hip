@@ -13,6 +13,8 @@
 //     group in a fixed order: S = Q K^T, dP = dO V^T land with one key per lane and 16 query rows
 //     in the registers, which is the B operand of dV^T += dO^T P and dK^T += Q^T dS.
 //     One workgroup owns a key row outright, so dK/dV are bit-reproducible.
+#include <type_traits>
+
 #include "kernels.hpp"
 #include "tile_common.hpp"
 
@@ -474,7 +476,16 @@ struct DkdvLds {
   static constexpr int V_BYTES = NW * 32 * D * 2;
   static constexpr int STAT_BASE = V_BASE + V_BYTES;          // [SLOTS][lse2[BMQ], delta[BMQ]] floats
   static constexpr int STAT_BYTES = 2 * BMQ * 4;
-  static constexpr int TOTAL = STAT_BASE + SLOTS * STAT_BYTES;
+  // K rows of the workgroup on their way into registers, 32 a wave: in ring slots 1 .. 3, which hold no tile yet, and behind the
+  // statistics
+  static constexpr int K_WAVE_BYTES = 32 * D * 2, K_PER_RING = (SLOTS - 1) * TILE_BYTES / K_WAVE_BYTES;
+  static constexpr int K_REST = NW > 2 * K_PER_RING ? NW - 2 * K_PER_RING : 0, K_BASE = STAT_BASE + SLOTS * STAT_BYTES;
+  static constexpr int k_stage(int wave) {
+    if (wave < K_PER_RING) return Q_BASE + TILE_BYTES + wave * K_WAVE_BYTES;
+    if (wave < 2 * K_PER_RING) return DO_BASE + TILE_BYTES + (wave - K_PER_RING) * K_WAVE_BYTES;
+    return K_BASE + (wave - 2 * K_PER_RING) * K_WAVE_BYTES;
+  }
+  static constexpr int TOTAL = K_BASE + K_REST * K_WAVE_BYTES;
 };
 
 template <int D, int NW, int BMQ, bool WITH_ACC, bool WITH_SCORES, int LOOK>
@@ -533,8 +544,8 @@ struct DkdvMatrixPhase {
   SP_DEV void mfma() {
     if constexpr (M < N_AC) {
       constexpr int h = M / (2 * DB), db = (M % (2 * DB)) / 2;
-      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(abuf[M % NBUF], st.pb[h / 2][h % 2], st.dv[db]);
-      else st.dk[db] = mfma32(abuf[M % NBUF], st.dsb[h / 2][h % 2], st.dk[db]);
+      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(st.pb[h / 2][h % 2], abuf[M % NBUF], st.dv[db]);
+      else st.dk[db] = mfma32(st.dsb[h / 2][h % 2], abuf[M % NBUF], st.dk[db]);
     } else {
       constexpr int j = M - N_AC, ks = ks_of(j), qb = qb_of(j);
       const f32x16 zero = {0};
@@ -640,16 +651,8 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
   const int kchunk = a.kv.n > 1 ? __builtin_amdgcn_readfirstlane((int)(tile_key0 / a.kv.len)) : 0;
   const int64_t chunk_row0 = tile_key0 - (int64_t)kchunk * a.kv.len;      // the tile's first row inside its chunk
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
-  const int64_t mykey = tile_key0 + wave_u * 32 + ql;
-  const int64_t mykey_c = mykey < a.kv_end ? mykey : a.kv_end - 1;
 
   DkdvState<D, BMQ> st;
-  {
-    // K as B operand: column = my key, k-slots = head_dim 16*ks + 8g ..
-    const bf16_t* kp = a.kv.k[kchunk] + head_off + (chunk_row0 + (mykey_c - tile_key0)) * a.kv_stride_s;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) st.kreg[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks + 8 * g);
-  }
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -788,8 +791,22 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       for (int part = 0; part < 4; ++part) copy_part(j, with_stats, part);
     };
 
-    // prologue: V rows of the workgroup that any row sees (dS of the others is P = 0 times dP: whatever the cache holds there must
-    // not reach dP; K only enters S, which the mask replaces), all threads; Q(0), Q(1) + statistics (group A), dO(0), dO(1) (group B)
+    // prologue: K rows (each wave its own), V rows of the workgroup that any row sees (dS of the others is P = 0 times dP: whatever
+    // the cache holds there must not reach dP; K only enters S, which the mask replaces), all threads; Q(0) + statistics (group A),
+    // dO(0) (group B).  K goes through LDS although it ends up in registers: a lane that reads its own key's row from memory
+    // shares a line with no neighbour, and the address unit takes such a load at a lane a clock.
+    const unsigned k_lds = smem_lds + (unsigned)L::k_stage(wave_u);
+    {
+      using Dma = WaveDma<D, 32>;
+      const bf16_t* kbase = a.kv.k[kchunk] + head_off + chunk_row0 * a.kv_stride_s;
+      const int64_t left = a.kv_end - tile_key0;
+      const int avail = left > BNK ? BNK : (int)left;        // keys past the end of the range are clamped
+#pragma unroll
+      for (int n = 0; n < Dma::PASSES; ++n) {
+        const int r = wave_u * 32 + lane / Dma::NC + Dma::RPP * n, rr = r < avail ? r : avail - 1;
+        dma16(kbase, mul24((uint32_t)rr, (uint32_t)a.kv_stride_s * 2) + Dma::chunk_off(lane, n), __builtin_amdgcn_readfirstlane(k_lds + n * 1024));
+      }
+    }
     {
       TileDma<D, BNK, T> dma_v;
       dma_v.init(tid);
@@ -803,16 +820,27 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
     int row0_cur = cc.row0;
     copy_all(make_copy(cc, 0), copies_q);
     cursor_next(cc);
-    int row0_nxt = cc.row0;
-    copy_all(make_copy(cc, 1), copies_q);
-    cursor_next(cc);
     wait_async();
+    {
+      // K as B operand: column = key, k-slots = head_dim 16*ks + 8g ..
+      RpBase<D> lo_k;
+      lo_k.init(lane, (int)k_lds);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) st.kreg[ks] = lds_rp<D>(lo_k, ks, 0);
+      // (in registers before the barrier: tiles are copied there behind it)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(st.kreg[ks]));
+    }
     TrBase<D> lo_qt;         // Q(u-1), transposed
     RpBase<D> lo_q, lo_v;    // Q(u) and this wave's V rows, row-packed
     lo_qt.init(lane, (int)smem_lds + L::Q_BASE + (SLOTS - 1) * TILE_BYTES);     // "Q(-1)": never read
     lo_q.init(lane, (int)smem_lds + L::Q_BASE);
     lo_v.init(lane, (int)smem_lds + L::V_BASE + wave_u * 32 * D * 2);
     __syncthreads();
+    const int row0_first_nxt = cc.row0;
+    copy_all(make_copy(cc, 1), copies_q);                 // (waited for behind the first matrix phase)
+    cursor_next(cc);
+    int row0_nxt = row0_first_nxt;
 
     int slot = 0;            // ring slot of tile u
     auto advance = [&]() {
@@ -874,49 +902,64 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
     if (!group_b) phase_end();
   }
 
-  // (the key is worked out afresh from an opaque copy of the lane number: otherwise its 64 bits stay in
-  // registers across the whole loop, and registers are what this kernel is short of)
-  const int tid_out = fresh(tid), ql_out = tid_out & 31, g_out = (tid_out >> 5) & 1;
-  const int64_t mykey_out = tile_key0 + wave_u * 32 + ql_out;
-  if (mykey_out >= a.kv_begin && mykey_out < a.kv_end) {
-    // one chunk: straight into the accumulators; several: this chunk's partial sums, added up in a
-    // fixed order by the reduce kernel
-    float* kdst;
-    float* vdst;
-    bool accumulate;
-    if (a.n_split > 1) {
-      const int64_t plane = (int64_t)a.dkdv_items[2] * a.dkdv_items[1] * a.nkeys_pad * D;          // one of dk / dv of one chunk
-      const int64_t row = (((int64_t)b * a.dkdv_items[1] + hk) * a.nkeys_pad + (mykey_out - grid0)) * D;
-      kdst = a.part + (int64_t)split * 2 * plane + row;
-      vdst = kdst + plane;
-      accumulate = false;
-    } else {
-      const int64_t base = head_off + (chunk_row0 + (mykey_out - tile_key0)) * a.kv_stride_s;
-      kdst = a.dk_acc[kchunk] + base;
-      vdst = a.dv_acc[kchunk] + base;
-      accumulate = a.dkv_accumulate != 0;
-    }
-    // One gradient at a time.  When the call adds to the accumulators, all 16 loads of the old values are issued
-    // before the first of them is needed: a load, add, store chain per 16 bytes pays the memory latency 16 times over
-    // (a store may alias a later load for all the compiler knows, so it does not batch them by itself), and with few
-    // query tiles per key tile (many KV heads, short slices) that was a sixth of the kernel's time.
-    auto flush = [&](const f32x16 (&acc)[DB], float* dst, float factor) {
-      f32x4 old[DB * 4];
-      if (accumulate) {
+  // one chunk: straight into the accumulators; several: this chunk's partial sums, added up in a fixed order by the reduce kernel
+  float *kdst, *vdst;          // row of the wave's first key
+  int64_t row_stride;
+  bool accumulate;
+  if (a.n_split > 1) {
+    const int64_t plane = (int64_t)a.dkdv_items[2] * a.dkdv_items[1] * a.nkeys_pad * D;          // one of dk / dv of one chunk
+    kdst = a.part + (int64_t)split * 2 * plane + (((int64_t)b * a.dkdv_items[1] + hk) * a.nkeys_pad + (tile_key0 - grid0) + wave_u * 32) * D;
+    vdst = kdst + plane;
+    row_stride = D;
+    accumulate = false;
+  } else {
+    const int64_t base = head_off + (chunk_row0 + wave_u * 32) * a.kv_stride_s;
+    kdst = a.dk_acc[kchunk] + base;
+    vdst = a.dv_acc[kchunk] + base;
+    row_stride = a.kv_stride_s;
+    accumulate = a.dkv_accumulate != 0;
+  }
+  // A lane holds head_dim 32 db + (lane & 31) of the keys 8*(i/4) + 4g + i%4: an instruction moves two whole 128-byte lines.  (With a
+  // key a lane, and 16 bytes of its row an instruction, no two neighbouring lanes share a line and the address unit takes one lane a
+  // clock.  From the end of the tile loop to the next item, 512 KB read and written at head_dim 128, one K/V head per query head: 23
+  // -> 13 us; without old values to add to 8 -> 6.)  When the call adds to the accumulators, the old values of a gradient are all asked
+  // for before the first is needed, those of dV behind the stores of dK.
+  const int64_t key0_out = tile_key0 + wave_u * 32;
+  const int kmin = key0_out < a.kv_begin ? (int)(a.kv_begin - key0_out < 32 ? a.kv_begin - key0_out : 32) : 0;     // keys [kmin, kmax) of the wave exist
+  const int kmax = key0_out + 32 > a.kv_end ? (int)(a.kv_end - key0_out > 0 ? a.kv_end - key0_out : 0) : 32;
+  const int lane_out = fresh(tid) & 63, g4 = (lane_out >> 5) * 4;
+  const uint32_t lane_off = mul24((uint32_t)g4, (uint32_t)row_stride) * 4u + (uint32_t)(lane_out & 31) * 4u;
+  auto at = [&](float* dst, int i, int db) {
+    return reinterpret_cast<float*>(reinterpret_cast<char*>(dst + (8 * (i >> 2) + (i & 3)) * row_stride + 32 * db) + lane_off);
+  };
+  auto flush = [&](auto whole) {
+    auto mine = [&](int i) { const int k = 8 * (i >> 2) + (i & 3) + g4; return decltype(whole)::value || (k >= kmin && k < kmax); };
+    float old[DB][16];
+    auto fetch = [&](float* dst, int db) {
 #pragma unroll
-        for (int j = 0; j < DB * 4; ++j) old[j] = *reinterpret_cast<const f32x4*>(dst + 32 * (j >> 2) + 8 * (j & 3) + 4 * g_out);
-      }
+      for (int i = 0; i < 16; ++i) old[db][i] = mine(i) ? *at(dst, i, db) : 0.f;
+    };
+    auto put = [&](float* dst, int db, const f32x16& acc, float factor) {
 #pragma unroll
-      for (int j = 0; j < DB * 4; ++j) {
-        const int db = j >> 2, i4 = j & 3;
-        f32x4 x4 = {acc[db][4 * i4] * factor, acc[db][4 * i4 + 1] * factor, acc[db][4 * i4 + 2] * factor, acc[db][4 * i4 + 3] * factor};
-        if (accumulate) x4 += old[j];
-        *reinterpret_cast<f32x4*>(dst + 32 * db + 8 * i4 + 4 * g_out) = x4;
+      for (int i = 0; i < 16; ++i) {
+        const float x = accumulate ? acc[i] * factor + old[db][i] : acc[i] * factor;
+        if (mine(i)) *at(dst, i, db) = x;
       }
     };
-    flush(st.dk, kdst, a.scale);
-    flush(st.dv, vdst, 1.0f);
-  }
+    if (accumulate) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db) fetch(kdst, db);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      put(kdst, db, st.dk[db], a.scale);
+      if (accumulate) fetch(vdst, db);
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) put(vdst, db, st.dv[db], 1.0f);
+  };
+  if (kmin == 0 && kmax == 32) flush(std::true_type{});
+  else if (kmin < kmax) flush(std::false_type{});
 }
 
 // Without ticket counters the workgroup's index is its one item.  With them (set to zero before the launch), the
