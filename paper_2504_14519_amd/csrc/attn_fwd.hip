@@ -121,34 +121,20 @@ SP_DEV void fwd_softmax(FwdState<D, BN>& st, float c, H&& hook) {
 }
 
 // out = O / l, lse = (m + log2 l) ln 2; rows that saw no key: out = 0, lse = -inf.
+// The rows leave through LDS (store_rows; the tile rings are not in use any more) and Q comes through it (stage_rows), in whole lines
+// either way: 777 rows on 33777 keys, 8/1 heads of 128, 10 ranges, 119.7 -> 117.6 us; 40/40 heads, 4096 on 20480, two ranges, 1352 ->
+// 1344; 1337 x 3 rows on 4238, 12/4 heads of 64: no difference (72.1).
 template <int D, int BN>
-SP_DEV void fwd_epilogue(const FwdArgs& a, FwdState<D, BN>& st, int myrow, int h, int b, int r, int g) {
-  constexpr int DB = D / 32;
+SP_DEV void fwd_epilogue(const FwdArgs& a, FwdState<D, BN>& st, float* part, int wrow0, int h, int b, int r, int lane) {
+  const int myrow = wrow0 + (lane & 31);
   const float l_tot = xhalf_sum(st.l_run);
   const bool has = l_tot > 0.f;
-  const float inv = has ? 1.0f / l_tot : 0.f;
-  if (myrow < a.s_q) {
-    if (g == 0) {
-      const float lse = has ? (st.m_run + __builtin_log2f(l_tot)) * kLn2 : -INFINITY;
-      a.lse[(int64_t)r * a.lse_range_stride + ((int64_t)b * a.n_q_heads + h) * a.s_q + myrow] = lse;
-    }
-    const int64_t obase = (int64_t)r * a.out_range_stride + (int64_t)b * a.o_stride_b + (int64_t)myrow * a.o_stride_s +
-                          (int64_t)h * a.o_stride_h;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const int d = 32 * db + 8 * i4 + 4 * g;
-        f32x4 v4 = {st.o[db][4 * i4] * inv, st.o[db][4 * i4 + 1] * inv, st.o[db][4 * i4 + 2] * inv,
-                    st.o[db][4 * i4 + 3] * inv};
-        if (a.out_f32) {
-          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(a.out) + obase + d) = v4;
-        } else {
-          bf16x4 h4 = __builtin_convertvector(v4, bf16x4);
-          *reinterpret_cast<bf16x4*>(reinterpret_cast<bf16_t*>(a.out) + obase + d) = h4;
-        }
-      }
+  if (lane < 32 && myrow < a.s_q) {
+    const float lse = has ? (st.m_run + __builtin_log2f(l_tot)) * kLn2 : -INFINITY;
+    a.lse[(int64_t)r * a.lse_range_stride + ((int64_t)b * a.n_q_heads + h) * a.s_q + myrow] = lse;
   }
+  const int64_t base = (int64_t)r * a.out_range_stride + (int64_t)b * a.o_stride_b + (int64_t)wrow0 * a.o_stride_s + (int64_t)h * a.o_stride_h;
+  store_rows<D>(part, st.o, has ? 1.0f / l_tot : 0.f, a.out, a.out_f32, false, base, a.o_stride_s, a.s_q - wrow0, lane);
 }
 
 // One matrix phase of the two-group kernel as an explicit software pipeline: the 2*KB*DB MFMAs of
@@ -215,13 +201,13 @@ struct FwdMatrixPhase {
 template <int D, int NW, int BN>
 __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   static_assert(NW == 8, "two groups of four waves");
-  constexpr int KS = D / 16, DB = D / 32, T = NW * 64;
+  constexpr int DB = D / 32, T = NW * 64;
   constexpr int TILE_BYTES = BN * D * 2;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   constexpr int KSLOTS = 3, VSLOTS = 2;
   constexpr int K_BASE = 0, V_BASE = KSLOTS * TILE_BYTES;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
   // Work item: index -> (query block, kv head, batch index x key range), the first fastest: the workgroup's own
@@ -244,15 +230,8 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
   const int64_t kv_begin = a.range_begin[r], kv_end = a.range_end[r];      // this workgroup's key range
   const WaveRows wr = wave_rows(qblk, wave_u, hk, a.s_q, a.group, a.head_waves);
   const int h = wr.h, wrow0 = wr.row0;
-  const int myrow = wrow0 + ql;
-  const int myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
 
   FwdState<D, BN> st;
-  {
-    const bf16_t* qp = a.q + (int64_t)b * a.q_stride_b + (int64_t)myrow_c * a.q_stride_s + (int64_t)h * a.q_stride_h;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) st.qreg[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * g);
-  }
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -341,11 +320,17 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
       asm volatile("" : "+v"(st.mx));      // keep it on this side of the phase barrier
     };
 
-    // prologue: K(0), K(1) (group A), V(0) (group B)
+    // prologue: the Q rows (each wave its own), K(0), K(1) (group A), V(0) (group B).  Q ends up in registers but goes through LDS, in
+    // the ring slots that hold no tile yet (K slot 2, V slot 1): a lane that reads its own row from memory shares a line with no
+    // other but its neighbour half-wave's, and the address unit takes such a load at a lane a clock
+    const unsigned q_lds = smem_lds + (wave_u < 4 ? K_BASE + 2 * TILE_BYTES : V_BASE + TILE_BYTES - 4 * 32 * D * 2) + wave_u * 32 * D * 2;
+    static_assert(KSLOTS == 3 && VSLOTS == 2 && TILE_BYTES >= 4 * 32 * D * 2, "32 rows of four waves in a free slot");
+    stage_rows<D>(q_lds, a.q + (int64_t)b * a.q_stride_b + (int64_t)h * a.q_stride_h, a.q_stride_s, wrow0, a.s_q, lane);
     const int first = (int)(kv_begin - lo);              // rows of tile 0 before the range
     copy_all(make_copy(0), first);
     if (copies_k) copy_all(make_copy(1), 0);
     wait_async();
+    read_rows<D>(q_lds, lane, st.qreg);
     RpOffsets<D> lo_k;       // K(t), row-packed (registers are plentiful here: one offset per head_dim block)
     TrOffsets<D> lo_v;       // V(t-1), transposed
     lo_k.init(lane, (int)smem_lds + K_BASE);
@@ -383,11 +368,14 @@ __global__ __launch_bounds__(NW * 64) void attn_fwd_kernel(const FwdArgs a) {
     phase_end();
     if (!group_b) phase_end();
   }
-  fwd_epilogue<D, BN>(a, st, myrow, h, b, r, g);
+  fwd_epilogue<D, BN>(a, st, reinterpret_cast<float*>(smem) + wave_u * 32 * kOutRow<D>, wrow0, h, b, r, lane);
 }
 
 template <int D>
-constexpr size_t fwd_lds_bytes() { return (size_t)5 * kFwdKeysPerTile * D * 2; }       // K ring of three, V ring of two
+constexpr size_t fwd_lds_bytes() {       // K ring of three, V ring of two; the output rows on their way out take their place
+  static_assert(8 * 32 * kOutRow<D> * 4 <= 5 * kFwdKeysPerTile * D * 2, "output rows of the eight waves");
+  return (size_t)5 * kFwdKeysPerTile * D * 2;
+}
 
 template <int D, int NW, int BN>
 static hipError_t launch_fwd_t(const FwdArgs& a, int batch, hipStream_t st) {

@@ -343,6 +343,14 @@ SP_DEV int kv_chunk_of(const KvChunks& kv, int64_t key) { return kv.n > 1 ? __bu
 
 // vmcnt(0), other counters untouched (gfx9 encoding: vmcnt[3:0]|[15:14], expcnt[6:4], lgkmcnt[11:8]).
 SP_DEV void wait_async() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+// At most N copies are still under way (N < 64); nothing is scheduled across the wait.
+template <int N>
+SP_DEV void wait_copies() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | (N >> 4) << 14);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
 
 // Query head and first row (within the slice) of a wave of a query block (see query_blocks); a wave past the last head
 // gets rows past the end of the slice.  Heads ascend and rows descend with decreasing block number, so that
@@ -354,6 +362,76 @@ SP_DEV WaveRows wave_rows(int qblk, int wave_u, int hk, int s_q, int group, int 
   if (hg >= group) return {hk * group, s_q};
   return {hk * group + group - 1 - hg, (int)(slot - (unsigned)hg * per) * 32};
 }
+// A wave's 32 rows of Q from row0 on (rows past the slice are clamped to its last one) into the LDS tile at `lds`, asynchronously, and,
+// once they have landed (wait_async), from there into registers as B operand: column = row, k-slots = head_dim 16*ks + 8g ..
+template <int D>
+SP_DEV void stage_rows(unsigned lds, const bf16_t* base, int64_t stride_s, int row0, int s_q, int lane) {
+  const int r0 = row0 < s_q ? row0 : s_q - 1;
+#pragma unroll
+  for (int n = 0; n < WaveDma<D, 32>::PASSES; ++n)
+    WaveDma<D, 32>::copy_pass(lds, uniform_ptr(base + (int64_t)r0 * stride_s), (uint32_t)stride_s * 2, s_q - r0, lane, n);
+}
+template <int D>
+SP_DEV void read_rows(unsigned lds, int lane, bf16x8 (&reg)[D / 16]) {
+  RpBase<D> lo;
+  lo.init(lane, (int)lds);
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) reg[ks] = lds_rp<D>(lo, ks, 0);
+  // (in registers before the barrier that follows: tiles may be copied there behind it)
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+v"(reg[ks]));
+}
+
+// A wave's 32 rows of `out` (row r of the wave at `base` + r * stride_s elements, `rows` of them exist, possibly none or less), held a
+// row a lane in C layout: register i of block db is head_dim 32 db + 8*(i/4) + 4g + i%4.  16 bytes of 64 different rows a store are a lane
+// a clock for the address unit, so the rows go through LDS (`part`: kOutRow<D> * 32 floats of the wave's own) and leave as whole rows.
+template <int D>
+constexpr int kOutRow = D + 4;      // floats per row: padded against bank conflicts
+template <int D>
+SP_DEV void store_rows(float* part, const f32x16 (&acc)[D / 32], float factor, void* out, bool f32, bool accumulate, int64_t base, int64_t stride_s,
+                       int rows, int lane) {
+  constexpr int ROW = kOutRow<D>;
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const f32x4 v = {acc[db][4 * i4] * factor, acc[db][4 * i4 + 1] * factor, acc[db][4 * i4 + 2] * factor, acc[db][4 * i4 + 3] * factor};
+      *reinterpret_cast<f32x4*>(part + (lane & 31) * ROW + 32 * db + 8 * i4 + 4 * (lane >> 5)) = v;
+    }
+  // (a wave's LDS instructions are carried out in order: what is left to rule out is that the compiler swaps them)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (f32) {
+    constexpr int PER = D / 4, RPP = 64 / PER;           // lanes per row, rows per instruction
+    const int row = lane / PER, d = lane % PER * 4;
+    float* dst = reinterpret_cast<float*>(out) + base + (int64_t)row * stride_s + d;
+    f32x4 old[32 / RPP];                                 // all asked for before the first is needed (a store may alias the next load)
+    if (accumulate) {
+#pragma unroll
+      for (int j = 0; j < 32 / RPP; ++j)
+        if (row + j * RPP < rows) old[j] = *reinterpret_cast<const f32x4*>(dst + (int64_t)j * RPP * stride_s);
+    }
+#pragma unroll
+    for (int j = 0; j < 32 / RPP; ++j)
+      if (row + j * RPP < rows) {
+        f32x4 v = *reinterpret_cast<const f32x4*>(part + (row + j * RPP) * ROW + d);
+        if (accumulate) v += old[j];
+        *reinterpret_cast<f32x4*>(dst + (int64_t)j * RPP * stride_s) = v;
+      }
+  } else {
+    constexpr int PER = D / 8, RPP = 64 / PER;
+    const int row = lane / PER, d = lane % PER * 8;
+    bf16_t* dst = reinterpret_cast<bf16_t*>(out) + base + (int64_t)row * stride_s + d;
+#pragma unroll
+    for (int j = 0; j < 32 / RPP; ++j, dst += RPP * stride_s) {
+      const float* src = part + (row + j * RPP) * ROW + d;
+      const bf16x4 lo = __builtin_convertvector(*reinterpret_cast<const f32x4*>(src), bf16x4);
+      const bf16x4 hi = __builtin_convertvector(*reinterpret_cast<const f32x4*>(src + 4), bf16x4);
+      if (row + j * RPP < rows) *reinterpret_cast<bf16x8*>(dst) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  }
+}
+
 // One past the last row that any wave of a query block holds (a block that reaches the end of a head: s_q).
 SP_DEV int block_row_end(int qblk, int s_q, int head_waves) {
   const unsigned per = (unsigned)head_waves, slot = (unsigned)qblk * 8u;
