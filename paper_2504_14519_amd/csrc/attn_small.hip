@@ -3,10 +3,12 @@
 // What bounds a small call is a chain: a 256-row block walks its keys tile after tile behind barriers on a chip that is mostly idle, and
 // key ranges shorten the chain only at the price of a merge launch.  Here eight waves walk eight tiles of the keys at the same time,
 // each with a K and a V tile of its own in LDS, copied by itself and waited for by itself (no barrier in the loop), and their
-// partial results meet in LDS.  512 rows on 2048 keys, 4 heads of 64 (64 workgroups): 18.1 -> 11.9 us; 512 rows of 8 heads of 128 on one
-// K/V head, 2048 keys: 34.6 -> 19.1; 1024 rows: 35.5 -> 19.8.  A wave's step (32 keys, 64 at head_dim 64) takes 1.3 us, most of it
-// latency of the copies: one K and one V tile per wave are all of LDS, so K of the next step is copied during softmax and P V, V
-// during the scores and the softmax.  Which calls come here: fwd_plan_within in api.hip.
+// partial results meet in LDS.  512 rows on 2048 keys, 4 heads of 64 (64 workgroups): 18.1 -> 11.2 us; 512 rows of 8 heads of 128 on one
+// K/V head, 2048 keys: 34.6 -> 16.9.  A wave's step (32 keys, 64 at head_dim 64) takes 1.3 us, 1 of which is the compute unit's path to
+// memory: eight K and V tiles are 128 KB at 64 bytes a clock.  One K and one V tile per wave are all of LDS, so K of the next step is
+// copied during softmax and P V, V during the scores and the softmax; what a wave does not need it does not ask for (a last tile copied
+// once more, and Q by loads that the compiler waits for together with every copy: 11.9 and 18.1 us).  Touching the lines of later
+// tiles ahead of their copies makes it slower (12.5), the path being what is short.  Which calls come here: fwd_plan_within in api.hip.
 // A wave's probabilities are rounded to bf16 relative to the maximum of the wave's own keys, so the roundings of P V fall elsewhere than in
 // the 256-row blocks (2.5e-3 of the result in the 2-norm).  There are as many bits; the error against 64 bits is smaller: float32 out,
 // 512 rows on 512 keys of 64, 1.12e-3 (blocks 1.17e-3), 280 rows on 1486 keys of 128, 1.32e-3 (1.52e-3), at scores of 4 times the size 2.4e-4 (5.1e-4).
@@ -21,7 +23,8 @@ struct FwdSmall {
   static constexpr int TILE_BYTES = BN * D * 2, WAVE_BYTES = 2 * TILE_BYTES;
   static constexpr int ROW = D + 4;                      // floats per row of a wave's partial output (padded against bank conflicts)
   static constexpr int PART_BYTES = 32 * ROW * 4, STAT_BASE = NW * PART_BYTES, COMBINE_BYTES = STAT_BASE + NW * 64 * 4;
-  static constexpr int LDS = NW * WAVE_BYTES > COMBINE_BYTES ? NW * WAVE_BYTES : COMBINE_BYTES;
+  static constexpr int Q_BASE = NW * WAVE_BYTES, TILES_END = Q_BASE + 32 * D * 2;      // the query rows, behind the tiles
+  static constexpr int LDS = TILES_END > COMBINE_BYTES ? TILES_END : COMBINE_BYTES;
 };
 
 template <int D>
@@ -37,7 +40,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   const int b = __builtin_amdgcn_readfirstlane(bz / a.n_ranges), range = bz - b * a.n_ranges;
   const int rb = __builtin_amdgcn_readfirstlane(hb / a.n_q_heads), h = hb - rb * a.n_q_heads;
   const int row0 = (row_blocks - 1 - rb) * 32, hk = h / a.group;
-  const int myrow = row0 + ql, myrow_c = myrow < a.s_q ? myrow : a.s_q - 1;
+  const int myrow = row0 + ql;
   const int64_t kv_begin = a.range_begin[range], kv_end = a.range_end[range];
   int64_t hi = kv_end;
   if (a.causal) {
@@ -49,12 +52,6 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   const int before = (int)(kv_begin - lo);               // rows of tile 0 before the range
   const float c = a.scale_log2e;
 
-  bf16x8 q[KS];
-  {
-    const bf16_t* qp = a.q + (int64_t)b * a.q_stride_b + (int64_t)myrow_c * a.q_stride_s + (int64_t)h * a.q_stride_h;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) q[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * g);
-  }
   f32x16 o[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -80,19 +77,30 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
     dma.copy(k ? k_lds : v_lds, base, row_bytes, first, left < BN ? (int)left : BN, lane);
   };
   constexpr int PASSES = WaveDma<D, BN>::PASSES;
+  // The query rows, one copy instruction per wave (as far as there are any).  Not by ordinary loads: the compiler counts those alone, so
+  // that in front of the first use of Q, in the loop, it would wait for every copy that is under way.
+  if (wave_u < WaveDma<D, 32>::PASSES) {
+    const bf16_t* qbase = uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)row0 * a.q_stride_s + (int64_t)h * a.q_stride_h);
+    WaveDma<D, 32>::copy_pass(smem_lds + F::Q_BASE, qbase, (uint32_t)a.q_stride_s * 2, a.s_q - row0, lane, wave_u);
+  }
   int t = wave_u;                                        // tiles w, w + 8, w + 16, .. are this wave's
   if (t < nt) {
     const int first = t == 0 ? before : 0;
     copy(true, t, first);
     copy(false, t, first);
+    wait_copies<2 * PASSES>();
+  } else {
+    wait_async();
   }
+  __syncthreads();                                       // the query rows have landed
+  RpBase<D> lo_q;
+  lo_q.init(lane, (int)smem_lds + F::Q_BASE);
+  bf16x8 q[KS];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) q[ks] = lds_rp<D>(lo_q, ks, 0);
   for (; t < nt; t += NW) {
-    const int tn = t + NW < nt ? t + NW : t;             // (past the end the last tile is copied again)
-    // K has landed (the copies of V may still be under way)
-    SP_FENCE();
-    __builtin_amdgcn_s_waitcnt(0x0F70 | PASSES);
-    asm volatile("" ::: "memory");
-    SP_FENCE();
+    const int tn = t + NW;
+    wait_copies<PASSES>();                               // K has landed (the copies of V may still be under way)
     f32x16 s[KB];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
@@ -103,7 +111,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
       }
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(s[kb]));      // the reads of K are done before K is copied over
-    copy(true, tn, 0);
+    if (tn < nt) copy(true, tn, 0);
     const int64_t key0 = lo + (int64_t)t * BN;
     if (key0 < kv_begin || key0 + BN > kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
       const int64_t kmin = kv_begin - key0;
@@ -150,19 +158,16 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
       p[kb][1] = pack8(s[kb], 8);
     }
     // V has landed (the copies of the next K may still be under way)
-    SP_FENCE();
-    __builtin_amdgcn_s_waitcnt(0x0F70 | PASSES);
-    asm volatile("" ::: "memory");
-    SP_FENCE();
+    if (tn < nt) wait_copies<PASSES>();
+    else wait_copies<0>();
 #pragma unroll
     for (int blk = 0; blk < 2 * KB; ++blk)
 #pragma unroll
       for (int db = 0; db < DB; ++db) o[db] = mfma32(lds_tr<D>(lo_v, db, blk * 16 * D * 2), p[blk / 2][blk % 2], o[db]);
 #pragma unroll
     for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(o[db]));      // the reads of V are done before V is copied over
-    copy(false, tn, 0);
+    if (tn < nt) copy(false, tn, 0);
   }
-  wait_async();
   __syncthreads();                                       // nobody reads or copies a tile any more
   // the eight partial results meet in LDS: out = sum of exp2(m_w - m) o_w over sum of exp2(m_w - m) l_w
   float* const part = reinterpret_cast<float*>(smem) + wave_u * (F::PART_BYTES / 4);
@@ -332,11 +337,8 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
     copy(false, t, first);
   }
   for (; t < nt; t += NW) {
-    const int tn = t + NW < nt ? t + NW : t;             // (past the end the last tile is copied again)
-    SP_FENCE();
-    wait_async();
-    asm volatile("" ::: "memory");
-    SP_FENCE();
+    const int tn = t + NW;
+    wait_copies<0>();
     f32x16 s[KB], dp[KB];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
@@ -355,7 +357,7 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
       for (int kb = 0; kb < KB; ++kb) dp[kb] = mfma32(lds_rp<D>(lo_v, ks, kb * 32 * D * 2), dO[ks], dp[kb]);
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) asm volatile("" : "+v"(dp[kb]));      // the reads of V are done before V is copied over
-    copy(false, tn, 0);
+    if (tn < nt) copy(false, tn, 0);
     const int64_t key0 = lo + (int64_t)t * BN;
     if (key0 < a.kv_begin || key0 + BN > kv_end || (a.causal && key0 + BN - 1 > a.q_offset + row0)) {
       const int64_t kmin = a.kv_begin - key0;
@@ -389,9 +391,8 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
       for (int db = 0; db < DB; ++db) dq[db] = mfma32(lds_tr<D>(lo_kt, db, blk * 16 * D * 2), ds[blk / 2][blk % 2], dq[db]);
 #pragma unroll
     for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(dq[db]));      // the reads of K are done before K is copied over
-    copy(true, tn, 0);
+    if (tn < nt) copy(true, tn, 0);
   }
-  wait_async();
   __syncthreads();                                       // nobody reads or copies a tile any more
   put_part<D>(smem + wave_u * S::PART_BYTES, dq, a.scale, ql, g);
   __syncthreads();
