@@ -229,10 +229,11 @@ hipError_t launch_fwd_small(const FwdArgs& a, int batch, int head_dim, hipStream
 }
 
 // ------------------------------------------------------------------------------------ backward
-// The same idea for both gradients, in one launch behind the delta kernel: a workgroup owns 32 query rows (dq) or 32 keys
+// The same idea for both gradients, in one launch: a workgroup owns 32 query rows (dq) or 32 keys
 // (dk/dv) and its eight waves share out the keys, or the query tiles of all heads of the group, each with tiles of its own; the
 // eight partial sums meet in LDS and are added up in wave order (bit-reproducible).  No partial sums in memory, no reduce launch.
-// 512 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.9 us for the call.  A step of dk/dv (32 query rows of a wave) takes 1 us at
+// 512 rows on 2048 keys, 4 heads of 64: 30.2 -> 16.6 us for the call (17.2 with rows of Q, dO and K loaded by every wave, a row a lane, and
+// a delta kernel before it; 512 rows on 512 keys 13.3 -> 10.8).  A step of dk/dv (32 query rows of a wave) takes 1 us at
 // head_dim 64, where the tiles are double-buffered, and 2 us at 128, where one Q and one dO tile per wave are all of LDS and the
 // copy of the next waits for the sums of this one.  Which calls come here: bwd_small_plan in api.hip.
 template <int D>
@@ -241,11 +242,13 @@ struct BwdSmall {
   static constexpr int ROW = D + 4, PART_BYTES = 32 * ROW * 4;
   // dq: a K and a V tile of BN keys per wave
   static constexpr int BN = D == 64 ? 64 : 32, KB = BN / 32, KV_BYTES = BN * D * 2;
-  // dk/dv: BUF x (Q and dO tile of 32 rows, their statistics) per wave, and the V rows of the workgroup
+  // ... and the workgroup's rows of Q, dO and O
+  static constexpr int ROWS_BYTES = 32 * D * 2, Q_BASE = NW * 2 * KV_BYTES, DO_BASE = Q_BASE + ROWS_BYTES, O_BASE = DO_BASE + ROWS_BYTES;
+  // dk/dv: BUF x (Q and dO tile of 32 rows, their statistics) per wave, and the V and K rows of the workgroup
   static constexpr int BUF = D == 64 ? 2 : 1, TILE_BYTES = 32 * D * 2, SET_BYTES = 2 * TILE_BYTES + 256;
-  static constexpr int V_BASE = NW * BUF * SET_BYTES;
+  static constexpr int V_BASE = NW * BUF * SET_BYTES, K_BASE = V_BASE + TILE_BYTES;
   static constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
-  static constexpr int LDS = max3(NW * 2 * KV_BYTES, V_BASE + TILE_BYTES, NW * PART_BYTES);
+  static constexpr int LDS = max3(O_BASE + ROWS_BYTES, K_BASE + TILE_BYTES, NW * PART_BYTES);
 };
 
 // Element d0 .. d0 + D/16 - 1 of row r (16 threads a row) of the sum of the eight waves' partial results.
@@ -271,6 +274,25 @@ SP_DEV void put_part(char* part, const f32x16 (&acc)[D / 32], float factor, int 
     }
 }
 
+// c + a . b
+SP_DEV float dot8(bf16x8 a, bf16x8 b, float c) {
+#pragma unroll
+  for (int j = 0; j < 8; j += 2) c = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{a[j], a[j + 1]}, bf16x2{b[j], b[j + 1]}, c, false);
+  return c;
+}
+// Sum over aligned groups of N = 8 or 16 lanes, in all of them.
+template <int N>
+SP_DEV float row_sum(float x) {
+  static_assert(N == 8 || N == 16, "within a DPP row");
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0xB1, 0xF, 0xF, true));       // lane ^ 1
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x4E, 0xF, 0xF, true));       // lane ^ 2
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x141, 0xF, 0xF, true));      // the other quad of eight lanes
+  if constexpr (N == 16) x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xF, 0xF, true));      // the other half of 16
+  return x;
+}
+// lse in log2 units; +inf for a row that saw no key, so that its p are exp2(-inf) = 0
+SP_DEV float lse_log2(float l) { return l == -INFINITY ? INFINITY : l * kLog2e; }
+
 // index -> (query head, 32-row block of a head, batch index)
 template <int D>
 SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
@@ -295,30 +317,31 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const int before = (int)(a.kv_begin - lo);             // rows of tile 0 before the range
   const float c = a.scale_log2e;
 
-  bf16x8 q[KS], dO[KS];
-  {
-    const bf16_t* qp = a.q + (int64_t)b * a.q_stride_b + (int64_t)myrow_c * a.q_stride_s + (int64_t)h * a.q_stride_h;
-    const bf16_t* dp = a.d_out + (int64_t)b * a.do_stride_b + (int64_t)myrow_c * a.do_stride_s + (int64_t)h * a.do_stride_h;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      q[ks] = *reinterpret_cast<const bf16x8*>(qp + 16 * ks + 8 * g);
-      dO[ks] = *reinterpret_cast<const bf16x8*>(dp + 16 * ks + 8 * g);
-    }
+  const unsigned smem_lds = lds_addr(smem);
+  // The rows of Q, dO and O, one copy instruction of each per wave (as far as there are any): eight waves that each load their lane's row
+  // of them are 64 lines an instruction, a lane a clock.
+  if (wave_u < WaveDma<D, 32>::PASSES) {
+    const int rows = a.s_q - row0;
+    WaveDma<D, 32>::copy_pass(smem_lds + S::Q_BASE, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)row0 * a.q_stride_s + (int64_t)h * a.q_stride_h),
+                              (uint32_t)a.q_stride_s * 2, rows, lane, wave_u);
+    WaveDma<D, 32>::copy_pass(smem_lds + S::DO_BASE, uniform_ptr(a.d_out + (int64_t)b * a.do_stride_b + (int64_t)row0 * a.do_stride_s + (int64_t)h * a.do_stride_h),
+                              (uint32_t)a.do_stride_s * 2, rows, lane, wave_u);
+    WaveDma<D, 32>::copy_pass(smem_lds + S::O_BASE, uniform_ptr(a.out + (int64_t)b * a.o_stride_b + (int64_t)row0 * a.o_stride_s + (int64_t)h * a.o_stride_h),
+                              (uint32_t)a.o_stride_s * 2, rows, lane, wave_u);
   }
-  const int64_t stat = ((int64_t)b * a.n_q_heads + h) * a.s_q + myrow_c;
-  const float lse2 = a.lse2[stat], ndelta = a.delta[stat];      // (+inf for an empty row -> p = 0; delta is stored negated)
   f32x16 dq[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) dq[db][i] = 0.f;
 
-  const unsigned k_lds = lds_addr(smem) + wave_u * 2 * S::KV_BYTES, v_lds = k_lds + S::KV_BYTES;
+  const unsigned k_lds = smem_lds + wave_u * 2 * S::KV_BYTES, v_lds = k_lds + S::KV_BYTES;
   RpBase<D> lo_k, lo_v;
   TrBase<D> lo_kt;
   lo_k.init(lane, (int)k_lds);
   lo_v.init(lane, (int)v_lds);
   lo_kt.init(lane, (int)k_lds);
+  const float lse_raw = a.lse[((int64_t)b * a.n_q_heads + h) * a.s_q + myrow_c];
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
@@ -335,7 +358,25 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
     const int first = t == 0 ? before : 0;
     copy(true, t, first);
     copy(false, t, first);
+    wait_copies<2 * WaveDma<D, BN>::PASSES>();
+  } else {
+    wait_async();
   }
+  __syncthreads();                                       // the rows have landed
+  bf16x8 q[KS], dO[KS];
+  float ndelta = 0.f;                                    // -dO . O of the lane's row: the initial accumulator of dP
+  {
+    RpBase<D> lo_r;
+    lo_r.init(lane, (int)smem_lds + S::Q_BASE);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      q[ks] = lds_rp<D>(lo_r, ks, 0);
+      dO[ks] = lds_rp<D>(lo_r, ks, S::ROWS_BYTES);
+      ndelta = dot8(lds_rp<D>(lo_r, ks, 2 * S::ROWS_BYTES), dO[ks], ndelta);
+    }
+  }
+  ndelta = -xhalf_sum(ndelta);
+  const float lse2 = lse_log2(lse_raw);
   for (; t < nt; t += NW) {
     const int tn = t + NW;
     wait_copies<0>();
@@ -414,8 +455,9 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   }
 }
 
-// index -> (32-key block, kv head, batch index)
-template <int D>
+// index -> (32-key block, kv head, batch index).  OWN_STATS: the wave works out the statistics of a tile's rows itself; otherwise the
+// delta kernel has, and they are copied with the tile.
+template <int D, bool OWN_STATS>
 SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   using S = BwdSmall<D>;
   constexpr int NW = S::NW, KS = S::KS, DB = S::DB, BUF = S::BUF, TILE_BYTES = S::TILE_BYTES;
@@ -432,12 +474,6 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
   const float c = a.scale_log2e;
 
-  bf16x8 k[KS];
-  {
-    const bf16_t* kp = a.kv.k[chunk] + head_off + (chunk_row0 + (ql < left ? ql : left - 1)) * a.kv_stride_s;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks + 8 * g);
-  }
   f32x16 dk[DB], dv[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -445,8 +481,11 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     for (int i = 0; i < 16; ++i) { dk[db][i] = 0.f; dv[db][i] = 0.f; }
 
   const unsigned smem_lds = lds_addr(smem);
-  // V rows of the workgroup: one copy instruction per wave (as far as there are any)
+  // K and V rows of the workgroup: one copy instruction of each per wave (as far as there are any)
   {
+    const bf16_t* kbase = uniform_ptr(a.kv.k[chunk] + head_off + chunk_row0 * a.kv_stride_s);
+    if (wave_u < WaveDma<D, 32>::PASSES)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::K_BASE, kbase, (uint32_t)a.kv_stride_s * 2, left < 32 ? (int)left : 32, lane, wave_u);
     const bf16_t* vbase = uniform_ptr(a.kv.v[chunk] + head_off + chunk_row0 * a.kv_stride_s);
     // (rows that some row sees: dS of the others is P = 0 times dP, and what the cache holds there must not reach dP)
     const int64_t seen = a.seen_end - key0;
@@ -465,7 +504,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   WaveDma<D, 32> dma_q, dma_do;
   dma_q.init(lane, q_bytes);
   dma_do.init(lane, do_bytes);
-  // the two statistics are arrays of one workspace (far below 4 GB): one uniform base and a 32-bit lane offset
+  // the delta kernel's two statistics are arrays of one workspace (far below 4 GB): one uniform base and a 32-bit lane offset
   const int64_t stat_gap = a.delta - a.lse2;
   const float* const stat_base = stat_gap < 0 ? a.delta : a.lse2;
   const uint32_t off_lse2 = stat_gap < 0 ? (uint32_t)(-stat_gap) * 4u : 0u, off_delta = stat_gap < 0 ? 0u : (uint32_t)stat_gap * 4u;
@@ -475,20 +514,45 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32, h = hk * a.group + hh, rows = a.s_q - row0;
     const unsigned dst = set_lds + buf * S::SET_BYTES;
     if (with_q) {
+      if constexpr (!OWN_STATS) {
+        // lanes 0..31: lse2 of the rows, lanes 32..63: -delta (clamped to the slice)
+        const int rr = ql < rows ? ql : rows - 1;
+        dma4(uniform_ptr(stat_base + ((int64_t)b * a.n_q_heads + h) * a.s_q + row0), (g ? off_delta : off_lse2) + (uint32_t)rr * 4u,
+             __builtin_amdgcn_readfirstlane(dst + 2 * TILE_BYTES));
+      }
       dma_q.copy(dst, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)h * a.q_stride_h + (int64_t)row0 * a.q_stride_s), q_bytes, 0, rows < 32 ? rows : 32, lane);
-      // lanes 0..31: lse2 of the rows, lanes 32..63: -delta (clamped to the slice)
-      const int rr = ql < rows ? ql : rows - 1;
-      dma4(uniform_ptr(stat_base + ((int64_t)b * a.n_q_heads + h) * a.s_q + row0), (g ? off_delta : off_lse2) + (uint32_t)rr * 4u,
-           __builtin_amdgcn_readfirstlane(dst + 2 * TILE_BYTES));
     }
     if (with_do)
       dma_do.copy(dst + TILE_BYTES, uniform_ptr(a.d_out + (int64_t)b * a.do_stride_b + (int64_t)h * a.do_stride_h + (int64_t)row0 * a.do_stride_s), do_bytes,
                   0, rows < 32 ? rows : 32, lane);
   };
+  // For the row statistics of a tile, asked for a step ahead: lse of row ql, and the 16 bytes of O that sit where lane and pass are in the
+  // copy of the dO tile (8 or 16 lanes a row; a row a lane would be 64 lines an instruction)
+  constexpr int NP = WaveDma<D, 32>::PASSES, NC = WaveDma<D, 32>::NC;
+  const uint32_t o_bytes = (uint32_t)a.o_stride_s * 2;
+  bf16x8 o_part[NP];
+  float lse_row = 0.f;
+  auto fetch_rows = [&](int j) {
+    const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32, h = hk * a.group + hh, rows = a.s_q - row0;
+    const char* op = reinterpret_cast<const char*>(uniform_ptr(a.out + (int64_t)b * a.o_stride_b + (int64_t)row0 * a.o_stride_s + (int64_t)h * a.o_stride_h));
+#pragma unroll
+    for (int n = 0; n < NP; ++n) o_part[n] = *reinterpret_cast<const bf16x8*>(op + WaveDma<D, 32>::pass_off(lane, n, o_bytes, rows));
+    lse_row = a.lse[((int64_t)b * a.n_q_heads + h) * a.s_q + row0 + (ql < rows ? ql : rows - 1)];
+  };
   int j = wave_u;
-  if (j < total) copy_tile(j, 0, true, true);
+  if (j < total) {
+    copy_tile(j, 0, true, true);
+    if constexpr (OWN_STATS) fetch_rows(j);
+  }
   wait_async();
-  __syncthreads();                                       // V has landed
+  __syncthreads();                                       // K and V have landed
+  bf16x8 k[KS];
+  {
+    RpBase<D> lo_k;
+    lo_k.init(lane, (int)smem_lds + S::K_BASE);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) k[ks] = lds_rp<D>(lo_k, ks, 0);
+  }
   RpBase<D> lo_q, lo_v;
   TrBase<D> lo_qt;
   lo_q.init(lane, (int)set_lds);
@@ -498,16 +562,32 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   for (; j < total; j += NW) {
     const int jn = j + NW;
     const int hh = head_of(j), row0 = (qt0 + j - hh * nv) * 32;
-    if constexpr (BUF == 2) {
-      if (jn < total) copy_tile(jn, buf ^ 1, true, true);
-      SP_FENCE();
-    }
     const int o = buf * S::SET_BYTES;
     RpBase<D> lq = lo_q;
     TrBase<D> lqt = lo_qt;
     lq.add(o);
     lqt.add(o);
-    const float* stat = reinterpret_cast<const float*>(smem + (set_lds - smem_lds) + o + 2 * TILE_BYTES) + 4 * g;
+    // statistics of the tile's rows: lse in log2 units, then -dO . O; through LDS to where the scores need them
+    float* const stats = reinterpret_cast<float*>(smem + (set_lds - smem_lds) + o + 2 * TILE_BYTES);
+    if constexpr (OWN_STATS) {
+      const char* dO = smem + (set_lds - smem_lds) + o + TILE_BYTES + lane * 16;
+      if (g == 0) stats[ql] = lse_log2(lse_row);
+#pragma unroll
+      for (int n = 0; n < NP; ++n) {
+        const float d = row_sum<NC>(dot8(*reinterpret_cast<const bf16x8*>(dO + n * 1024), o_part[n], 0.f));
+        if (lane % NC == 0) stats[32 + lane / NC + 64 / NC * n] = -d;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    const float* stat = stats + 4 * g;
+    if constexpr (BUF == 2) {
+      if (jn < total) {
+        copy_tile(jn, buf ^ 1, true, true);
+        if constexpr (OWN_STATS) fetch_rows(jn);
+      }
+      SP_FENCE();
+    }
     f32x16 s, dp;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -591,20 +671,21 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
 }
 
 // dq and dk/dv items, the kind that takes longer first.
-template <int D>
+template <int D, bool OWN_STATS>
 __global__ __launch_bounds__(512) void attn_bwd_small_kernel(const BwdArgs a, int n_dq, int n_dkdv) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
   if ((i < first) == (a.dq_first != 0)) dq_small_item<D>(a, a.dq_first ? i : i - n_dkdv, smem);
-  else dkdv_small_item<D>(a, a.dq_first ? i - n_dq : i, smem);
+  else dkdv_small_item<D, OWN_STATS>(a, a.dq_first ? i - n_dq : i, smem);
 }
 
-hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, hipStream_t st) {
+hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, bool own_stats, hipStream_t st) {
   const int64_t n_dq = ((int64_t)a.s_q + 31) / 32 * a.n_q_heads * batch;
   const int64_t n_dkdv = (a.kv_end - kv_grid_origin(a.kv_begin, a.kv.n, 32) + 31) / 32 * a.n_kv_heads * batch;
   const dim3 grid((unsigned)(n_dq + n_dkdv)), block(512);
-  if (head_dim == 128) hipLaunchKernelGGL(attn_bwd_small_kernel<128>, grid, block, BwdSmall<128>::LDS, st, a, (int)n_dq, (int)n_dkdv);
-  else hipLaunchKernelGGL(attn_bwd_small_kernel<64>, grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  if (head_dim == 128) hipLaunchKernelGGL((attn_bwd_small_kernel<128, false>), grid, block, BwdSmall<128>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  else if (own_stats) hipLaunchKernelGGL((attn_bwd_small_kernel<64, true>), grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  else hipLaunchKernelGGL((attn_bwd_small_kernel<64, false>), grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
   return hipGetLastError();
 }
 
@@ -614,8 +695,9 @@ hipError_t opt_in_small_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<128>), attr, FwdSmall<128>::LDS);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<64>), attr, FwdSmall<64>::LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<128>), attr, BwdSmall<128>::LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<128, false>), attr, BwdSmall<128>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, true>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, false>), attr, BwdSmall<64>::LDS);
   return e;
 }
 
