@@ -387,13 +387,17 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // The line at 32 dq items is no line of speed: below it the small kernel wins too (252 calls of 1 to 32 items: 1.54 times as fast in the mean,
 // 0.90 at worst), but the launches of a call of 32 items are what the per-kernel timing is pinned to, kind by kind.  With 33 to 63 items (48
 // calls) it is 1.61 times as fast in the mean, 0.95 at worst (480 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.5 us).
+// key_blocks: at head_dim 64 a dk/dv item can own two blocks of 32 keys, four waves each: half the items, of twice the steps.  That pays where it
+// spares a round of the compute units, by the makespans of 6.5 us + 1 a step and 7.5 + 1.1 a step.  One / two blocks: 512 rows on 2048 keys,
+// 4/4 heads (64 dq items and 256 or 128) 16.6 / 13.4 us, 1024 on 2048 22.1 / 19.2, 256 on 1256, 16/16 heads, 21.6 / 19.2; but 512 on
+// 1536, 4/4 (256 items or 160, one round either way) 11.0 / 13.2, 300 on 2300, 8/2 heads, 14.7 / 21.5.  Over 13 shapes the pick is the faster one.
 // own_stats: the dk/dv items work out the row statistics of their query tiles, and no delta kernel runs before.  That saves its launch, 3 us and
 // the host's 4, and costs each step of a wave 0.4 us (O comes along with Q and dO): calls of up to 6 steps of head_dim 64.  With / without,
 // steps: 512 rows on 2048 keys, 4/4 heads, 2 steps, 16.6 / 17.6 us; 500 on 1200, 12/4 heads, 6 steps, 18.1 / 19.6; 777 on 777, 12/4, 9.4
 // steps, 22.5 / 20.9; 1024 on 1024, 8/1, 32 steps, 57.7 / 43.8.  At head_dim 128 a step pays 1 us (256 rows on 512 keys, 8/1 heads, 8 steps, 30.9 / 24.9).
-struct BwdSmallPlan { bool use, dq_first, own_stats; };
+struct BwdSmallPlan { bool use, dq_first, own_stats; int key_blocks; };
 BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) {
-  if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false, false};
+  if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false, false, 1};
   const bool d64 = p->head_dim == 64;
   const int64_t keys = p->kv_end - p->kv_begin, cus = compute_units();
   const int64_t row_blocks = ((int64_t)p->s_q + 31) / 32, key_blocks = (keys + 31) / 32;
@@ -403,9 +407,13 @@ BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) 
   const double sq = (double)keys / (d64 ? 512 : 256), sk = (double)(row_blocks * (p->n_q_heads / p->n_kv_heads)) / 8;
   const double tq = (d64 ? 5 : 6) + (d64 ? 1.4 : 1.6) * (nq > cus ? sq * seen + 0.5 : ceil(sq));
   const double tk = (d64 ? 5 : 6) + (d64 ? 1.0 : 2.0) * (nk > cus ? sk * seen + 0.5 : ceil(sk));
-  const double us = (d64 ? 5.5 : 4) + (tq > tk ? list_makespan(cus, nq, tq, nk, tk) : list_makespan(cus, nk, tk, nq, tq));
+  auto makespan = [&](int64_t n, double t) { return tq > t ? list_makespan(cus, nq, tq, n, t) : list_makespan(cus, n, t, nq, tq); };
+  const double us = (d64 ? 5.5 : 4) + makespan(nk, tk);
   const bool use = nq > 32 && us < 60 && us * 1.05 < plan.us + 7;
-  return {use, tq > tk, use && d64 && sk <= 6};
+  const int64_t nk2 = (key_blocks + 1) / 2 * p->n_kv_heads * p->batch;
+  const double tk2 = 7.5 + 1.1 * (nk2 > cus ? 2 * sk * seen + 0.5 : ceil(2 * sk));
+  const bool two = d64 && makespan(nk2, tk2) < 0.95 * makespan(nk, tk + 1.5);
+  return {use, tq > (two ? tk2 : tk), use && d64 && sk * (two ? 2 : 1) <= 6, two ? 2 : 1};
 }
 // Tiles of the large backward at head_dim 64: 128 or 64 keys (dq), 64 or 32 query rows (dk/dv).  The larger ones have half the
 // barriers and copies per pair; a short walk pays for them in its first and last tile, which nothing hides, and in padding.
@@ -847,7 +855,7 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
     return SLIMPIPE_ELAUNCH;
   if (sm.use) {
     a.dq_first = sm.dq_first;
-    return timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_small(a, p->batch, p->head_dim, sm.own_stats, st); }, events) == hipSuccess
+    return timed(SLIMPIPE_KERNEL_BWD_BOTH, st, [&] { return launch_bwd_small(a, p->batch, p->head_dim, sm.own_stats, sm.key_blocks, st); }, events) == hipSuccess
                ? SLIMPIPE_OK : SLIMPIPE_ELAUNCH;
   }
   if (plan.both) {

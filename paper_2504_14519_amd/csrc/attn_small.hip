@@ -246,21 +246,23 @@ struct BwdSmall {
   static constexpr int ROWS_BYTES = 32 * D * 2, Q_BASE = NW * 2 * KV_BYTES, DO_BASE = Q_BASE + ROWS_BYTES, O_BASE = DO_BASE + ROWS_BYTES;
   // dk/dv: BUF x (Q and dO tile of 32 rows, their statistics) per wave, and the V and K rows of the workgroup
   static constexpr int BUF = D == 64 ? 2 : 1, TILE_BYTES = 32 * D * 2, SET_BYTES = 2 * TILE_BYTES + 256;
-  static constexpr int V_BASE = NW * BUF * SET_BYTES, K_BASE = V_BASE + TILE_BYTES;
+  static constexpr int MAX_BLOCKS = D == 64 ? 2 : 1;      // of 32 keys a workgroup can own
+  static constexpr int V_BASE = NW * BUF * SET_BYTES, K_BASE = V_BASE + MAX_BLOCKS * TILE_BYTES;
   static constexpr int max3(int a, int b, int c) { return a > b ? (a > c ? a : c) : (b > c ? b : c); }
-  static constexpr int LDS = max3(O_BASE + ROWS_BYTES, K_BASE + TILE_BYTES, NW * PART_BYTES);
+  static constexpr int LDS = max3(O_BASE + ROWS_BYTES, K_BASE + MAX_BLOCKS * TILE_BYTES, NW * PART_BYTES);
+  static constexpr int GRADS = 2 * NW * PART_BYTES <= LDS ? 2 : 1;      // of dk and dv, whose partial sums fit LDS at a time
 };
 
-// Element d0 .. d0 + D/16 - 1 of row r (16 threads a row) of the sum of the eight waves' partial results.
-template <int D>
-SP_DEV void sum_parts(const char* smem, int r, int d0, f32x4 (&sum)[D / 64]) {
+// Elements d0 .. d0 + 4 * N - 1 of row r of the sum of WAVES waves' partial results, the first at `parts`.
+template <int D, int WAVES, int N>
+SP_DEV void sum_parts(const char* parts, int r, int d0, f32x4 (&sum)[N]) {
   using S = BwdSmall<D>;
 #pragma unroll
-  for (int j = 0; j < D / 64; ++j) sum[j] = *reinterpret_cast<const f32x4*>(smem + (r * S::ROW + d0 + 4 * j) * 4);
+  for (int j = 0; j < N; ++j) sum[j] = *reinterpret_cast<const f32x4*>(parts + (r * S::ROW + d0 + 4 * j) * 4);
 #pragma unroll
-  for (int w = 1; w < S::NW; ++w)
+  for (int w = 1; w < WAVES; ++w)
 #pragma unroll
-    for (int j = 0; j < D / 64; ++j) sum[j] += *reinterpret_cast<const f32x4*>(smem + w * S::PART_BYTES + (r * S::ROW + d0 + 4 * j) * 4);
+    for (int j = 0; j < N; ++j) sum[j] += *reinterpret_cast<const f32x4*>(parts + w * S::PART_BYTES + (r * S::ROW + d0 + 4 * j) * 4);
 }
 // A wave's accumulators (lane = column of the C layout, registers = head_dim) into its partial result, `factor` times.
 template <int D>
@@ -440,7 +442,7 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const int r = tid >> 4, d0 = (tid & 15) * (D / 16), row = row0 + r;
   if (row < a.s_q) {
     f32x4 sum[D / 64];
-    sum_parts<D>(smem, r, d0, sum);
+    sum_parts<D, NW>(smem, r, d0, sum);
     const int64_t base = (int64_t)b * a.q_stride_b + (int64_t)row * a.q_stride_s + (int64_t)h * a.q_stride_h + d0;
 #pragma unroll
     for (int j = 0; j < D / 64; ++j) {
@@ -455,20 +457,25 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   }
 }
 
-// index -> (32-key block, kv head, batch index).  OWN_STATS: the wave works out the statistics of a tile's rows itself; otherwise the
-// delta kernel has, and they are copied with the tile.
-template <int D, bool OWN_STATS>
+// index -> (BLOCKS blocks of 32 keys, kv head, batch index).  With two blocks four of the waves belong to each and walk its query tiles.
+// OWN_STATS: the wave works out the statistics of a tile's rows itself; otherwise the delta kernel has, and they are copied with the tile.
+template <int D, bool OWN_STATS, int BLOCKS>
 SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   using S = BwdSmall<D>;
-  constexpr int NW = S::NW, KS = S::KS, DB = S::DB, BUF = S::BUF, TILE_BYTES = S::TILE_BYTES;
+  constexpr int NW = S::NW / BLOCKS, KS = S::KS, DB = S::DB, BUF = S::BUF, TILE_BYTES = S::TILE_BYTES;      // NW: waves of a key block
+  static_assert(BLOCKS <= S::MAX_BLOCKS && WaveDma<D, 32>::PASSES <= NW, "");
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
   item = __builtin_amdgcn_readfirstlane(item);
   const int64_t grid0 = kv_grid_origin(a.kv_begin, a.kv.n, 32);
-  const int key_blocks = (int)((a.kv_end - grid0 + 31) / 32), per_b = key_blocks * a.n_kv_heads;
+  const int key_blocks = (int)((a.kv_end - grid0 + 32 * BLOCKS - 1) / (32 * BLOCKS)), per_b = key_blocks * a.n_kv_heads;
   const int b = __builtin_amdgcn_readfirstlane(item / per_b), hb = item - b * per_b;
   const int hk = __builtin_amdgcn_readfirstlane(hb / key_blocks), kblk = hb - hk * key_blocks;
-  const int64_t key0 = grid0 + (int64_t)kblk * 32, mykey = key0 + ql;
+  const int block = wave_u / NW, wave_b = wave_u % NW;   // the wave's key block and its number among the waves of that
+  int64_t key0 = grid0 + (int64_t)(kblk * BLOCKS + block) * 32;
+  const bool exists = BLOCKS == 1 || key0 < a.kv_end;    // (a last, second block may lie behind the range: its waves copy and store nothing)
+  if (!exists) key0 -= 32;
+  const int64_t mykey = key0 + ql;
   const int chunk = kv_chunk_of(a.kv, key0);
   const int64_t chunk_row0 = key0 - (int64_t)chunk * a.kv.len, left = a.kv_end - key0;      // (>= 1)
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
@@ -484,22 +491,22 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   // K and V rows of the workgroup: one copy instruction of each per wave (as far as there are any)
   {
     const bf16_t* kbase = uniform_ptr(a.kv.k[chunk] + head_off + chunk_row0 * a.kv_stride_s);
-    if (wave_u < WaveDma<D, 32>::PASSES)
-      WaveDma<D, 32>::copy_pass(smem_lds + S::K_BASE, kbase, (uint32_t)a.kv_stride_s * 2, left < 32 ? (int)left : 32, lane, wave_u);
+    if (wave_b < WaveDma<D, 32>::PASSES)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::K_BASE + block * TILE_BYTES, kbase, (uint32_t)a.kv_stride_s * 2, left < 32 ? (int)left : 32, lane, wave_b);
     const bf16_t* vbase = uniform_ptr(a.kv.v[chunk] + head_off + chunk_row0 * a.kv_stride_s);
     // (rows that some row sees: dS of the others is P = 0 times dP, and what the cache holds there must not reach dP)
     const int64_t seen = a.seen_end - key0;
-    if (wave_u < WaveDma<D, 32>::PASSES && seen > 0)
-      WaveDma<D, 32>::copy_pass(smem_lds + S::V_BASE, vbase, (uint32_t)a.kv_stride_s * 2, seen < 32 ? (int)seen : 32, lane, wave_u);
+    if (wave_b < WaveDma<D, 32>::PASSES && seen > 0)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::V_BASE + block * TILE_BYTES, vbase, (uint32_t)a.kv_stride_s * 2, seen < 32 ? (int)seen : 32, lane, wave_b);
   }
-  // query tiles that see the block: [qt0, nqt) of every head of the group, tile j of this list for wave j mod 8
+  // query tiles that see the block: [qt0, nqt) of every head of the group, tile j of this list for wave j mod NW of the block
   const int nqt = (int)(((int64_t)a.s_q + 31) / 32);
   int qt0 = 0;
   if (a.causal && key0 > a.q_offset) {
     const int64_t first = key0 - a.q_offset;
     qt0 = first >= a.s_q ? nqt : (int)(first / 32);
   }
-  const int nv = nqt - qt0, total = nv * a.group;
+  const int nv = nqt - qt0, total = exists ? nv * a.group : 0;
   const uint32_t q_bytes = (uint32_t)a.q_stride_s * 2, do_bytes = (uint32_t)a.do_stride_s * 2;
   WaveDma<D, 32> dma_q, dma_do;
   dma_q.init(lane, q_bytes);
@@ -539,7 +546,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     for (int n = 0; n < NP; ++n) o_part[n] = *reinterpret_cast<const bf16x8*>(op + WaveDma<D, 32>::pass_off(lane, n, o_bytes, rows));
     lse_row = a.lse[((int64_t)b * a.n_q_heads + h) * a.s_q + row0 + (ql < rows ? ql : rows - 1)];
   };
-  int j = wave_u;
+  int j = wave_b;
   if (j < total) {
     copy_tile(j, 0, true, true);
     if constexpr (OWN_STATS) fetch_rows(j);
@@ -549,7 +556,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   bf16x8 k[KS];
   {
     RpBase<D> lo_k;
-    lo_k.init(lane, (int)smem_lds + S::K_BASE);
+    lo_k.init(lane, (int)smem_lds + S::K_BASE + block * TILE_BYTES);
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) k[ks] = lds_rp<D>(lo_k, ks, 0);
   }
@@ -557,7 +564,7 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
   TrBase<D> lo_qt;
   lo_q.init(lane, (int)set_lds);
   lo_qt.init(lane, (int)set_lds);
-  lo_v.init(lane, (int)smem_lds + S::V_BASE);
+  lo_v.init(lane, (int)smem_lds + S::V_BASE + block * TILE_BYTES);
   int buf = 0;
   for (; j < total; j += NW) {
     const int jn = j + NW;
@@ -648,45 +655,63 @@ SP_DEV void dkdv_small_item(const BwdArgs& a, int item, char* smem) {
     if constexpr (BUF == 2) buf ^= 1;
   }
   wait_async();
-  const int r = tid >> 4, d0 = (tid & 15) * (D / 16);
+  // the waves' sums meet in LDS and are added up in wave order, 16 / BLOCKS threads a row; what the accumulators hold is asked for before
+  constexpr int PER = D * BLOCKS / 16, N4 = PER / 4;     // head_dim elements of a thread
+  const int tb = tid & (NW * 64 - 1), r = tb / (16 / BLOCKS), d0 = tb % (16 / BLOCKS) * PER;
   const int64_t key = key0 + r;
-  const bool mine = key >= a.kv_begin && key < a.kv_end;
+  const bool mine = exists && key >= a.kv_begin && key < a.kv_end;
+  const int64_t dst_off = head_off + (chunk_row0 + r) * a.kv_stride_s + d0;
+  f32x4 old[2][N4];
+  if (a.dkv_accumulate && mine) {
 #pragma unroll
-  for (int grad = 0; grad < 2; ++grad) {
+    for (int grad = 0; grad < 2; ++grad)
+#pragma unroll
+      for (int j4 = 0; j4 < N4; ++j4) old[grad][j4] = *reinterpret_cast<const f32x4*>((grad ? a.dv_acc[chunk] : a.dk_acc[chunk]) + dst_off + 4 * j4);
+  }
+  constexpr int GRADS = S::GRADS, PLANE = S::NW * S::PART_BYTES;
+#pragma unroll
+  for (int g0 = 0; g0 < 2; g0 += GRADS) {
     __syncthreads();                                     // nobody reads what is there any more
-    put_part<D>(smem + wave_u * S::PART_BYTES, grad ? dv : dk, grad ? 1.0f : a.scale, ql, g);
+#pragma unroll
+    for (int grad = g0; grad < g0 + GRADS; ++grad)
+      put_part<D>(smem + (grad - g0) * PLANE + wave_u * S::PART_BYTES, grad ? dv : dk, grad ? 1.0f : a.scale, ql, g);
     __syncthreads();
     if (mine) {
-      f32x4 sum[D / 64];
-      sum_parts<D>(smem, r, d0, sum);
-      float* dst = (grad ? a.dv_acc[chunk] : a.dk_acc[chunk]) + head_off + (chunk_row0 + r) * a.kv_stride_s + d0;
 #pragma unroll
-      for (int j4 = 0; j4 < D / 64; ++j4) {
-        f32x4* p = reinterpret_cast<f32x4*>(dst + 4 * j4);
-        if (a.dkv_accumulate) sum[j4] += *p;
-        *p = sum[j4];
+      for (int grad = g0; grad < g0 + GRADS; ++grad) {
+        f32x4 sum[N4];
+        sum_parts<D, NW>(smem + (grad - g0) * PLANE + block * NW * S::PART_BYTES, r, d0, sum);
+        float* dst = (grad ? a.dv_acc[chunk] : a.dk_acc[chunk]) + dst_off;
+#pragma unroll
+        for (int j4 = 0; j4 < N4; ++j4) {
+          if (a.dkv_accumulate) sum[j4] += old[grad][j4];
+          *reinterpret_cast<f32x4*>(dst + 4 * j4) = sum[j4];
+        }
       }
     }
   }
 }
 
 // dq and dk/dv items, the kind that takes longer first.
-template <int D, bool OWN_STATS>
+template <int D, bool OWN_STATS, int BLOCKS>
 __global__ __launch_bounds__(512) void attn_bwd_small_kernel(const BwdArgs a, int n_dq, int n_dkdv) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
   if ((i < first) == (a.dq_first != 0)) dq_small_item<D>(a, a.dq_first ? i : i - n_dkdv, smem);
-  else dkdv_small_item<D, OWN_STATS>(a, a.dq_first ? i - n_dq : i, smem);
+  else dkdv_small_item<D, OWN_STATS, BLOCKS>(a, a.dq_first ? i - n_dq : i, smem);
 }
 
-hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, bool own_stats, hipStream_t st) {
+template <int D, bool OWN_STATS, int BLOCKS>
+static hipError_t launch_bwd_small_t(const BwdArgs& a, int batch, hipStream_t st) {
   const int64_t n_dq = ((int64_t)a.s_q + 31) / 32 * a.n_q_heads * batch;
-  const int64_t n_dkdv = (a.kv_end - kv_grid_origin(a.kv_begin, a.kv.n, 32) + 31) / 32 * a.n_kv_heads * batch;
-  const dim3 grid((unsigned)(n_dq + n_dkdv)), block(512);
-  if (head_dim == 128) hipLaunchKernelGGL((attn_bwd_small_kernel<128, false>), grid, block, BwdSmall<128>::LDS, st, a, (int)n_dq, (int)n_dkdv);
-  else if (own_stats) hipLaunchKernelGGL((attn_bwd_small_kernel<64, true>), grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
-  else hipLaunchKernelGGL((attn_bwd_small_kernel<64, false>), grid, block, BwdSmall<64>::LDS, st, a, (int)n_dq, (int)n_dkdv);
+  const int64_t n_dkdv = (a.kv_end - kv_grid_origin(a.kv_begin, a.kv.n, 32) + 32 * BLOCKS - 1) / (32 * BLOCKS) * a.n_kv_heads * batch;
+  hipLaunchKernelGGL((attn_bwd_small_kernel<D, OWN_STATS, BLOCKS>), dim3((unsigned)(n_dq + n_dkdv)), dim3(512), BwdSmall<D>::LDS, st, a, (int)n_dq, (int)n_dkdv);
   return hipGetLastError();
+}
+hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, bool own_stats, int key_blocks, hipStream_t st) {
+  if (head_dim == 128) return launch_bwd_small_t<128, false, 1>(a, batch, st);
+  if (key_blocks == 2) return own_stats ? launch_bwd_small_t<64, true, 2>(a, batch, st) : launch_bwd_small_t<64, false, 2>(a, batch, st);
+  return own_stats ? launch_bwd_small_t<64, true, 1>(a, batch, st) : launch_bwd_small_t<64, false, 1>(a, batch, st);
 }
 
 int small_dq_tile_keys(int head_dim) { return head_dim == 128 ? BwdSmall<128>::BN : BwdSmall<64>::BN; }
@@ -695,9 +720,11 @@ hipError_t opt_in_small_kernels() {
   const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
   hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<128>), attr, FwdSmall<128>::LDS);
   if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_fwd_small_kernel<64>), attr, FwdSmall<64>::LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<128, false>), attr, BwdSmall<128>::LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, true>), attr, BwdSmall<64>::LDS);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, false>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<128, false, 1>), attr, BwdSmall<128>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, true, 1>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, false, 1>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, true, 2>), attr, BwdSmall<64>::LDS);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_bwd_small_kernel<64, false, 2>), attr, BwdSmall<64>::LDS);
   return e;
 }
 

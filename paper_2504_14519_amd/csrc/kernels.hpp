@@ -139,7 +139,8 @@ hipError_t launch_dkdv_reduce(const BwdArgs& a, int batch, int head_dim, hipStre
 hipError_t launch_dq_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_bwd_both(const BwdArgs& a, int head_dim, hipStream_t st);
 int small_dq_tile_keys(int head_dim);
-hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, bool own_stats, hipStream_t st);      // own_stats: no delta launch before
+// own_stats: no delta launch before; key_blocks: of 32 keys that a dk/dv item owns (1; head_dim 64: or 2)
+hipError_t launch_bwd_small(const BwdArgs& a, int batch, int head_dim, bool own_stats, int key_blocks, hipStream_t st);
 hipError_t launch_both_reduce(const BwdArgs& a, int batch, int head_dim, hipStream_t st);
 hipError_t launch_merge(const MergeArgs& a, hipStream_t st);
 hipError_t launch_finalize(const float* acc, __bf16* dst, int64_t n, hipStream_t st);

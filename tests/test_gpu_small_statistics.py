@@ -56,3 +56,50 @@ def test_statistics_of_small_calls(s, N, Hq, Hkv, off, b, launches_delta):
         err = rel_l2(g, w)
         say("%s rel-L2 %.3e" % (name, err))
         assert err <= TOL_GRAD, name
+
+
+# Calls of more dk/dv items than fit beside the dq items in one round, so that an item owns two blocks of 32 keys
+@pytest.mark.parametrize("s,N,off,b,e,chunk", [
+    (512, 2048, 1536, 0, 2048, 0),
+    (500, 2010, 1510, 0, 2010, 0),         # 63 key blocks a head: the last item has one, of 26 keys
+    (300, 2600, 2200, 37, 2500, 0),        # a range that begins and ends inside a block; 77 blocks
+    (300, 2560, 2200, 37, 2500, 256),      # the same on the grid of a chunked cache
+    (600, 2048, 1500, 0, 2048, 0),         # 19 query tiles; the last rows see every key
+    (512, 2048, 1400, 0, 2048, 0),         # keys that no row sees
+])
+def test_two_key_blocks_an_item(s, N, off, b, e, chunk):
+    import torch
+    import paper_2504_14519_amd as sp
+    B, H, D = 1, 4, 64
+    scale = 1.0 / math.sqrt(D)
+    say("small backward, two key blocks: s=%d N=%d off=%d [%d,%d) chunk %d" % (s, N, off, b, e, chunk))
+    bits = {t: normal_bf16((B, N if t in "kv" else s, H, D), 73, t) for t in ("q", "k", "v", "do")}
+    r = {t: bf16_bits_to_f64(x) for t, x in bits.items()}
+    dev = {t: dev_bf16(x) for t, x in bits.items()}
+    dev["k"][:, e:], dev["v"][:, e:] = float("nan"), float("nan")          # what the cache holds behind the range is not read
+    o_ref, l_ref = attn_fwd(r["q"], r["k"], r["v"], off, b, e, True, scale)
+    out, lse = torch.from_numpy(o_ref).to("cuda:0").to(torch.bfloat16), torch.from_numpy(l_ref).to("cuda:0").float()
+    want = attn_bwd(r["q"], r["k"], r["v"], host_f64(out), r["do"], l_ref, off, b, e, True, scale)
+    p = sp.make_params(dev["q"], dev["k"], out, off, b, e, True, scale)
+    ws = torch.full((sp.slimpipe_attn_workspace_bytes(p, True),), 255, device="cuda:0", dtype=torch.uint8)
+    assert sp.slimpipe_attn_call_path(p, True, -(-N // chunk) if chunk else 1, ws.numel()).small == 1
+    res = []
+    for add in (True, True, False):
+        dk, dv = torch.full((B, N, H, D), 0.5, device="cuda:0"), torch.full((B, N, H, D), -0.25, device="cuda:0")
+        kw = dict(dq_dtype=sp.F32, dkv_accumulate=add, workspace=ws)
+        if chunk:
+            cut = lambda x: [x[:, i:i + chunk].contiguous() for i in range(0, N, chunk)]
+            dkc, dvc = cut(dk), cut(dv)
+            dq = sp.slimpipe_attn_bwd_chunked(dev["q"], cut(dev["k"]), cut(dev["v"]), out, dev["do"], lse, off, b, e, dkc, dvc, True, scale, **kw)
+            dk, dv = torch.cat(dkc, 1), torch.cat(dvc, 1)
+        else:
+            dq = sp.slimpipe_attn_bwd(dev["q"], dev["k"], dev["v"], out, dev["do"], lse, off, b, e, dk, dv, True, scale, **kw)
+        torch.cuda.synchronize()
+        res.append((dq, dk, dv))
+        inside = slice(b, e)
+        for name, g, w, old in (("dq", dq, want[0], 0.0), ("dk", dk[:, inside], want[1][:, inside], 0.5), ("dv", dv[:, inside], want[2][:, inside], -0.25)):
+            g = host_f64(g) - (old if add else 0.0)
+            assert np.isfinite(g).all() and rel_l2(g, w) <= TOL_GRAD, name
+        for x, old in ((dk, 0.5), (dv, -0.25)):
+            assert (x[:, :b] == old).all() and (x[:, e:] == old).all(), "keys outside the range keep what they held"
+    assert all(torch.equal(x, y) for x, y in zip(res[0], res[1])), "bit-reproducible"
