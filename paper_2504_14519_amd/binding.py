@@ -8,6 +8,11 @@ import ctypes
 import math
 import os
 
+# torch before the library: the tensors and streams handed to the library come from torch's HIP runtime, so that runtime has
+# to be the one already in the process when the library's dependency on libamdhip64 is resolved (loaded the other
+# way round, the library can end up on a second runtime instance that sees no device)
+import torch
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libslimpipe_attn.so")
 
@@ -56,10 +61,6 @@ def _load():
         except Exception as e:
             raise ImportError("libslimpipe_attn.so is not built and building it failed (%s): run "
                               "`python paper_2504_14519_amd/build.py`" % e)
-    # torch first: the tensors and streams handed to the library come from torch's HIP runtime, so that runtime has
-    # to be the one already in the process when the library's dependency on libamdhip64 is resolved (loaded the other
-    # way round, the library can end up on a second runtime instance that sees no device)
-    import torch  # noqa: F401
     L = ctypes.CDLL(_LIB_PATH)
     P = ctypes.POINTER(AttnParams)
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
@@ -122,12 +123,13 @@ def _check(rc, what):
 def _stream():
     # the raw handle of the current device's current stream, through two private functions of torch: 0.3 us; the public call
     # builds a stream object, 2.9 us
-    import torch
     return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _same_strides(a, b):
     """Equal shapes and equal strides on every dimension longer than one."""
+    if a.stride() == b.stride() and a.shape == b.shape:
+        return True
     return a.shape == b.shape and all(sa == sb for n, sa, sb in zip(a.shape, a.stride(), b.stride()) if n > 1)
 
 
@@ -135,10 +137,20 @@ def make_params(q, k, out_like, q_offset, kv_begin, kv_end, causal, scale, out_d
     """Fill the parameter block from tensor shapes/strides.  q [B,s,Hq,D], k [B,Nkv,Hkv,D]."""
     B, s, Hq, D = q.shape
     o_strides = out_like.stride(0), out_like.stride(1), out_like.stride(2)
-    # in the order of AttnParams; the strides of d_out are those of out until the backward overrides them
+    # in the order of AttnParams; the strides of d_out are those of out
     return AttnParams(B, s, Hq, k.shape[2], D, 1 if causal else 0, k.shape[1], q_offset, kv_begin, kv_end,
                       float(scale) if scale is not None else 1.0 / math.sqrt(D), out_dtype, q.stride(0), q.stride(1), q.stride(2),
                       k.stride(0), k.stride(1), k.stride(2), *o_strides, *o_strides)
+
+
+def _params(q, k, out_like, d_out, q_offset, kv_begin, kv_end, causal, scale, out_dtype):
+    # make_params for the calls themselves: strides of whole tensors, each asked for once (a question to a tensor is 0.1 us: 2.3 -> 1.3 us)
+    B, s, Hq, D = q.shape
+    k_shape, sq, sk, so, sd = k.shape, q.stride(), k.stride(), out_like.stride(), d_out.stride()
+    # in the order of AttnParams
+    return AttnParams(B, s, Hq, k_shape[2], D, 1 if causal else 0, k_shape[1], q_offset, kv_begin, kv_end,
+                      float(scale) if scale is not None else 1.0 / math.sqrt(D), out_dtype, sq[0], sq[1], sq[2],
+                      sk[0], sk[1], sk[2], so[0], so[1], so[2], sd[0], sd[1], sd[2])
 
 
 def slimpipe_attn_init():
@@ -160,17 +172,23 @@ def _ws(workspace):
     return (workspace.data_ptr(), workspace.numel()) if workspace is not None else (None, 0)
 
 
-def slimpipe_attn_fwd(q_slice, k_prefix, v_prefix, q_offset, kv_begin, kv_end, causal=True, scale=None,
-                      out_dtype=BF16, out=None, lse=None, workspace=None):
-    """-> (out, lse).  out [B,s,Hq,D] (bf16 or fp32), lse [B,Hq,s] fp32.  workspace: uint8 tensor the library may
-    use to cut a short slice over a long cache into key ranges (slimpipe_attn_workspace_bytes(p, False))."""
-    import torch
+def _outputs(q_slice, out_dtype, out, lse):
+    """out and lse of a forward call, allocated where the caller gave none."""
     B, s, Hq, D = q_slice.shape
     if out is None:
         out = torch.empty((B, s, Hq, D), device=q_slice.device, dtype=torch.float32 if out_dtype == F32 else torch.bfloat16)
     if lse is None:
         lse = torch.empty((B, Hq, s), device=q_slice.device, dtype=torch.float32)
-    p = make_params(q_slice, k_prefix, out, q_offset, kv_begin, kv_end, causal, scale, out_dtype)
+    return out, lse
+
+
+def slimpipe_attn_fwd(q_slice, k_prefix, v_prefix, q_offset, kv_begin, kv_end, causal=True, scale=None,
+                      out_dtype=BF16, out=None, lse=None, workspace=None):
+    """-> (out, lse).  out [B,s,Hq,D] (bf16 or fp32), lse [B,Hq,s] fp32.  workspace: uint8 tensor the library may
+    use to cut a short slice over a long cache into key ranges (slimpipe_attn_workspace_bytes(p, False))."""
+    if out is None or lse is None:
+        out, lse = _outputs(q_slice, out_dtype, out, lse)
+    p = _params(q_slice, k_prefix, out, out, q_offset, kv_begin, kv_end, causal, scale, out_dtype)
     _check(lib.slimpipe_attn_fwd(ctypes.byref(p), q_slice.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
                                  out.data_ptr(), lse.data_ptr(), *_ws(workspace), _stream()), "slimpipe_attn_fwd")
     return out, lse
@@ -180,13 +198,11 @@ def slimpipe_attn_bwd(q_slice, k_prefix, v_prefix, out, d_out, lse, q_offset, kv
                       causal=True, scale=None, dq=None, dq_dtype=BF16, dq_accumulate=False, dkv_accumulate=True,
                       workspace=None):
     """-> dq.  dk_acc/dv_acc (fp32, shaped like k_prefix) get rows [kv_begin, kv_end) written or incremented."""
-    import torch
     if dq is None:
         dq = torch.empty_like(q_slice, dtype=torch.float32 if dq_dtype == F32 else torch.bfloat16)
     if not (_same_strides(dq, q_slice) and _same_strides(dk_acc, k_prefix) and _same_strides(dv_acc, k_prefix)):
         raise SlimpipeError("dq must have the strides of q; dk_acc/dv_acc those of k")
-    p = make_params(q_slice, k_prefix, out, q_offset, kv_begin, kv_end, causal, scale)
-    p.do_stride_b, p.do_stride_s, p.do_stride_h = d_out.stride(0), d_out.stride(1), d_out.stride(2)
+    p = _params(q_slice, k_prefix, out, d_out, q_offset, kv_begin, kv_end, causal, scale, BF16)
     if workspace is None:
         workspace = torch.empty(slimpipe_attn_workspace_bytes(p, True), device=q_slice.device, dtype=torch.uint8)
     _check(lib.slimpipe_attn_bwd(ctypes.byref(p), q_slice.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
@@ -201,11 +217,9 @@ def slimpipe_attn_bwd_noalloc(q_slice, k_prefix, v_prefix, out, d_out, lse, q_of
                               causal=True, scale=None, dq_accumulate=False, dkv_accumulate=True):
     """slimpipe_attn_bwd without a workspace and without any allocation (the binding allocates nothing either: dq is
     the caller's, float32 or bf16 by its dtype).  -> the status code's check; results in dq, dk_acc, dv_acc."""
-    import torch
     if not (_same_strides(dq, q_slice) and _same_strides(dk_acc, k_prefix) and _same_strides(dv_acc, k_prefix)):
         raise SlimpipeError("dq must have the strides of q; dk_acc/dv_acc those of k")
-    p = make_params(q_slice, k_prefix, out, q_offset, kv_begin, kv_end, causal, scale)
-    p.do_stride_b, p.do_stride_s, p.do_stride_h = d_out.stride(0), d_out.stride(1), d_out.stride(2)
+    p = _params(q_slice, k_prefix, out, d_out, q_offset, kv_begin, kv_end, causal, scale, BF16)
     _check(lib.slimpipe_attn_bwd_noalloc(ctypes.byref(p), q_slice.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
                                          out.data_ptr(), d_out.data_ptr(), lse.data_ptr(), dq.data_ptr(),
                                          F32 if dq.dtype == torch.float32 else BF16, 1 if dq_accumulate else 0,
@@ -230,20 +244,16 @@ class _ChunkedKV:
         self.shape = (c0.shape[0], len(chunks) * c0.shape[1], c0.shape[2], c0.shape[3])
         self._strides = c0.stride()
 
-    def stride(self, i):
-        return self._strides[i]
+    def stride(self, i=None):
+        return self._strides if i is None else self._strides[i]
 
 
 def slimpipe_attn_fwd_chunked(q_slice, k_chunks, v_chunks, q_offset, kv_begin, kv_end, causal=True, scale=None,
                               out_dtype=BF16, out=None, lse=None, workspace=None):
     """As slimpipe_attn_fwd with K/V given as lists of equally shaped chunks [B, chunk_len, Hkv, D]."""
-    import torch
-    B, s, Hq, D = q_slice.shape
-    if out is None:
-        out = torch.empty((B, s, Hq, D), device=q_slice.device, dtype=torch.float32 if out_dtype == F32 else torch.bfloat16)
-    if lse is None:
-        lse = torch.empty((B, Hq, s), device=q_slice.device, dtype=torch.float32)
-    p = make_params(q_slice, _ChunkedKV(k_chunks), out, q_offset, kv_begin, kv_end, causal, scale, out_dtype)
+    if out is None or lse is None:
+        out, lse = _outputs(q_slice, out_dtype, out, lse)
+    p = _params(q_slice, _ChunkedKV(k_chunks), out, out, q_offset, kv_begin, kv_end, causal, scale, out_dtype)
     _check(lib.slimpipe_attn_fwd_chunked(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
                                          len(k_chunks), k_chunks[0].shape[1], out.data_ptr(), lse.data_ptr(), *_ws(workspace),
                                          _stream()),
@@ -256,7 +266,6 @@ def slimpipe_attn_fwd_ranges(q_slice, k_chunks, v_chunks, q_offset, ranges, caus
     """One launch over several key ranges [(kv_begin, kv_end), ...] of one query slice; k_chunks / v_chunks: a list
     of chunks, or one tensor.  -> (part_out [R,B,s,Hq,D] fp32, part_lse [R,B,Hq,s], out, lse); out and lse are the
     merged result, or None with merged=False."""
-    import torch
     if not isinstance(k_chunks, (list, tuple)):
         k_chunks, v_chunks = [k_chunks], [v_chunks]
     B, s, Hq, D = q_slice.shape
@@ -271,7 +280,7 @@ def slimpipe_attn_fwd_ranges(q_slice, k_chunks, v_chunks, q_offset, ranges, caus
     else:
         out = lse = None
     kv = _ChunkedKV(k_chunks)
-    p = make_params(q_slice, kv, out if merged else part_out[0], q_offset, 0, kv.shape[1], causal, scale, out_dtype)
+    p = _params(q_slice, kv, out if merged else part_out[0], q_offset, 0, kv.shape[1], causal, scale, out_dtype)
     begins = (ctypes.c_int64 * R)(*[int(a) for a, _ in ranges])
     ends = (ctypes.c_int64 * R)(*[int(b) for _, b in ranges])
     _check(lib.slimpipe_attn_fwd_ranges(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
@@ -285,7 +294,6 @@ def slimpipe_attn_bwd_chunked(q_slice, k_chunks, v_chunks, out, d_out, lse, q_of
                               causal=True, scale=None, dq=None, dq_dtype=BF16, dq_accumulate=False, dkv_accumulate=True,
                               workspace=None):
     """As slimpipe_attn_bwd with K/V and the fp32 dK/dV accumulators given as lists of chunks."""
-    import torch
     if dq is None:
         dq = torch.empty_like(q_slice, dtype=torch.float32 if dq_dtype == F32 else torch.bfloat16)
     if not _same_strides(dq, q_slice):
@@ -293,8 +301,7 @@ def slimpipe_attn_bwd_chunked(q_slice, k_chunks, v_chunks, out, d_out, lse, q_of
     for c in list(dk_chunks) + list(dv_chunks):
         if not _same_strides(c, k_chunks[0]):
             raise SlimpipeError("dk/dv chunks must have the strides of the k chunks")
-    p = make_params(q_slice, _ChunkedKV(k_chunks), out, q_offset, kv_begin, kv_end, causal, scale)
-    p.do_stride_b, p.do_stride_s, p.do_stride_h = d_out.stride(0), d_out.stride(1), d_out.stride(2)
+    p = _params(q_slice, _ChunkedKV(k_chunks), out, d_out, q_offset, kv_begin, kv_end, causal, scale, BF16)
     if workspace is None:
         workspace = torch.empty(slimpipe_attn_workspace_bytes(p, True), device=q_slice.device, dtype=torch.uint8)
     _check(lib.slimpipe_attn_bwd_chunked(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
@@ -308,7 +315,6 @@ def slimpipe_attn_bwd_chunked(q_slice, k_chunks, v_chunks, out, d_out, lse, q_of
 
 def slimpipe_attn_merge(outs, lses, out_dtype=BF16, out=None, lse=None):
     """Merge partial (out, lse) pairs over disjoint key sets -> (out, lse)."""
-    import torch
     n = len(outs)
     B, s, Hq, D = outs[0].shape
     part_dtype = F32 if outs[0].dtype == torch.float32 else BF16
@@ -327,7 +333,6 @@ def slimpipe_attn_merge(outs, lses, out_dtype=BF16, out=None, lse=None):
 
 
 def slimpipe_attn_finalize_bf16(acc, dst=None):
-    import torch
     if dst is None:
         dst = torch.empty(acc.shape, device=acc.device, dtype=torch.bfloat16)
     _check(lib.slimpipe_attn_finalize_bf16(acc.data_ptr(), dst.data_ptr(), acc.numel(), _stream()), "finalize_bf16")
@@ -340,7 +345,6 @@ KERNEL_KINDS = ("fwd", "delta", "dq", "dkdv", "merge", "finalize", "dkdv_reduce"
 
 def slimpipe_attn_mfma_rate(random_operands):
     """-> TFLOP/s of a pure bf16 MFMA stream on this GPU (constant or random operands)."""
-    import torch
     sink = torch.zeros(4, device="cuda", dtype=torch.float32)
     tf = ctypes.c_double(0.0)
     _check(lib.slimpipe_attn_mfma_rate(1 if random_operands else 0, sink.data_ptr(), ctypes.byref(tf), _stream()), "mfma_rate")
@@ -349,7 +353,6 @@ def slimpipe_attn_mfma_rate(random_operands):
 
 def slimpipe_attn_dq_atomic_probe(s_q, heads, key_tiles, rows_per_step, placement, rotate, filler_mfma, with_atomics):
     """-> (ms, every element of dq holds the expected count, workgroups not on XCD w % 8 [placement 1 only])."""
-    import torch
     dq = torch.zeros((s_q, heads, 128), device="cuda", dtype=torch.float32)
     mism = torch.zeros(1, device="cuda", dtype=torch.int32)
     ms = ctypes.c_double(0.0)
@@ -364,7 +367,6 @@ def slimpipe_attn_dq_atomic_probe(s_q, heads, key_tiles, rows_per_step, placemen
 
 def slimpipe_attn_xcd_rate(iters=20000, rounds=4):
     """-> {xcd: (workgroups, mean workgroup ms, last end ms)} for `rounds` workgroups of equal matrix work per compute unit."""
-    import torch
     n = rounds * torch.cuda.get_device_properties(0).multi_processor_count
     t0 = torch.zeros(n, device="cuda", dtype=torch.int64)
     t1 = torch.zeros(n, device="cuda", dtype=torch.int64)
