@@ -280,7 +280,7 @@ def slimpipe_attn_fwd_ranges(q_slice, k_chunks, v_chunks, q_offset, ranges, caus
     else:
         out = lse = None
     kv = _ChunkedKV(k_chunks)
-    p = _params(q_slice, kv, out if merged else part_out[0], q_offset, 0, kv.shape[1], causal, scale, out_dtype)
+    p = make_params(q_slice, kv, out if merged else part_out[0], q_offset, 0, kv.shape[1], causal, scale, out_dtype)
     begins = (ctypes.c_int64 * R)(*[int(a) for a, _ in ranges])
     ends = (ctypes.c_int64 * R)(*[int(b) for _, b in ranges])
     _check(lib.slimpipe_attn_fwd_ranges(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
