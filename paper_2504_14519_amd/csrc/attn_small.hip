@@ -3,8 +3,8 @@
 // What bounds a small call is a chain: a 256-row block walks its keys tile after tile behind barriers on a chip that is mostly idle, and
 // key ranges shorten the chain only at the price of a merge launch.  Here eight waves walk eight tiles of the keys at the same time,
 // each with a K and a V tile of its own in LDS, copied by itself and waited for by itself (no barrier in the loop), and their
-// partial results meet in LDS.  512 rows on 2048 keys, 4 heads of 64 (64 workgroups): 18.1 -> 11.2 us; 512 rows of 8 heads of 128 on one
-// K/V head, 2048 keys: 34.6 -> 16.9.  A wave's step (32 keys, 64 at head_dim 64) takes 1.3 us, 1 of which is the compute unit's path to
+// partial results meet in LDS.  512 rows on 2048 keys, 4 heads of 64 (64 workgroups): 18.1 -> 10.9 us; 512 rows of 8 heads of 128 on one
+// K/V head, 2048 keys: 34.6 -> 15.9.  A wave's step (32 keys, 64 at head_dim 64) takes 1.3 us, 1 of which is the compute unit's path to
 // memory: eight K and V tiles are 128 KB at 64 bytes a clock.  One K and one V tile per wave are all of LDS, so K of the next step is
 // copied during softmax and P V, V during the scores and the softmax; what a wave does not need it does not ask for (a last tile copied
 // once more, and Q by loads that the compiler waits for together with every copy: 11.9 and 18.1 us).  Touching the lines of later
@@ -16,6 +16,15 @@
 #include "tile_common.hpp"
 
 namespace slimpipe {
+
+// Row of a key in the chunk that holds it; `first` is the first chunk's base, asked for ahead (the only one, as a rule): a pointer that is looked
+// up by a computed chunk number is a second trip to the kernel's arguments before the first copy (with the block index as a grid of three
+// dimensions instead of two divisions 512 rows on 2048 keys, 8/1 heads of 128, 16.9 -> 15.9 us).
+SP_DEV const bf16_t* kv_row(const bf16_t* const* table, const bf16_t* first, const KvChunks& kv, int64_t key, int64_t stride_s) {
+  if (kv.n <= 1) return first + key * stride_s;
+  const int chunk = kv_chunk_of(kv, key);
+  return table[chunk] + (key - (int64_t)chunk * kv.len) * stride_s;
+}
 
 template <int D>
 struct FwdSmall {
@@ -34,12 +43,14 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ql = lane & 31;
   const int wave_u = __builtin_amdgcn_readfirstlane(tid >> 6);
-  // block index -> (query head, 32-row block of a head, batch index x range), row blocks with the longest key ranges first
-  const int row_blocks = a.items[0], per_z = row_blocks * a.n_q_heads;
-  const int bz = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / (unsigned)per_z)), hb = blockIdx.x - bz * per_z;
-  const int b = __builtin_amdgcn_readfirstlane(bz / a.n_ranges), range = bz - b * a.n_ranges;
-  const int rb = __builtin_amdgcn_readfirstlane(hb / a.n_q_heads), h = hb - rb * a.n_q_heads;
-  const int row0 = (row_blocks - 1 - rb) * 32, hk = h / a.group;
+  // block index = (query head, 32-row block of a head, batch index x range), row blocks with the longest key ranges first
+  const int row_blocks = a.items[0], h = blockIdx.x, rb = blockIdx.y;
+  int b = blockIdx.z, range = 0;
+  if (a.n_ranges > 1) {
+    b = __builtin_amdgcn_readfirstlane(b / a.n_ranges);
+    range = blockIdx.z - b * a.n_ranges;
+  }
+  const int row0 = (row_blocks - 1 - rb) * 32, hk = __builtin_amdgcn_readfirstlane(h / a.group);
   const int myrow = row0 + ql;
   const int64_t kv_begin = a.range_begin[range], kv_end = a.range_end[range];
   int64_t hi = kv_end;
@@ -68,12 +79,11 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
   dma.init(lane, row_bytes);
+  const bf16_t *const k_first = a.kv.k[0], *const v_first = a.kv.v[0];
   auto copy = [&](bool k, int t, int first) {
-    const int64_t key0 = lo + (int64_t)t * BN;
-    const int chunk = kv_chunk_of(a.kv, key0);
     // (a tile lies inside one chunk; rows outside the range are clamped to its first and last key)
-    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;
-    const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
+    const int64_t key0 = lo + (int64_t)t * BN, left = kv_end - key0;
+    const bf16_t* base = uniform_ptr(kv_row(k ? a.kv.k : a.kv.v, k ? k_first : v_first, a.kv, key0, a.kv_stride_s) + head_off);
     dma.copy(k ? k_lds : v_lds, base, row_bytes, first, left < BN ? (int)left : BN, lane);
   };
   constexpr int PASSES = WaveDma<D, BN>::PASSES;
@@ -222,7 +232,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_kernel(const FwdArgs a) {
 }
 
 hipError_t launch_fwd_small(const FwdArgs& a, int batch, int head_dim, hipStream_t st) {
-  const dim3 grid((unsigned)((int64_t)a.items[0] * a.n_q_heads * batch * a.n_ranges)), block(512);
+  const dim3 grid((unsigned)a.n_q_heads, (unsigned)a.items[0], (unsigned)(batch * a.n_ranges)), block(512);      // (y: of less than 256 blocks of 256 rows; z: fwd_impl checks it)
   if (head_dim == 128) hipLaunchKernelGGL(attn_fwd_small_kernel<128>, grid, block, FwdSmall<128>::LDS, st, a);
   else hipLaunchKernelGGL(attn_fwd_small_kernel<64>, grid, block, FwdSmall<64>::LDS, st, a);
   return hipGetLastError();
@@ -348,11 +358,10 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
   dma.init(lane, row_bytes);
+  const bf16_t *const k_first = a.kv.k[0], *const v_first = a.kv.v[0];
   auto copy = [&](bool k, int t, int first) {
-    const int64_t key0 = lo + (int64_t)t * BN;
-    const int chunk = kv_chunk_of(a.kv, key0);
-    const int64_t row = key0 - (int64_t)chunk * a.kv.len, left = kv_end - key0;      // (a tile lies inside one chunk; clamped as in the forward)
-    const bf16_t* base = uniform_ptr((k ? a.kv.k[chunk] : a.kv.v[chunk]) + head_off + row * a.kv_stride_s);
+    const int64_t key0 = lo + (int64_t)t * BN, left = kv_end - key0;      // (a tile lies inside one chunk; clamped as in the forward)
+    const bf16_t* base = uniform_ptr(kv_row(k ? a.kv.k : a.kv.v, k ? k_first : v_first, a.kv, key0, a.kv_stride_s) + head_off);
     dma.copy(k ? k_lds : v_lds, base, row_bytes, first, left < BN ? (int)left : BN, lane);
   };
   int t = wave_u;                                        // tiles w, w + 8, w + 16, .. are this wave's
