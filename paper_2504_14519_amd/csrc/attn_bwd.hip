@@ -437,7 +437,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // in a ring of four; group A copies Q(u+2) and the statistics, group B copies dO(u+2).
 
 // Query rows of a tile.  At head_dim 64 the scores of 64 rows take the registers that head_dim 128 needs for its operands and
-// accumulators, and as many spill (75 against 54; 48 against 32 in one launch), in front of the tile loop and behind it as there; twice the
+// accumulators, and about as many spill (62 against 52; 48 against 32 in one launch), in front of the tile loop and behind it as there; twice the
 // work per tile halves the barriers, cursor steps and copy instructions per pair: 8192 rows on 40960 keys, 16/2 heads, 2635 -> 2437
 // us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 212 -> 206 us the call.
 // Calls that this does not pay for keep 32: dkdv_tile_rows in api.hip.
