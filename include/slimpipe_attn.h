@@ -111,7 +111,7 @@ int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd);
  * adds up in range order; that room is included too and used as far as it is there.  A backward call with fewer than
  * two work items per compute unit computes dq and dk/dv in one launch (and adds up their partial sums in one), but for calls
  * of long items that a workspace without room for partial sums leaves undivided.  The smallest of these, given the room
- * returned here, go through workgroups of 32 rows or keys that keep their partial sums to themselves and leave the room unused. */
+ * returned here, go through workgroups of 32 rows, or of 32 or 64 keys, that keep their partial sums to themselves and leave the room unused. */
 int slimpipe_attn_workspace_bytes(const slimpipe_attn_params* p, int is_bwd, size_t* bytes);
 
 /* Forward of one query slice against keys [kv_begin, kv_end) of the cached prefix
@@ -143,8 +143,11 @@ int slimpipe_attn_fwd(const slimpipe_attn_params* p,
  *              owned by one workgroup (or a fixed number of them whose partial sums are added in a
  *              fixed order) that sums queries and the heads of a GQA group in a fixed order, so
  *              results are bit-reproducible from run to run for the same workspace size.
+ *   shared memory : out and lse are read before any gradient is written, so dq, dk_acc and dv_acc may lie over them (a bf16 dq
+ *              in place of out, for one).  No gradient may share memory with q, k, v, d_out, the workspace or another gradient.
  * Enqueues the delta pre-pass, then the dq kernel and the dk/dv kernel, each with a reduce kernel when it was cut, or
- * for small calls one kernel for both and one reduce kernel when either was cut (slimpipe_attn_workspace_bytes). */
+ * for small calls one kernel for both and one reduce kernel when either was cut (slimpipe_attn_workspace_bytes).  The smallest calls
+ * of head_dim 64 whose gradients do not lie over out or lse enqueue no delta pre-pass: their one kernel does its work. */
 int slimpipe_attn_bwd(const slimpipe_attn_params* p,
                       const void* q_slice, const void* k_prefix, const void* v_prefix,
                       const void* out, const void* d_out, const float* lse,

@@ -395,6 +395,7 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // the host's 4, and costs each step of a wave 0.4 us (O comes along with Q and dO): calls of up to 6 steps of head_dim 64.  With / without,
 // steps: 512 rows on 2048 keys, 4/4 heads, 2 steps, 16.6 / 17.6 us; 500 on 1200, 12/4 heads, 6 steps, 18.1 / 19.6; 777 on 777, 12/4, 9.4
 // steps, 22.5 / 20.9; 1024 on 1024, 8/1, 32 steps, 57.7 / 43.8.  At head_dim 128 a step pays 1 us (256 rows on 512 keys, 8/1 heads, 8 steps, 30.9 / 24.9).
+// (A call whose gradients lie over its out or lse has the delta kernel all the same: bwd_impl.)
 struct BwdSmallPlan { bool use, dq_first, own_stats; int key_blocks; };
 BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) {
   if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false, false, 1};
@@ -751,6 +752,24 @@ int slimpipe_attn_fwd_ranges(const slimpipe_attn_params* p, const void* q_slice,
                   lse_elems, out, lse, hip_stream);
 }
 
+// Whether a gradient of the call may lie over its out or lse (by the memory they span: tensors that interleave count as well).
+static bool gradients_over_saved(const slimpipe_attn_params* p, int32_t n_chunks, int64_t chunk_len, const void* out, const float* lse, const void* dq,
+                                 int32_t dq_dtype, float* const* dk_chunks, float* const* dv_chunks) {
+  const Span saved[2] = {span_of(out, 2, p->batch, p->s_q, p->n_q_heads, p->head_dim, p->o_stride_b, p->o_stride_s, p->o_stride_h),
+                         span_of(lse, 4, 1, 1, 1, (int64_t)p->batch * p->n_q_heads * p->s_q, 1, 1, 1)};
+  auto over = [&](const Span& g) { return share_memory(g, saved[0]) || share_memory(g, saved[1]); };
+  if (over(span_of(dq, dq_dtype == SLIMPIPE_F32 ? 4 : 2, p->batch, p->s_q, p->n_q_heads, p->head_dim, p->q_stride_b, p->q_stride_s, p->q_stride_h))) return true;
+  for (int i = 0; i < n_chunks; ++i) {
+    // rows of the chunk that the range holds
+    const int64_t lo = p->kv_begin - i * chunk_len, hi = p->kv_end - i * chunk_len;
+    const int64_t r0 = lo > 0 ? lo : 0, rows = (hi < chunk_len ? hi : chunk_len) - r0;
+    for (float* g : {dk_chunks[i], dv_chunks[i]})
+      if (rows > 0 && over(span_of(g + r0 * p->kv_stride_s, 4, p->batch, rows, p->n_kv_heads, p->head_dim, p->kv_stride_b, p->kv_stride_s, p->kv_stride_h)))
+        return true;
+  }
+  return false;
+}
+
 static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const void* const* k_chunks,
                     const void* const* v_chunks, int32_t n_chunks, int64_t chunk_len, const void* out,
                     const void* d_out, const float* lse, void* dq, int32_t dq_dtype, int32_t dq_accumulate,
@@ -849,7 +868,10 @@ static int bwd_impl(const slimpipe_attn_params* p, const void* q_slice, const vo
   a.do_stride_b = p->do_stride_b; a.do_stride_s = p->do_stride_s; a.do_stride_h = p->do_stride_h;
   if (ensure_device_ready() != SLIMPIPE_OK) return SLIMPIPE_ELAUNCH;
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
-  const BwdSmallPlan sm = bwd_small_plan(p, plan);
+  BwdSmallPlan sm = bwd_small_plan(p, plan);
+  // out and lse are read before any gradient is written, so that gradients may lie over them: by the delta kernel, ahead of the others; items
+  // that read them are in one launch with items that write gradients.
+  if (sm.own_stats && gradients_over_saved(p, n_chunks, chunk_len, out, lse, dq, dq_dtype, dk_chunks, dv_chunks)) sm.own_stats = false;
   if (!sm.own_stats &&
       timed(SLIMPIPE_KERNEL_DELTA, st, [&] { return launch_delta(a, p->batch, p->head_dim, st); }, events) != hipSuccess)
     return SLIMPIPE_ELAUNCH;

@@ -252,7 +252,7 @@ struct BwdSmall {
   static constexpr int ROW = D + 4, PART_BYTES = 32 * ROW * 4;
   // dq: a K and a V tile of BN keys per wave
   static constexpr int BN = D == 64 ? 64 : 32, KB = BN / 32, KV_BYTES = BN * D * 2;
-  // ... and the workgroup's rows of Q, dO and O
+  // ... and the workgroup's rows of Q, dO and (own statistics) O
   static constexpr int ROWS_BYTES = 32 * D * 2, Q_BASE = NW * 2 * KV_BYTES, DO_BASE = Q_BASE + ROWS_BYTES, O_BASE = DO_BASE + ROWS_BYTES;
   // dk/dv: BUF x (Q and dO tile of 32 rows, their statistics) per wave, and the V and K rows of the workgroup
   static constexpr int BUF = D == 64 ? 2 : 1, TILE_BYTES = 32 * D * 2, SET_BYTES = 2 * TILE_BYTES + 256;
@@ -305,8 +305,9 @@ SP_DEV float row_sum(float x) {
 // lse in log2 units; +inf for a row that saw no key, so that its p are exp2(-inf) = 0
 SP_DEV float lse_log2(float l) { return l == -INFINITY ? INFINITY : l * kLog2e; }
 
-// index -> (query head, 32-row block of a head, batch index)
-template <int D>
+// index -> (query head, 32-row block of a head, batch index).  OWN_STATS: the item works out -dO . O of its rows from out and lse;
+// otherwise the delta kernel has (and nothing of this launch reads out or lse: gradients may lie over them).
+template <int D, bool OWN_STATS>
 SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   using S = BwdSmall<D>;
   constexpr int NW = S::NW, BN = S::BN, KB = S::KB, KS = S::KS, DB = S::DB;
@@ -330,16 +331,17 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   const float c = a.scale_log2e;
 
   const unsigned smem_lds = lds_addr(smem);
-  // The rows of Q, dO and O, one copy instruction of each per wave (as far as there are any): eight waves that each load their lane's row
-  // of them are 64 lines an instruction, a lane a clock.
+  // The rows of Q, dO and (OWN_STATS) O, one copy instruction of each per wave (as far as there are any): eight waves that each load their
+  // lane's row of them are 64 lines an instruction, a lane a clock.
   if (wave_u < WaveDma<D, 32>::PASSES) {
     const int rows = a.s_q - row0;
     WaveDma<D, 32>::copy_pass(smem_lds + S::Q_BASE, uniform_ptr(a.q + (int64_t)b * a.q_stride_b + (int64_t)row0 * a.q_stride_s + (int64_t)h * a.q_stride_h),
                               (uint32_t)a.q_stride_s * 2, rows, lane, wave_u);
     WaveDma<D, 32>::copy_pass(smem_lds + S::DO_BASE, uniform_ptr(a.d_out + (int64_t)b * a.do_stride_b + (int64_t)row0 * a.do_stride_s + (int64_t)h * a.do_stride_h),
                               (uint32_t)a.do_stride_s * 2, rows, lane, wave_u);
-    WaveDma<D, 32>::copy_pass(smem_lds + S::O_BASE, uniform_ptr(a.out + (int64_t)b * a.o_stride_b + (int64_t)row0 * a.o_stride_s + (int64_t)h * a.o_stride_h),
-                              (uint32_t)a.o_stride_s * 2, rows, lane, wave_u);
+    if constexpr (OWN_STATS)
+      WaveDma<D, 32>::copy_pass(smem_lds + S::O_BASE, uniform_ptr(a.out + (int64_t)b * a.o_stride_b + (int64_t)row0 * a.o_stride_s + (int64_t)h * a.o_stride_h),
+                                (uint32_t)a.o_stride_s * 2, rows, lane, wave_u);
   }
   f32x16 dq[DB];
 #pragma unroll
@@ -353,7 +355,9 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   lo_k.init(lane, (int)k_lds);
   lo_v.init(lane, (int)v_lds);
   lo_kt.init(lane, (int)k_lds);
-  const float lse_raw = a.lse[((int64_t)b * a.n_q_heads + h) * a.s_q + myrow_c];
+  // statistics of the lane's row: lse in log2 units (+inf for a row that saw no key) and -dO . O, the initial accumulator of dP
+  const int64_t stat = ((int64_t)b * a.n_q_heads + h) * a.s_q + myrow_c;
+  float lse2 = OWN_STATS ? a.lse[stat] : a.lse2[stat], ndelta = OWN_STATS ? 0.f : a.delta[stat];
   const int64_t head_off = (int64_t)b * a.kv_stride_b + (int64_t)hk * a.kv_stride_h;
   const uint32_t row_bytes = (uint32_t)a.kv_stride_s * 2;
   WaveDma<D, BN> dma;
@@ -375,7 +379,6 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
   }
   __syncthreads();                                       // the rows have landed
   bf16x8 q[KS], dO[KS];
-  float ndelta = 0.f;                                    // -dO . O of the lane's row: the initial accumulator of dP
   {
     RpBase<D> lo_r;
     lo_r.init(lane, (int)smem_lds + S::Q_BASE);
@@ -383,11 +386,13 @@ SP_DEV void dq_small_item(const BwdArgs& a, int item, char* smem) {
     for (int ks = 0; ks < KS; ++ks) {
       q[ks] = lds_rp<D>(lo_r, ks, 0);
       dO[ks] = lds_rp<D>(lo_r, ks, S::ROWS_BYTES);
-      ndelta = dot8(lds_rp<D>(lo_r, ks, 2 * S::ROWS_BYTES), dO[ks], ndelta);
+      if constexpr (OWN_STATS) ndelta = dot8(lds_rp<D>(lo_r, ks, 2 * S::ROWS_BYTES), dO[ks], ndelta);
     }
   }
-  ndelta = -xhalf_sum(ndelta);
-  const float lse2 = lse_log2(lse_raw);
+  if constexpr (OWN_STATS) {
+    ndelta = -xhalf_sum(ndelta);
+    lse2 = lse_log2(lse2);
+  }
   for (; t < nt; t += NW) {
     const int tn = t + NW;
     wait_copies<0>();
@@ -706,7 +711,7 @@ template <int D, bool OWN_STATS, int BLOCKS>
 __global__ __launch_bounds__(512) void attn_bwd_small_kernel(const BwdArgs a, int n_dq, int n_dkdv) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
-  if ((i < first) == (a.dq_first != 0)) dq_small_item<D>(a, a.dq_first ? i : i - n_dkdv, smem);
+  if ((i < first) == (a.dq_first != 0)) dq_small_item<D, OWN_STATS>(a, a.dq_first ? i : i - n_dkdv, smem);
   else dkdv_small_item<D, OWN_STATS, BLOCKS>(a, a.dq_first ? i - n_dq : i, smem);
 }
 

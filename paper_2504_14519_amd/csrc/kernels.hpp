@@ -36,6 +36,18 @@ inline __host__ __device__ int packed_head_waves(int s_q) { return (int)(((unsig
 inline __host__ __device__ int padded_head_waves(int s_q) { return (int)(((unsigned)s_q + 255u) / 256u * 8u); }
 inline __host__ __device__ int64_t query_blocks(int head_waves, int group) { return ((int64_t)group * head_waves + 7) / 8; }
 
+// The memory from the first element of a [batch, rows, heads, head_dim] tensor (strides in elements, all positive) to its last.
+struct Span {
+  uintptr_t begin, end;      // [begin, end); empty without elements
+};
+inline Span span_of(const void* first, int64_t elem_bytes, int64_t batch, int64_t rows, int64_t heads, int64_t head_dim, int64_t stride_b, int64_t stride_s,
+                    int64_t stride_h) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(first);
+  if (batch < 1 || rows < 1 || heads < 1 || head_dim < 1) return {p, p};
+  return {p, p + (uintptr_t)(((batch - 1) * stride_b + (rows - 1) * stride_s + (heads - 1) * stride_h + head_dim) * elem_bytes)};
+}
+inline bool share_memory(const Span& a, const Span& b) { return a.begin < a.end && b.begin < b.end && a.begin < b.end && b.begin < a.end; }
+
 struct FwdArgs {
   const __bf16* q;
   KvChunks kv;
