@@ -8,7 +8,7 @@
 //   * dq kernel, query-stationary (same shape as the forward): S^T = K Q^T and dP^T = V dO^T
 //     land with one query per lane, so lse/delta are per-lane scalars and dS^T feeds
 //     dQ^T += K^T dS^T directly as the B operand (K through the transposed LDS read).
-//   * dk/dv kernel, key-stationary: each wave owns 32 keys (K, V as B operands in registers,
+//   * dk/dv kernel, key-stationary: each wave owns 32 keys (K in registers and V in LDS as B operands,
 //     dK^T/dV^T accumulators in registers) and walks the query tiles of every head of its GQA
 //     group in a fixed order: S = Q K^T, dP = dO V^T land with one key per lane and 16 query rows
 //     in the registers, which is the B operand of dV^T += dO^T P and dK^T += Q^T dS.
@@ -437,7 +437,7 @@ hipError_t launch_bwd_dq(const BwdArgs& a, int batch, int head_dim, hipStream_t 
 // in a ring of four; group A copies Q(u+2) and the statistics, group B copies dO(u+2).
 
 // Query rows of a tile.  At head_dim 64 the scores of 64 rows take the registers that head_dim 128 needs for its operands and
-// accumulators, and about as many spill (62 against 52; 48 against 32 in one launch), in front of the tile loop and behind it as there; twice the
+// accumulators, and about as many spill (71 against 43; 49 against 69 in one launch), in front of the tile loop and behind it as there; twice the
 // work per tile halves the barriers, cursor steps and copy instructions per pair: 8192 rows on 40960 keys, 16/2 heads, 2635 -> 2437
 // us, and 1337 rows on 4238 keys, 3 x 12/4 heads, dq and dk/dv in one launch 212 -> 206 us the call.
 // Calls that this does not pay for keep 32: dkdv_tile_rows in api.hip.
@@ -462,16 +462,9 @@ struct DkdvLds {
   static constexpr int V_BYTES = NW * 32 * D * 2;
   static constexpr int STAT_BASE = V_BASE + V_BYTES;          // [SLOTS][lse2[BMQ], delta[BMQ]] floats
   static constexpr int STAT_BYTES = 2 * BMQ * 4;
-  // K rows of the workgroup on their way into registers, 32 a wave: in ring slots 1 .. 3, which hold no tile yet, and behind the
-  // statistics
-  static constexpr int K_WAVE_BYTES = 32 * D * 2, K_PER_RING = (SLOTS - 1) * TILE_BYTES / K_WAVE_BYTES;
-  static constexpr int K_REST = NW > 2 * K_PER_RING ? NW - 2 * K_PER_RING : 0, K_BASE = STAT_BASE + SLOTS * STAT_BYTES;
-  static constexpr int k_stage(int wave) {
-    if (wave < K_PER_RING) return Q_BASE + TILE_BYTES + wave * K_WAVE_BYTES;
-    if (wave < 2 * K_PER_RING) return DO_BASE + TILE_BYTES + (wave - K_PER_RING) * K_WAVE_BYTES;
-    return K_BASE + (wave - 2 * K_PER_RING) * K_WAVE_BYTES;
-  }
-  static constexpr int TOTAL = K_BASE + K_REST * K_WAVE_BYTES;
+  // ... and, in place of all that, the dk or dv rows of the workgroup on their way out
+  static constexpr int RINGS = STAT_BASE + SLOTS * STAT_BYTES, OUT_BYTES = NW * 32 * kOutRow<D> * 4;
+  static constexpr int TOTAL = RINGS > OUT_BYTES ? RINGS : OUT_BYTES;
 };
 
 template <int D, int NW, int BMQ, bool WITH_ACC, bool WITH_SCORES, int LOOK>
@@ -530,8 +523,8 @@ struct DkdvMatrixPhase {
   SP_DEV void mfma() {
     if constexpr (M < N_AC) {
       constexpr int h = M / (2 * DB), db = (M % (2 * DB)) / 2;
-      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(st.pb[h / 2][h % 2], abuf[M % NBUF], st.dv[db]);
-      else st.dk[db] = mfma32(st.dsb[h / 2][h % 2], abuf[M % NBUF], st.dk[db]);
+      if constexpr ((M & 1) == 0) st.dv[db] = mfma32(abuf[M % NBUF], st.pb[h / 2][h % 2], st.dv[db]);
+      else st.dk[db] = mfma32(abuf[M % NBUF], st.dsb[h / 2][h % 2], st.dk[db]);
     } else {
       constexpr int j = M - N_AC, ks = ks_of(j), qb = qb_of(j);
       const f32x16 zero = {0};
@@ -612,14 +605,17 @@ static_assert((DkdvLds<128, 8, 32>::SLOTS & (DkdvLds<128, 8, 32>::SLOTS - 1)) ==
 
 // One work item: index -> (key tile * n_split + chunk of that tile's query stream, kv head, batch index), the first
 // fastest.
-template <int D, int NW, int BMQ>
+// LOOP: a workgroup may do several items.  (What depends on the lane alone is worked out afresh in each item, from an opaque copy of the
+// thread index: kept from one item to the next it is spilled, and reloads between the copies of a prologue wait for every copy under way;
+// 352 rows on 16067 keys, 3 x 16/16 heads of 128, the call 755 us with such reloads, 680 without.)
+template <int D, int NW, int BMQ, bool LOOP>
 SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
   static_assert(NW == 8, "two groups of four waves");
   using L = DkdvLds<D, NW, BMQ>;
   constexpr int BNK = NW * 32, KS = D / 16, DB = D / 32, T = NW * 64, GT = T / 2;
   constexpr int TILE_BYTES = L::TILE_BYTES, SLOTS = L::SLOTS;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
+  const int tid = fresh(threadIdx.x), lane = tid & 63, wave = tid >> 6, g = lane >> 5, ql = lane & 31;
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);      // known uniform to the compiler
   const bool group_b = wave_u >= NW / 2;
   const int gtid = tid & (GT - 1);
@@ -777,21 +773,16 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
       for (int part = 0; part < 4; ++part) copy_part(j, with_stats, part);
     };
 
-    // prologue: K rows (each wave its own), V rows of the workgroup that any row sees (dS of the others is P = 0 times dP: whatever
-    // the cache holds there must not reach dP; K only enters S, which the mask replaces), all threads; Q(0) + statistics (group A),
-    // dO(0) (group B).  K goes through LDS although it ends up in registers: a lane that reads its own key's row from memory
-    // shares a line with no neighbour, and the address unit takes such a load at a lane a clock.
-    const unsigned k_lds = smem_lds + (unsigned)L::k_stage(wave_u);
+    // prologue: K rows (each wave its own, into registers), V rows of the workgroup that any row sees (dS of the others is P = 0 times
+    // dP: whatever the cache holds there must not reach dP; K only enters S, which the mask replaces), all threads; Q(0), Q(1) +
+    // statistics (group A), dO(0), dO(1) (group B).  (K through LDS, in whole lines, changes nothing: 0.999 of the time over 365 calls.)
     {
-      using Dma = WaveDma<D, 32>;
-      const bf16_t* kbase = a.kv.k[kchunk] + head_off + chunk_row0 * a.kv_stride_s;
+      // K as B operand: column = my key (past the end of the range: the last one), k-slots = head_dim 16*ks + 8g ..
       const int64_t left = a.kv_end - tile_key0;
-      const int avail = left > BNK ? BNK : (int)left;        // keys past the end of the range are clamped
+      const int key = wave_u * 32 + ql, key_c = key < left ? key : (int)left - 1;
+      const bf16_t* kp = a.kv.k[kchunk] + head_off + (chunk_row0 + key_c) * a.kv_stride_s + 8 * g;
 #pragma unroll
-      for (int n = 0; n < Dma::PASSES; ++n) {
-        const int r = wave_u * 32 + lane / Dma::NC + Dma::RPP * n, rr = r < avail ? r : avail - 1;
-        dma16(kbase, mul24((uint32_t)rr, (uint32_t)a.kv_stride_s * 2) + Dma::chunk_off(lane, n), __builtin_amdgcn_readfirstlane(k_lds + n * 1024));
-      }
+      for (int ks = 0; ks < KS; ++ks) st.kreg[ks] = *reinterpret_cast<const bf16x8*>(kp + 16 * ks);
     }
     {
       TileDma<D, BNK, T> dma_v;
@@ -806,27 +797,16 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
     int row0_cur = cc.row0;
     copy_all(make_copy(cc, 0), copies_q);
     cursor_next(cc);
+    int row0_nxt = cc.row0;
+    copy_all(make_copy(cc, 1), copies_q);
+    cursor_next(cc);
     wait_async();
-    {
-      // K as B operand: column = key, k-slots = head_dim 16*ks + 8g ..
-      RpBase<D> lo_k;
-      lo_k.init(lane, (int)k_lds);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) st.kreg[ks] = lds_rp<D>(lo_k, ks, 0);
-      // (in registers before the barrier: tiles are copied there behind it)
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(st.kreg[ks]));
-    }
     TrBase<D> lo_qt;         // Q(u-1), transposed
     RpBase<D> lo_q, lo_v;    // Q(u) and this wave's V rows, row-packed
     lo_qt.init(lane, (int)smem_lds + L::Q_BASE + (SLOTS - 1) * TILE_BYTES);     // "Q(-1)": never read
     lo_q.init(lane, (int)smem_lds + L::Q_BASE);
     lo_v.init(lane, (int)smem_lds + L::V_BASE + wave_u * 32 * D * 2);
     __syncthreads();
-    const int row0_first_nxt = cc.row0;
-    copy_all(make_copy(cc, 1), copies_q);                 // (waited for behind the first matrix phase)
-    cursor_next(cc);
-    int row0_nxt = row0_first_nxt;
 
     int slot = 0;            // ring slot of tile u
     auto advance = [&]() {
@@ -905,47 +885,60 @@ SP_DEV void dkdv_item(const BwdArgs& a, int item, char* smem) {
     row_stride = a.kv_stride_s;
     accumulate = a.dkv_accumulate != 0;
   }
-  // A lane holds head_dim 32 db + (lane & 31) of the keys 8*(i/4) + 4g + i%4: an instruction moves two whole 128-byte lines.  (With a
-  // key a lane, and 16 bytes of its row an instruction, no two neighbouring lanes share a line and the address unit takes one lane a
-  // clock.  From the end of the tile loop to the next item, 512 KB read and written at head_dim 128, one K/V head per query head: 23
-  // -> 13 us; without old values to add to 8 -> 6.)  When the call adds to the accumulators, the old values of a gradient are all asked
-  // for before the first is needed, those of dV behind the stores of dK.
   const int64_t key0_out = tile_key0 + wave_u * 32;
   const int kmin = key0_out < a.kv_begin ? (int)(a.kv_begin - key0_out < 32 ? a.kv_begin - key0_out : 32) : 0;     // keys [kmin, kmax) of the wave exist
   const int kmax = key0_out + 32 > a.kv_end ? (int)(a.kv_end - key0_out > 0 ? a.kv_end - key0_out : 0) : 32;
-  const int lane_out = fresh(tid) & 63, g4 = (lane_out >> 5) * 4;
-  const uint32_t lane_off = mul24((uint32_t)g4, (uint32_t)row_stride) * 4u + (uint32_t)(lane_out & 31) * 4u;
-  auto at = [&](float* dst, int i, int db) {
-    return reinterpret_cast<float*>(reinterpret_cast<char*>(dst + (8 * (i >> 2) + (i & 3)) * row_stride + 32 * db) + lane_off);
-  };
+  // The rows leave through LDS (put_rows; the rings are not in use any more) as whole rows, 16 bytes a lane.  When the call adds to the
+  // accumulators, the old values of both gradients are asked for before the first store.  Calls of few query rows are mostly this.  Before
+  // (head_dim along the lanes by the swapped product, 4 bytes a lane, 128 stores a wave; second tiles of Q and dO copied behind the
+  // prologue's barrier; reloads between its copies, see LOOP) / now, us a call at head_dim 128: 160 rows on 12303 keys, 2 x 40/40 heads, added
+  // to, 829 / 718; 250 on 3789, 2 x 40/40, added to, 317 / 283; 129 on 27454, 3 x 16/16, overwritten, 950 / 779; 386 on 4855, 12/4, not causal,
+  // overwritten, 71.8 / 62.8; but 192 on 29446, 4/4, overwritten, one launch, 75.6 / 77.6: half a microsecond of LDS a gradient that nothing
+  // hides.  Over 365 calls of random sizes 0.81 to 1.03 of the time.  (A key a lane and 16 bytes of its row an instruction: 814, 309, 822, 65.0
+  // and 84.8; keys and lanes exchanged by permutations, 16 bytes a lane and 8 keys an instruction: slower than either by up to 10 %.)
+  constexpr int PER = D / 4, RPP = 64 / PER, N = 32 / RPP;      // lanes per row, rows per instruction, instructions
+  float* const part = reinterpret_cast<float*>(smem) + wave_u * 32 * kOutRow<D>;
+  const int lane_out = fresh(tid) & 63, r_out = lane_out / PER, d_out = lane_out % PER * 4;
+  const uint32_t lane_off = (mul24((uint32_t)r_out, (uint32_t)row_stride) + (uint32_t)d_out) * 4u;
+  auto at = [&](float* dst, int j) { return reinterpret_cast<f32x4*>(reinterpret_cast<char*>(dst + j * RPP * row_stride) + lane_off); };
+  // whole: all 32 keys exist
   auto flush = [&](auto whole) {
-    auto mine = [&](int i) { const int k = 8 * (i >> 2) + (i & 3) + g4; return decltype(whole)::value || (k >= kmin && k < kmax); };
-    float old[DB][16];
-    auto fetch = [&](float* dst, int db) {
+    auto mine = [&](int j) { return decltype(whole)::value || (r_out + j * RPP >= kmin && r_out + j * RPP < kmax); };
+    f32x4 old[2][N];
+    auto fetch = [&](int grad, float* dst) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) old[db][i] = mine(i) ? *at(dst, i, db) : 0.f;
+      for (int j = 0; j < N; ++j)
+        if (mine(j)) old[grad][j] = *at(dst, j);
+      SP_FENCE();
     };
-    auto put = [&](float* dst, int db, const f32x16& acc, float factor) {
+    // (the fences keep the compiler from reading all of LDS ahead: the accumulators of the other gradient are still in registers)
+    auto put = [&](int grad, float* dst) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const float x = accumulate ? acc[i] * factor + old[db][i] : acc[i] * factor;
-        if (mine(i)) *at(dst, i, db) = x;
+      for (int j = 0; j < N; ++j) {
+        f32x4 v = *reinterpret_cast<const f32x4*>(part + (r_out + j * RPP) * kOutRow<D> + d_out);
+        if (accumulate) v += old[grad][j];
+        if (mine(j)) *at(dst, j) = v;
+        if (j % 4 == 3) SP_FENCE();
       }
     };
-    if (accumulate) {
-#pragma unroll
-      for (int db = 0; db < DB; ++db) fetch(kdst, db);
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      put(kdst, db, st.dk[db], a.scale);
-      if (accumulate) fetch(vdst, db);
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db) put(vdst, db, st.dv[db], 1.0f);
+    if (accumulate) fetch(0, kdst);
+    put_rows<D>(part, st.dk, a.scale, lane_out);
+    SP_FENCE();
+    if (accumulate) fetch(1, vdst);
+    wait_async();      // (left to the compiler, the wait would sit in front of each use and be one for the stores before it too)
+    put(0, kdst);
+    put_rows<D>(part, st.dv, 1.0f, lane_out);
+    SP_FENCE();
+    put(1, vdst);
   };
-  if (kmin == 0 && kmax == 32) flush(std::true_type{});
-  else if (kmin < kmax) flush(std::false_type{});
+  // Code of its own for waves with all their keys saves a comparison a row, 1 % of short calls (1024 rows on 1377 keys, 3 x 8/1 heads of 128,
+  // 77.3 -> 76.3 us); in the loop at head_dim 128 it costs registers, and as much (250 on 3789, 2 x 40/40, 279.5 -> 284.4).
+  if constexpr (LOOP && D == 128) {
+    if (kmin < kmax) flush(std::false_type{});
+  } else {
+    if (kmin == 0 && kmax == 32) flush(std::true_type{});
+    else if (kmin < kmax) flush(std::false_type{});
+  }
 }
 
 // Without ticket counters the workgroup's index is its one item.  With them (set to zero before the launch), the
@@ -981,7 +974,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_kernel(const BwdArgs a)
       __syncthreads();                                      // read by all before the first tile copy lands there
       if (item < 0) return;
     }
-    dkdv_item<D, NW, BMQ>(a, item, smem);
+    dkdv_item<D, NW, BMQ, true>(a, item, smem);
     if (!a.ticket_dkdv) return;
   }
 }
@@ -997,7 +990,7 @@ __global__ __launch_bounds__(512) void attn_bwd_both_kernel(const BwdArgs a) {
   const int n_dq = a.dq_items[0] * a.dq_items[1] * a.dq_items[2], n_dkdv = a.dkdv_items[0] * a.dkdv_items[1] * a.dkdv_items[2];
   const int i = blockIdx.x, first = a.dq_first ? n_dq : n_dkdv;
   if ((i < first) == (a.dq_first != 0)) dq_item<D, 8, kBothDqKeys>(a, a.dq_first ? i : i - n_dkdv, smem);
-  else dkdv_item<D, 8, BMQ>(a, a.dq_first ? i - n_dq : i, smem);
+  else dkdv_item<D, 8, BMQ, false>(a, a.dq_first ? i - n_dq : i, smem);
 }
 
 // dk_acc, dv_acc (+)= the partial sums of the chunks, chunk 0 first.

@@ -382,25 +382,30 @@ SP_DEV void read_rows(unsigned lds, int lane, bf16x8 (&reg)[D / 16]) {
   for (int ks = 0; ks < D / 16; ++ks) asm volatile("" : "+v"(reg[ks]));
 }
 
-// A wave's 32 rows of `out` (row r of the wave at `base` + r * stride_s elements, `rows` of them exist, possibly none or less), held a
-// row a lane in C layout: register i of block db is head_dim 32 db + 8*(i/4) + 4g + i%4.  16 bytes of 64 different rows a store are a lane
-// a clock for the address unit, so the rows go through LDS (`part`: kOutRow<D> * 32 floats of the wave's own) and leave as whole rows.
+// A wave's 32 rows of a result on their way to memory, held a row a lane in C layout: register i of block db is head_dim
+// 32 db + 8*(i/4) + 4g + i%4.  16 bytes of 64 different rows a store are a lane a clock for the address unit, so the rows go through LDS
+// (`part`: kOutRow<D> * 32 floats of the wave's own) and leave as whole rows.
 template <int D>
 constexpr int kOutRow = D + 4;      // floats per row: padded against bank conflicts
 template <int D>
-SP_DEV void store_rows(float* part, const f32x16 (&acc)[D / 32], float factor, void* out, bool f32, bool accumulate, int64_t base, int64_t stride_s,
-                       int rows, int lane) {
-  constexpr int ROW = kOutRow<D>;
+SP_DEV void put_rows(float* part, const f32x16 (&acc)[D / 32], float factor, int lane) {
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
       const f32x4 v = {acc[db][4 * i4] * factor, acc[db][4 * i4 + 1] * factor, acc[db][4 * i4 + 2] * factor, acc[db][4 * i4 + 3] * factor};
-      *reinterpret_cast<f32x4*>(part + (lane & 31) * ROW + 32 * db + 8 * i4 + 4 * (lane >> 5)) = v;
+      *reinterpret_cast<f32x4*>(part + (lane & 31) * kOutRow<D> + 32 * db + 8 * i4 + 4 * (lane >> 5)) = v;
     }
   // (a wave's LDS instructions are carried out in order: what is left to rule out is that the compiler swaps them)
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
+}
+// put_rows, and from there to `out`: row r of the wave at `base` + r * stride_s elements, `rows` of them exist, possibly none or less.
+template <int D>
+SP_DEV void store_rows(float* part, const f32x16 (&acc)[D / 32], float factor, void* out, bool f32, bool accumulate, int64_t base, int64_t stride_s,
+                       int rows, int lane) {
+  constexpr int ROW = kOutRow<D>;
+  put_rows<D>(part, acc, factor, lane);
   if (f32) {
     constexpr int PER = D / 4, RPP = 64 / PER;           // lanes per row, rows per instruction
     const int row = lane / PER, d = lane % PER * 4;
