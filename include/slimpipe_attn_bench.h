@@ -54,6 +54,16 @@ typedef struct slimpipe_call_path {
 } slimpipe_call_path;
 int slimpipe_attn_call_path(const slimpipe_attn_params* p, int is_bwd, int32_t n_chunks, size_t workspace_bytes, slimpipe_call_path* path);
 
+/* How the kernel of 32-row and 32-key items would do a backward call that takes it (slimpipe_attn_call_path: small), for gradients that do
+ * not lie over out or lse (there own_statistics is 0).  All zero for other calls.  Host code only, nothing is launched. */
+typedef struct slimpipe_small_bwd_plan {
+  int32_t small;           /* the call takes that kernel */
+  int32_t key_blocks;      /* blocks of 32 keys a dk/dv item owns (1 or 2) */
+  int32_t own_statistics;  /* no delta kernel ahead of it: the items work out the row statistics themselves */
+  int32_t dq_first;        /* the dq items come first */
+} slimpipe_small_bwd_plan;
+int slimpipe_attn_small_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_small_bwd_plan* plan);
+
 /* The rate, in TFLOP/s, at which this GPU sustains a pure stream of the bf16 MFMA instruction the attention
  * kernels use, with constant operands (random_operands == 0) or with random ones (!= 0), under which the chip
  * is power limited and clocks lower.  Runs two short kernels (about 20 ms each) on the stream and waits for them.

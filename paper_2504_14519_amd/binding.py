@@ -47,6 +47,10 @@ class CallPath(ctypes.Structure):
     _fields_ = [("small", ctypes.c_int32), ("ranges", ctypes.c_int32), ("dq_tile_keys", ctypes.c_int32), ("dkdv_tile_rows", ctypes.c_int32)]
 
 
+class SmallBwdPlan(ctypes.Structure):
+    _fields_ = [("small", ctypes.c_int32), ("key_blocks", ctypes.c_int32), ("own_statistics", ctypes.c_int32), ("dq_first", ctypes.c_int32)]
+
+
 def library_path():
     return _LIB_PATH
 
@@ -103,6 +107,8 @@ def _load():
     L.slimpipe_attn_bwd_plan.restype = ctypes.c_int
     L.slimpipe_attn_call_path.argtypes = [P, ctypes.c_int, i32, ctypes.c_size_t, ctypes.POINTER(CallPath)]
     L.slimpipe_attn_call_path.restype = ctypes.c_int
+    L.slimpipe_attn_small_bwd_plan.argtypes = [P, i32, ctypes.c_size_t, ctypes.POINTER(SmallBwdPlan)]
+    L.slimpipe_attn_small_bwd_plan.restype = ctypes.c_int
     L.slimpipe_attn_strerror.argtypes = [ctypes.c_int]
     L.slimpipe_attn_strerror.restype = ctypes.c_char_p
     return L
@@ -394,6 +400,13 @@ def slimpipe_attn_call_path(params, is_bwd, n_chunks, workspace_bytes):
     path = CallPath()
     _check(lib.slimpipe_attn_call_path(ctypes.byref(params), 1 if is_bwd else 0, n_chunks, workspace_bytes, ctypes.byref(path)), "call_path")
     return path
+
+
+def slimpipe_attn_small_bwd_plan(params, n_chunks, workspace_bytes):
+    """How the kernel of 32-row and 32-key items would do a backward call that takes it; all zero for others (host code only)."""
+    plan = SmallBwdPlan()
+    _check(lib.slimpipe_attn_small_bwd_plan(ctypes.byref(params), n_chunks, workspace_bytes, ctypes.byref(plan)), "small_bwd_plan")
+    return plan
 
 
 def slimpipe_attn_profile_enable(enable):

@@ -567,6 +567,18 @@ int slimpipe_attn_call_path(const slimpipe_attn_params* p, int is_bwd, int32_t n
   return SLIMPIPE_OK;
 }
 
+int slimpipe_attn_small_bwd_plan(const slimpipe_attn_params* p, int32_t n_chunks, size_t workspace_bytes, slimpipe_small_bwd_plan* out) {
+  if (!p || !out) return SLIMPIPE_EINVAL_NULL;
+  int rc = slimpipe_attn_validate(p, 1);
+  if (rc != SLIMPIPE_OK) return rc;
+  if (n_chunks < 1 || n_chunks > kMaxChunks) return SLIMPIPE_EINVAL_SHAPE;
+  if (workspace_bytes < delta_bytes(p)) return SLIMPIPE_EWORKSPACE;
+  memset(out, 0, sizeof(*out));
+  const BwdSmallPlan sm = bwd_small_plan(p, bwd_plan_within(p, n_chunks, workspace_bytes));
+  if (sm.use) *out = {1, sm.key_blocks, sm.own_stats, sm.dq_first};
+  return SLIMPIPE_OK;
+}
+
 int slimpipe_attn_validate(const slimpipe_attn_params* p, int is_bwd) {
   if (!p) return SLIMPIPE_EINVAL_NULL;
   if (p->batch <= 0 || p->s_q <= 0 || p->n_q_heads <= 0 || p->n_kv_heads <= 0) return SLIMPIPE_EINVAL_SHAPE;
