@@ -387,16 +387,35 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // The line at 32 dq items is no line of speed: below it the small kernel wins too (252 calls of 1 to 32 items: 1.54 times as fast in the mean,
 // 0.90 at worst), but the launches of a call of 32 items are what the per-kernel timing is pinned to, kind by kind.  With 33 to 63 items (48
 // calls) it is 1.61 times as fast in the mean, 0.95 at worst (480 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.5 us).
-// key_blocks: at head_dim 64 a dk/dv item can own two blocks of 32 keys, four waves each: half the items, of twice the steps.  That pays where it
-// spares a round of the compute units, by the makespans of 6.5 us + 1 a step and 7.5 + 1.1 a step.  One / two blocks: 512 rows on 2048 keys,
-// 4/4 heads (64 dq items and 256 or 128) 16.6 / 13.4 us, 1024 on 2048 22.1 / 19.2, 256 on 1256, 16/16 heads, 21.6 / 19.2; but 512 on
-// 1536, 4/4 (256 items or 160, one round either way) 11.0 / 13.2, 300 on 2300, 8/2 heads, 14.7 / 21.5.  Over 13 shapes the pick is the faster one.
-// own_stats: the dk/dv items work out the row statistics of their query tiles, and no delta kernel runs before.  That saves its launch, 3 us and
-// the host's 4, and costs each step of a wave 0.4 us (O comes along with Q and dO): calls of up to 6 steps of head_dim 64.  With / without,
-// steps: 512 rows on 2048 keys, 4/4 heads, 2 steps, 16.6 / 17.6 us; 500 on 1200, 12/4 heads, 6 steps, 18.1 / 19.6; 777 on 777, 12/4, 9.4
-// steps, 22.5 / 20.9; 1024 on 1024, 8/1, 32 steps, 57.7 / 43.8.  At head_dim 128 a step pays 1 us (256 rows on 512 keys, 8/1 heads, 8 steps, 30.9 / 24.9).
-// (A call whose gradients lie over its out or lse has the delta kernel all the same: bwd_impl.)
+// key_blocks: at head_dim 64 a dk/dv item can own two blocks of 32 keys, four waves each: half the items, of twice the steps.
+// own_stats: the items work out the row statistics themselves and no delta kernel runs before.  That saves its launch, 3 us and the
+// host's 4, and costs each step of a dk/dv wave 0.5 us (O comes along with Q and dO); at head_dim 128 1 us (256 rows on 512 keys, 8/1 heads, 8
+// steps, 30.9 with / 24.9 without), so only head_dim 64 has it.  (A call whose gradients lie over its out or lse has the delta kernel all the
+// same: bwd_impl.)  Where every item has a compute unit to itself, the steps decide: calls of up to 6 have no delta kernel (with / without it
+// 1.27, 1.15, 1.09, 1.04, 1.00, 0.98, 0.94 of the time at 2 to 8 steps, in the mean).  Otherwise small_bwd_us does, and so it does between one
+// block and two: one block, with more items than units behind a delta kernel, unless another way is 5 % faster (the sums are 4 % off in the
+// mean).  Over 1170 calls, all four ways timed, the pick takes 1.007 of the best one's time in the mean, 1.19 at worst, and 0.93 of that of one
+// block behind a delta kernel, 1.09 at worst, more than 1.05 twice.  (Two blocks by makespans of other times, and no delta kernel up to 6
+// steps whatever the items: 1.014, 1.41; 0.935, 1.36, more than 1.05 in 34 calls.)  One block with / without delta kernel, two blocks with / without, us:
+// 512 rows on 2048 keys, 4/4 heads, 17.6 / 16.6, - / 13.4; 1024 on 1061, 2 x 2/2, 14.2 / 12.5, 17.6 / 19.6; 1334 on 12925, 2/2, not causal, 54.9 /
+// 64.8, 57.2 / 64.4.
 struct BwdSmallPlan { bool use, dq_first, own_stats; int key_blocks; };
+// Microseconds of a call of head_dim 64 through the small kernel: its launch (with the delta launch's), and the longest item, or with more items
+// than compute units what each unit gets in the mean and two thirds of a short item for the uneven end, if that is longer.  sq, sk: steps
+// of a wave of a dq item and of a dk/dv item of one block, were every row to see every key; seen: the share that it does see.
+double small_bwd_us(int64_t cus, int64_t nq, int64_t nk, double sq, double sk, double seen, int key_blocks, bool own_stats, bool* dq_first) {
+  const double step = (key_blocks == 2 ? 1.1 : 1.15) + (own_stats ? 0.5 : 0.0);
+  auto dq = [](double steps) { return 3.4 + 1.32 * steps; };
+  auto dkdv = [&](double steps) { return (key_blocks == 2 ? 4.5 : 3.6) + step * steps; };
+  const double tq = dq(ceil(sq)), tk = dkdv(ceil(key_blocks * sk)), mean_q = dq(sq * seen + 0.4), mean_k = dkdv(key_blocks * sk * seen + 0.4);
+  *dq_first = tq > tk;
+  double t = tq > tk ? tq : tk;
+  if (nq + nk > cus) {
+    const double even = (nq * mean_q + nk * mean_k) / cus + 0.67 * (mean_q < mean_k ? mean_q : mean_k);
+    if (even > t) t = even;
+  }
+  return (own_stats ? 2.7 : 5.4) + t;
+}
 BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) {
   if (!plan.both || !plan.full || (plan.split == 1 && plan.dq_ranges == 1)) return {false, false, false, 1};
   const bool d64 = p->head_dim == 64;
@@ -408,13 +427,23 @@ BwdSmallPlan bwd_small_plan(const slimpipe_attn_params* p, const BwdPlan& plan) 
   const double sq = (double)keys / (d64 ? 512 : 256), sk = (double)(row_blocks * (p->n_q_heads / p->n_kv_heads)) / 8;
   const double tq = (d64 ? 5 : 6) + (d64 ? 1.4 : 1.6) * (nq > cus ? sq * seen + 0.5 : ceil(sq));
   const double tk = (d64 ? 5 : 6) + (d64 ? 1.0 : 2.0) * (nk > cus ? sk * seen + 0.5 : ceil(sk));
-  auto makespan = [&](int64_t n, double t) { return tq > t ? list_makespan(cus, nq, tq, n, t) : list_makespan(cus, n, t, nq, tq); };
-  const double us = (d64 ? 5.5 : 4) + makespan(nk, tk);
-  const bool use = nq > 32 && us < 60 && us * 1.05 < plan.us + 7;
-  const int64_t nk2 = (key_blocks + 1) / 2 * p->n_kv_heads * p->batch;
-  const double tk2 = 7.5 + 1.1 * (nk2 > cus ? 2 * sk * seen + 0.5 : ceil(2 * sk));
-  const bool two = d64 && makespan(nk2, tk2) < 0.95 * makespan(nk, tk + 1.5);
-  return {use, tq > (two ? tk2 : tk), use && d64 && sk * (two ? 2 : 1) <= 6, two ? 2 : 1};
+  const double us = (d64 ? 5.5 : 4) + (tq > tk ? list_makespan(cus, nq, tq, nk, tk) : list_makespan(cus, nk, tk, nq, tq));
+  BwdSmallPlan best{nq > 32 && us < 60 && us * 1.05 < plan.us + 7, tq > tk, false, 1};
+  if (!best.use || !d64) return best;
+  const int64_t items[2] = {nk, (key_blocks + 1) / 2 * p->n_kv_heads * p->batch};
+  auto one_round = [&](int blocks) { return nq + items[blocks - 1] <= cus; };
+  auto few_steps = [&](int blocks) { return blocks * sk <= 6; };
+  double best_us = 0.0;
+  auto consider = [&](int blocks, bool own, double factor) {
+    BwdSmallPlan other{true, false, own, blocks};
+    const double t = factor * small_bwd_us(cus, nq, items[blocks - 1], sq, sk, seen, blocks, own, &other.dq_first);
+    if (best_us == 0.0 || t < best_us) { best_us = t; best = other; }
+  };
+  consider(1, one_round(1) && few_steps(1), 0.95);
+  for (int blocks = 1; blocks <= 2; ++blocks)
+    for (int own = 0; own < 2; ++own)
+      if (!one_round(blocks) || (own != 0) == few_steps(blocks)) consider(blocks, own != 0, 1.0);
+  return best;
 }
 // Tiles of the large backward at head_dim 64: 128 or 64 keys (dq), 64 or 32 query rows (dk/dv).  The larger ones have half the
 // barriers and copies per pair; a short walk pays for them in its first and last tile, which nothing hides, and in padding.

@@ -22,6 +22,26 @@ def way(sp, p, n_chunks=1, room=None):
     return m.small, m.key_blocks, m.own_statistics
 
 
+@pytest.mark.parametrize("B,s,N,Hq,Hkv,causal,blocks,own", [
+    (1, 512, 2048, 4, 4, True, 2, 1),
+    (1, 300, 700, 4, 4, True, 1, 1),
+    (1, 192, 500, 8, 1, True, 1, 1),           # 6 steps of a wave, every item on a unit of its own
+    (1, 193, 500, 8, 1, True, 1, 0),
+    (1, 618, 3090, 12, 4, True, 2, 0),
+    # measured with one block / two: 19.5 / 25.6, 20.4 / 23.6, 14.2 / 17.6, 19.8 / 22.6 us
+    (1, 1920, 2679, 2, 2, True, 1, 0),
+    (1, 1632, 1644, 4, 4, True, 1, 1),
+    (2, 1024, 1061, 2, 2, True, 1, 1),
+    (1, 1536, 1613, 4, 4, True, 1, 1),
+    # measured behind a delta kernel / without: 54.9 / 64.8, 33.6 / 37.5 us
+    (1, 1334, 12925, 2, 2, False, None, 0),
+    (1, 378, 3621, 12, 4, True, None, 0),
+])
+def test_two_blocks_and_own_statistics_where_they_are_faster(sp, B, s, N, Hq, Hkv, causal, blocks, own):
+    small, b, o = way(sp, params(sp, B, s, N, Hq, Hkv, causal=causal))
+    assert small == 1 and o == own and b in ((1, 2) if blocks is None else (blocks,))
+
+
 @pytest.mark.parametrize("s,N,off,b,e,chunk", [
     (512, 2048, 1536, 0, 2048, 0), (500, 2010, 1510, 0, 2010, 0), (300, 2600, 2200, 37, 2500, 0), (300, 2560, 2200, 37, 2500, 256),
     (600, 2048, 1500, 0, 2048, 0), (512, 2048, 1400, 0, 2048, 0)])
