@@ -139,24 +139,30 @@ def _same_strides(a, b):
     return a.shape == b.shape and all(sa == sb for n, sa, sb in zip(a.shape, a.stride(), b.stride()) if n > 1)
 
 
-def make_params(q, k, out_like, q_offset, kv_begin, kv_end, causal, scale, out_dtype=BF16):
-    """Fill the parameter block from tensor shapes/strides.  q [B,s,Hq,D], k [B,Nkv,Hkv,D]."""
-    B, s, Hq, D = q.shape
-    o_strides = out_like.stride(0), out_like.stride(1), out_like.stride(2)
-    # in the order of AttnParams; the strides of d_out are those of out
-    return AttnParams(B, s, Hq, k.shape[2], D, 1 if causal else 0, k.shape[1], q_offset, kv_begin, kv_end,
-                      float(scale) if scale is not None else 1.0 / math.sqrt(D), out_dtype, q.stride(0), q.stride(1), q.stride(2),
-                      k.stride(0), k.stride(1), k.stride(2), *o_strides, *o_strides)
-
-
 def _params(q, k, out_like, d_out, q_offset, kv_begin, kv_end, causal, scale, out_dtype):
-    # make_params for the calls themselves: strides of whole tensors, each asked for once (a question to a tensor is 0.1 us: 2.3 -> 1.3 us)
+    # strides as whole tuples: a question to a tensor is 0.1 us, and every call fills one of these (2.3 -> 1.3 us)
     B, s, Hq, D = q.shape
     k_shape, sq, sk, so, sd = k.shape, q.stride(), k.stride(), out_like.stride(), d_out.stride()
     # in the order of AttnParams
     return AttnParams(B, s, Hq, k_shape[2], D, 1 if causal else 0, k_shape[1], q_offset, kv_begin, kv_end,
                       float(scale) if scale is not None else 1.0 / math.sqrt(D), out_dtype, sq[0], sq[1], sq[2],
                       sk[0], sk[1], sk[2], so[0], so[1], so[2], sd[0], sd[1], sd[2])
+
+
+class _Layout:
+    """Shape and strides of anything that has a shape and answers stride(i)."""
+    def __init__(self, x):
+        self.shape = x.shape
+        self._strides = x.stride(0), x.stride(1), x.stride(2)
+
+    def stride(self):
+        return self._strides
+
+
+def make_params(q, k, out_like, q_offset, kv_begin, kv_end, causal, scale, out_dtype=BF16):
+    """Fill the parameter block from shapes/strides.  q [B,s,Hq,D], k [B,Nkv,Hkv,D]; the strides of d_out are those of out."""
+    out_like = _Layout(out_like)
+    return _params(_Layout(q), _Layout(k), out_like, out_like, q_offset, kv_begin, kv_end, causal, scale, out_dtype)
 
 
 def slimpipe_attn_init():
@@ -244,14 +250,14 @@ def _chunk_table(chunks):
 
 
 class _ChunkedKV:
-    """What make_params needs to know of a chunk list: the shape and strides of the virtual prefix."""
+    """What _params needs to know of a chunk list: the shape and strides of the virtual prefix."""
     def __init__(self, chunks):
         c0 = chunks[0]
         self.shape = (c0.shape[0], len(chunks) * c0.shape[1], c0.shape[2], c0.shape[3])
         self._strides = c0.stride()
 
-    def stride(self, i=None):
-        return self._strides if i is None else self._strides[i]
+    def stride(self):
+        return self._strides
 
 
 def slimpipe_attn_fwd_chunked(q_slice, k_chunks, v_chunks, q_offset, kv_begin, kv_end, causal=True, scale=None,
@@ -278,15 +284,9 @@ def slimpipe_attn_fwd_ranges(q_slice, k_chunks, v_chunks, q_offset, ranges, caus
     R = len(ranges)
     part_out = torch.empty((R, B, s, Hq, D), device=q_slice.device, dtype=torch.float32)
     part_lse = torch.empty((R, B, Hq, s), device=q_slice.device, dtype=torch.float32)
-    if merged:
-        if out is None:
-            out = torch.empty((B, s, Hq, D), device=q_slice.device, dtype=torch.float32 if out_dtype == F32 else torch.bfloat16)
-        if lse is None:
-            lse = torch.empty((B, Hq, s), device=q_slice.device, dtype=torch.float32)
-    else:
-        out = lse = None
-    kv = _ChunkedKV(k_chunks)
-    p = make_params(q_slice, kv, out if merged else part_out[0], q_offset, 0, kv.shape[1], causal, scale, out_dtype)
+    out, lse = _outputs(q_slice, out_dtype, out, lse) if merged else (None, None)
+    kv, out_like = _ChunkedKV(k_chunks), out if merged else part_out[0]
+    p = _params(q_slice, kv, out_like, out_like, q_offset, 0, kv.shape[1], causal, scale, out_dtype)
     begins = (ctypes.c_int64 * R)(*[int(a) for a, _ in ranges])
     ends = (ctypes.c_int64 * R)(*[int(b) for _, b in ranges])
     _check(lib.slimpipe_attn_fwd_ranges(ctypes.byref(p), q_slice.data_ptr(), _chunk_table(k_chunks), _chunk_table(v_chunks),
