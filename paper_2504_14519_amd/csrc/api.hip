@@ -250,10 +250,10 @@ FwdPlan fwd_blocks_plan(const slimpipe_attn_params* p, size_t room) {
 }
 // What the forward would do with all the room it wants.
 // With less than one 256-row block per compute unit the small kernel is taken, in the number of ranges (none shorter than the
-// 256-row blocks may have) that makes it fastest, where its time is shorter.  Over 57 calls of up to 1.2 x 65536 (row, head) pairs, both kernels timed in 1 to 8
-// ranges: the pick is within 2 % of the best in the mean, at most 1.7 % slower than the 256-row blocks, 1.53 times as fast in the mean
-// and up to 2.6 times (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).  It loses where keys are long: every workgroup
-// reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
+// 256-row blocks may have) that makes it fastest, where its time is shorter.  Over 567 calls, both kernels timed in 1 to 8 ranges, the pick is within 1 %
+// of the best in the mean (1.58 and 1.74 times its time at worst, at head_dim 64 and 128: long keys left on the blocks), and where it is the
+// small kernel 1.61 and 1.95 times as fast as the 256-row blocks, 0.99 at worst, 3.1 at best (256 rows of 8 heads on 2648 keys 42.4 -> 16.9 us).
+// It loses where keys are long: every workgroup reads all its keys for 32 rows (676 rows of 8 heads on 17519 keys: 98 us against 69).
 FwdPlan fwd_plan_wanted(const slimpipe_attn_params* p) {
   const FwdPlan blocks = fwd_blocks_plan(p, SIZE_MAX);
   const int64_t w = all_query_blocks(p, blocks.head_waves), keys = p->kv_end - p->kv_begin, cus = compute_units();
@@ -380,13 +380,15 @@ BwdPlan bwd_plan_within(const slimpipe_attn_params* p, int n_chunks, size_t work
 // given the workspace it is asked for: with less, and where nothing would be cut, it keeps the sums of the undivided items.
 // Microseconds: a dq item 6 (head_dim 64: 5) + 1.6 (1.4) per step of a wave, which is 32 (64) keys, a dk/dv item 6 (5) + 2 (1) per 32
 // query rows of a wave, and 4 (5.5) for the launch; against the model of bwd_plan + 7, what the delta and reduce launches
-// cost beyond it.  Over 164 calls, both kernels timed: the pick is within 1 % of the faster in the mean and 1.17 times as fast as
-// the 256-row items (512 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.9 us; 100 rows of 8/2 heads of 128 on 448 keys, batch 2: 31.9 ->
-// 17.1).  Long calls stay out: a workgroup reads the whole other side for 32 rows or keys, and the model does not know what
-// that costs a full chip (1969 rows on 4976 keys, 8/1 heads of 64: 80 us by the model, 104 measured, 90 through the 256-row items).
-// The line at 32 dq items is no line of speed: below it the small kernel wins too (252 calls of 1 to 32 items: 1.54 times as fast in the mean,
-// 0.90 at worst), but the launches of a call of 32 items are what the per-kernel timing is pinned to, kind by kind.  With 33 to 63 items (48
-// calls) it is 1.61 times as fast in the mean, 0.95 at worst (480 rows on 2048 keys, 4 heads of 64: 30.2 -> 17.5 us).
+// cost beyond it.  These are the times of the first small kernel, which took longer: they err towards the 256-row items.  Of random calls,
+// both kernels timed, the small kernel takes 1 / 1.56 of their time at head_dim 64 where it is picked (1170 calls, 0.86 at worst; 512 rows on 2048
+// keys, 4 heads, 30.2 -> 13.4 us) and 1 / 1.41 at 128 (159 calls, 0.92; 100 rows of 8/2 heads on 448 keys, batch 2, 31.9 -> 17.1); where it is not it
+// would be 0.96 and 0.87 times as fast (412 and 96 calls), by up to 1.44 and 1.27 faster.  Long calls stay out: a workgroup reads
+// the whole other side for 32 rows or keys, and the model does not know what that costs a full chip (1969 rows on 4976 keys, 8/1 heads of
+// 64: 80 us by the model, 104 measured, 90 through the 256-row items).
+// The line at 32 dq items is no line of speed: below it the small kernel wins too (318 calls of 17 to 32 items of head_dim 64: 1.62 times as fast in
+// the mean), but the launches of a call of 32 items are what the per-kernel timing is pinned to, kind by kind.  With 33 to 63 items (280
+// calls) it is 1.78 times as fast in the mean, 0.96 at worst.
 // key_blocks: at head_dim 64 a dk/dv item can own two blocks of 32 keys, four waves each: half the items, of twice the steps.
 // own_stats: the items work out the row statistics themselves and no delta kernel runs before.  That saves its launch, 3 us and the
 // host's 4, and costs each step of a dk/dv wave 0.5 us (O comes along with Q and dO); at head_dim 128 1 us (256 rows on 512 keys, 8/1 heads, 8

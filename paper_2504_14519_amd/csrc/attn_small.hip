@@ -242,8 +242,8 @@ hipError_t launch_fwd_small(const FwdArgs& a, int batch, int head_dim, hipStream
 // The same idea for both gradients, in one launch: a workgroup owns 32 query rows (dq) or 32 keys
 // (dk/dv) and its eight waves share out the keys, or the query tiles of all heads of the group, each with tiles of its own; the
 // eight partial sums meet in LDS and are added up in wave order (bit-reproducible).  No partial sums in memory, no reduce launch.
-// 512 rows on 2048 keys, 4 heads of 64: 30.2 -> 16.6 us for the call (17.2 with rows of Q, dO and K loaded by every wave, a row a lane, and
-// a delta kernel before it; 512 rows on 512 keys 13.3 -> 10.8).  A step of dk/dv (32 query rows of a wave) takes 1 us at
+// 512 rows on 2048 keys, 4 heads of 64: 30.2 -> 13.4 us for the call (16.6 with one key block an item; 17.2 with rows of Q, dO and K loaded by
+// every wave, a row a lane, and a delta kernel before it; 512 rows on 512 keys 13.3 -> 10.8).  A step of dk/dv (32 query rows of a wave) takes 1 us at
 // head_dim 64, where the tiles are double-buffered, and 2 us at 128, where one Q and one dO tile per wave are all of LDS and the
 // copy of the next waits for the sums of this one.  Which calls come here: bwd_small_plan in api.hip.
 template <int D>
